@@ -70,7 +70,7 @@ typedef enum nimble_dtype { NIMBLE_BF16 = 0, NIMBLE_F32 = 1 } nimble_dtype;
  * suits their number (see nimble_plan.split_rows). */
 typedef enum nimble_variant {
   NIMBLE_VAR_AUTO = -1,
-  NIMBLE_VAR_GENERIC = 0,    /* any M,N,K; fully bounds checked, scalar FMA       */
+  NIMBLE_VAR_GENERIC = 0,    /* any M,N,K and alignment; MFMA, bounds checked     */
   NIMBLE_VAR_SKINNY16 = 1,   /* M tile 16: weights streamed from HBM once         */
   NIMBLE_VAR_T32x128 = 2,    /* LDS-tiled MFMA, 32 x 128 macro tile               */
   NIMBLE_VAR_T64x128 = 3,
@@ -89,7 +89,9 @@ typedef enum nimble_variant {
  * paying a mostly empty last round: the residue handling of Section 3.5 applied one level up. */
 #define NIMBLE_FORCE_TILE_ROWS(rows) ((((rows) / 16) & 0xff) << 16)
 
-/* What the dispatch function decided for one run-time shape (host only). */
+/* What the dispatch function decided for one run-time shape (host only).  A tiled plan whose shape the
+ * ring kernels cannot run (K not a multiple of 32, N not of 8) or whose last tile column would be a large
+ * part of the work is launched in the 64 x 64 tiles of the generic variant instead. */
 typedef struct nimble_plan {
   int32_t variant;        /* nimble_variant                                       */
   int32_t bm, bn, bk;     /* macro tile of the launch (bm may be a reduced height)  */
@@ -220,8 +222,8 @@ int nimble_dense_noalloc_dyn(const void* x, const void* w, const void* bias, voi
  *   trans_b == 0: c[t,m,n] = alpha * sum_k a[t,m,k] * b[t,k,n]
  * a, b bf16; c of out_dtype; f32 accumulation.  With trans_b == 0 the tiled kernels run on b
  * transposed into the workspace (nimble_batch_matmul_plan gives its size, batch*N*K*2 bytes,
- * when K is a multiple of 8 and a tile suits the shape); with less workspace than that, or none,
- * a bounds-checked kernel reads b as it is. */
+ * when K is a multiple of 8 and a tile suits the shape); with less workspace than that, or none, and
+ * below 4 G multiply-adds anyway, the kernel for any alignment reads b as it is. */
 int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch, int64_t M,
                             int64_t N, int64_t K, int trans_b, float alpha, int out_dtype,
                             void* workspace, size_t workspace_bytes, void* stream);

@@ -79,6 +79,32 @@ __device__ __forceinline__ float epilogue(float acc, float alpha, float bias, in
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
+// Eight bf16 from an address that is only known to be 2-byte aligned (one global_load_dwordx4: the
+// hardware takes unaligned vector loads from global memory).
+__device__ __forceinline__ uint4 load8_unaligned(const u16* p) {
+  uint4 v;
+  __builtin_memcpy(&v, p, 16);
+  return v;
+}
+// The first `left` (1..7) of them, the rest zero: the last chunk of a row of `len` elements, past which
+// nothing may be read.  The row's last eight elements are loaded instead and shifted down (element by
+// element, each load behind a branch, this chunk alone took 3.5 us at K = 1003).
+__device__ __forceinline__ uint4 load8_tail(const u16* p, int left, int len) {
+  if (len < 8) {
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 7; ++e)
+      if (e < left) w[e >> 1] |= (uint32_t)p[e] << (16 * (e & 1));
+    return make_uint4(w[0], w[1], w[2], w[3]);
+  }
+  const uint4 v = load8_unaligned(p + left - 8);
+  const uint64_t lo = ((uint64_t)v.y << 32) | v.x, hi = ((uint64_t)v.w << 32) | v.z;
+  const int sh = 16 * (8 - left);  // 16 .. 112 bits
+  const uint64_t rlo = sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : hi >> (sh - 64);
+  const uint64_t rhi = sh < 64 ? hi >> sh : 0;
+  return make_uint4((uint32_t)rlo, (uint32_t)(rlo >> 32), (uint32_t)rhi, (uint32_t)(rhi >> 32));
+}
+
 // Two float32 -> two bfloat16 (round to nearest even) in one v_cvt_pk_bf16_f32; lo in bits 0..15.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));

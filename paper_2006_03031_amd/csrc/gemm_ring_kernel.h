@@ -5,7 +5,6 @@
 #include <type_traits>
 
 #include "device_common.h"
-#include "gemm_tile_kernel.h"
 
 namespace nimble {
 
@@ -53,7 +52,11 @@ struct RingLink {
   int parity = 0;       // bias slot of this tile (the next tile's is the other one)
 };
 
-template <int BM, int BN, int WGM, int WGN, int S, bool MEDGE, int MODE, bool PF = false>
+// EDGE: the tile reaches past the last row or the last column of the output.  Rows of A past M-1 and of B
+// past N-1 are fetched from the last one, so every load stays in bounds and the pipeline is the interior
+// one; their products land in rows and columns the epilogue does not store (N is a multiple of 8 here, so
+// a 16-byte piece of an output row is stored whole or not at all).
+template <int BM, int BN, int WGM, int WGN, int S, bool EDGE, int MODE, bool PF = false>
 __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, const int n0,
                                               uint4* smem, const RingLink lk = RingLink{}) {
   constexpr bool WIDE = MODE == RING_WIDE;
@@ -103,8 +106,6 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
 
   // loads: pass i covers chunk ids i*NT + tid: row = i*(NT/4) + (tid >> 2), slot = tid & 3.
   // Address = uniform base of (tile row 0, pass i, stage k0) + per-lane byte offset.
-  // MEDGE (the last tile along M when r != 0): rows past M-1 are fetched from row M-1, so
-  // every load stays in bounds; their products land in rows the epilogue never stores.
   const int ld_row = tid / CH;
   const int ld_c = (tid & (CH - 1)) ^ ((ld_row >> 1) & (CH - 1));
   uint32_t a_off[A_LD];
@@ -117,11 +118,21 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       a_off[i] = (uint32_t)(row * g.lda + ld_c * 8) * 2u;
     }
   };
-  set_a_off(m0, MEDGE);
-  const uint32_t b_off = (uint32_t)(ld_row * g.ldb + ld_c * 8) * 2u;
+  set_a_off(m0, EDGE);
+  // (interior tiles: one offset for all passes, the pass goes into the scalar base)
+  uint32_t b_off[EDGE ? B_LD : 1];
+  auto set_b_off = [&](const int tile_n0) {
+#pragma unroll
+    for (int i = 0; i < (EDGE ? B_LD : 1); ++i) {
+      int row = ld_row + i * PASS;
+      if (EDGE) row = (tile_n0 + row < g.N) ? row : (g.N - 1 - tile_n0);
+      b_off[i] = (uint32_t)(row * g.ldb + ld_c * 8) * 2u;
+    }
+  };
+  set_b_off(n0);
   const u16* a_base = A + (long long)m0 * g.lda;
   const u16* b_base = B + (long long)n0 * g.ldb;
-  const long long b_pass = (long long)PASS * g.ldb;
+  const long long b_pass = EDGE ? 0 : (long long)PASS * g.ldb;
   const uint32_t a_dst = __builtin_amdgcn_readfirstlane(lds_addr_of(&As[0][wave * 64]));
   const uint32_t b_dst = __builtin_amdgcn_readfirstlane(lds_addr_of(&Bs[0][wave * 64]));
   auto dma = [&](int ks, int slot) {
@@ -131,7 +142,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       dma16_so(a_off[i], a_base + k0, a_dst + slot * (BMP * CH * 16) + i * NT * 16);
 #pragma unroll
     for (int i = 0; i < B_LD; ++i)
-      dma16_so(b_off, b_base + i * b_pass + k0, b_dst + slot * (BN * CH * 16) + i * NT * 16);
+      dma16_so(b_off[EDGE ? i : 0], b_base + i * b_pass + k0, b_dst + slot * (BN * CH * 16) + i * NT * 16);
   };
 
   // fragment reads: lane -> row (lane & 15), logical chunk (lane >> 4)
@@ -162,8 +173,13 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
   auto fetch_bias = [&](const int tile_n0, u16* dst) {
     if (park_bias && wave < BN / 128) {  // whole waves
       const int wu = __builtin_amdgcn_readfirstlane(wave);
-      dma4_so((uint32_t)lane * 4u, (const u16*)g.bias + tile_n0 + wu * 128,
-              __builtin_amdgcn_readfirstlane(lds_addr_of(dst)) + wu * 256);
+      int n = tile_n0 + wu * 128;
+      uint32_t voff = (uint32_t)lane * 4u;
+      if (EDGE) {  // values past N are not used: fetch the row's last ones instead
+        if (n + 2 * lane >= g.N) voff = 0;
+        n = n < g.N - 2 ? n : g.N - 2;
+      }
+      dma4_so(voff, (const u16*)g.bias + n, __builtin_amdgcn_readfirstlane(lds_addr_of(dst)) + wu * 256);
     }
   };
   // whether the waits of this tile's first S-1 stages may leave the previous epilogue's stores in flight
@@ -323,7 +339,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       if (u < A_LD)
         dma16_so(a_off[u], a_base + k0, a_dst + slot_ * (BMP * CH * 16) + u * NT * 16);
       else
-        dma16_so(b_off, b_base + (u - A_LD) * b_pass + k0, b_dst + slot_ * (BN * CH * 16) + (u - A_LD) * NT * 16);
+        dma16_so(b_off[EDGE ? u - A_LD : 0], b_base + (u - A_LD) * b_pass + k0, b_dst + slot_ * (BN * CH * 16) + (u - A_LD) * NT * 16);
     };
     // second halves (CUR == 1) also issue the ring loads of one stage, spread over their weight
     // tiles (ld_k0 < 0 in a two-slot ring: past the end of K, nothing to load)
@@ -386,6 +402,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
     __syncthreads();
     if (lk.next) {
       set_a_off(lk.next_m0, true);
+      if (EDGE) set_b_off(lk.next_n0);
       a_base = A + (long long)lk.next_m0 * g.lda;
       b_base = B + (long long)lk.next_n0 * g.ldb;
       fetch_bias(lk.next_n0, reinterpret_cast<u16*>(smem + S * (BMP + BN) * CH) + (lk.parity ^ 1) * BN);
@@ -402,7 +419,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
   for (int i = 0; i < TN; ++i) {
 #pragma unroll
     for (int v = 0; v < 4; ++v) bias4[i][v] = 0.f;
-    if (epi != NIMBLE_EPI_NONE) {
+    if (epi != NIMBLE_EPI_NONE && (!EDGE || park_bias || n0 + wn * WN + i * 16 + fr_q * 4 < g.N)) {
       const uint2 bb = park_bias ? *(const uint2*)(bias_lds + wn * WN + i * 16 + fr_q * 4)
                                  : *(const uint2*)((const u16*)g.bias + n0 + wn * WN + i * 16 + fr_q * 4);
       bias4[i][0] = bf2f((u16)(bb.x & 0xffff));
@@ -416,10 +433,11 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
 #pragma unroll
     for (int j = 0; j < TM; ++j) {
       const int m = m0 + wm * WM + j * 16 + fr_row;
-      if (MEDGE && m >= g.M) continue;
+      if (EDGE && m >= g.M) continue;
 #pragma unroll
       for (int i = 0; i < TN; ++i) {
         const int n = n0 + wn * WN + i * 16 + fr_q * 4;
+        if (EDGE && n >= g.N) continue;
         float4 o;
         o.x = epilogue(acc[i][j][0], alpha, bias4[i][0], epi);
         o.y = epilogue(acc[i][j][1], alpha, bias4[i][1], epi);
@@ -457,11 +475,11 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
           const int row = p * 8 + (lane >> 3);
           const int c = lane & 7;
           const uint4 v = *(const uint4*)(region + h * (16 * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
-          if (MEDGE && m0 + wm * WM + j * 16 + row >= g.M) continue;
+          if (EDGE && (m0 + wm * WM + j * 16 + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
           *(uint4*)(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8) = v;
         }
     }
-    return MEDGE ? -1 : NST;
+    return EDGE ? -1 : NST;
   }
   // bf16: every wave stages its [WM][WN] block in LDS as WN/64 blocks of [WM][64] (rows of 128
   // bytes, chunk c of row r at slot c ^ ((r >> 1) & 7)) and writes it back out as full 128-byte lines
@@ -490,7 +508,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       const int row = p * 8 + (lane >> 3);
       const int c = lane & 7;
       const uint4 v = *(const uint4*)(region + h * (WM * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
-      if (MEDGE && m0 + wm * WM + row >= g.M) continue;
+      if (EDGE && (m0 + wm * WM + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
       uint4* dst = (uint4*)(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8);
       *dst = v;
     }
@@ -516,9 +534,8 @@ __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per
   constexpr int kCh = WIDE ? 8 : 4;
   constexpr int kPass = WGM * WGN * 64 / kCh;  // rows per load pass: the ring holds whole passes of A
   constexpr int kBmp = (BM + kPass - 1) / kPass * kPass;
-  // the ring (which also holds the masked body's two 64-wide tiles), then BN bias values where they fit
+  // the ring, then BN bias values where they fit
   constexpr int kRing = S * (kBmp + BN) * kCh;
-  static_assert(kRing >= 2 * (BM + BN) * 8, "the masked body needs two 64-wide tiles");
   // Wherever two bias slots and a 16-row staging area per wave fit behind a 64-wide ring, a tile's
   // epilogue leaves the ring alone and the next tile's first stages load while it runs (RingLink).
   constexpr int kStage = WGM * WGN * 16 * (BN / WGN) * 2 / 16;  // uint4
@@ -534,8 +551,6 @@ __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per
   // is a multiple of 8 whenever a workgroup gets more than one tile, so a workgroup's tiles stay in
   // the run of tile ids of its own XCD.)
   const int tiles_total = tiles_m * tiles_n;
-  // launch-wide reasons for the fully masked body: K not whole stages, output rows not 16-byte aligned
-  const bool ragged_launch = RESIDUE && (((g.K & (WIDE ? 63 : 31)) != 0) || ((g.ldc & 7) != 0));
   RingLink lk;
   for (int t = blockIdx.x; t < tiles_total; t += gridDim.x) {
     // the previous tile's epilogue is done with the LDS (a handed-over ring was free before it began)
@@ -546,29 +561,19 @@ __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per
     if constexpr (kPF) {
       const int t2 = t + (int)gridDim.x;
       lk.next = false;
-      if (t2 < tiles_total && !ragged_launch) {
+      if (t2 < tiles_total) {
         int m2, n2;
         tile_of_block(t2, tiles_total, tiles_m, tiles_n, group_m, m2, n2);
         lk.next_m0 = m2 * BM;
         lk.next_n0 = n2 * BN;
-        lk.next = !RESIDUE || lk.next_n0 + BN <= g.N;  // never ahead of a fully masked tile
+        lk.next = !RESIDUE || lk.next_n0 + BN <= g.N;  // (an interior body does not clamp rows of B)
       }
     }
-    if (RESIDUE) {
-      // the packed epilogue needs 16-byte aligned output rows; K must be whole stages
-      const bool ragged = ragged_launch || (n0 + BN > g.N);
-      if (ragged) {  // ragged N or K, or output rows not 16-byte aligned: the fully masked body
-        // (the reduced tile heights are only dispatched to shapes without ragged N or K)
-        if constexpr (BM % 128 == 0 || BN == 128) gemm_tile_body<BM, BN, WGM, WGN, true>(g, m0, n0, smem);
-        lk.filled = false;
-        continue;
-      }
-      if (m0 + BM > g.M) {  // the last tile along M: same pipeline, clamped loads, masked stores
-        lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, true, kMode, kPF>(g, m0, n0, smem, lk);
-        lk.filled = kPF && lk.next;
-        lk.parity ^= 1;
-        continue;
-      }
+    if (RESIDUE && (m0 + BM > g.M || n0 + BN > g.N)) {  // same pipeline, clamped loads, masked stores
+      lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, true, kMode, kPF>(g, m0, n0, smem, lk);
+      lk.filled = kPF && lk.next;
+      lk.parity ^= 1;
+      continue;
     }
     lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, false, kMode, kPF>(g, m0, n0, smem, lk);
     lk.filled = kPF && lk.next;

@@ -1,35 +1,9 @@
-// Fully bounds-checked GEMM for any shape, row softmax, fused attention for head dimension 64.
+// Row softmax, transpose, fused attention for head dimension 64.
 #ifndef NIMBLE_MISC_KERNELS_H_
 #define NIMBLE_MISC_KERNELS_H_
 #include "device_common.h"
 
 namespace nimble {
-
-// ---------------------------------------------------------------------------
-// Fully bounds-checked kernel for any shape, stride and B layout.
-// ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) generic_kernel(GemmArgs g) {
-  const int n = blockIdx.x * 16 + (threadIdx.x & 15);
-  const int m = blockIdx.y * 16 + (threadIdx.x >> 4);
-  const int z = blockIdx.z;
-  if (m >= g.M || n >= g.N) return;
-  const u16* __restrict__ a = (const u16*)g.a + (long long)z * g.sa + (long long)m * g.lda;
-  const u16* __restrict__ b = (const u16*)g.b + (long long)z * g.sb;
-  float acc = 0.f;
-  if (g.b_is_kn) {
-    for (int k = 0; k < g.K; ++k) acc = fmaf(bf2f(a[k]), bf2f(b[(long long)k * g.ldb + n]), acc);
-  } else {
-    b += (long long)n * g.ldb;
-    for (int k = 0; k < g.K; ++k) acc = fmaf(bf2f(a[k]), bf2f(b[k]), acc);
-  }
-  const float bias = (g.epilogue != NIMBLE_EPI_NONE) ? bf2f(((const u16*)g.bias)[n]) : 0.f;
-  const float v = epilogue(acc, g.alpha, bias, g.epilogue);
-  const long long o = (long long)z * g.sc + (long long)m * g.ldc + n;
-  if (g.out_f32)
-    ((float*)g.c)[o] = v;
-  else
-    ((u16*)g.c)[o] = f2bf(v);
-}
 
 // ---------------------------------------------------------------------------
 // Row softmax, f32 in, bf16 out; one wave per row, four rows per workgroup.

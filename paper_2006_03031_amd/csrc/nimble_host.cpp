@@ -28,7 +28,7 @@ void clear_error() { g_err[0] = '\0'; }
 
 const VariantInfo kVariants[NIMBLE_VAR_COUNT] = {
     // name       bm   bn   bk  threads
-    {"generic", 16, 16, 1, 256},
+    {"generic", 64, 64, 64, 256},
     {"skinny16", 16, 16, 32, 256},
     {"t32x128", 32, 128, 32, 128},
     {"t64x128", 64, 128, 32, 256},
@@ -398,17 +398,22 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
   }
 
   if (variant == NIMBLE_VAR_GENERIC) {
-    const VariantInfo& v = kVariants[variant];
+    // Any shape and alignment.  A grid of at most two workgroups per compute unit, or a single block of
+    // rows, streams both operands in 16 x 16 blocks whose waves share K; everything else runs in 64 x 64
+    // tiles (any_kernel).  Measured at K = 1003 on N = 1001: 64 rows 6.7 us against 11.4, 128 rows 10.5
+    // against 11.4, 64 rows on N = 4001 13.1 against 11.5; 256 x 256 6.6 against 11.3.
+    const int64_t cols16 = ceil_div(N, 16), rows16 = ceil_div(M, 16);
+    const bool rows = opt.generic_rows && batch == 1 && K > 0 && rows16 <= 65535 &&
+                      (rows16 <= 1 || cols16 * rows16 <= 2 * kCUs);
     p->variant = variant;
-    p->bm = v.bm;
-    p->bn = v.bn;
-    p->bk = v.bk;
-    p->k = M / v.bm;
-    p->r = (int32_t)(M % v.bm);
+    p->bm = p->bn = rows ? 16 : 64;
+    p->bk = rows ? 32 : 64;
+    p->k = M / p->bm;
+    p->r = (int32_t)(M % p->bm);
     p->residue_copy = 1;
     p->split_k = 1;
-    p->grid[0] = (uint32_t)ceil_div(N, v.bn);
-    p->grid[1] = (uint32_t)ceil_div(M, v.bm);
+    p->grid[0] = (uint32_t)(rows ? cols16 : ceil_div(M, 64) * ceil_div(N, 64));
+    p->grid[1] = (uint32_t)(rows ? rows16 : 1);
     p->grid[2] = (uint32_t)batch;
     p->block = 256;
     return NIMBLE_OK;
@@ -671,6 +676,7 @@ int nimble_batch_matmul_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int
   PlanOptions bmm;
   bmm.allow_row_split = false;
   bmm.use_table = false;
+  bmm.generic_rows = trans_b != 0;
   if (!trans_b) {
     // b is (T,K,N): its rows are not K-contiguous.  Where the tiled kernels could run the product
     // on b transposed (K a multiple of 8 and whole 16-byte batch strides), the plan is that NT

@@ -8,11 +8,10 @@
 //       accumulators, the next stage's fragments read in between the MFMAs, an epilogue that
 //       transposes through LDS so every store is a full 128-byte line.  RESIDUE=false is the
 //       copy for r = 0: no bounds code at all.  RESIDUE=true is the copy for r != 0: decided
-//       once per workgroup, the last tile along M runs the same pipeline with clamped loads
-//       and masked stores, ragged N/K tiles run the fully masked body.  Also the split-K
-//       reduction kernel.
-//   gemm_tile_kernel.h   gemm_tile_body: that fully masked body (register-staged K tiles of 64,
-//       32x32x16 MFMA, every access bounds-checked).
+//       once per tile, tiles past the last row or column run the same pipeline with clamped loads
+//       and masked stores.  Also the split-K reduction kernel.
+//   any_kernel.h         any_kernel: 64x64 tiles for operands and outputs of any shape, alignment
+//       and B layout (register-staged, unaligned loads, zero-filled K tail).
 //   skinny_kernel.h      skinny_kernel<MT,LSTM>: M <= 64 per workgroup, the weights are
 //       streamed from HBM exactly once straight into MFMA operands, the four waves of a
 //       workgroup split K and reduce through LDS.  LSTM=true gathers the four gate rows of
@@ -31,9 +30,9 @@
 #include <cstdlib>
 #include <mutex>
 
+#include "any_kernel.h"
 #include "device_common.h"
 #include "gemm_ring_kernel.h"
-#include "gemm_tile_kernel.h"
 #include "misc_kernels.h"
 #include "nimble_internal.h"
 #include "nimble_probe.h"
@@ -143,27 +142,62 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
   return check_hip(hipGetLastError(), "skinny kernel launch");
 }
 
+static SkinnyArgs skinny_args(const GemmArgs& g) {
+  SkinnyArgs s{};
+  s.x = (const u16*)g.a;
+  s.w = (const u16*)g.b;
+  s.bias = (const u16*)g.bias;
+  s.y = g.c;
+  s.M = g.M;
+  s.N = g.N;
+  s.K = g.K;
+  s.epilogue = g.epilogue;
+  s.out_f32 = g.out_f32;
+  s.alpha = g.alpha;
+  return s;
+}
+
+// Operands of any alignment in 64 x 64 tiles.  Two groups of waves share a tile's K where a workgroup
+// per compute unit is all there is and K is long enough to pay for handing the sums over (measured at
+// K = 1003: 700 x 1001 12.5 -> 11.5 us, 12 x 512 x 64 x 512 as A.B 7.4 -> 6.3; at K = 64 12 x 509 x 509
+// 6.2 -> 8.4; with 512 tiles at K = 1000 14.0 -> 15.1).
+static int launch_any(const GemmArgs& g, hipStream_t st) {
+  const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
+  const dim3 grid((unsigned)tiles_m * (unsigned)tiles_n, 1, (unsigned)g.batch);
+  const bool two = g.K >= 512 && (long long)grid.x * g.batch <= kComputeUnits;
+  if (g.b_is_kn) {
+    if (two)
+      hipLaunchKernelGGL((any_kernel<64, 64, true, 4, 2>), grid, dim3(512), 0, st, g, tiles_m, tiles_n);
+    else
+      hipLaunchKernelGGL((any_kernel<64, 64, true, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
+  } else {
+    if (two)
+      hipLaunchKernelGGL((any_kernel<64, 64, false, 4, 2>), grid, dim3(512), 0, st, g, tiles_m, tiles_n);
+    else
+      hipLaunchKernelGGL((any_kernel<64, 64, false, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
+  }
+  return check_hip(hipGetLastError(), "any kernel launch");
+}
+
+// Tiled plans whose shape the ring kernels cannot run (K not whole stages, output rows not 16-byte
+// aligned) run on any_kernel, and so do smaller products whose last tile column is partly empty: that
+// column then is a large part of the work (1000 x 1000 x 1024: 9.2 us against 15.4 on 64 x 128 tiles,
+// 4000 rows 20.7 against 23.8, 16000 rows 68 against 52: the line lies at 5 G multiply-adds).
+static bool wants_any(const GemmArgs& g, const nimble_plan& p) {
+  if ((g.K & 31) != 0 || (g.ldc & 7) != 0) return true;
+  return g.N % p.bn != 0 && (double)g.batch * g.M * g.N * g.K < 5e9;
+}
+
 static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
+  if (p.variant >= NIMBLE_VAR_T32x128 && wants_any(g, p)) return launch_any(g, st);
   switch (p.variant) {
-    case NIMBLE_VAR_GENERIC: {
-      dim3 grid(p.grid[0], p.grid[1], p.grid[2]), block(256);
-      hipLaunchKernelGGL(generic_kernel, grid, block, 0, st, g);
-      return check_hip(hipGetLastError(), "generic kernel launch");
-    }
-    case NIMBLE_VAR_SKINNY16: {
-      SkinnyArgs s{};
-      s.x = (const u16*)g.a;
-      s.w = (const u16*)g.b;
-      s.bias = (const u16*)g.bias;
-      s.y = g.c;
-      s.M = g.M;
-      s.N = g.N;
-      s.K = g.K;
-      s.epilogue = g.epilogue;
-      s.out_f32 = g.out_f32;
-      s.alpha = g.alpha;
-      return launch_skinny<false>(s, p, st);
-    }
+    case NIMBLE_VAR_GENERIC:
+      if (p.bm == 16) {
+        hipLaunchKernelGGL((skinny_kernel<1, false, 8, true>), dim3(p.grid[0], p.grid[1]), dim3(256), 0, st, skinny_args(g));
+        return check_hip(hipGetLastError(), "skinny kernel launch");
+      }
+      return launch_any(g, st);
+    case NIMBLE_VAR_SKINNY16: return launch_skinny<false>(skinny_args(g), p, st);
     case NIMBLE_VAR_T32x128: return launch_ring<32, 128, 1, 2, 3>(g, p, st);
     case NIMBLE_VAR_T64x128: return launch_ring<64, 128, 2, 2, 3>(g, p, st);
     case NIMBLE_VAR_T128x128: return launch_ring<128, 128, 2, 2>(g, p, st);
@@ -345,6 +379,8 @@ int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch
   if (workspace_bytes > 0 && !workspace) return fail(NIMBLE_ERR_NULL, "workspace_bytes > 0 with a null workspace");
   if (workspace && misaligned(workspace)) return fail(NIMBLE_ERR_ALIGN, "workspace must be 16-byte aligned");
   nimble_plan p;
+  PlanOptions any_b;
+  any_b.generic_rows = trans_b != 0;
   int rc = nimble_batch_matmul_plan(batch, M, N, K, trans_b, out_dtype, &p);
   if (rc != NIMBLE_OK) return rc;
   if (batch == 0 || M == 0 || N == 0) return NIMBLE_OK;
@@ -353,12 +389,14 @@ int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch
     return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
   // the NN product on the tiled kernels needs b transposed into the workspace: without enough of
   // it the bounds-checked kernel does the job (the plan is made within the scratch the caller brought)
+  // (below 4 G multiply-adds reading b as it is wins also where the workspace is there: 12 x 512 x 64 x 512
+  // 6.3 us against 13.4, 1000^3 11.0 against 14.8, 12 x 2048 x 64 x 2048 32.6 against 35.4; 2048^3 49 against 33)
   bool transpose_b = false;
   if (!trans_b && p.variant >= NIMBLE_VAR_T32x128) {
-    if (workspace_bytes >= p.workspace_bytes && batch <= 65535) {
+    if (workspace_bytes >= p.workspace_bytes && (double)batch * (double)M * (double)N * (double)K >= 4e9) {
       transpose_b = true;
     } else {
-      rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_GENERIC, PlanOptions(), &p);
+      rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_GENERIC, any_b, &p);
       if (rc != NIMBLE_OK) return rc;
     }
   }
@@ -392,7 +430,7 @@ int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch
   }
   // batch slices of a K-contiguous operand stay 16-byte aligned only if M*K (N*K) is a multiple of 8
   if (p.variant != NIMBLE_VAR_GENERIC && (((M * K) & 7) != 0 || ((N * K) & 7) != 0)) {
-    rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_GENERIC, PlanOptions(), &p);
+    rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_GENERIC, any_b, &p);
     if (rc != NIMBLE_OK) return rc;
   }
   // one launch over all rows: a plan that splits rows or K would run the r = 0 copy past M

@@ -36,7 +36,13 @@ struct SkinnyArgs {
 // 7-9 % faster, 134 MB layers (two workgroups per compute unit) unchanged at one row and 7-10 %
 // slower at 8-16 rows, K = 768 layers 3 % slower (the steps past the end still cost an MFMA
 // each), hence the conditions.
-template <int MT, bool LSTM, int U = 8>
+template <bool ANYK>
+__device__ __forceinline__ uint4 load_chunk(const u16* p, int left, int K) {
+  if (!ANYK) return *(const uint4*)p;
+  return left >= 8 ? load8_unaligned(p) : load8_tail(p, left, K);
+}
+
+template <int MT, bool LSTM, int U = 8, bool ANYK = false>
 __global__ void __launch_bounds__(256) skinny_kernel(SkinnyArgs s) {
   __shared__ float red[4][MT][16][17];
 
@@ -113,7 +119,7 @@ __global__ void __launch_bounds__(256) skinny_kernel(SkinnyArgs s) {
     for (int u = 0; u < U; ++u) {
       const int k = (s0 + u) * 32 + gq * 8;
       const bool ok = (s0 + u < s_end) && (k < K);
-      wv[u] = ok ? *(const uint4*)(wp + (long long)(s0 + u) * 32) : make_uint4(0, 0, 0, 0);
+      wv[u] = ok ? load_chunk<ANYK>(wp + (long long)(s0 + u) * 32, K - k, K) : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
     for (int t = 0; t < MT; ++t) {
@@ -123,7 +129,7 @@ __global__ void __launch_bounds__(256) skinny_kernel(SkinnyArgs s) {
         const int k = (s0 + u) * 32 + gq * 8;
         const bool ok = mvalid[t] && (s0 + u < s_end) && (k < K);
         const u16* src = (LSTM && k >= s.Ix) ? hp[t] : xp[t];
-        xv[u] = ok ? *(const uint4*)(src + k) : make_uint4(0, 0, 0, 0);
+        xv[u] = ok ? load_chunk<ANYK>(src + k, K - k, K) : make_uint4(0, 0, 0, 0);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u)
