@@ -392,7 +392,7 @@ def small_m_probe():
         del gr
         # algorithmic bytes: q, k, v in and o out for the fused kernel; the chain adds S (f32 out and in) and P
         # (bf16 out and in): 144 L^2
-        res["roofline"] = _roof("hbm", 6144.0 * L / res["fused_us_graph"] / 1e3, "GB/s", kernel="attention64_kernel",
+        res["roofline"] = _roof("hbm", 6144.0 * L / res["fused_us_graph"] / 1e3, "GB/s", kernel="attention_kernel",
                                 timing="20 launches replayed as a HIP graph",
                                 note="latency-bound: a few hundred KB per call, 24-96 workgroups")
         res["roofline_chain"] = _roof("hbm", (6144.0 * L + 144.0 * L * L) / res["chain_us"] / 1e3, "GB/s",

@@ -7,14 +7,6 @@
 
 namespace nimble {
 
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
-// Transposing LDS read: the 16 lanes of a group each name 8 bytes; they are taken as 4 rows of 16
-// 16-bit values (lanes 4 r .. 4 r + 3 hold row r) and lane i of the group receives column i.
-__device__ __forceinline__ uint2 lds_read_tr16(uint32_t lds_addr) {
-  typedef __attribute__((address_space(3))) s16x4_t* ptr;
-  return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((ptr)(uintptr_t)lds_addr));
-}
-
 // ---------------------------------------------------------------------------
 // C = epi(alpha A.B + bias) with no condition on the shape.  A row of an operand with K % 8 != 0
 // starts at any even address, so neither the direct global->LDS loads nor aligned vector loads can

@@ -1,0 +1,285 @@
+// Fused attention for head dimension 64.
+#ifndef NIMBLE_ATTENTION_KERNEL_H_
+#define NIMBLE_ATTENTION_KERNEL_H_
+#include <type_traits>
+
+#include "device_common.h"
+
+namespace nimble {
+
+// ---------------------------------------------------------------------------
+// O = softmax(alpha Q.K^T) V per head, in one launch, the scores never leave the chip.
+//   Workgroup: RW waves of 32 query rows each, times KG key groups.  Key group g walks the blocks of 64
+//   keys g, g + KG, ... with a running score reference and row sum; with KG > 1 the groups' results meet
+//   in LDS at the end.
+//   scores:  MFMA 32x32x16 with 32 key rows on the A side and the wave's 32 query rows on the B side: a
+//            lane holds, for its query row lane & 31, the keys 32 t + 8 b + 4 (lane >> 5) + e of key
+//            tile t (b, e = 0..3).
+//   P.V:     k runs over keys, in an order that is free: the 8 k slots of half h = lane >> 5 in MFMA u are
+//            DEFINED as the 8 keys the half already holds, 16 u + 4 h + (0..3) and 16 u + 8 + 4 h + (0..3), so P
+//            goes from the score accumulators to the MFMA operand without leaving the lane.  The matching
+//            values of V come out of the row-major tile with the transposing LDS read.
+//   K and V blocks: direct global->LDS loads of whole 128-byte rows, S slots each per key group; chunk c of
+//   K row r sits at c ^ ((r >> 1) & 7), of V row r at c ^ (4 ((r >> 1) & 1)) (conflict-free for the 16-byte
+//   reads and for the transposing reads).
+//   Pipeline: the scores of block i + 1 are multiplied while the probabilities of block i are formed; K of
+//   block i + 2 and V of block i + 1 load meanwhile.
+//   Softmax in base 2 on the raw scores (alpha > 0, checked by the entry point): p = 2^(a2 s - a2 max) with
+//   a2 = alpha log2 e is one fused multiply-add and one exp2 per score; the running output is rescaled only when
+//   some row's maximum moved.  (Rescaling only once a maximum has grown by 2^8 saves a tenth of the time, but then the
+//   largest probabilities are no longer exactly 1 and the error against 64 bits grows from 2.19e-3 to 2.3e-3.)
+//   What bounds it: per block of 64 keys and 32 rows about 1050 clocks of vector instructions, half of them the
+//   exponentials, under which 512 clocks of MFMA run; 96 heads of 2048 keys: 122 us (845 TFLOP/s), the vector
+//   instructions alone 84-96 at 2.1-2.4 GHz.  The kernel before it (16 rows per wave, V transposed through
+//   registers with 2-byte LDS writes): 216 us; 12 heads of 512 keys 9.8 -> 5.8.  Without the overlap of
+//   two blocks 140; eight row waves per workgroup 123, two 152.
+// ---------------------------------------------------------------------------
+template <int RW, int KG, int S>
+__global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_eu(2, 4)))
+    attention_kernel(const u16* __restrict__ q, const u16* __restrict__ k, const u16* __restrict__ v,
+                     u16* __restrict__ o, int L, float alpha) {
+  constexpr int D = 64, BJ = 64;
+  constexpr int TILE = BJ * 8;         // uint4 per tile of K or V
+  constexpr int LD = 8 / RW;           // direct loads per wave and tile
+  static_assert(8 % RW == 0 && (S == 1 || S == 2), "tiles are filled in 8 loads");
+  // per key group: S tiles of K, then S tiles of V
+  __shared__ __attribute__((aligned(256))) uint4 ring[KG][2][S][TILE];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rw = wave % RW, kg = wave / RW;
+  const int r32 = lane & 31, h = lane >> 5;
+  // contiguous runs of (head, query block) per XCD: the query blocks of a head meet in one L2
+  int qb, head_i;
+  {
+    const unsigned nb = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned per = nb >> 3, rem = nb & 7, xcd = id & 7;
+    const unsigned pid = xcd * per + (xcd < rem ? xcd : rem) + (id >> 3);
+    head_i = (int)(pid / gridDim.x);
+    qb = (int)(pid % gridDim.x);
+  }
+  const long long head = (long long)head_i * L * D;
+  const int m_row = (qb * RW + rw) * 32 + r32;
+  const int m_ld = m_row < L ? m_row : L - 1;
+
+  const int nblk = (L + BJ - 1) / BJ;            // key blocks of the head
+  const int steps = (nblk + KG - 1) / KG;        // walked by every group (the barriers are the workgroup's)
+  const int mine = (nblk - kg + KG - 1) / KG;    // of this group
+
+  // direct loads: instruction j of a tile brings rows 8 j .. 8 j + 7, lane -> row 8 j + (lane >> 3), physical
+  // chunk lane & 7
+  const int rr = lane >> 3;
+  const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(lds_addr_of(&ring[kg][0][0][0]));
+  auto issue = [&](auto is_v, int i) {  // K or V tile of block i of this group
+    constexpr bool V = decltype(is_v)::value;
+    const int j0 = (i * KG + kg) * BJ;
+    const u16* base = (V ? v : k) + head + (long long)j0 * D;
+    const uint32_t dst = ring_lds + ((V ? S : 0) + (S == 1 ? 0 : (i & 1))) * (TILE * 16);
+    const int last = L - 1 - j0;                 // rows past the head's last one repeat it
+#pragma unroll
+    for (int n = 0; n < LD; ++n) {
+      const int j = rw * LD + n;
+      int row = j * 8 + rr;
+      const int c = (lane & 7) ^ (V ? 4 * ((row >> 1) & 1) : ((row >> 1) & 7));
+      row = row < last ? row : last;
+      dma16_so((uint32_t)(row * D + c * 8) * 2u, base, dst + j * 1024);
+    }
+  };
+  using K_TILE = std::false_type;
+  using V_TILE = std::true_type;
+  if (mine > 0) issue(K_TILE{}, 0), issue(V_TILE{}, 0);
+  if (S > 1 && mine > 1) issue(K_TILE{}, 1);
+
+  // the wave's query fragments: row m, d = 16 dd + 8 h .. + 7
+  bf16x8 qf[4];
+#pragma unroll
+  for (int dd = 0; dd < 4; ++dd)
+    qf[dd] = as_bf16x8(*(const uint4*)(q + head + (long long)m_ld * D + dd * 16 + h * 8));
+
+  f32x16 oacc[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
+  float ref = -3.0e38f;                          // in raw-score units; finite: a block of infinitely low scores adds zeros
+  float sum0 = 0.f, sum1 = 0.f;                  // this lane's share of the row sum
+  const float a2 = alpha * 1.4426950408889634f;
+
+  // fragment addresses within a tile: K chunk 2 dd + h of row r32, and the transposing reads of V
+  const int ksw = (r32 >> 1) & 7;
+  const int i16 = lane & 15, dh = (lane >> 4) & 1;
+  const uint32_t v_off = (uint32_t)((4 * h + (i16 >> 2)) * 128 +
+                                    (((2 * dh + ((i16 & 3) >> 1)) ^ (4 * ((i16 >> 3) & 1))) * 16) + (i16 & 1) * 8);
+  auto qk = [&](f32x16& s, int ks_slot, int t, int dd) {
+    const uint4* ks = &ring[kg][0][ks_slot][0];
+    const bf16x8 kf = as_bf16x8(ks[(t * 32 + r32) * 8 + ((2 * dd + h) ^ ksw)]);
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[dd], dd == 0 ? zero : s, 0, 0, 0);
+  };
+
+  // Block i: its scores are in `s`; the scores of block i + 1 go to `sn` (NEXT) while the probabilities of
+  // block i are formed, so the matrix core works under the exponentials.
+  auto block = [&](auto next_tag, auto slot_tag, int i, f32x16 (&s)[2], f32x16 (&sn)[2]) {
+    constexpr bool NEXT = decltype(next_tag)::value;
+    constexpr int SL = decltype(slot_tag)::value, KN = S == 1 ? 0 : SL ^ 1;
+    if (!NEXT) {
+      const int j0 = (i * KG + kg) * BJ;
+      if (j0 + BJ > L) {  // uniform; keys past L exist only in the head's last block
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int e = 0; e < 16; ++e)
+            if (j0 + t * 32 + (e >> 2) * 8 + h * 4 + (e & 3) >= L) s[t][e] = -INFINITY;
+      }
+    }
+    if (NEXT) {
+      qk(sn[0], KN, 0, 0);
+      qk(sn[1], KN, 1, 0);
+    }
+    float bmax = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+    for (int e = 1; e < 16; ++e) bmax = fmaxf(fmaxf(bmax, s[0][e]), s[1][e]);
+    {  // the row's other half
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bmax), __float_as_uint(bmax), false, false);
+      bmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    }
+    if (__any(bmax > ref)) {
+      const float nref = fmaxf(ref, bmax);
+      const float rescale = __builtin_amdgcn_exp2f((ref - nref) * a2);  // (of zeros in the first block)
+      sum0 *= rescale;
+      sum1 *= rescale;
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[t][e] *= rescale;
+      ref = nref;
+    }
+    const float nm2 = -ref * a2;
+    const uint32_t vs0 = lds_addr_of(&ring[kg][1][S == 1 ? 0 : SL][0]) + v_off, vs1 = vs0 ^ 64;  // d 0..31, 32..63
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (NEXT && u < 3) {
+        qk(sn[0], KN, 0, u + 1);
+        qk(sn[1], KN, 1, u + 1);
+      }
+      // 16 keys: probabilities, then O += P.V
+      float p[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        p[e] = __builtin_amdgcn_exp2f(fmaf(s[u >> 1][(u & 1) * 8 + e], a2, nm2));
+        if (e & 1) sum1 += p[e]; else sum0 += p[e];
+      }
+      const bf16x8 pf = as_bf16x8(make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
+                                             pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7])));
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint32_t a = (t ? vs1 : vs0) + u * 2048;
+        const uint2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 1024);
+        oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)), pf, oacc[t], 0, 0, 0);
+      }
+    }
+  };
+  auto arrive = [&](int i) {  // K of block i + 1 and V of block i are there; the tiles read before are refilled
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (S > 1) {
+      if (i + 2 < mine) issue(K_TILE{}, i + 2);
+      if (i + 1 < mine) issue(V_TILE{}, i + 1);
+    }
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  f32x16 sa[2], sb[2];
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (KG == 1 || mine > 0) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int dd = 0; dd < 4; ++dd) qk(sa[t], 0, t, dd);
+  }
+  if constexpr (S == 1) {
+    if (mine > 0) block(std::false_type{}, S0{}, 0, sa, sb);
+  } else {
+    int i = 0;
+    for (; i + 2 < mine; i += 2) {
+      arrive(i);
+      block(std::true_type{}, S0{}, i, sa, sb);
+      arrive(i + 1);
+      block(std::true_type{}, S1{}, i + 1, sb, sa);
+    }
+    if (i + 1 < mine) {
+      arrive(i);
+      block(std::true_type{}, S0{}, i, sa, sb);
+      arrive(i + 1);
+      block(std::false_type{}, S1{}, i + 1, sb, sa);
+    } else if (KG == 1 || i < mine) {
+      arrive(i);
+      block(std::false_type{}, S0{}, i, sa, sb);
+    }
+    if (KG > 1 && mine < steps) arrive(mine);    // (every group passes as many barriers)
+  }
+  float sum = sum0 + sum1;
+  sum += __shfl_xor(sum, 32, 64);
+
+  if constexpr (KG == 1) {
+    const float inv = 1.0f / sum;
+    if (m_row < L) {
+      // accumulator element e of tile t: d = 32 t + 8 (e >> 2) + 4 h + (e & 3)
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          uint2 pk;
+          pk.x = pack_bf16x2(oacc[t][4 * b] * inv, oacc[t][4 * b + 1] * inv);
+          pk.y = pack_bf16x2(oacc[t][4 * b + 2] * inv, oacc[t][4 * b + 3] * inv);
+          *(uint2*)(o + head + (long long)m_row * D + t * 32 + b * 8 + h * 4) = pk;
+        }
+    }
+  } else {
+    // the groups' outputs [group][row][64 d] (a row's 16-byte pieces spread over the banks) and their
+    // (ref, sum) pairs; each wave then finishes its share of the rows, adding the groups in order
+    constexpr int ROWS = RW * 32, T = RW * KG * 64;
+    static_assert(KG * ROWS * 64 * 4 <= KG * S * 2 * TILE * 16, "the partial outputs reuse the ring");
+    __shared__ float2 stat[KG][ROWS];
+    float4* part = (float4*)&ring[0][0][0][0];
+    const int row = rw * 32 + r32;
+    if (h == 0) stat[kg][row] = make_float2(ref, sum);
+    __syncthreads();
+    float top = stat[0][row].x;
+#pragma unroll
+    for (int g2 = 1; g2 < KG; ++g2) top = fmaxf(top, stat[g2][row].x);
+    const float scale = __builtin_amdgcn_exp2f((ref - top) * a2);  // 0 for a group without a block
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        const int c = t * 8 + b * 2 + h;
+        part[(kg * ROWS + row) * 16 + (c ^ (row & 15))] =
+            make_float4(oacc[t][4 * b] * scale, oacc[t][4 * b + 1] * scale, oacc[t][4 * b + 2] * scale, oacc[t][4 * b + 3] * scale);
+      }
+    __syncthreads();
+#pragma unroll
+    for (int x = tid; x < ROWS * 16; x += T) {
+      const int rrow = x >> 4, c = x & 15, m = qb * ROWS + rrow;
+      float tp = stat[0][rrow].x;
+#pragma unroll
+      for (int g2 = 1; g2 < KG; ++g2) tp = fmaxf(tp, stat[g2][rrow].x);
+      float total = 0.f;
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int g2 = 0; g2 < KG; ++g2) {
+        const float2 st = stat[g2][rrow];
+        total += st.y * __builtin_amdgcn_exp2f((st.x - tp) * a2);
+        const float4 w = part[(g2 * ROWS + rrow) * 16 + (c ^ (rrow & 15))];
+        a.x += w.x, a.y += w.y, a.z += w.z, a.w += w.w;
+      }
+      const float inv = 1.0f / total;
+      if (m < L)
+        *(uint2*)(o + head + (long long)m * D + c * 4) =
+            make_uint2(pack_bf16x2(a.x * inv, a.y * inv), pack_bf16x2(a.z * inv, a.w * inv));
+    }
+  }
+}
+
+}  // namespace nimble
+#endif

@@ -20,9 +20,9 @@
 //       workgroup and K in whole 64-wide stages: operands staged through per-wave LDS rings by
 //       direct global->LDS loads of whole 128-byte lines (what bounds skinny_kernel is cache-line
 //       look-ups, 64 per KiB with its register-layout loads).
-//   misc_kernels.h       generic_kernel (any shape and stride, one thread per output),
-//       softmax_rows_kernel (f32 scores -> bf16 probabilities), attention64_kernel (fused
-//       softmax(alpha Q.K^T).V for head dimension 64).
+//   attention_kernel.h   attention_kernel<RW,KG,S>: fused softmax(alpha Q.K^T).V for head dimension 64, K and V
+//       streamed through LDS, the keys optionally spread over groups of waves.
+//   misc_kernels.h       softmax_rows_kernel (f32 scores -> bf16 probabilities), transpose_kn_kernel.
 //   probe_kernels.h      calibration probes: a register-only MFMA loop and a streaming read.
 #include <hip/hip_runtime.h>
 
@@ -31,6 +31,7 @@
 #include <mutex>
 
 #include "any_kernel.h"
+#include "attention_kernel.h"
 #include "device_common.h"
 #include "gemm_ring_kernel.h"
 #include "misc_kernels.h"
@@ -216,6 +217,44 @@ static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
       }
     default: return fail(NIMBLE_ERR_ARG, "unknown variant %d", p.variant);
   }
+}
+
+template <int RW, int KG, int S>
+static void launch_attention_as(const u16* q, const u16* k, const u16* v, u16* o, int heads, int L, float alpha,
+                                hipStream_t st) {
+  const dim3 grid((unsigned)((L + RW * 32 - 1) / (RW * 32)), (unsigned)heads), block(RW * KG * 64);
+  hipLaunchKernelGGL((attention_kernel<RW, KG, S>), grid, block, 0, st, q, k, v, o, L, alpha);
+}
+
+// Waves per workgroup and how the keys are split, by how many workgroups the query rows give and how many
+// blocks of 64 keys there are.  While tiles of 32 (64) rows do not fill the compute units the keys are
+// spread over groups of waves: one block per group where that is enough (nothing is ever reloaded: one slot), a ring
+// of two slots beyond.  Measured as graph replays, microseconds, chosen variant against the next one:
+// 12 x 512: 5.8 (one row wave, eight groups) / 6.6 (four groups); 24 x 333 (264 tiles of 32 rows) 8.9 / 7.1 (two
+// row waves, four groups), hence the line at one workgroup per compute unit; 12 x 1024 10.0 / 13.8 (four
+// row waves, two groups); 12 x 2048 (384 tiles of 64 rows) 28.3 / 23.2; 48 x 512 9.8 / 9.6 (no groups), but with
+// more than eight blocks, 24 x 1024, 14.2 / 15.4; 48 x 1024 26.8 / 23.3.
+static int launch_attention(const u16* q, const u16* k, const u16* v, u16* o, int heads, int L, float alpha,
+                            hipStream_t st) {
+  const int blocks = (L + 63) / 64;
+  auto tiles = [&](int rows) { return (long long)heads * ((L + rows - 1) / rows); };
+  if (blocks == 1)
+    launch_attention_as<1, 1, 1>(q, k, v, o, heads, L, alpha, st);
+  else if (blocks <= 4 && tiles(32) <= kComputeUnits)
+    launch_attention_as<1, 4, 1>(q, k, v, o, heads, L, alpha, st);
+  else if (blocks <= 8 && tiles(32) <= kComputeUnits)
+    launch_attention_as<1, 8, 1>(q, k, v, o, heads, L, alpha, st);
+  else if (blocks <= 2 && tiles(64) <= kComputeUnits)
+    launch_attention_as<2, 2, 1>(q, k, v, o, heads, L, alpha, st);
+  else if (blocks <= 4 && tiles(64) <= kComputeUnits)
+    launch_attention_as<2, 4, 1>(q, k, v, o, heads, L, alpha, st);
+  else if (tiles(64) <= kComputeUnits)
+    launch_attention_as<2, 4, 2>(q, k, v, o, heads, L, alpha, st);
+  else if (blocks > 8 && tiles(128) <= kComputeUnits)
+    launch_attention_as<4, 2, 2>(q, k, v, o, heads, L, alpha, st);
+  else
+    launch_attention_as<4, 1, 2>(q, k, v, o, heads, L, alpha, st);
+  return check_hip(hipGetLastError(), "attention kernel launch");
 }
 
 static inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
@@ -465,14 +504,7 @@ int nimble_attention_dyn(const void* q, const void* k, const void* v, void* o, i
   if (!q || !k || !v || !o) return fail(NIMBLE_ERR_NULL, "null tensor pointer");
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o))
     return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
-  dim3 grid((unsigned)((L + 63) / 64), (unsigned)heads);
-  static const bool blocks64 = std::getenv("NIMBLE_ATT_BLOCK64") != nullptr;  // measurement knob
-  const u16 *qp = (const u16*)q, *kp = (const u16*)k, *vp = (const u16*)v;
-  if (L <= 64 || blocks64)
-    hipLaunchKernelGGL(attention64_kernel<64>, grid, dim3(256), 0, (hipStream_t)stream, qp, kp, vp, (u16*)o, (int)L, alpha);
-  else
-    hipLaunchKernelGGL(attention64_kernel<128>, grid, dim3(256), 0, (hipStream_t)stream, qp, kp, vp, (u16*)o, (int)L, alpha);
-  return check_hip(hipGetLastError(), "attention kernel launch");
+  return launch_attention((const u16*)q, (const u16*)k, (const u16*)v, (u16*)o, (int)heads, (int)L, alpha, (hipStream_t)stream);
 }
 
 int nimble_lstm_gates_dyn(const void* x, const void* h_prev, const void* w, const void* bias,
