@@ -242,6 +242,15 @@ int nimble_softmax_rows_dyn(const void* s_f32, void* p_bf16, int64_t rows, int64
 int nimble_attention_dyn(const void* q, const void* k, const void* v, void* o, int64_t heads,
                          int64_t L, int64_t D, float alpha, void* stream);
 
+/* The same chain with its intermediate results as outputs: s [heads, M, N] f32 = alpha q.k^T,
+ * p [heads, M, N] bf16 = softmax rows of s, o [heads, M, Dv] bf16 = p.v, for q [heads, M, D],
+ * k [heads, N, D], v [heads, N, Dv] and any alpha.  One launch for D = Dv = 64 and M = N <= 512;
+ * other shapes run nimble_batch_matmul_dyn, nimble_softmax_rows_dyn and nimble_batch_matmul_dyn
+ * (workspace: as there, for the second product). */
+int nimble_attention_chain_dyn(const void* q, const void* k, const void* v, void* s, void* p, void* o,
+                               int64_t heads, int64_t M, int64_t N, int64_t D, int64_t Dv, float alpha,
+                               void* workspace, size_t workspace_bytes, void* stream);
+
 /* Fused LSTM cell with dynamic batch B (gate blocks of w and bias in the order
  * i, f, g, o, H rows each):
  *   G = [x | h_prev] . w^T + bias;  c_out = sig(f) c_prev + sig(i) tanh(g);

@@ -107,6 +107,8 @@ def load():
                                             ctypes.c_size_t, vp]
     lib.nimble_softmax_rows_dyn.argtypes = [vp, vp, i64, i64, vp]
     lib.nimble_attention_dyn.argtypes = [vp, vp, vp, vp, i64, i64, i64, ctypes.c_float, vp]
+    lib.nimble_attention_chain_dyn.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, i64, ctypes.c_float, vp,
+                                               ctypes.c_size_t, vp]
     lib.nimble_lstm_gates_dyn.argtypes = [vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, vp, ctypes.c_size_t, vp]
     lib.nimble_lstm_gates_pre_dyn.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, vp]
     lib.nimble_lstm_seq_shape.argtypes = [ip, ip, ip, ip, ip, ip]
@@ -346,6 +348,13 @@ def nimble_softmax_rows_dyn(s_f32: int, p_bf16: int, rows: int, cols: int, strea
 def nimble_attention_dyn(q: int, k: int, v: int, o: int, heads: int, L: int, D: int, alpha: float,
                          stream: int = 0) -> None:
     _check(load().nimble_attention_dyn(q, k, v, o, heads, L, D, alpha, stream))
+
+
+def nimble_attention_chain_dyn(q: int, k: int, v: int, s: int, p: int, o: int, heads: int, M: int, N: int, D: int,
+                               Dv: int, alpha: float, workspace: int = 0, workspace_bytes: int = 0,
+                               stream: int = 0) -> None:
+    _check(load().nimble_attention_chain_dyn(q, k, v, s, p, o, heads, M, N, D, Dv, alpha, workspace, workspace_bytes,
+                                             stream))
 
 
 def nimble_lstm_gates_dyn(x: int, h_prev: int, w: int, bias: int, c_prev: int, c_out: int, h_out: int,

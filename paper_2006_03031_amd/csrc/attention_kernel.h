@@ -1,4 +1,4 @@
-// Fused attention for head dimension 64.
+// Fused attention for head dimension 64, without and with its intermediate results.
 #ifndef NIMBLE_ATTENTION_KERNEL_H_
 #define NIMBLE_ATTENTION_KERNEL_H_
 #include <type_traits>
@@ -278,6 +278,235 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
         *(uint2*)(o + head + (long long)m * D + c * 4) =
             make_uint2(pack_bf16x2(a.x * inv, a.y * inv), pack_bf16x2(a.z * inv, a.w * inv));
     }
+  }
+}
+
+// A wave's LDS accesses execute in the order issued; this keeps the compiler from issuing them in another
+// order than the source's where one piece of LDS is used as different types in turn.
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
+// ---------------------------------------------------------------------------
+// The attention chain with its intermediate results, in one launch: S = alpha Q.K^T (f32), P = softmax rows of S
+// (bf16), O = P.V, for head dimension 64 and up to 64 KG keys.
+//   Workgroup: 32 query rows, KG waves; wave g owns keys 64 g .. 64 g + 63 and keeps their scores in registers,
+//   in the layout of attention_kernel, from the first product to the second: S and P are written out once and never
+//   read back.  The waves' row maxima, row sums and shares of O meet in LDS.  S and P leave through the wave's K
+//   tile, which is free by then, so that a store covers whole row segments (their rows start at any element: L is
+//   any number).  The loads of K and V are all issued at the start.
+//   What bounds it: the launch and the chain load, score, reduce, store; with many heads the 6 L^2 bytes per head
+//   that leave.  Graph replays, microseconds, three launches -> one: 12 heads of 23 tokens 10.5 -> 5.4, 333 20.7 -> 8.5,
+//   512 27.9 -> 9.6; 96 heads of 512 99 -> 44 (at 151 MB written 3.5 TB/s).  A last block written element by element
+//   instead of in pieces of 16 bytes cost 2.6 us.
+// ---------------------------------------------------------------------------
+template <int KG>
+__global__ void __launch_bounds__(KG * 64)
+    attention_chain_kernel(const u16* __restrict__ q, const u16* __restrict__ k, const u16* __restrict__ v,
+                           float* __restrict__ s_out, u16* __restrict__ p_out, u16* __restrict__ o, int L, float alpha) {
+  constexpr int D = 64, BJ = 64, TILE = BJ * 8, T = KG * 64;
+  __shared__ __attribute__((aligned(256))) uint4 tiles[KG][2][TILE];  // K, V
+  __shared__ float red_max[KG][32], red_sum[KG][32];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int kg = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r32 = lane & 31, h = lane >> 5;
+  int qb, head_i;
+  {  // contiguous runs of (head, query block) per XCD
+    const unsigned nb = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
+    const unsigned per = nb >> 3, rem = nb & 7, xcd = id & 7;
+    const unsigned pid = xcd * per + (xcd < rem ? xcd : rem) + (id >> 3);
+    head_i = (int)(pid / gridDim.x);
+    qb = (int)(pid % gridDim.x);
+  }
+  const long long head = (long long)head_i * L * D, plane = (long long)head_i * L * L;
+  const int m0 = qb * 32;
+  const int m_ld = m0 + r32 < L ? m0 + r32 : L - 1;
+  const int j0 = kg * BJ;
+  const int keys = L - j0 < BJ ? (L - j0 < 0 ? 0 : L - j0) : BJ;  // of this wave (uniform)
+
+  const int rr = lane >> 3;
+  const uint32_t k_lds = __builtin_amdgcn_readfirstlane(lds_addr_of(&tiles[kg][0][0]));
+  if (keys > 0) {
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {  // 8 rows each: K, then V
+      int row = (j & 7) * 8 + rr;
+      const int c = (lane & 7) ^ (j >= 8 ? 4 * ((row >> 1) & 1) : ((row >> 1) & 7));
+      row = row < keys ? row : keys - 1;
+      dma16_so((uint32_t)(row * D + c * 8) * 2u, (j >= 8 ? v : k) + head + (long long)j0 * D, k_lds + j * 1024);
+    }
+  }
+  bf16x8 qf[4];
+#pragma unroll
+  for (int dd = 0; dd < 4; ++dd)
+    qf[dd] = as_bf16x8(*(const uint4*)(q + head + (long long)m_ld * D + dd * 16 + h * 8));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the tiles are the wave's own: no barrier)
+  if (keys > 0 && keys < BJ && lane < BJ - keys) {
+    // rows of V past the last key are multiplied by zeros: they must be finite
+#pragma unroll
+    for (int c = 0; c < 8; ++c) tiles[kg][1][(keys + lane) * 8 + c] = make_uint4(0, 0, 0, 0);
+  }
+
+  f32x16 s[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) s[t][e] = 0.f;
+  float mx = -INFINITY;
+  uint4* const stage = &tiles[kg][0][0];
+  if (keys > 0) {
+    const int ksw = (r32 >> 1) & 7;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int dd = 0; dd < 4; ++dd) {
+        const bf16x8 kf = as_bf16x8(stage[(t * 32 + r32) * 8 + ((2 * dd + h) ^ ksw)]);
+        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[dd], s[t], 0, 0, 0);
+      }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s[t][e] = fmaf(alpha, s[t][e], 0.f);  // (the products' epilogue)
+    lds_order();
+    // S through the K tile: [32 rows][16 chunks of 4 keys], chunk c of row r at c ^ (r & 15)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        ((float4*)stage)[r32 * 16 + ((t * 8 + b * 2 + h) ^ (r32 & 15))] =
+            make_float4(s[t][4 * b], s[t][4 * b + 1], s[t][4 * b + 2], s[t][4 * b + 3]);
+    if (keys < BJ) {  // uniform
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          if (t * 32 + (e >> 2) * 8 + h * 4 + (e & 3) >= keys) s[t][e] = -INFINITY;
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+  }
+  if (KG > 1) {
+    if (h == 0) red_max[kg][r32] = mx;
+    __syncthreads();
+    mx = red_max[0][r32];
+#pragma unroll
+    for (int g = 1; g < KG; ++g) mx = fmaxf(mx, red_max[g][r32]);
+  }
+  lds_order();
+  if (keys > 0) {
+    float* C = s_out + plane + j0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = i * 4 + (lane >> 4), c = lane & 15;
+      const float4 w = ((const float4*)stage)[row * 16 + (c ^ (row & 15))];
+      if (m0 + row < L && c * 4 + 4 <= keys) __builtin_memcpy(C + (long long)(m0 + row) * L + c * 4, &w, 16);
+    }
+    if (keys & 3) {  // the piece of a row that the last key ends
+      const int row = r32, c = keys >> 2;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int e = 2 * i + h;
+        const float w = ((const float*)stage)[(row * 16 + (c ^ (row & 15))) * 4 + e];
+        if (m0 + row < L && e < (keys & 3)) C[(long long)(m0 + row) * L + c * 4 + e] = w;
+      }
+    }
+  }
+  // probabilities: 2^((s - max) log2 e)
+  float sum = 0.f;
+  constexpr float kLog2e = 1.4426950408889634f;
+  const float nm2 = -mx * kLog2e;
+  if (keys > 0) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        s[t][e] = __builtin_amdgcn_exp2f(fmaf(s[t][e], kLog2e, nm2));
+        sum += s[t][e];
+      }
+  }
+  sum += __shfl_xor(sum, 32, 64);
+  if (KG > 1) {
+    if (h == 0) red_sum[kg][r32] = sum;
+    __syncthreads();
+    sum = red_sum[0][r32];
+#pragma unroll
+    for (int g = 1; g < KG; ++g) sum += red_sum[g][r32];
+  }
+  const float inv = 1.0f / sum;
+  f32x16 oacc[2];
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
+  if (keys > 0) {
+    uint4 pw[4];  // 16 keys each: the operand of P.V, and what P holds
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const f32x16& e = s[u >> 1];
+      const int b = (u & 1) * 8;
+      pw[u] = make_uint4(pack_bf16x2(e[b] * inv, e[b + 1] * inv), pack_bf16x2(e[b + 2] * inv, e[b + 3] * inv),
+                         pack_bf16x2(e[b + 4] * inv, e[b + 5] * inv), pack_bf16x2(e[b + 6] * inv, e[b + 7] * inv));
+    }
+    lds_order();
+    // P through the K tile: [32 rows][8 chunks of 8 keys], chunk c of row r at c ^ (r & 7)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      uint2* row = (uint2*)(stage + r32 * 8);
+      row[((2 * u) ^ (r32 & 7)) * 2 + h] = make_uint2(pw[u].x, pw[u].y);
+      row[((2 * u + 1) ^ (r32 & 7)) * 2 + h] = make_uint2(pw[u].z, pw[u].w);
+    }
+    const int i16 = lane & 15, dh = (lane >> 4) & 1;
+    const uint32_t vs0 = lds_addr_of(&tiles[kg][1][0]) +
+                         (uint32_t)((4 * h + (i16 >> 2)) * 128 +
+                                    (((2 * dh + ((i16 & 3) >> 1)) ^ (4 * ((i16 >> 3) & 1))) * 16) + (i16 & 1) * 8);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const uint32_t a = (t ? vs0 ^ 64 : vs0) + u * 2048;
+        const uint2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 1024);
+        oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)), as_bf16x8(pw[u]),
+                                                          oacc[t], 0, 0, 0);
+      }
+    lds_order();
+    u16* C = p_out + plane + j0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = i * 8 + (lane >> 3), c = lane & 7;
+      const uint4 w = stage[row * 8 + (c ^ (row & 7))];
+      if (m0 + row < L && c * 8 + 8 <= keys) __builtin_memcpy(C + (long long)(m0 + row) * L + c * 8, &w, 16);
+    }
+    if (keys & 7) {
+      const int row = r32, c = keys >> 3;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int e = 2 * i + h;
+        const u16 w = ((const u16*)stage)[(row * 8 + (c ^ (row & 7))) * 8 + e];
+        if (m0 + row < L && e < (keys & 7)) C[(long long)(m0 + row) * L + c * 8 + e] = w;
+      }
+    }
+  }
+  // the waves' shares of O, 8 KiB each over their own tiles, added in order
+  lds_order();
+  float4* part = (float4*)&tiles[0][0][0];  // group g at g * 1024: [32 rows][16 chunks of 4 d]
+#pragma unroll
+  for (int t = 0; t < 2; ++t)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      part[kg * 1024 + r32 * 16 + ((t * 8 + b * 2 + h) ^ (r32 & 15))] =
+          make_float4(oacc[t][4 * b], oacc[t][4 * b + 1], oacc[t][4 * b + 2], oacc[t][4 * b + 3]);
+  if (KG > 1) __syncthreads();
+  lds_order();
+#pragma unroll
+  for (int x = tid; x < 32 * 16; x += T) {
+    const int row = x >> 4, c = x & 15;
+    float4 a = part[row * 16 + (c ^ (row & 15))];
+#pragma unroll
+    for (int g = 1; g < KG; ++g) {
+      const float4 w = part[g * 1024 + row * 16 + (c ^ (row & 15))];
+      a.x += w.x, a.y += w.y, a.z += w.z, a.w += w.w;
+    }
+    if (m0 + row < L)
+      *(uint2*)(o + head + (long long)(m0 + row) * D + c * 4) = make_uint2(pack_bf16x2(a.x, a.y), pack_bf16x2(a.z, a.w));
   }
 }
 

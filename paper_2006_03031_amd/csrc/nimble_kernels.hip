@@ -21,7 +21,8 @@
 //       direct global->LDS loads of whole 128-byte lines (what bounds skinny_kernel is cache-line
 //       look-ups, 64 per KiB with its register-layout loads).
 //   attention_kernel.h   attention_kernel<RW,KG,S>: fused softmax(alpha Q.K^T).V for head dimension 64, K and V
-//       streamed through LDS, the keys optionally spread over groups of waves.
+//       streamed through LDS, the keys optionally spread over groups of waves; attention_chain_kernel<KG>: the same
+//       for callers who want the scores and probabilities too.
 //   misc_kernels.h       softmax_rows_kernel (f32 scores -> bf16 probabilities), transpose_kn_kernel.
 //   probe_kernels.h      calibration probes: a register-only MFMA loop and a streaming read.
 #include <hip/hip_runtime.h>
@@ -505,6 +506,38 @@ int nimble_attention_dyn(const void* q, const void* k, const void* v, void* o, i
   if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(o))
     return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
   return launch_attention((const u16*)q, (const u16*)k, (const u16*)v, (u16*)o, (int)heads, (int)L, alpha, (hipStream_t)stream);
+}
+
+int nimble_attention_chain_dyn(const void* q, const void* k, const void* v, void* s, void* p, void* o, int64_t heads,
+                               int64_t M, int64_t N, int64_t D, int64_t Dv, float alpha, void* workspace,
+                               size_t workspace_bytes, void* stream) {
+  clear_error();
+  // one launch where a workgroup's waves hold all the scores of its rows; the three calls otherwise
+  if (D == 64 && Dv == 64 && M == N && N > 0 && N <= 512 && heads > 0 && heads <= 65535) {
+    if (!q || !k || !v || !s || !p || !o) return fail(NIMBLE_ERR_NULL, "null tensor pointer");
+    if (misaligned(q) || misaligned(k) || misaligned(v) || misaligned(s) || misaligned(p) || misaligned(o))
+      return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
+    if (workspace_bytes > 0 && !workspace) return fail(NIMBLE_ERR_NULL, "workspace_bytes > 0 with a null workspace");
+    if (workspace && misaligned(workspace)) return fail(NIMBLE_ERR_ALIGN, "workspace must be 16-byte aligned");
+    const dim3 grid((unsigned)((N + 31) / 32), (unsigned)heads);
+    hipStream_t st = (hipStream_t)stream;
+    const u16 *qp = (const u16*)q, *kp = (const u16*)k, *vp = (const u16*)v;
+    const int L = (int)N;
+    if (L <= 64)
+      hipLaunchKernelGGL(attention_chain_kernel<1>, grid, dim3(64), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
+    else if (L <= 128)
+      hipLaunchKernelGGL(attention_chain_kernel<2>, grid, dim3(128), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
+    else if (L <= 256)
+      hipLaunchKernelGGL(attention_chain_kernel<4>, grid, dim3(256), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
+    else
+      hipLaunchKernelGGL(attention_chain_kernel<8>, grid, dim3(512), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
+    return check_hip(hipGetLastError(), "attention chain launch");
+  }
+  int rc = nimble_batch_matmul_dyn(q, k, s, heads, M, N, D, 1, alpha, NIMBLE_F32, workspace, workspace_bytes, stream);
+  if (rc == NIMBLE_OK) rc = nimble_softmax_rows_dyn(s, p, N > 0 ? heads * M : 0, N, stream);
+  if (rc == NIMBLE_OK)
+    rc = nimble_batch_matmul_dyn(p, v, o, heads, M, Dv, N, 0, 1.0f, NIMBLE_BF16, workspace, workspace_bytes, stream);
+  return rc;
 }
 
 int nimble_lstm_gates_dyn(const void* x, const void* h_prev, const void* w, const void* bias,

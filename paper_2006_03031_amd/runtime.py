@@ -158,10 +158,16 @@ def softmax_rows(s: torch.Tensor, out: Optional[torch.Tensor] = None) -> torch.T
 
 def attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
               alpha: float = 0.125) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
-    """S = alpha Q.K^T (f32), P = softmax rows (bf16), O = P.V (bf16)."""
-    s = batch_matmul(q, k, True, alpha, nb.F32)
-    p = softmax_rows(s)
-    o = batch_matmul(p, v, False, 1.0, nb.BF16)
+    """S = alpha Q.K^T (f32), P = softmax rows (bf16), O = P.V (bf16), through one entry point: one launch
+    for head dimension 64 and up to 512 tokens, the three calls otherwise."""
+    T, M, N = nb.batch_matmul_shape(tuple(q.shape), tuple(k.shape), True)
+    _, _, Dv = nb.batch_matmul_shape((T, M, N), tuple(v.shape), False)
+    s, p = _alloc((T, M, N), nb.F32, q.device), _alloc((T, M, N), nb.BF16, q.device)
+    o = _alloc((T, M, Dv), nb.BF16, q.device)
+    ws = default_workspace(q.device)
+    nb.nimble_attention_chain_dyn(_ptr(q, _BF, "q"), _ptr(k, _BF, "k"), _ptr(v, _BF, "v"), _ptr(s, _F32, "s"),
+                                  _ptr(p, _BF, "p"), _ptr(o, _BF, "o"), T, M, N, q.shape[2], Dv, alpha, ws.data_ptr(),
+                                  ws.numel() * ws.element_size(), _stream())
     return s, p, o
 
 

@@ -1,4 +1,4 @@
-"""Fused attention at the edges of its tiles, key blocks and launch shapes, against float64."""
+"""Fused attention and the attention chain at the edges of its tiles, key blocks and launch shapes, against float64."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -39,3 +39,43 @@ def test_fused_attention_launch_shapes(rt, heads, L, growing):
     row = ((o.double() - ref).norm(dim=-1) / (ref.norm(dim=-1) + 1e-2 * ref.norm(dim=-1).mean())).max().item()
     assert row <= 4 * TOL, row
     assert bool((buf[heads * L * 64:] == 768.0).all())
+
+
+# one, two, four and eight waves; a last wave with 1, 63 and 64 keys and waves without any; a last query tile of one
+# row; odd L (rows of S and P at any alignment); 513: the three calls
+@pytest.mark.parametrize("heads,L", [(1, 1), (3, 31), (2, 33), (5, 63), (3, 64), (2, 65), (2, 127), (3, 128), (2, 129), (1, 193),
+                                     (2, 256), (3, 257), (2, 333), (2, 448), (3, 449), (2, 511), (2, 512), (2, 513)])
+@pytest.mark.parametrize("alpha", [0.125, -0.25])
+def test_attention_chain_edges(rt, heads, L, alpha):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1000 * heads + L)
+    q, k, v = (torch.empty((heads, L, 64), device="cuda").normal_(0, 1, generator=gen).to(torch.bfloat16) for _ in range(3))
+    import paper_2006_03031_amd as nb
+    n = heads * L * L
+    sb = torch.full((n + 256,), 768.0, device="cuda")
+    pb = torch.full((n + 256,), 768.0, dtype=torch.bfloat16, device="cuda")
+    ob = torch.full((heads * L * 64 + 256,), 768.0, dtype=torch.bfloat16, device="cuda")
+    ws = rt.default_workspace(q.device)
+    nb.nimble_attention_chain_dyn(q.data_ptr(), k.data_ptr(), v.data_ptr(), sb.data_ptr(), pb.data_ptr(), ob.data_ptr(), heads,
+                                  L, L, 64, 64, alpha, ws.data_ptr(), ws.numel(), rt._stream())
+    s, p, o = sb[:n].view(heads, L, L), pb[:n].view(heads, L, L), ob[:heads * L * 64].view(heads, L, 64)
+    rs = torch.matmul(q.double(), k.double().transpose(1, 2).contiguous()) * alpha
+    rp = torch.softmax(rs, -1)
+    # S: 64 products summed in f32; P: one rounding to bf16 (2^-9) of an f32 softmax; O: its own rounding, from the P given
+    assert ((s.double() - rs).abs().max() / rs.abs().max()).item() <= 64 * 2.0 ** -24
+    assert ((p.double() - rp).abs() / rp).max().item() <= 2.0 ** -8
+    ro = torch.matmul(p.double(), v.double())
+    assert ((o.double() - ro).abs() / (ro.abs() + ro.abs().mean())).max().item() <= 2.0 ** -8
+    for b, m in ((sb, n), (pb, n), (ob, heads * L * 64)):
+        assert bool((b[m:] == 768.0).all())
+
+
+def test_attention_chain_passes_infinite_values_on(rt):
+    """The last key's row of V is infinite: the keys past it, which a wave's tile has too, add nothing."""
+    L = 333
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    q, k, v = (torch.empty((2, L, 64), device="cuda").normal_(0, 1, generator=gen).to(torch.bfloat16) for _ in range(3))
+    v[:, L - 1] = float("inf")
+    _, p, o = rt.attention(q, k, v)
+    assert bool((p[:, :, L - 1] > 0).all()) and bool((o == float("inf")).all())
