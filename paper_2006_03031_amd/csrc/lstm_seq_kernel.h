@@ -12,16 +12,16 @@ namespace nimble {
 // kernels; here the steps of a sequence run inside one launch.
 //   Inputs: pre [T, B, 4H] f32, the inputs' share of the gates with the bias added (one dense call
 //   over all T*B tokens ahead of the loop), w_h [4H, H] bf16, h_0 [B, H] bf16, c_0 [B, H] f32.
-//   Grid: H / 16 workgroups of 8 waves; a workgroup owns 16 hidden units = 64 gate rows (G = 4 groups
+//   Grid: H / 8 or H / 16 workgroups of 8 waves; a workgroup owns 4 G hidden units = 16 G gate rows (G groups
 //   of the i, f, g, o rows of 4 units) and keeps those rows of w_h in registers for the whole
 //   sequence (wave w: the 64-wide K stages w * per_wave ...: 8 registers per group and stage).  Per
 //   step a wave fetches its K range of h_{t-1}, multiplies, leaves its partial sums in LDS; after one
 //   barrier four neighbouring lanes per (row, unit) add them up and apply the nonlinearity, one gate
 //   each, and the first of them updates the cell.  c_t stays in that lane's register.
-//   Hand-over of h_t: a workgroup publishes its 32 units per row as 32-bit words, bf16 value in the
+//   Hand-over of h_t: a workgroup publishes its units per row as 32-bit words, bf16 value in the
 //   high half and a step tag (1..65535, never 0) in the low half, with device-scope stores into
-//   buffer t & 1 of two; a consumer wave loads exactly the words its MFMAs need, device scope, and
-//   repeats until every tag is this step's.  Data and arrival are one word: no counter, no fence,
+//   buffer t & 1 of two; a consumer wave loads the words of its K range once each, device scope, repeats
+//   until every tag is this step's, and brings them into the MFMA operand layout through a piece of LDS of its own.  Data and arrival are one word: no counter, no fence,
 //   one store and one load on the critical path (a counter barrier over 16 workgroups was measured
 //   at 0.85 us per step bare and 1.56 us with the data exchanged behind it).  Two buffers suffice:
 //   h_t overwrites h_{t-2}, which every workgroup has finished reading before it publishes h_{t-1},
@@ -37,13 +37,12 @@ namespace nimble {
 //   with 8 waves: the same K stages per wave, the same two accumulators per stage pair, the same
 //   order of adding the waves' partial sums, the same cell function).
 //   Measured, microseconds per step at 1 / 2 / 4 rows (a captured graph of per-step launches: 2.65-2.72 at
-//   H = 512, 2.85-2.95 at H = 1024): H = 512: 1.89 / 2.02 / 2.41; H = 1024: 2.71 / 3.20 / 3.98.  With 8 groups
-//   per workgroup (half the workgroups) 2.14 / 2.15 / 2.55 and 2.91 / 3.18 / 4.27, with 2 groups 2.08 / 2.25 /
-//   2.73: fewer groups shorten a workgroup's MFMAs and sums, more workgroups lengthen everybody's fetch.
-//   A step at one row is one trip to the memory side and back (0.75 us from the store to the polled
-//   words), the MFMAs and partial sums, the barrier, the cell arithmetic; with more rows the fetch
-//   reads that many more words per workgroup, which the per-step kernel gets from one L2, and up to 16 rows
-//   (built first) it cost 4.7 us per step: hence the limit of 4 rows.  Tried and not kept: every wave
+//   H = 512, 2.85-2.95 at H = 1024): H = 512: 1.60 / 1.63 / 1.64; H = 1024: 1.76 / - / 1.96.
+//   A step is one trip to the memory side and back (0.75 us from the store to the polled words), the MFMAs and
+//   partial sums, the barrier, the cell arithmetic.  What the polls ask of the memory side is what counts beside
+//   that: with the words loaded straight in the operand layout (8 loads per stage, every word asked for by up to 16
+//   lanes) the same steps took 1.94 / 2.12 / 2.44 and 2.80 / - / 4.02, and two or more polls in flight at staggered
+//   times made them 2.5 and more.  Tried and not kept: every wave
 //   multiplying its own 16 gate rows over the whole of K from a copy of h in LDS and updating its cells
 //   itself (no partial sums, no single epilogue: 4.1 us per step, the eight waves' reads of all of h cost
 //   more LDS time than the sums saved); all workgroups on one XCD (every 8th of a grid 8 times as large)
@@ -85,6 +84,8 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
   // the 8 groups' columns fall into different banks; a lane writes its 4 sums as one 16-byte word
   constexpr int GS = 16 * 16 + 4;
   __shared__ __attribute__((aligned(16))) float red[2][8][G * GS];
+  constexpr int RP = 2;  // pairs of rows (at most 4 rows)
+  __shared__ __attribute__((aligned(16))) uint32_t hbuf[8][2 * RP][PW * 32];  // [wave][row][two k of its range]
   __shared__ int s_abort[2];  // by step parity: a wave already polling for step t+1 never writes the word step t reads
 
   const int wg = (int)blockIdx.x;
@@ -101,7 +102,7 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
   const int st_end = (st_begin + per_wave) < stages ? (st_begin + per_wave) : stages;
   const int n_st = st_end > st_begin ? st_end - st_begin : 0;  // <= PW (the launcher picks PW = per_wave)
 
-  // recurrent weights of this workgroup's 128 gate rows over this wave's stages, in the MFMA operand
+  // recurrent weights of this workgroup's 16 G gate rows over this wave's stages, in the MFMA operand
   // layout: lane (r, gq) holds 8 k of tile row r = gate r >> 2 of unit 4 g + (r & 3)
   uint4 wa[G][PW], wb[G][PW];
 #pragma unroll
@@ -123,7 +124,7 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
     }
   }
 
-  // cell update: thread -> (row mm < 4, unit u of the workgroup's 32, gate q): four neighbouring lanes share a
+  // cell update: thread -> (row mm < 4, unit u of the workgroup's 4 G, gate q): four neighbouring lanes share a
   // cell, each adds up and activates one gate; the lane of gate 0 owns c and writes h
   const int mm = tid / (4 * U), u = (tid >> 2) & (U - 1), q = tid & 3;
   const int unit = wg * U + u;
@@ -135,6 +136,9 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
 
   const int xrow = r < B ? r : 0;  // rows past B read row 0: their accumulator columns are never used
   const long long plane = (long long)B * H;
+  int ask_row[RP];  // row of this lane's words, one load per pair of rows (an odd last row is asked for twice)
+#pragma unroll
+  for (int p = 0; p < RP; ++p) ask_row[p] = 2 * p + (lane >> 5) < B ? 2 * p + (lane >> 5) : B - 1;
 
   // The inputs' share of the gates streams from memory, a fresh line per step: it is fetched one step
   // ahead, and behind the wave's poll loads (loads return in order: in front of them it would hold
@@ -142,9 +146,10 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
   float pr = 0.f, pr_next = 0.f;
   if (owner) pr = a.pre[((long long)mm * 4 + q) * H + unit];
   for (int t = 1; t <= T; ++t) {
-    // h_{t-1}: this wave's k range of row xrow, polled until every word carries the tag of step t-1
+    // h_{t-1}: this wave's k range of every row, polled until every word carries the tag of step t-1.  A
+    // lane asks for two words of a row (lane & 31) in one load per pair of rows and stage.
     const uint32_t want = lstm_seq_tag(t - 1);
-    const uint32_t* src = a.exch + (long long)((t - 1) & 1) * plane + (long long)xrow * H;
+    const uint32_t* src = a.exch + (long long)((t - 1) & 1) * plane;
     uint4 xa[PW], xb[PW];
     bool gave_up = false;
     if (n_st > 0) {
@@ -159,36 +164,47 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
         // the give-up word travels with the data words, not ahead of them: one round trip per poll
         const uint32_t others_gave_up = __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, SCOPE);
         uint32_t bad = 0;
+        unsigned long long v[RP][PW];
 #pragma unroll
-        for (int s = 0; s < PW; ++s) {
-          if (s < n_st) {
-            const unsigned long long* p =
-                (const unsigned long long*)(src + (st_begin + s) * 64 + gq * 8);
-            unsigned long long v[8];
+        for (int p = 0; p < RP; ++p)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              v[j] = __hip_atomic_load(p + j, __ATOMIC_RELAXED, SCOPE);           // k + 0..7
-              v[4 + j] = __hip_atomic_load(p + 16 + j, __ATOMIC_RELAXED, SCOPE);  // k + 32..39
-            }
-            uint32_t pk[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              const uint32_t lo = (uint32_t)v[j], hi = (uint32_t)(v[j] >> 32);
-              bad |= ((lo ^ want) | (hi ^ want)) & 0xffffu;
-              pk[j] = (lo >> 16) | (hi & 0xffff0000u);
-            }
-            xa[s] = make_uint4(pk[0], pk[1], pk[2], pk[3]);
-            xb[s] = make_uint4(pk[4], pk[5], pk[6], pk[7]);
-          } else {
-            xa[s] = xb[s] = make_uint4(0, 0, 0, 0);
+          for (int s = 0; s < PW; ++s) {
+            v[p][s] = want | ((unsigned long long)want << 32);
+            if (2 * p < B && s < n_st)
+              v[p][s] = __hip_atomic_load(
+                  (const unsigned long long*)(src + (long long)ask_row[p] * H + (st_begin + s) * 64) + (lane & 31),
+                  __ATOMIC_RELAXED, SCOPE);
           }
+#pragma unroll
+        for (int p = 0; p < RP; ++p)
+#pragma unroll
+          for (int s = 0; s < PW; ++s) {
+            const uint32_t lo = (uint32_t)v[p][s], hi = (uint32_t)(v[p][s] >> 32);
+            bad |= ((lo ^ want) | (hi ^ want)) & 0xffffu;
+          }
+        if (__all(bad == 0u)) {
+          // to the MFMA operand layout through the wave's own piece of LDS
+#pragma unroll
+          for (int p = 0; p < RP; ++p)
+#pragma unroll
+            for (int s = 0; s < PW; ++s)
+              if (2 * p < B)
+                hbuf[wave][2 * p + (lane >> 5)][s * 32 + (lane & 31)] =
+                    ((uint32_t)v[p][s] >> 16) | ((uint32_t)(v[p][s] >> 32) & 0xffff0000u);
+          break;
         }
-        if (__all(bad == 0u)) break;
         if (others_gave_up != 0u) {
           gave_up = true;
           break;
         }
       }
+      asm volatile("" ::: "memory");  // (a wave's LDS accesses execute in the order issued)
+#pragma unroll
+      for (int s = 0; s < PW; ++s) {
+        xa[s] = *(const uint4*)&hbuf[wave][xrow][s * 32 + gq * 4];
+        xb[s] = *(const uint4*)&hbuf[wave][xrow][s * 32 + 16 + gq * 4];
+      }
+      asm volatile("" ::: "memory");
       if (gave_up) {
         if (lane == 0) __hip_atomic_store(a.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         s_abort[t & 1] = 1;

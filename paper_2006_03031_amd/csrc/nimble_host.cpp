@@ -591,7 +591,8 @@ int nimble_lstm_seq_supported(int64_t B, int64_t H) {
 }
 
 // Measured against a captured graph of per-step launches (microseconds per step at 1 / 2 / 4 rows):
-// H = 512: 1.89 / 2.02 / 2.41 against 2.65-2.72; H = 1024: 2.71 / 3.20 / 3.98 against 2.85-2.95.
+// H = 512: 1.60 / 1.63 / 1.64 against 2.65-2.72; H = 1024: 1.76 / - / 1.96 against 2.85-2.95.  (The rule is older
+// than the kernel's present form, which wins at H = 1024 with several rows too; it is kept as callers know it.)
 int nimble_lstm_seq_preferred(int64_t B, int64_t H) {
   return nimble_lstm_seq_supported(B, H) && (H <= 512 || B == 1);
 }

@@ -637,27 +637,11 @@ int nimble_lstm_seq_pre_dyn(const void* pre, const void* w_h, const void* h0, co
   hipLaunchKernelGGL(lstm_seq_init_kernel, dim3((words + 255) / 256), dim3(256), 0, st, a);
   int rc = check_hip(hipGetLastError(), "lstm sequence fill launch");
   if (rc != NIMBLE_OK) return rc;
-  // H / 16 workgroups (at most 64; 128 with the knob at 2): fewer than the chip holds at once
-  static const int groups = [] {  // measurement knob: groups of 4 units per workgroup
-    const char* e = std::getenv("NIMBLE_LSTM_SEQ_G");
-    const int v = e ? std::atoi(e) : 0;
-    return (v == 2 || v == 4 || v == 8) ? v : 4;
-  }();
-  const bool one_stage = H <= 512;
-  switch (groups) {
-    case 2:
-      if (one_stage) hipLaunchKernelGGL((lstm_seq_kernel<1, 2>), dim3((unsigned)(H / 8)), dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((lstm_seq_kernel<2, 2>), dim3((unsigned)(H / 8)), dim3(512), 0, st, a);
-      break;
-    case 8:
-      if (one_stage) hipLaunchKernelGGL((lstm_seq_kernel<1, 8>), dim3((unsigned)(H / 32)), dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((lstm_seq_kernel<2, 8>), dim3((unsigned)(H / 32)), dim3(512), 0, st, a);
-      break;
-    default:
-      if (one_stage) hipLaunchKernelGGL((lstm_seq_kernel<1, 4>), dim3((unsigned)(H / 16)), dim3(512), 0, st, a);
-      else hipLaunchKernelGGL((lstm_seq_kernel<2, 4>), dim3((unsigned)(H / 16)), dim3(512), 0, st, a);
-      break;
-  }
+  // At most 64 workgroups, fewer than the chip holds at once: 8 units each up to H = 512, 16 beyond
+  // (microseconds per step at 1 / 4 rows with 8, 16 and 32 units: H = 512 1.60 / 1.64, 1.66 / 1.77, 1.91 / 2.09;
+  // H = 1024 1.76 / 2.24, 1.76 / 1.96, 2.09 / 2.39).
+  if (H <= 512) hipLaunchKernelGGL((lstm_seq_kernel<1, 2>), dim3((unsigned)(H / 8)), dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((lstm_seq_kernel<2, 4>), dim3((unsigned)(H / 16)), dim3(512), 0, st, a);
   return check_hip(hipGetLastError(), "lstm sequence launch");
 }
 
