@@ -649,8 +649,8 @@ int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up) {
   clear_error();
   if (!workspace || !gave_up) return fail(NIMBLE_ERR_NULL, "null pointer");
   uint32_t word = 0;
-  hipError_t e = hipStreamSynchronize((hipStream_t)stream);
-  if (e == hipSuccess) e = hipMemcpy(&word, workspace, sizeof(word), hipMemcpyDeviceToHost);
+  // the copy on the loop's own stream, one wait for both
+  const hipError_t e = hipMemcpyWithStream(&word, workspace, sizeof(word), hipMemcpyDeviceToHost, (hipStream_t)stream);
   if (e != hipSuccess) return fail(NIMBLE_ERR_HIP, "lstm sequence status: %s", hipGetErrorString(e));
   *gave_up = word != 0;
   return NIMBLE_OK;
