@@ -61,7 +61,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
                                               uint4* smem, const RingLink lk = RingLink{}) {
   constexpr bool WIDE = MODE == RING_WIDE;
   static_assert(!PF || WIDE, "only the 64-wide ring hands tiles over");
-  static_assert(WIDE ? (S == 2 || S == 3) : (S >= 4 || (MODE == RING_SOLO && S == 3)),
+  static_assert(WIDE ? (S >= 2 && S <= 4) : (S >= 4 || (MODE == RING_SOLO && S == 3)),
                 "the pipeline keeps S-2 stages in flight");
   constexpr int CH = WIDE ? 8 : 4;      // 16-byte chunks per row and stage
   constexpr int KSH = WIDE ? 6 : 5;     // log2 of the stage width in k

@@ -30,7 +30,7 @@ const VariantInfo kVariants[NIMBLE_VAR_COUNT] = {
     // name       bm   bn   bk  threads
     {"generic", 64, 64, 64, 256},
     {"skinny16", 16, 16, 32, 256},
-    {"t32x128", 32, 128, 32, 128},
+    {"t32x128", 32, 128, 32, 256},
     {"t64x128", 64, 128, 32, 256},
     {"t128x128", 128, 128, 32, 256},
     {"t256x128", 256, 128, 32, 512},
@@ -94,6 +94,29 @@ static const double kLaunchGapUs = 3.5;
 // hardware queue has already decoded while the first kernel runs.
 static const double kSplitGapUs = 1.80;
 
+bool wide_stages_ok(int64_t K, int64_t slices) {
+  static const bool off = std::getenv("NIMBLE_RING32") != nullptr;
+  const int64_t stages = K >> 6, per = slices > 0 ? ceil_div(stages, slices) : 0;
+  return !off && K > 0 && (K & 63) == 0 && per * (slices - 1) < stages;
+}
+
+// The 128-wide tiles up to 128 rows on the 64-wide ring, at most two tiles per compute unit, microseconds: a
+// lone tile's fixed time plus its walk over the K stages (32 k each), slower the more tiles there are; from
+// one tile per compute unit on, two workgroups share one.  Fitted to graph-timed launches over K = 768 .. 4096
+// and 24 .. 450 tiles; GELU adds half a microsecond.
+static double few_tiles_us(int v, int64_t tiles, int64_t stages, bool gelu) {
+  const double t = (double)(tiles < kCUs ? tiles : kCUs);
+  double fixed, per_stage, shared = 1.65, more = 0.25;
+  switch (v) {
+    case NIMBLE_VAR_T32x128:
+      fixed = 0.85, per_stage = 0.108 + 0.0002 * t < 0.142 ? 0.108 + 0.0002 * t : 0.142, shared = 1.38, more = 0.2;
+      break;
+    case NIMBLE_VAR_T64x128: fixed = 1.1, per_stage = 0.105 + 0.0003 * t < 0.148 ? 0.105 + 0.0003 * t : 0.148; break;
+    default: fixed = 2.2, per_stage = 0.183 + 0.00036 * (t > 100 ? t - 100 : 0); break;
+  }
+  const double us = fixed + (gelu ? 0.5 : 0.0) + per_stage * (double)stages;
+  return tiles <= kCUs ? us : us * (shared + more * (double)(tiles - kCUs) / (double)kCUs);
+}
 
 // Estimated time of one launch of tiled variant v over `rows` rows with K cut into `sk`
 // slices, microseconds.  The tiles run in rounds of one per compute unit.  A full round runs
@@ -117,21 +140,26 @@ static double tiled_cost_us(int v, int64_t batch, int64_t rows, int64_t N, int64
   static const double kLoneTile[NIMBLE_VAR_COUNT] = {0, 0, 0.185, 0.388, 0.678, 0.598, 0.659};
   const int64_t stages = ceil_div(k_slice, 32);
   const bool gelu = sk == 1 && epilogue == NIMBLE_EPI_BIAS_GELU_ERF;
-  const double latency_floor = (double)stages * kStageFloorUs[v] + (gelu ? 0.05 : 0.0);
-  const double t_full = tile_cost(v, k_slice, sk > 1 ? NIMBLE_EPI_NONE : epilogue, bm) * kUsPerUnit;
-  // a round is one tile per compute unit for the 8-wave tiles, two for the smaller ones
-  const int64_t slots = kCUs * kTilesPerCU[v];
-  const int64_t full_rounds = tiles / slots, rem = tiles % slots;
-  double us = (double)full_rounds * (t_full > latency_floor ? t_full : latency_floor);
-  if (rem > 0) {
-    const double occ = (double)rem / (double)slots;
-    const double t_part = t_full * (kLoneTile[v] + (1.0 - kLoneTile[v]) * occ);
-    us += t_part > latency_floor ? t_part : latency_floor;
+  double us;
+  if (v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
+    us = few_tiles_us(v, tiles, stages, gelu);
+  } else {
+    const double latency_floor = (double)stages * kStageFloorUs[v] + (gelu ? 0.05 : 0.0);
+    const double t_full = tile_cost(v, k_slice, sk > 1 ? NIMBLE_EPI_NONE : epilogue, bm) * kUsPerUnit;
+    // a round is one tile per compute unit for the 8-wave tiles, two for the smaller ones
+    const int64_t slots = kCUs * kTilesPerCU[v];
+    const int64_t full_rounds = tiles / slots, rem = tiles % slots;
+    us = (double)full_rounds * (t_full > latency_floor ? t_full : latency_floor);
+    if (rem > 0) {
+      const double occ = (double)rem / (double)slots;
+      const double t_part = t_full * (kLoneTile[v] + (1.0 - kLoneTile[v]) * occ);
+      us += t_part > latency_floor ? t_part : latency_floor;
+    }
+    // all workgroups together pull about 14 TB/s from the L2s into LDS with real operand data:
+    // many small tiles re-fetch the operand panels often enough to hit that before anything else
+    const double dma_us = (double)tiles * (double)stages * (double)((bm > 0 ? bm : vi.bm) + vi.bn) * 64.0 / 13.9e6;
+    if (us < dma_us) us = dma_us;
   }
-  // all workgroups together pull about 14 TB/s from the L2s into LDS with real operand data:
-  // many small tiles re-fetch the operand panels often enough to hit that before anything else
-  const double dma_us = (double)tiles * (double)stages * (double)((bm > 0 ? bm : vi.bm) + vi.bn) * 64.0 / 13.9e6;
-  if (us < dma_us) us = dma_us;
   // a layer too large to stay in the caches streams its weights from HBM: about 4.2 TB/s with
   // one workgroup per compute unit, 6.4 TB/s from two up
   if ((double)N * (double)K * 2.0 > kCachedWeightBytes) {
@@ -234,6 +262,9 @@ static const nimble_table_entry* table_lookup(int64_t M, int64_t N, int64_t K, i
   return nullptr;
 }
 
+// Slice counts considered for a K split (three: 600 x 1024 x 4096 15.8 us on 64-row tiles, two 17.2, four 19.5).
+static const int kSplits[] = {1, 2, 3, 4, 8, 16};
+
 struct Launch {
   int variant = -1;
   int split_k = 1;
@@ -256,11 +287,13 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
   for (int v = NIMBLE_VAR_T32x128; v <= NIMBLE_VAR_T256x256; ++v) {
     if (!tiled_variant_ok(v, rows, N, K)) continue;
     if (v > NIMBLE_VAR_T32x128 && rows <= kVariants[v - 1].bm) break;  // tile taller than needed
-    for (int sk = 1; sk <= 16; sk *= 2) {
+    for (int sk : kSplits) {
       if (!split_k_ok(v, batch, N, K, sk)) continue;
       if (sk > 1 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > max_workspace) continue;
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, sk);
-      if (best.variant < 0 || us < best.us) {
+      // (a finer cut of the same tile takes more workspace: it has to win by more than the estimate is good for)
+      const double bar = best.variant == v && best.split_k > 1 ? 0.95 * best.us : best.us;
+      if (best.variant < 0 || us < bar) {
         best.variant = v;
         best.split_k = sk;
         best.bm = 0;
@@ -308,7 +341,7 @@ static void fill_tiled(nimble_plan* p, int variant, int split_k, int64_t batch, 
   p->grid[0] = (uint32_t)(ceil_div(M, v.bm) * ceil_div(N, v.bn));
   p->grid[1] = (uint32_t)split_k;
   p->grid[2] = (uint32_t)batch;
-  p->block = (uint32_t)v.threads;
+  p->block = eight_waves(variant, (uint64_t)p->grid[0] * p->grid[1] * p->grid[2], K, split_k) ? 512u : (uint32_t)v.threads;
   p->workspace_bytes = split_k > 1 ? (uint64_t)split_k * (uint64_t)M * (uint64_t)N * 4u : 0;
 }
 

@@ -30,6 +30,23 @@ bool tile_rows_ok(int variant, int bm, int64_t N, int64_t K);
 // as cache-resident, which is what a layer loop or a token loop sees.
 constexpr double kCachedWeightBytes = 64e6;
 
+// Whether every one of `slices` K slices gets whole 64-wide stages (the 64-wide ring).  NIMBLE_RING32 (a
+// measurement knob, read once) turns that ring off.
+bool wide_stages_ok(int64_t K, int64_t slices);
+// Whether a launch of the 64- or 128-row tile (128 wide) runs with eight waves per tile and a compute unit
+// to itself: at most one tile per compute unit (all slices and batches counted), K in 64-wide stages.  A lone
+// tile is a serial chain of stages, and eight waves walk it in less time than four: microseconds with four / eight
+// waves, 64 rows: 509 x 2304 x 768 8.3 / 7.8, 509 x 3072 x 768 (GELU) 9.0 / 8.4; 128 rows: 800 x 4096 x 1024 (GELU)
+// 15.3 / 13.6, 4000 x 1024 x 4096 45.7 / 36.8.  With more tiles two workgroups of four waves share a
+// compute unit, which is the better use of it (600 x 4096 x 1024, 320 tiles of 64 rows: 14.4 / 16.9); 64 rows also
+// stay with four waves where the chip is nearly full of long tiles, which all pull on the L2s (2600 x 768 x 3072,
+// 246 tiles: 19.6 / 20.4; with 204 tiles 19.4 / 19.0), and with K cut (509 x 1024 x 4096 in four: 14.5 / 15.8).
+inline bool eight_waves(int variant, uint64_t tiles, int64_t K, int64_t slices) {
+  if (tiles > (uint64_t)kComputeUnits || !wide_stages_ok(K, slices)) return false;
+  if (variant == NIMBLE_VAR_T64x128) return slices == 1 && (K <= 2048 || tiles <= (uint64_t)kComputeUnits * 7 / 8);
+  return variant == NIMBLE_VAR_T128x128;
+}
+
 // Whether a weight-streaming launch of 16-row blocks over an [N, K] weight can run the LDS-staged
 // streaming kernel (the LSTM cell needs Ix % 64 == 0 besides).
 bool stream_kernel_shape_ok(int64_t N, int64_t K);

@@ -78,9 +78,7 @@ static int launch_ring(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
   }
   dim3 grid(wgs, slices, p.grid[2]), block(WGM * WGN * 64);
   if constexpr (WS > 0) {
-    static const bool ring32_only = std::getenv("NIMBLE_RING32") != nullptr;  // measurement knob
-    const int stages = g.K >> 6, per = (stages + slices - 1) / slices;
-    if (!ring32_only && g.K > 0 && (g.K & 63) == 0 && per * (slices - 1) < stages) {
+    if (wide_stages_ok(g.K, slices)) {
       if (p.residue_copy)
         hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, WS, true>), grid, block, 0, st, g, tiles_m,
                            tiles_n, group_m);
@@ -96,6 +94,19 @@ static int launch_ring(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
   else
     hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, false, S>), grid, block, 0, st, g, tiles_m,
                        tiles_n, group_m);
+  return check_hip(hipGetLastError(), "ring kernel launch");
+}
+
+// One tile per workgroup on the 64-wide ring only (the caller has checked that K fits it).
+template <int BM, int BN, int WGM, int WGN, int WS>
+static int launch_lone(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  const dim3 grid(p.grid[0], p.split_k > 1 ? p.split_k : 1, p.grid[2]), block(WGM * WGN * 64);
+  const int group_m = tiles_m < 4 ? tiles_m : 4;
+  if (p.residue_copy)
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, WS, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
+  else
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, false, WS, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
   return check_hip(hipGetLastError(), "ring kernel launch");
 }
 
@@ -192,6 +203,8 @@ static bool wants_any(const GemmArgs& g, const nimble_plan& p) {
 
 static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
   if (p.variant >= NIMBLE_VAR_T32x128 && wants_any(g, p)) return launch_any(g, st);
+  const bool lone = eight_waves(p.variant, (uint64_t)p.grid[0] * (p.split_k > 1 ? p.split_k : 1) * p.grid[2], g.K,
+                                p.split_k > 1 ? p.split_k : 1);
   switch (p.variant) {
     case NIMBLE_VAR_GENERIC:
       if (p.bm == 16) {
@@ -200,9 +213,16 @@ static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
       }
       return launch_any(g, st);
     case NIMBLE_VAR_SKINNY16: return launch_skinny<false>(skinny_args(g), p, st);
-    case NIMBLE_VAR_T32x128: return launch_ring<32, 128, 1, 2, 3>(g, p, st);
-    case NIMBLE_VAR_T64x128: return launch_ring<64, 128, 2, 2, 3>(g, p, st);
-    case NIMBLE_VAR_T128x128: return launch_ring<128, 128, 2, 2>(g, p, st);
+    case NIMBLE_VAR_T32x128: return launch_ring<32, 128, 2, 2, 3>(g, p, st);
+    case NIMBLE_VAR_T64x128:
+      if (lone) return launch_lone<64, 128, 4, 2, 3>(g, p, st);
+      return launch_ring<64, 128, 2, 2, 3>(g, p, st);
+    case NIMBLE_VAR_T128x128:
+      // (three slots up to K = 2048, where filling the fourth does not pay: 800 x 3072 x 768 11.2 us against 11.4;
+      // 3200 x 1024 x 4096 35.1 with three, 32.7 with four)
+      if (lone && g.K <= 2048) return launch_lone<128, 128, 4, 2, 3>(g, p, st);
+      if (lone) return launch_lone<128, 128, 4, 2, 4>(g, p, st);
+      return launch_ring<128, 128, 2, 2>(g, p, st);
     case NIMBLE_VAR_T256x128:
       return launch_ring<256, 128, 4, 2, 3>(g, p, st);
     case NIMBLE_VAR_T256x256:
