@@ -17,11 +17,12 @@ namespace nimble {
 //   never stored.
 //   KN: B is [K, N]; its tile keeps its rows (64 k of BN n) in LDS and the fragments come out of
 //   the transposing LDS read.
-//   KG = 2: two groups of four waves take alternate stages of one tile and add their sums at the end.
+//   KG = 4: four groups of four waves take the stages in turn and add their sums at the end.
 //   What bounds it: a few hundred tiles of some ten stages are the whole launch, so the chain load ->
 //   LDS -> MFMA per stage (0.32 us at 64 x 64, 0.5 with rows that start at odd addresses: a 16-byte load
 //   then spans two pieces of a line).  Measured, 515 x 1001 x 1003 to f32: 671 us with the scalar kernel
-//   it replaces (one thread per output) -> 13.4 (two register sets) -> 12.4 (four) -> 11.8 (KG = 2);
+//   it replaces (one thread per output) -> 13.3 (one group, four register sets) -> 12.1 (two groups) -> 11.5 (four
+//   groups, two register sets each; with four 12.7), the same with K = 1000 9.4; 500 x 500 x 2003 20.6 -> 18.0 -> 16.8;
 //   12 x 333 x 64 x 333 as A.B 88 -> 6.6 us.  128 x 128 tiles were measured too: no faster even at
 //   8000 x 1001 x 1003 (54 us against 51), half the speed on small grids.
 // ---------------------------------------------------------------------------
@@ -180,21 +181,25 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
     if (P > 2 && s + 2 < KT0) stage(s + 2, S2{});
     if (P > 2 && s + 3 < KT0) stage(s + 3, S3{});
   }
-  if constexpr (KG == 2) {  // the second group hands its sums to the first, which finishes the tile
-    f32x4* part = (f32x4*)&smem_all[1][0][0] + wave * (TM * TN * 64) + lane;
-    static_assert(4 * TM * TN * 64 <= 2 * BUF, "the partial sums reuse the group's operand buffers");
-    if (grp == 1) {
+  if constexpr (KG > 1) {  // the other groups hand their sums to the first, which adds them in order and finishes the tile
+    static_assert(4 * TM * TN * 64 <= 2 * BUF, "the partial sums reuse a group's operand buffers");
+    if (grp > 0) {
+      f32x4* part = (f32x4*)&smem_all[grp][0][0] + wave * (TM * TN * 64) + lane;
 #pragma unroll
       for (int i = 0; i < TN; ++i)
 #pragma unroll
         for (int j = 0; j < TM; ++j) part[(i * TM + j) * 64] = acc[i][j];
     }
     __syncthreads();
-    if (grp == 1) return;
+    if (grp > 0) return;
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
+    for (int g2 = 1; g2 < KG; ++g2) {
+      const f32x4* part = (const f32x4*)&smem_all[g2][0][0] + wave * (TM * TN * 64) + lane;
 #pragma unroll
-      for (int j = 0; j < TM; ++j) acc[i][j] += part[(i * TM + j) * 64];
+      for (int i = 0; i < TN; ++i)
+#pragma unroll
+        for (int j = 0; j < TM; ++j) acc[i][j] += part[(i * TM + j) * 64];
+    }
   }
 
   // epilogue: 16 rows at a time through the wave's own staging area, written back row by row so that a

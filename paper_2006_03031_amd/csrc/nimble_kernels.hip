@@ -170,22 +170,22 @@ static SkinnyArgs skinny_args(const GemmArgs& g) {
   return s;
 }
 
-// Operands of any alignment in 64 x 64 tiles.  Two groups of waves share a tile's K where a workgroup
+// Operands of any alignment in 64 x 64 tiles.  Four groups of waves share a tile's K where a workgroup
 // per compute unit is all there is and K is long enough to pay for handing the sums over (measured at
-// K = 1003: 700 x 1001 12.5 -> 11.5 us, 12 x 512 x 64 x 512 as A.B 7.4 -> 6.3; at K = 64 12 x 509 x 509
-// 6.2 -> 8.4; with 512 tiles at K = 1000 14.0 -> 15.1).
+// K = 1000: 1000 x 1000 as A.B 13.2 -> 10.5 us, 515 x 1001 10.6 -> 9.4; K = 512: 7.4 -> 7.0; K = 257 7.3 -> 6.8, 256
+// 6.0 -> 6.2, 127 6.4 -> 6.8; with 512 tiles at K = 1000 two groups already took 14.0 -> 15.1).
 static int launch_any(const GemmArgs& g, hipStream_t st) {
   const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
   const dim3 grid((unsigned)tiles_m * (unsigned)tiles_n, 1, (unsigned)g.batch);
-  const bool two = g.K >= 512 && (long long)grid.x * g.batch <= kComputeUnits;
+  const bool four = g.K >= 512 && (long long)grid.x * g.batch <= kComputeUnits;
   if (g.b_is_kn) {
-    if (two)
-      hipLaunchKernelGGL((any_kernel<64, 64, true, 4, 2>), grid, dim3(512), 0, st, g, tiles_m, tiles_n);
+    if (four)
+      hipLaunchKernelGGL((any_kernel<64, 64, true, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
     else
       hipLaunchKernelGGL((any_kernel<64, 64, true, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
   } else {
-    if (two)
-      hipLaunchKernelGGL((any_kernel<64, 64, false, 4, 2>), grid, dim3(512), 0, st, g, tiles_m, tiles_n);
+    if (four)
+      hipLaunchKernelGGL((any_kernel<64, 64, false, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
     else
       hipLaunchKernelGGL((any_kernel<64, 64, false, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
   }

@@ -35,7 +35,7 @@ def _guarded(shape, dtype):
     return buf, buf[:n].view(shape)
 
 
-# K: shorter than a chunk, a chunk's and a stage's edges, many stages for one and for two groups of waves;
+# K: shorter than a chunk, a chunk's and a stage's edges, many stages for one and for four groups of waves;
 # M and N: one row, edges of the 16-row blocks and of the 64-wide tiles, too many blocks for the row kernel
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (3, 5, 3), (17, 33, 7), (16, 16, 9), (65, 63, 15), (64, 64, 65), (130, 129, 71),
                                    (1, 257, 1003), (16, 9000, 63), (33, 130, 511), (600, 300, 1), (600, 1000, 7), (577, 961, 63),
