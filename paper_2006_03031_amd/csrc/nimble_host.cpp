@@ -413,9 +413,11 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
           for (int c = 0; c < 2; ++c) {
             const int64_t head = cuts[c], rest = M - head;
             if (head <= 0 || rest <= 0 || (c == 1 && head == cuts[0])) continue;
+            const double head_us = tiled_cost_us(v, 1, head, N, K, epilogue) + kLaunchGapUs;
+            if (head_us >= best_us) continue;  // (the tail's search is most of what a plan costs)
             const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true);
             if (tail.variant < 0) continue;
-            const double us = tiled_cost_us(v, 1, head, N, K, epilogue) + kLaunchGapUs + tail.us;
+            const double us = head_us + tail.us;
             if (us < best_us) {
               best_us = us;
               variant = v;
