@@ -290,6 +290,9 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
     for (int sk : kSplits) {
       if (!split_k_ok(v, batch, N, K, sk)) continue;
       if (sk > 1 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > max_workspace) continue;
+      // (three slices only within the built-in scratch, so that the entry point that lives on it keeps taking
+      // the calls it took when K was cut by powers of two)
+      if (sk == 3 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > (uint64_t)NIMBLE_NOALLOC_SCRATCH_BYTES) continue;
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, sk);
       // (a finer cut of the same tile takes more workspace: it has to win by more than the estimate is good for)
       const double bar = best.variant == v && best.split_k > 1 ? 0.95 * best.us : best.us;
