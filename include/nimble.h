@@ -287,12 +287,11 @@ int nimble_lstm_seq_shape(const int64_t* pre_shape, const int64_t* h0_shape, con
                           const int64_t* wh_shape, int64_t* h_seq_shape, int64_t* c_out_shape);
 
 /* 1 when nimble_lstm_seq_pre_dyn runs (B, H): 1 <= B <= 4, H a multiple of 64, 64 <= H <= 1024
- * (H/16 workgroups of 64 gate rows, all resident at once); else 0: run the steps one by one. */
+ * (at most 64 workgroups, all resident at once); else 0: run the steps one by one. */
 int nimble_lstm_seq_supported(int64_t B, int64_t H);
 
 /* 1 when, besides, the one launch measured faster than one launch per step (H <= 512, or one row up to
- * H = 1024: a step is then bound by what separates the steps; with more rows or a larger H by the words
- * every workgroup has to fetch per step); the hint a caller's dispatch takes. */
+ * H = 1024); the hint a caller's dispatch takes. */
 int nimble_lstm_seq_preferred(int64_t B, int64_t H);
 
 /* Bytes of device workspace the call needs: 256 bytes of control words, then two (B,H) planes of
