@@ -31,7 +31,7 @@ namespace nimble {
 //   one request per channel and clock whatever its size: all compute units together pulled
 //   13.5-15.5 TB/s into LDS in 64-byte pieces and 22-26 TB/s in whole lines (loads only, no
 //   MFMA), and the 32-wide ring ran within 10 % of the former.  Rows are 8 chunks, chunk c of row
-//   r at slot c ^ ((r >> 1) & 7); S = 2 or 3 slots; one barrier per 64 k, placed between the two
+//   r at slot c ^ ((r >> 1) & 7); S = 2 to 4 slots; one barrier per 64 k, placed between the two
 //   32-wide halves of a stage: by then every wave has issued (and waited for) its last reads of
 //   the slot of stage s, so the slot is refilled with stage s+S, and stage s+1 has landed, whose
 //   first fragments are read during the second half's MFMAs.
@@ -526,7 +526,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
 template <int BM, int BN, int WGM, int WGN, bool RESIDUE, int S = 4, bool WIDE = false>
 __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
-  // WIDE: stages of 64 k (K must be a multiple of 64; the launcher sees to that), S = 2 or 3.
+  // WIDE: stages of 64 k (K must be a multiple of 64; the launcher sees to that), S = 2 to 4.
   // Else stages of 32 k: the straight-line schedule with two fragment sets wherever accumulators
   // and both sets fit in a wave's 256 registers (wave tiles up to 128 rows by 64 columns); the
   // two-group ping-pong with one set for the 288- and 320-row heights of the 256-wide tile
