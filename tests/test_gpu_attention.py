@@ -79,3 +79,30 @@ def test_attention_chain_passes_infinite_values_on(rt):
     v[:, L - 1] = float("inf")
     _, p, o = rt.attention(q, k, v)
     assert bool((p[:, :, L - 1] > 0).all()) and bool((o == float("inf")).all())
+
+
+# one to eight waves, and the three calls; all scores of a row equal (up to a row of one huge negative value), or far apart
+@pytest.mark.parametrize("L", [1, 64, 130, 512, 513])
+@pytest.mark.parametrize("score", [1e5, 2e9, -5e9, 1e10, -1e10, -1e30])
+def test_attention_chain_of_large_scores(rt, L, score):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(L)
+    v = torch.empty((2, L, 64), device="cuda").normal_(0, 1, generator=gen).to(torch.bfloat16)
+    # head 0: query row m's scores are all (1 + m) score, whatever the key; head 1: key j adds a part of its own
+    q = torch.zeros((2, L, 64), device="cuda")
+    k = torch.zeros((2, L, 64), device="cuda")
+    q[:, :, 0] = 1 + torch.arange(L, device="cuda") % 100
+    k[:, :, 0] = score
+    q[1, :, 1] = 1
+    k[1, :, 1] = torch.empty(L, device="cuda").normal_(0, 1, generator=gen) * abs(score) * 0.1
+    q, k = q.to(torch.bfloat16), k.to(torch.bfloat16)
+    s, p, o = rt.attention(q, k, v, alpha=1.0)
+    # P against the S that was returned (S's own rounding is a large step at these magnitudes): one rounding to bf16
+    rp = torch.softmax(s.double(), -1)
+    finite = [bool(torch.isfinite(t).all()) for t in (s, p, o)]
+    assert all(finite), finite
+    assert ((p.double() - rp).abs() / (rp + 1e-30)).max().item() <= 2.0 ** -8
+    if L > 1:
+        assert bool((p[0].float() * L - 1).abs().max() <= 2.0 ** -8)
+    ro = torch.matmul(p.double(), v.double())
+    assert ((o.double() - ro).abs() / (ro.abs() + ro.abs().mean())).max().item() <= 2.0 ** -8
