@@ -47,6 +47,27 @@ inline bool eight_waves(int variant, uint64_t tiles, int64_t K, int64_t slices) 
   return variant == NIMBLE_VAR_T128x128;
 }
 
+// Whether the ring kernels can run an [M, N] output over K: whole 32-wide stages, output rows of whole 16-byte pieces.
+inline bool ring_shape_ok(int64_t N, int64_t K) { return K % 32 == 0 && N % 8 == 0; }
+
+// Where they cannot (K is a multiple of 8): whether gemm_tile_kernel in the variant's own tiles, `tiles` of them over
+// all batches, beats any_kernel in tiles of 64 x 64.  It does where its tiles fill the chip; with fewer, small
+// tiles with K shared by groups of waves are the better use of it.  Microseconds, tile kernel / any_kernel, to f32:
+// 64- and 128-row tiles: 392 (3130 x 1024 x 904) 18 / 24, 306 (1117 x 4240 x 2648) 53 / 70, 225 (606 x 5760 x 1608) 36 / 39,
+// 190 (2332 x 432 x 712) 11.2 / 9.8; 256-wide tiles: 234 (6421 x 2304 x 2808) 124 / 210, 165 (2771 x 3656 x 4560) 168 / 219,
+// 136 (951 x 8632 x 2256) 85 / 84, 126 (1484 x 2688 x 3416) 79 / 70.  Its lanes write the columns they own, four at a time,
+// where any_kernel writes whole rows: K has to be long enough to make up for that.  6000 x 4096 to f32 25 / 29 at K = 40
+// and 84 / 113 at 1000, to bf16 42 / 34 at 136, 54 / 54 at 328, 79 / 83 at 648; 6000 x 4100 (rows of whole 8-byte pieces)
+// to f32 39 / 38 at 136, 77 / 83 at 648, to bf16 71 / 68 at 456, 106 / 114 at 1000; with N not a multiple of 4 the columns are
+// written one by one: 4434 x 2078 x 2016 104 / 83, 2771 x 3471 x 4560 with GELU 181 / 199.
+inline bool tile_kernel_wins(int variant, int64_t tiles, int64_t N, int64_t K, bool out_f32) {
+  if (variant < NIMBLE_VAR_T64x128) return false;
+  if (tiles < (variant <= NIMBLE_VAR_T128x128 ? 256 : 160)) return false;
+  if (N % 4 != 0) return K >= 4096;
+  if (out_f32) return N % 8 == 0 || K >= 512;
+  return K >= (N % 8 == 0 ? 448 : 896);
+}
+
 // Whether a weight-streaming launch of 16-row blocks over an [N, K] weight can run the LDS-staged
 // streaming kernel (the LSTM cell needs Ix % 64 == 0 besides).
 bool stream_kernel_shape_ok(int64_t N, int64_t K);

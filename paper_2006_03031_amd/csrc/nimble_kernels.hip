@@ -10,6 +10,8 @@
 //       copy for r = 0: no bounds code at all.  RESIDUE=true is the copy for r != 0: decided
 //       once per tile, tiles past the last row or column run the same pipeline with clamped loads
 //       and masked stores.  Also the split-K reduction kernel.
+//   gemm_tile_kernel.h   gemm_tile_kernel: the same tiles register-staged and bounds-checked throughout,
+//       for K that is not whole stages and output rows of any alignment, where these fill the chip.
 //   any_kernel.h         any_kernel: 64x64 tiles for operands and outputs of any shape, alignment
 //       and B layout (register-staged, unaligned loads, zero-filled K tail).
 //   skinny_kernel.h      skinny_kernel<MT,LSTM>: M <= 64 per workgroup, the weights are
@@ -35,6 +37,7 @@
 #include "attention_kernel.h"
 #include "device_common.h"
 #include "gemm_ring_kernel.h"
+#include "gemm_tile_kernel.h"
 #include "misc_kernels.h"
 #include "nimble_internal.h"
 #include "nimble_probe.h"
@@ -192,17 +195,37 @@ static int launch_any(const GemmArgs& g, hipStream_t st) {
   return check_hip(hipGetLastError(), "any kernel launch");
 }
 
+// The variant's own tiles, every access bounds-checked; as many workgroups as are resident at once walk them.
+template <int BM, int BN, int WGM, int WGN>
+static int launch_tile(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+  const unsigned resident = (unsigned)(kComputeUnits * kTilesPerCU[p.variant]);
+  const dim3 grid(p.grid[2] == 1 && p.grid[0] > resident ? resident : p.grid[0], 1, p.grid[2]);
+  hipLaunchKernelGGL((gemm_tile_kernel<BM, BN, WGM, WGN>), grid, dim3(WGM * WGN * 64), 0, st, g, tiles_m, tiles_n);
+  return check_hip(hipGetLastError(), "tile kernel launch");
+}
+
 // Tiled plans whose shape the ring kernels cannot run (K not whole stages, output rows not 16-byte
-// aligned) run on any_kernel, and so do smaller products whose last tile column is partly empty: that
+// aligned) run on any_kernel or, where tile_kernel_wins, on gemm_tile_kernel, and smaller products whose last
+// tile column is partly empty run on any_kernel: that
 // column then is a large part of the work (1000 x 1000 x 1024: 9.2 us against 15.4 on 64 x 128 tiles,
 // 4000 rows 20.7 against 23.8, 16000 rows 68 against 52: the line lies at 5 G multiply-adds).
 static bool wants_any(const GemmArgs& g, const nimble_plan& p) {
-  if ((g.K & 31) != 0 || (g.ldc & 7) != 0) return true;
+  if (!ring_shape_ok(g.N, g.K))
+    return g.b_is_kn || !tile_kernel_wins(p.variant, (int64_t)p.grid[0] * p.grid[2], g.N, g.K, g.out_f32 != 0);
   return g.N % p.bn != 0 && (double)g.batch * g.M * g.N * g.K < 5e9;
 }
 
 static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
   if (p.variant >= NIMBLE_VAR_T32x128 && wants_any(g, p)) return launch_any(g, st);
+  if (p.variant >= NIMBLE_VAR_T32x128 && !ring_shape_ok(g.N, g.K)) {
+    switch (p.variant) {
+      case NIMBLE_VAR_T64x128: return launch_tile<64, 128, 2, 2>(g, p, st);
+      case NIMBLE_VAR_T128x128: return launch_tile<128, 128, 2, 2>(g, p, st);
+      case NIMBLE_VAR_T256x128: return launch_tile<256, 128, 4, 2>(g, p, st);
+      default: return launch_tile<256, 256, 2, 4>(g, p, st);
+    }
+  }
   const bool lone = eight_waves(p.variant, (uint64_t)p.grid[0] * (p.split_k > 1 ? p.split_k : 1) * p.grid[2], g.K,
                                 p.split_k > 1 ? p.split_k : 1);
   switch (p.variant) {
