@@ -206,14 +206,15 @@ static int launch_tile(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
 }
 
 // Tiled plans whose shape the ring kernels cannot run (K not whole stages, output rows not 16-byte
-// aligned) run on any_kernel or, where tile_kernel_wins, on gemm_tile_kernel, and smaller products whose last
-// tile column is partly empty run on any_kernel: that
-// column then is a large part of the work (1000 x 1000 x 1024: 9.2 us against 15.4 on 64 x 128 tiles,
-// 4000 rows 20.7 against 23.8, 16000 rows 68 against 52: the line lies at 5 G multiply-adds).
+// aligned) run on any_kernel or, where tile_kernel_wins, on gemm_tile_kernel.  Where they can, a partly empty last
+// tile column costs the ring kernels no more than its loads (ring / any_kernel, microseconds: 423 x 2928 x 3648 20 / 37,
+// 12456 x 200 x 1024 12.5 / 19.6, 1240 x 1112 x 512 6.2 / 8.0), but a handful of tiles leaves the chip to few
+// workgroups, and the smaller ones with K shared by four groups of waves are done earlier (953 x 64 x 512, 15 of them,
+// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0).
 static bool wants_any(const GemmArgs& g, const nimble_plan& p) {
   if (!ring_shape_ok(g.N, g.K))
     return g.b_is_kn || !tile_kernel_wins(p.variant, (int64_t)p.grid[0] * p.grid[2], g.N, g.K, g.out_f32 != 0);
-  return g.N % p.bn != 0 && (double)g.batch * g.M * g.N * g.K < 5e9;
+  return g.N % p.bn != 0 && (int64_t)g.batch * ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 40;
 }
 
 static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {

@@ -63,17 +63,20 @@ def test_batch_matmul(nb, T, M, N, K):
             _check(buf[:T * M * N].view(T, M, N)[t], 0.5 * (a[t].double() @ b[t].double().T.contiguous()), od == nb.F32, (t, T, M, N, K))
 
 
-def test_large_products_do_not_run_in_small_tiles(nb):
-    """The automatic plan against the generic variant (64 x 64 tiles), timed: 1.8 times as fast at this size."""
+@pytest.mark.parametrize("M,N,K,part", [(4096, 4096, 4104, 0.8),    # K not whole stages: 153 us against 287 in 64 x 64 tiles
+                                        (423, 2928, 3648, 0.8)])   # a partly empty last tile column: 20 against 37
+def test_large_products_do_not_run_in_small_tiles(nb, M, N, K, part):
+    """The automatic plan against the generic variant (64 x 64 tiles), timed."""
     from paper_2006_03031_amd import runtime as rt
-    x, w, b = _operands(4096, 4096, 4104)
+    x, w, b = _operands(M, N, K)
     times = {}
     for variant in (nb.VAR_AUTO, 0, nb.VAR_AUTO, 0):
         ev = [torch.cuda.Event(enable_timing=True) for _ in range(12)]
         for e in ev:
-            rt.dense(x, w, b, nb.EPI_BIAS, force_variant=variant)
+            for _ in range(4):   # (more work than the calls take on the host)
+                rt.dense(x, w, b, nb.EPI_BIAS, force_variant=variant)
             e.record()
         torch.cuda.synchronize()
         ts = sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(11))
         times[variant] = min(times.get(variant, 1e9), ts[5])
-    assert times[nb.VAR_AUTO] < 0.8 * times[0], times
+    assert times[nb.VAR_AUTO] < part * times[0], times
