@@ -89,9 +89,11 @@ typedef enum nimble_variant {
  * paying a mostly empty last round: the residue handling of Section 3.5 applied one level up. */
 #define NIMBLE_FORCE_TILE_ROWS(rows) ((((rows) / 16) & 0xff) << 16)
 
-/* What the dispatch function decided for one run-time shape (host only).  A tiled plan whose shape the
- * ring kernels cannot run (K not a multiple of 32, N not of 8) or whose last tile column would be a large
- * part of the work is launched in the 64 x 64 tiles of the generic variant instead. */
+/* What the dispatch function decided for one run-time shape (host only).  Where the 64 x 64 tiles of the
+ * generic variant suit a shape better than the kernels of the tiled variant that its size asks for (K not a
+ * multiple of 32, N not of 8, a partly empty last column of very few tiles), the plan keeps that variant's
+ * name and bm, bn, bk, grid and block are those of the 64 x 64 tiles that are launched.  A variant that the
+ * caller forces or a tuned entry names is launched in its own tiles. */
 typedef struct nimble_plan {
   int32_t variant;        /* nimble_variant                                       */
   int32_t bm, bn, bk;     /* macro tile of the launch (bm may be a reduced height)  */

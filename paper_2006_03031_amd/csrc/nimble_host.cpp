@@ -348,6 +348,20 @@ static void fill_tiled(nimble_plan* p, int variant, int split_k, int64_t batch, 
   p->workspace_bytes = split_k > 1 ? (uint64_t)split_k * (uint64_t)M * (uint64_t)N * 4u : 0;
 }
 
+// Makes `p` a launch of any_kernel: 64 x 64 tiles.
+static void fill_any(nimble_plan* p, int64_t batch, int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
+  p->bm = p->bn = p->bk = 64;
+  p->k = M / 64;
+  p->r = (int32_t)(M % 64);
+  p->residue_copy = 1;
+  p->split_k = 1;
+  p->grid[0] = (uint32_t)tiles;
+  p->grid[1] = 1;
+  p->grid[2] = (uint32_t)batch;
+  p->block = any_four_groups(tiles * batch, K) ? 1024u : 256u;
+}
+
 int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int force_variant,
                const PlanOptions& opt, nimble_plan* p) {
   std::memset(p, 0, sizeof(*p));
@@ -382,6 +396,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
   int64_t split_rows = 0;
   int residue_variant = NIMBLE_VAR_AUTO;
   int split_k = 1;
+  bool chosen = forced;  // by the caller or a tuned entry: launched as named
   if (variant == NIMBLE_VAR_AUTO) {
     if (!aligned_k || M == 0 || N == 0) {
       variant = NIMBLE_VAR_GENERIC;
@@ -391,6 +406,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
                       (e->split_k <= 1 ||
                        (uint64_t)e->split_k * (uint64_t)M * (uint64_t)N * 4u <= opt.max_workspace)))) {
       variant = e->variant;  // tuned: one launch of this configuration
+      chosen = true;
       split_k = e->split_k > 1 ? e->split_k : 1;
     } else {
       const Launch single = best_launch(batch, M, N, K, epilogue, opt.max_workspace, true);
@@ -444,16 +460,16 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
     const bool rows = opt.generic_rows && batch == 1 && K > 0 && rows16 <= 65535 &&
                       (rows16 <= 1 || cols16 * rows16 <= 2 * kCUs);
     p->variant = variant;
-    p->bm = p->bn = rows ? 16 : 64;
-    p->bk = rows ? 32 : 64;
-    p->k = M / p->bm;
-    p->r = (int32_t)(M % p->bm);
-    p->residue_copy = 1;
-    p->split_k = 1;
-    p->grid[0] = (uint32_t)(rows ? cols16 : ceil_div(M, 64) * ceil_div(N, 64));
-    p->grid[1] = (uint32_t)(rows ? rows16 : 1);
-    p->grid[2] = (uint32_t)batch;
-    p->block = 256;
+    fill_any(p, batch, M, N, K);
+    if (rows) {
+      p->bm = p->bn = 16;
+      p->bk = 32;
+      p->k = M / 16;
+      p->r = (int32_t)(M % 16);
+      p->grid[0] = (uint32_t)cols16;
+      p->grid[1] = (uint32_t)rows16;
+      p->block = 256;
+    }
     return NIMBLE_OK;
   }
   if (variant == NIMBLE_VAR_SKINNY16) {
@@ -497,6 +513,9 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
     split_k = forced_sk;
   }
   fill_tiled(p, variant, split_k, batch, split_rows > 0 ? split_rows : M, N, K, tile_rows);
+  if (!chosen && split_rows == 0 &&
+      small_tiles_win(variant, (int64_t)p->grid[0] * batch, batch * ceil_div(M, 64) * ceil_div(N, 64), p->bn, N, K, opt.out_f32))
+    fill_any(p, batch, M, N, K);
   if (split_rows > 0) {
     // k and r describe the whole call; grid and residue_copy describe the first launch; the second
     // launch is planned here exactly as the entry point plans it, so that what is reported (its
@@ -675,6 +694,7 @@ int nimble_dense_plan(int64_t M, int64_t N, int64_t K, int epilogue, int out_dty
   if (dtype_size(out_dtype) == 0) return fail(NIMBLE_ERR_DTYPE, "unknown dtype %d", out_dtype);
   PlanOptions opt;
   opt.max_workspace = ~0ull;  // report the plan for a caller that provides what it asks for
+  opt.out_f32 = out_dtype == NIMBLE_F32;
   return plan_dense(1, M, N, K, epilogue, force_variant, opt, plan);
 }
 
@@ -716,6 +736,7 @@ int nimble_batch_matmul_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int
   bmm.allow_row_split = false;
   bmm.use_table = false;
   bmm.generic_rows = trans_b != 0;
+  bmm.out_f32 = out_dtype == NIMBLE_F32;
   if (!trans_b) {
     // b is (T,K,N): its rows are not K-contiguous.  Where the tiled kernels could run the product
     // on b transposed (K a multiple of 8 and whole 16-byte batch strides), the plan is that NT

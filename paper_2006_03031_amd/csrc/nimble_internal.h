@@ -68,6 +68,23 @@ inline bool tile_kernel_wins(int variant, int64_t tiles, int64_t N, int64_t K, b
   return K >= (N % 8 == 0 ? 448 : 896);
 }
 
+// Whether a tiled plan the dispatch function made is launched in the 64 x 64 tiles of any_kernel instead (`tiles`: of
+// the variant's own, over all batches; `small`: of 64 x 64).  Where the ring kernels can run, a partly empty last
+// tile column costs them no more than its loads (ring / any_kernel, microseconds: 423 x 2928 x 3648 20 / 37,
+// 12456 x 200 x 1024 12.5 / 19.6, 1240 x 1112 x 512 6.2 / 8.0), but a handful of tiles leaves the chip to few
+// workgroups, and the smaller ones with K shared by four groups of waves are done earlier (953 x 64 x 512, 15 of them,
+// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0).
+inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, int64_t N, int64_t K, bool out_f32) {
+  if (!ring_shape_ok(N, K)) return !tile_kernel_wins(variant, tiles, N, K, out_f32);
+  return N % bn != 0 && small <= 40;
+}
+
+// Whether a launch of any_kernel shares each tile's K among four groups of waves: a workgroup per compute unit is all
+// there is, and K is long enough to pay for handing the sums over (measured at K = 1000: 1000 x 1000 as A.B 13.2 -> 10.5
+// us, 515 x 1001 10.6 -> 9.4; K = 512: 7.4 -> 7.0; K = 257 7.3 -> 6.8, 256 6.0 -> 6.2, 127 6.4 -> 6.8; with 512 tiles at
+// K = 1000 two groups already took 14.0 -> 15.1).
+inline bool any_four_groups(int64_t tiles, int64_t K) { return K >= 512 && tiles <= kComputeUnits; }
+
 // Whether a weight-streaming launch of 16-row blocks over an [N, K] weight can run the LDS-staged
 // streaming kernel (the LSTM cell needs Ix % 64 == 0 besides).
 bool stream_kernel_shape_ok(int64_t N, int64_t K);
@@ -77,6 +94,7 @@ struct PlanOptions {
   bool allow_row_split = true;  // may dispatch x = bm*k + r as two launches
   int force_split_k = 0;        // > 0 with a forced variant: cut K into exactly this many slices
   bool generic_rows = true;     // the generic variant may run in 16-row blocks (b is [N, K])
+  bool out_f32 = false;         // the output is f32 (which kernel is better for a shape the ring kernels cannot run)
   bool use_table = true;        // consult the tuned dispatch table before the cost model
 };
 

@@ -173,14 +173,11 @@ static SkinnyArgs skinny_args(const GemmArgs& g) {
   return s;
 }
 
-// Operands of any alignment in 64 x 64 tiles.  Four groups of waves share a tile's K where a workgroup
-// per compute unit is all there is and K is long enough to pay for handing the sums over (measured at
-// K = 1000: 1000 x 1000 as A.B 13.2 -> 10.5 us, 515 x 1001 10.6 -> 9.4; K = 512: 7.4 -> 7.0; K = 257 7.3 -> 6.8, 256
-// 6.0 -> 6.2, 127 6.4 -> 6.8; with 512 tiles at K = 1000 two groups already took 14.0 -> 15.1).
+// Operands of any alignment in 64 x 64 tiles.
 static int launch_any(const GemmArgs& g, hipStream_t st) {
   const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
   const dim3 grid((unsigned)tiles_m * (unsigned)tiles_n, 1, (unsigned)g.batch);
-  const bool four = g.K >= 512 && (long long)grid.x * g.batch <= kComputeUnits;
+  const bool four = any_four_groups((int64_t)grid.x * g.batch, g.K);
   if (g.b_is_kn) {
     if (four)
       hipLaunchKernelGGL((any_kernel<64, 64, true, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
@@ -205,22 +202,11 @@ static int launch_tile(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
   return check_hip(hipGetLastError(), "tile kernel launch");
 }
 
-// Tiled plans whose shape the ring kernels cannot run (K not whole stages, output rows not 16-byte
-// aligned) run on any_kernel or, where tile_kernel_wins, on gemm_tile_kernel.  Where they can, a partly empty last
-// tile column costs the ring kernels no more than its loads (ring / any_kernel, microseconds: 423 x 2928 x 3648 20 / 37,
-// 12456 x 200 x 1024 12.5 / 19.6, 1240 x 1112 x 512 6.2 / 8.0), but a handful of tiles leaves the chip to few
-// workgroups, and the smaller ones with K shared by four groups of waves are done earlier (953 x 64 x 512, 15 of them,
-// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0).
-static bool wants_any(const GemmArgs& g, const nimble_plan& p) {
-  if (!ring_shape_ok(g.N, g.K))
-    return g.b_is_kn || !tile_kernel_wins(p.variant, (int64_t)p.grid[0] * p.grid[2], g.N, g.K, g.out_f32 != 0);
-  return g.N % p.bn != 0 && (int64_t)g.batch * ((g.M + 63) / 64) * ((g.N + 63) / 64) <= 40;
-}
-
 static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
-  if (p.variant >= NIMBLE_VAR_T32x128 && wants_any(g, p)) return launch_any(g, st);
+  if (p.variant >= NIMBLE_VAR_T32x128 && p.bn == 64) return launch_any(g, st);  // (see small_tiles_win)
   if (p.variant >= NIMBLE_VAR_T32x128 && !ring_shape_ok(g.N, g.K)) {
     switch (p.variant) {
+      case NIMBLE_VAR_T32x128: return launch_tile<32, 128, 1, 4>(g, p, st);
       case NIMBLE_VAR_T64x128: return launch_tile<64, 128, 2, 2>(g, p, st);
       case NIMBLE_VAR_T128x128: return launch_tile<128, 128, 2, 2>(g, p, st);
       case NIMBLE_VAR_T256x128: return launch_tile<256, 128, 4, 2>(g, p, st);
@@ -378,6 +364,7 @@ int nimble_dense_noalloc_dyn(const void* x, const void* w, const void* bias, voi
   // fits the built-in scratch, planning within the built-in scratch gives the same plan
   PlanOptions opt;
   opt.max_workspace = ~0ull;
+  opt.out_f32 = out_dtype == NIMBLE_F32;
   nimble_plan p;
   int rc = plan_dense(1, M, N, K, epilogue, NIMBLE_VAR_AUTO, opt, &p);
   if (rc != NIMBLE_OK) return rc;
@@ -410,6 +397,7 @@ int nimble_dense_variant_dyn(const void* x, const void* w, const void* bias, voi
   // the dispatch function plans within the scratch the caller brought: no scratch, no K split
   PlanOptions opt;
   opt.max_workspace = workspace_bytes;
+  opt.out_f32 = out_dtype == NIMBLE_F32;
   nimble_plan p;
   int rc = plan_dense(1, M, N, K, epilogue, force_variant, opt, &p);
   if (rc != NIMBLE_OK) return rc;
@@ -476,7 +464,7 @@ int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch
   // (below 4 G multiply-adds reading b as it is wins also where the workspace is there: 12 x 512 x 64 x 512
   // 6.3 us against 13.4, 1000^3 11.0 against 14.8, 12 x 2048 x 64 x 2048 32.6 against 35.4; 2048^3 49 against 33)
   bool transpose_b = false;
-  if (!trans_b && p.variant >= NIMBLE_VAR_T32x128) {
+  if (!trans_b && p.variant >= NIMBLE_VAR_T32x128 && p.bn != 64) {
     if (workspace_bytes >= p.workspace_bytes && (double)batch * (double)M * (double)N * (double)K >= 4e9) {
       transpose_b = true;
     } else {

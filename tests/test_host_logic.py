@@ -365,6 +365,31 @@ def test_plan_invariants_on_random_shapes():
     assert {"skinny16", "t32x128", "t256x256"} <= names
 
 
+def test_plans_describe_the_tiles_that_are_launched():
+    """Shapes that the ring kernels cannot run: the launch is either in the variant's own tiles or in those of 64 x 64,
+    and bm, bn, bk, grid and block say which; a forced variant keeps its own."""
+    small = lambda p: (p.bm, p.bn, p.bk) == (64, 64, 64)
+    for M, N, K in ((515, 1001, 1000), (130, 4096, 4104), (953, 64, 512), (600, 600, 1000)):
+        p = nb.dense_plan(M, N, K)
+        tiles = -(-M // 64) * -(-N // 64)
+        assert p.name != "generic" and small(p) and p.grid == (tiles, 1, 1), (M, N, K, p)
+        assert (p.k, p.r, p.split_k, p.workspace_bytes) == (M // 64, M % 64, 1, 0)
+        assert p.block == (1024 if tiles <= 256 and K >= 512 else 256)
+        for variant, (bm, bn) in TILED.items():
+            f = nb.dense_plan(M, N, K, force_variant=variant)
+            assert (f.bm, f.bn) == (bm, bn)
+    for M, N, K in ((4096, 4096, 4104), (8000, 4096, 1000), (8000, 4100, 1000), (2900, 3471, 4568), (423, 2928, 3648)):
+        p = nb.dense_plan(M, N, K)
+        assert (p.bm, p.bn) == TILED[p.variant], (M, N, K, p)
+    # any_kernel writes whole rows of bf16, the tile kernel single pieces: a short K does not make up for that
+    assert small(nb.dense_plan(6000, 4096, 136, out_dtype=nb.BF16)) and not small(nb.dense_plan(6000, 4096, 136, out_dtype=nb.F32))
+    p = nb.batch_matmul_plan(8, 1000, 1000, 1000, True)
+    assert (p.bm, p.bn) == TILED[p.variant] and p.grid[2] == 8
+    p = nb.batch_matmul_plan(96, 500, 500, 64, True)
+    assert small(p) and p.grid == (64, 1, 96)
+    assert nb.dense_plan(515, 1001, 1003).block == 1024 and nb.dense_plan(2000, 2001, 1003).block == 256   # the generic variant
+
+
 def test_batch_matmul_plan_nn_workspace():
     # NN on the tiled kernels needs b transposed: the plan asks for exactly that much scratch
     p = nb.batch_matmul_plan(12, 512, 64, 512, False)
