@@ -225,7 +225,8 @@ int nimble_dense_noalloc_dyn(const void* x, const void* w, const void* bias, voi
  * a, b bf16; c of out_dtype; f32 accumulation.  With trans_b == 0 the tiled kernels run on b
  * transposed into the workspace (nimble_batch_matmul_plan gives its size, batch*N*K*2 bytes,
  * when K is a multiple of 8 and a tile suits the shape); with less workspace than that, or none, and
- * below 4 G multiply-adds anyway, the kernel for any alignment reads b as it is. */
+ * where that is estimated to be faster (for most plans in 64 x 64 tiles), the kernel for any alignment
+ * reads b as it is and the workspace is left alone. */
 int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch, int64_t M,
                             int64_t N, int64_t K, int trans_b, float alpha, int out_dtype,
                             void* workspace, size_t workspace_bytes, void* stream);

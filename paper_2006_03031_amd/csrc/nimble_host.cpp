@@ -536,6 +536,42 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
   return NIMBLE_OK;
 }
 
+// One launch of any_kernel, microseconds: a lone tile's walk over its stages of 64 k (a quarter of them where four
+// groups of waves share it), or what a compute unit's tiles take one behind the other; b [K, N] takes longer than [N, K].
+static double any_cost_us(int64_t batch, int64_t M, int64_t N, int64_t K, bool b_is_kn) {
+  const int64_t tiles = batch * ceil_div(M, 64) * ceil_div(N, 64), stages = ceil_div(K, 64);
+  const double deep = (double)(any_four_groups(tiles, K) ? ceil_div(stages, 4) : stages);
+  double per_cu = (double)tiles / (double)kCUs;
+  if (per_cu > 1.0 && per_cu < 2.0) per_cu = 2.0;
+  double lone, many;
+  if (b_is_kn) {
+    lone = any_four_groups(tiles, K) ? 3.5 + 1.14 * deep : 3.0 + 0.67 * deep;
+    many = 3.0 + per_cu * (0.6 + 0.42 * (double)stages);
+  } else {
+    lone = any_four_groups(tiles, K) ? 3.2 + 1.28 * deep : 4.0 + 0.56 * deep;
+    many = 4.0 + per_cu * (0.69 + 0.27 * (double)stages);
+  }
+  return lone > many ? lone : many;
+}
+
+// Whether the product A.B with b [K, N] is done sooner by the launch `p` on b transposed (a graph node more, and 0.3
+// microseconds per megabyte of b written and read back) than by any_kernel on b as it is.  The tiled estimates leave
+// out the launch and what the operands take to memory and back, which counts for short K; the tile kernel for
+// shapes that the ring kernels cannot run takes twice their time.  Checked on 290 products of 30 M to 40 G
+// multiply-adds, 1 .. 96 batches: the choice costs 0.6 % over the better one of each.  any_kernel / transposed, microseconds:
+// 12 x 512 x 64 x 512 6.1 / 13.2, 1 x 1000^3 9.9 / 20.4, 96 x 512 x 64 x 512 20 / 27, 24 x 1151 x 320 x 256 19 / 23;
+// 1 x 4096 x 1024 x 512 15.5 / 13.0, 8 x 1000^3 56 / 48, 1 x 2048 x 2048 x 2040 62 / 51, 4 x 1905 x 2048 x 1408 123 / 62.
+bool nn_transposes(const nimble_plan& p, int64_t batch, int64_t M, int64_t N, int64_t K) {
+  double us = 8.0 + 0.3e-6 * (double)(batch * N * K * 2);
+  if (p.bn == 64) {
+    us += any_cost_us(batch, M, N, K, false) - 2.5;
+  } else {
+    const double tiled = tiled_cost_us(p.variant, batch, M, N, K, NIMBLE_EPI_NONE, 1, p.bm);
+    us += (ring_shape_ok(N, K) ? tiled : 2.0 * tiled) + 0.12e-6 * (double)(batch * (M * K + N * K + M * N) * 2);
+  }
+  return us < any_cost_us(batch, M, N, K, true);
+}
+
 static size_t dtype_size(int dtype) {
   switch (dtype) {
     case NIMBLE_BF16: return 2;
@@ -739,17 +775,17 @@ int nimble_batch_matmul_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int
   bmm.out_f32 = out_dtype == NIMBLE_F32;
   if (!trans_b) {
     // b is (T,K,N): its rows are not K-contiguous.  Where the tiled kernels could run the product
-    // on b transposed (K a multiple of 8 and whole 16-byte batch strides), the plan is that NT
-    // launch and its workspace is the transposed copy of b; the entry point falls back to the
-    // bounds-checked kernel, which reads b strided, when the caller brings less.
-    // (worth the extra launch from about 32 M multiply-adds: the bounds-checked kernel takes
-    // 0.35 us per million, 4 us at config 4's L = 128 and 70 us at L = 512)
+    // on b transposed (K a multiple of 8 and whole 16-byte batch strides) from about 32 M multiply-adds on,
+    // the plan is that NT launch and its workspace is the transposed copy of b, unless any_kernel, which reads b
+    // as it is, is done sooner: then the plan is in its 64 x 64 tiles.  The entry point runs any_kernel on b as it
+    // is too when the caller brings less workspace.
     if (K > 0 && K % 8 == 0 && ((M * K) & 7) == 0 && ((N * K) & 7) == 0 && batch > 0 && M > 0 && N > 0 &&
         (double)batch * (double)M * (double)N * (double)K >= 32e6) {
       int rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_AUTO, bmm, plan);
       if (rc != NIMBLE_OK) return rc;
       if (plan->variant >= NIMBLE_VAR_T32x128) {
         plan->workspace_bytes = (uint64_t)batch * (uint64_t)N * (uint64_t)K * 2u;
+        if (!nn_transposes(*plan, batch, M, N, K)) fill_any(plan, batch, M, N, K);
         return NIMBLE_OK;
       }
     }

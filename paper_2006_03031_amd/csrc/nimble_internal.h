@@ -102,6 +102,9 @@ struct PlanOptions {
 int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int force_variant,
                const PlanOptions& opt, nimble_plan* p);
 
+// Whether the batch_matmul plan `p` with b [K, N], a tiled one, is launched on b transposed.
+bool nn_transposes(const nimble_plan& p, int64_t batch, int64_t M, int64_t N, int64_t K);
+
 // One C = epi(alpha * A.B^T + bias) problem as the kernels see it.  A is
 // [M,K] with row stride lda, B is [N,K] with row stride ldb (or, when
 // b_is_kn, [K,N] with row stride ldb), C is [M,N] with row stride ldc; strides

@@ -460,17 +460,12 @@ int nimble_batch_matmul_dyn(const void* a, const void* b, void* c, int64_t batch
   if (misaligned(a) || misaligned(b) || misaligned(c))
     return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
   // the NN product on the tiled kernels needs b transposed into the workspace: without enough of
-  // it the bounds-checked kernel does the job (the plan is made within the scratch the caller brought)
-  // (below 4 G multiply-adds reading b as it is wins also where the workspace is there: 12 x 512 x 64 x 512
-  // 6.3 us against 13.4, 1000^3 11.0 against 14.8, 12 x 2048 x 64 x 2048 32.6 against 35.4; 2048^3 49 against 33)
+  // it any_kernel does the job (the plan is made within the scratch the caller brought)
   bool transpose_b = false;
-  if (!trans_b && p.variant >= NIMBLE_VAR_T32x128 && p.bn != 64) {
-    if (workspace_bytes >= p.workspace_bytes && (double)batch * (double)M * (double)N * (double)K >= 4e9) {
-      transpose_b = true;
-    } else {
-      rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_GENERIC, any_b, &p);
-      if (rc != NIMBLE_OK) return rc;
-    }
+  if (!trans_b && p.variant >= NIMBLE_VAR_T32x128) {
+    transpose_b = workspace_bytes >= p.workspace_bytes && nn_transposes(p, batch, M, N, K);
+    if (!transpose_b) rc = plan_dense(batch, M, N, K, NIMBLE_EPI_NONE, NIMBLE_VAR_GENERIC, any_b, &p);
+    if (rc != NIMBLE_OK) return rc;
   }
   GemmArgs g{};
   g.a = a;

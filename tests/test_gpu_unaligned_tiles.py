@@ -63,6 +63,29 @@ def test_batch_matmul(nb, T, M, N, K):
             _check(buf[:T * M * N].view(T, M, N)[t], 0.5 * (a[t].double() @ b[t].double().T.contiguous()), od == nb.F32, (t, T, M, N, K))
 
 
+# b [T, K, N] transposed into the workspace, then the ring kernels (whole and partly empty last tiles) or the tile kernel
+@pytest.mark.parametrize("T,M,N,K", [(1, 4096, 1024, 512), (4, 1905, 2048, 1408), (12, 2311, 392, 896), (24, 1590, 1536, 384),
+                                     (2, 937, 2464, 1120), (8, 1000, 1000, 1000), (3, 2050, 1032, 1048)])
+def test_batch_matmul_on_b_transposed(nb, T, M, N, K):
+    from paper_2006_03031_amd import runtime as rt
+    p = nb.batch_matmul_plan(T, M, N, K, False)
+    assert p.bn != 64 and p.workspace_bytes == 2 * T * N * K, p   # this launch, not the one that reads b as it is
+    a, b, _ = _operands(M, N, K, T)
+    b = b.transpose(1, 2).contiguous()
+    print(f"batch_matmul A.B {T} x {M} x {N} x {K}", flush=True)
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    exact = torch.empty(p.workspace_bytes + 256, dtype=torch.uint8, device="cuda").fill_(77)
+    for od, dt in ((nb.F32, torch.float32), (nb.BF16, torch.bfloat16)):
+        for ws in (exact[:p.workspace_bytes], none):
+            buf = torch.full((T * M * N + 256,), 768.0, dtype=dt, device="cuda")
+            rt.batch_matmul(a, b, False, 0.5, od, out=buf[:T * M * N].view(T, M, N), workspace=ws)
+            assert bool((buf[T * M * N:] == 768.0).all()) and bool((exact[p.workspace_bytes:] == 77).all())
+            rows = torch.cat([torch.arange(0, 3), torch.arange(M - 260, M)]).cuda()
+            for t in (0, T - 1):
+                _check(buf[:T * M * N].view(T, M, N)[t][rows], 0.5 * (a[t][rows].double() @ b[t].double()), od == nb.F32,
+                       (t, T, M, N, K, ws.numel()))
+
+
 @pytest.mark.parametrize("M,N,K,part", [(4096, 4096, 4104, 0.8),    # K not whole stages: 153 us against 287 in 64 x 64 tiles
                                         (423, 2928, 3648, 0.8)])   # a partly empty last tile column: 20 against 37
 def test_large_products_do_not_run_in_small_tiles(nb, M, N, K, part):

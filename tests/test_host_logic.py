@@ -400,6 +400,19 @@ def test_batch_matmul_plan_nn_workspace():
     assert nb.batch_matmul_plan(12, 512, 512, 64, True).workspace_bytes == 0
 
 
+def test_batch_matmul_plan_nn_says_whether_b_is_transposed():
+    """b [T,K,N]: short and narrow products read b as it is, in 64 x 64 tiles; where a copy of b costs less than its
+    tiled launch saves the plan is tiled."""
+    for T, M, N, K in ((12, 512, 64, 512), (1, 1000, 1000, 1000), (96, 512, 64, 512), (12, 2050, 8, 1024), (4, 128, 2048, 1024),
+                       (2, 2048, 1001, 1024), (4, 300, 1028, 1000)):
+        p = nb.batch_matmul_plan(T, M, N, K, False)
+        assert (p.bm, p.bn) == (64, 64), (T, M, N, K, p)
+        assert p.grid == (-(-M // 64) * -(-N // 64), 1, T)
+    for T, M, N, K in ((1, 4096, 1024, 512), (8, 1000, 1000, 1000), (4, 1094, 256, 1088), (4, 1905, 2048, 1408)):
+        p = nb.batch_matmul_plan(T, M, N, K, False)
+        assert p.bn in (128, 256) and p.workspace_bytes == T * N * K * 2, (T, M, N, K, p)
+
+
 def test_batch_matmul_plans_are_one_launch_covering_every_row():
     """batch_matmul launches its plan as it stands: the plan must never split the rows in two
     launches or cut K, and the r = 0 copy (no bounds code) may only be chosen when no tile is ragged."""
