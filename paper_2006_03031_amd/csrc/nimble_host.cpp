@@ -103,7 +103,9 @@ bool wide_stages_ok(int64_t K, int64_t slices) {
 // The 128-wide tiles up to 128 rows on the 64-wide ring, at most two tiles per compute unit, microseconds: a
 // lone tile's fixed time plus its walk over the K stages (32 k each), slower the more tiles there are; from
 // one tile per compute unit on, two workgroups share one.  Fitted to graph-timed launches over K = 768 .. 4096
-// and 24 .. 450 tiles; GELU adds half a microsecond.
+// and 24 .. 450 tiles; GELU adds half a microsecond.  At K below 320 only up to one 64-row tile per compute unit:
+// against the taller tiles, priced without a fixed time, 12 x 512 x 512 x 64 was run in 96 tiles of 256 rows, 6.3 us instead
+// of 5.3 in 384 of 64, and 4956 x 1664 x 128 in 11.1 instead of 8.8.
 static double few_tiles_us(int v, int64_t tiles, int64_t stages, bool gelu) {
   const double t = (double)(tiles < kCUs ? tiles : kCUs);
   double fixed, per_stage, shared = 1.65, more = 0.25;
@@ -141,7 +143,10 @@ static double tiled_cost_us(int v, int64_t batch, int64_t rows, int64_t N, int64
   const int64_t stages = ceil_div(k_slice, 32);
   const bool gelu = sk == 1 && epilogue == NIMBLE_EPI_BIAS_GELU_ERF;
   double us;
-  if (v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
+  // (with K this short the fixed time in the first estimate, which the second leaves out, would decide between them:
+  // it is used only where all three tiles are priced by it)
+  const bool few = v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && (K >= 320 || batch * ceil_div(rows, 64) * ceil_div(N, 128) <= kCUs);
+  if (few && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
     us = few_tiles_us(v, tiles, stages, gelu);
   } else {
     const double latency_floor = (double)stages * kStageFloorUs[v] + (gelu ? 0.05 : 0.0);

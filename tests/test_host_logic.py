@@ -365,6 +365,16 @@ def test_plan_invariants_on_random_shapes():
     assert {"skinny16", "t32x128", "t256x256"} <= names
 
 
+def test_short_k_is_not_run_in_tiles_that_leave_the_chip_idle():
+    """K of one to four stages of 64: with a few hundred 64-row tiles to hand the plan is not in a third of as many 256-row ones."""
+    for T, M, N, K in ((12, 512, 512, 64), (12, 448, 512, 64), (12, 512, 512, 128), (8, 512, 1024, 128), (48, 256, 256, 64), (12, 640, 640, 64)):
+        p = nb.batch_matmul_plan(T, M, N, K, True)
+        assert p.bm <= 128 and p.grid[0] * p.grid[2] >= 192, (T, M, N, K, p)
+    for M, N, K in ((4956, 1664, 128), (1176, 3712, 128), (1909, 2304, 64), (1797, 1792, 64), (1388, 3328, 256), (1201, 3456, 192)):
+        p = nb.dense_plan(M, N, K)
+        assert p.bm <= 128 and p.grid[0] >= 192, (M, N, K, p)
+
+
 def test_plans_describe_the_tiles_that_are_launched():
     """Shapes that the ring kernels cannot run: the launch is either in the variant's own tiles or in those of 64 x 64,
     and bm, bn, bk, grid and block say which; a forced variant keeps its own."""
