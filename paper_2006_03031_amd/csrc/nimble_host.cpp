@@ -237,7 +237,10 @@ static double skinny_cost_us(int64_t rows, int64_t N, int64_t K) {
       walk = (double)wgs * (2.0 + 0.11 * (double)ceil_div(ceil_div(K, 64), 4)) / (4.0 * (double)kCUs);
       if (walk < 0.8) walk = 0.8;
     }
-    return kLaunchUs + (stream > walk ? stream : walk);
+    const double us = kLaunchUs + (stream > walk ? stream : walk);
+    // (more than the four to a compute unit that are resident: a last, partly empty round, which shows with long walks:
+    // 378 x 768 x 4032 15.0 us against 12.9 in tiles with K in four, but 198 x 1536 x 576 4.6 against 5.5)
+    return cached && wgs > 4 * kCUs && K >= 1024 ? 1.05 * us : us;
   }
   const int64_t nblocks = skinny_row_blocks(rows, N, K, false);
   const double mt = (double)ceil_div(rows, 16 * nblocks);
@@ -282,7 +285,7 @@ struct Launch {
 static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int epilogue,
                           uint64_t max_workspace, bool allow_skinny) {
   Launch best;
-  double skinny_us = -1.0;
+  double skinny_us = -1.0, least_tiled_us = 1e30;
   // weight streaming: up to 64 rows, and beyond that in 16-row blocks of the streaming kernel while
   // the layer is small enough for the blocks' re-reads to come from L2
   if (allow_skinny && batch == 1 &&
@@ -299,6 +302,7 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
       // the calls it took when K was cut by powers of two)
       if (sk == 3 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > (uint64_t)NIMBLE_NOALLOC_SCRATCH_BYTES) continue;
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, sk);
+      if (us < least_tiled_us) least_tiled_us = us;
       // (a finer cut of the same tile takes more workspace: it has to win by more than the estimate is good for)
       const double bar = best.variant == v && best.split_k > 1 ? 0.95 * best.us : best.us;
       if (best.variant < 0 || us < bar) {
@@ -323,9 +327,10 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
         }
       }
   }
-  // up to 64 rows the small tiles (with K cut) compete with weight streaming (compared launch included);
+  // up to 64 rows the small tiles (with K cut) compete with weight streaming (compared launch included, and at
+  // the least of their estimates: 59 x 6656 x 2624 13.1 us with K in four, 15.5 streamed);
   // up to 16 rows the streaming kernel was the fastest choice on every layer measured
-  if (skinny_us >= 0.0 && (best.variant < 0 || skinny_us <= best.us + kLaunchUs ||
+  if (skinny_us >= 0.0 && (best.variant < 0 || skinny_us <= least_tiled_us + kLaunchUs ||
                            (rows <= 16 && stream_kernel_shape_ok(N, K)))) {
     best = Launch();
     best.variant = NIMBLE_VAR_SKINNY16;
