@@ -106,6 +106,9 @@ bool wide_stages_ok(int64_t K, int64_t slices) {
 // and 24 .. 450 tiles; GELU adds half a microsecond.  At K below 320 only up to one 64-row tile per compute unit:
 // against the taller tiles, priced without a fixed time, 12 x 512 x 512 x 64 was run in 96 tiles of 256 rows, 6.3 us instead
 // of 5.3 in 384 of 64, and 4956 x 1664 x 128 in 11.1 instead of 8.8.
+// Nor from K = 12288 on, too far from the fit (1960 x 1792 x 16384 121 -> 131 us, 450 x 896 x 12288 with K in three
+// 24 -> 32): there the older estimate decides alone, over cuts of K by powers of two.
+static const int64_t kLongestFitted = 12288;
 static double few_tiles_us(int v, int64_t tiles, int64_t stages, bool gelu) {
   const double t = (double)(tiles < kCUs ? tiles : kCUs);
   double fixed, per_stage, shared = 1.65, more = 0.25;
@@ -145,7 +148,7 @@ static double tiled_cost_us(int v, int64_t batch, int64_t rows, int64_t N, int64
   double us;
   // (with K this short the fixed time in the first estimate, which the second leaves out, would decide between them:
   // it is used only where all three tiles are priced by it)
-  const bool few = v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && (K >= 320 || batch * ceil_div(rows, 64) * ceil_div(N, 128) <= kCUs);
+  const bool few = v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && K < kLongestFitted && (K >= 320 || batch * ceil_div(rows, 64) * ceil_div(N, 128) <= kCUs);
   if (few && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
     us = few_tiles_us(v, tiles, stages, gelu);
   } else {
@@ -300,11 +303,12 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
       if (sk > 1 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > max_workspace) continue;
       // (three slices only within the built-in scratch, so that the entry point that lives on it keeps taking
       // the calls it took when K was cut by powers of two)
+      if (sk == 3 && K >= kLongestFitted) continue;
       if (sk == 3 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > (uint64_t)NIMBLE_NOALLOC_SCRATCH_BYTES) continue;
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, sk);
       if (us < least_tiled_us) least_tiled_us = us;
       // (a finer cut of the same tile takes more workspace: it has to win by more than the estimate is good for)
-      const double bar = best.variant == v && best.split_k > 1 ? 0.95 * best.us : best.us;
+      const double bar = best.variant == v && best.split_k > 1 && K < kLongestFitted ? 0.95 * best.us : best.us;
       if (best.variant < 0 || us < bar) {
         best.variant = v;
         best.split_k = sk;

@@ -601,6 +601,14 @@ def test_forced_variant_and_k_split_from_the_environment():
     assert out.stdout.split() == ["t128x128", "2", str(2 * 300 * 768 * 4)]
 
 
+def test_no_alloc_entry_point_keeps_taking_long_layers_whose_cuts_fit_its_scratch():
+    # plans of K far beyond the range the lone tiles' estimate is fitted to: their scratch stays within the built-in one
+    for M, N, K in ((5206, 1024, 16384), (6908, 768, 16384), (3393, 1536, 16384), (115, 4608, 18432), (119, 4608, 20480),
+                    (121, 5376, 14848), (2868, 1792, 15744)):
+        for epi in (nb.EPI_NONE, nb.EPI_BIAS, nb.EPI_BIAS_GELU_ERF):
+            assert nb.dense_plan(M, N, K, epi).workspace_bytes <= nb.NOALLOC_SCRATCH_BYTES, (M, N, K, epi)
+
+
 def test_no_alloc_entry_point_refuses_what_its_scratch_cannot_hold():
     # host-side validation only (no GPU in this process): the refusal comes before any device access
     lib = nb.load()
