@@ -307,8 +307,12 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
       if (sk == 3 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > (uint64_t)NIMBLE_NOALLOC_SCRATCH_BYTES) continue;
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, sk);
       if (us < least_tiled_us) least_tiled_us = us;
-      // (a finer cut of the same tile takes more workspace: it has to win by more than the estimate is good for)
-      const double bar = best.variant == v && best.split_k > 1 && K < kLongestFitted ? 0.95 * best.us : best.us;
+      // (a finer cut takes more workspace and more of the memory's time: of the same tile, or of one of up to 128 rows
+      // against a smaller tile, it has to win by more than the estimates are good for: 879 x 1024 x 6528 in 128-row
+      // tiles with K in four 29.9 us, in 64-row tiles with K in two 23.1; 149 x 3712 x 6272 the same, 26.5 and 21.1)
+      const bool finer = best.split_k > 1 && K < kLongestFitted &&
+                         (best.variant == v || (sk > best.split_k && v <= NIMBLE_VAR_T128x128));
+      const double bar = finer ? 0.95 * best.us : best.us;
       if (best.variant < 0 || us < bar) {
         best.variant = v;
         best.split_k = sk;
