@@ -374,8 +374,8 @@ static void fill_any(nimble_plan* p, int64_t batch, int64_t M, int64_t N, int64_
   p->r = (int32_t)(M % 64);
   p->residue_copy = 1;
   p->split_k = 1;
-  p->grid[0] = (uint32_t)tiles;
-  p->grid[1] = 1;
+  p->grid[0] = (uint32_t)(tiles < kAnyTilesAlongX ? tiles : kAnyTilesAlongX);
+  p->grid[1] = (uint32_t)(tiles > 0 ? ceil_div(tiles, kAnyTilesAlongX) : 1);
   p->grid[2] = (uint32_t)batch;
   p->block = any_four_groups(tiles * batch, K) ? 1024u : 256u;
 }

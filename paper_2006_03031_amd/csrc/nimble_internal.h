@@ -85,6 +85,9 @@ inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, i
 // K = 1000 two groups already took 14.0 -> 15.1).
 inline bool any_four_groups(int64_t tiles, int64_t K) { return K >= 512 && tiles <= kComputeUnits; }
 
+// Tiles of any_kernel along the first dimension of the grid, which holds less than 2^32 threads; the rest go to the second.
+constexpr int64_t kAnyTilesAlongX = 1 << 22;
+
 // Whether a weight-streaming launch of 16-row blocks over an [N, K] weight can run the LDS-staged
 // streaming kernel (the LSTM cell needs Ix % 64 == 0 besides).
 bool stream_kernel_shape_ok(int64_t N, int64_t K);

@@ -176,8 +176,10 @@ static SkinnyArgs skinny_args(const GemmArgs& g) {
 // Operands of any alignment in 64 x 64 tiles.
 static int launch_any(const GemmArgs& g, hipStream_t st) {
   const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
-  const dim3 grid((unsigned)tiles_m * (unsigned)tiles_n, 1, (unsigned)g.batch);
-  const bool four = any_four_groups((int64_t)grid.x * g.batch, g.K);
+  const int64_t tiles = (int64_t)tiles_m * tiles_n;
+  const dim3 grid((unsigned)(tiles < kAnyTilesAlongX ? tiles : kAnyTilesAlongX),
+                  (unsigned)((tiles + kAnyTilesAlongX - 1) / kAnyTilesAlongX), (unsigned)g.batch);
+  const bool four = any_four_groups(tiles * g.batch, g.K);
   if (g.b_is_kn) {
     if (four)
       hipLaunchKernelGGL((any_kernel<64, 64, true, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);

@@ -57,6 +57,29 @@ def test_dense_of_any_shape(nb, M, N, K):
                od == nb.F32)
 
 
+def test_more_tiles_than_one_grid_dimension_holds(nb):
+    """4.4 million tiles of 64 x 64 (an output of 36 GB): the second grid dimension takes the rest."""
+    from paper_2006_03031_amd import runtime as rt
+    M, N, K = 400_003, 45_001, 40
+    p = nb.dense_plan(M, N, K, nb.EPI_NONE)
+    assert (p.bm, p.bn) == (64, 64) and p.grid[1] == 2
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    x = torch.empty((M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    w = torch.empty((N, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    print(f"dense {M} x {N} x {K}", flush=True)
+    buf = torch.empty(M * N + 256, dtype=torch.bfloat16, device="cuda").fill_(768.0)
+    y = rt.dense(x, w, None, nb.EPI_NONE, nb.BF16, out=buf[:M * N].view(M, N))
+    assert bool((buf[M * N:] == 768.0).all())
+    rows = torch.cat([torch.arange(0, 2), torch.arange(M // 2, M // 2 + 2), torch.arange(M - 66, M)]).cuda()
+    ref = x[rows].double() @ w.double().T.contiguous()
+    assert ((y[rows].double() - ref).abs() / (ref.abs() + ref.abs().mean())).max().item() <= 2.0 ** -8
+    for r0 in range(0, M, 20_000):   # every tile was written
+        assert bool((y[r0:r0 + 20_000, ::64] != 768.0).all()), r0
+    del buf, y
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("T,M,N,K", [(3, 65, 64, 33), (2, 64, 63, 64), (2, 1, 1, 1), (3, 70, 7, 9), (2, 129, 65, 257), (1, 63, 72, 600),
                                      (12, 33, 64, 513), (5, 200, 200, 1003), (2, 64, 8, 512)])
 @pytest.mark.parametrize("trans_b", [False, True])

@@ -385,6 +385,15 @@ def test_close_estimates_of_streaming_and_tiles():
         assert nb.dense_plan(M, N, K).name == "skinny16", (M, N, K)
 
 
+def test_launches_of_very_large_outputs_stay_within_the_grid():
+    # 2^32 threads along the first dimension: an output of 80 G elements (160 GB in bf16) is more tiles of 64 x 64 than that
+    for M, N, K in ((1_000_000, 80_001, 1003), (80_001, 1_000_000, 8), (1_000_000, 80_001, 64), (300, 400, 7)):
+        p = nb.dense_plan(M, N, K)
+        tiles = -(-M // p.bm) * -(-N // p.bn)
+        assert p.grid[0] * p.block < 2 ** 32 and p.grid[1] <= 65535, (M, N, K, p)
+        assert tiles <= p.grid[0] * p.grid[1] < tiles + p.grid[0]
+
+
 def test_a_finer_cut_of_k_in_a_taller_tile_has_to_win_clearly():
     """Within a few percent by estimate, 64-row tiles with K in two beat 128-row ones with K in four: 23.1 us against 29.9
     at 879 x 1024 x 6528, 21.1 against 26.5 at 149 x 3712 x 6272."""
