@@ -11,11 +11,11 @@ namespace nimble {
 // C = epi(alpha A.B + bias) with no condition on the shape.  A row of an operand with K % 8 != 0
 // starts at any even address, so neither the direct global->LDS loads nor aligned vector loads can
 // fetch it; here every lane brings 16-byte chunks through registers with unaligned loads.
-//   Tile BM x BN, 4 waves (2 x 2), stages of 64 k, two LDS buffers, one barrier per stage; the
+//   Tile 64 x 64, 4 waves (2 x 2), stages of 64 k, two LDS buffers, one barrier per stage; the
 //   chunks of the next P stages are on their way while a stage is multiplied (P register sets, 2 or 4).  K past
 //   the end is zero-filled in the chunk that holds it, rows past M (N) repeat the last one and are
 //   never stored.
-//   KN: B is [K, N]; its tile keeps its rows (64 k of BN n) in LDS and the fragments come out of
+//   KN: B is [K, N]; its tile keeps its rows (64 k of 64 n) in LDS and the fragments come out of
 //   the transposing LDS read.
 //   KG = 4: four groups of four waves take the stages in turn and add their sums at the end.
 //   What bounds it: a few hundred tiles of some ten stages are the whole launch, so the chain load ->
@@ -26,8 +26,9 @@ namespace nimble {
 //   12 x 333 x 64 x 333 as A.B 88 -> 6.6 us.  128 x 128 tiles were measured too: no faster even at
 //   8000 x 1001 x 1003 (54 us against 51), half the speed on small grids.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, bool KN, int P, int KG>
+template <bool KN, int P, int KG>
 __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, int tiles_n) {
+  constexpr int BM = 64, BN = 64;
   constexpr int A_CH = BM * 8 / 256, B_CH = BN * 8 / 256;  // 16-byte chunks per thread and stage
   constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 16, TN = WN / 16;
   constexpr int ELD = WN + 4;  // floats per row of a wave's output staging area
@@ -73,7 +74,7 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
   // chunks stay together, spread so that the 8 rows a transposing read touches fall into different banks
   auto phys = [](int row, int c) { return row * 8 + (c ^ ((row >> 1) & 7)); };
   auto phys_kn = [](int k, int c) {
-    const int f = BN == 64 ? (((k >> 1) & 1) | (((k >> 3) & 1) << 1)) : ((k & 3) | (((k >> 3) & 1) << 2));
+    const int f = ((k >> 1) & 1) | (((k >> 3) & 1) << 1);
     return k * NC + (c ^ (f << 1));
   };
 
@@ -232,7 +233,7 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
     }
     // (wave-private: a wave's LDS accesses execute in order)
     if (g.out_f32) {
-      constexpr int RP = 64 / WN < 1 ? 1 : 64 / WN;  // rows per store
+      constexpr int RP = 64 / WN;  // rows per store
       float* C = (float*)g.c + (long long)z * g.sc;
 #pragma unroll
       for (int p = 0; p < 16 / RP; ++p) {

@@ -182,14 +182,14 @@ static int launch_any(const GemmArgs& g, hipStream_t st) {
   const bool four = any_four_groups(tiles * g.batch, g.K);
   if (g.b_is_kn) {
     if (four)
-      hipLaunchKernelGGL((any_kernel<64, 64, true, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
+      hipLaunchKernelGGL((any_kernel<true, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
     else
-      hipLaunchKernelGGL((any_kernel<64, 64, true, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
+      hipLaunchKernelGGL((any_kernel<true, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
   } else {
     if (four)
-      hipLaunchKernelGGL((any_kernel<64, 64, false, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
+      hipLaunchKernelGGL((any_kernel<false, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
     else
-      hipLaunchKernelGGL((any_kernel<64, 64, false, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
+      hipLaunchKernelGGL((any_kernel<false, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
   }
   return check_hip(hipGetLastError(), "any kernel launch");
 }
