@@ -98,8 +98,8 @@ def test_batch_matmul_of_any_shape(nb, T, M, N, K, trans_b):
                od == nb.F32)
 
 
-# above 5 G multiply-adds a partly empty last tile column runs in the ring kernels: 1000 and 1032 columns leave
-# 104 and 8 of them in the last tile; every tile of the family, both outputs
+# a partly empty last tile column in the ring kernels: 1000 and 1032 columns leave 104 and 8 of them in the last tile;
+# every tile of the family, both outputs
 @pytest.mark.parametrize("name", ["t32x128", "t64x128", "t128x128", "t256x128", "t256x256"])
 @pytest.mark.parametrize("N,K", [(1000, 1024), (1032, 1056)])
 def test_ring_kernels_mask_the_last_columns(nb, name, N, K):
@@ -118,3 +118,31 @@ def test_ring_kernels_mask_the_last_columns(nb, name, N, K):
         got = from_dev(buf)
         assert np.all(got[M * N:] == 768.0), "wrote past the output"
         _check(got[:M * N].reshape(M, N)[rows], oracle.dense(x.f32[rows], w.f32, b.f32, ename), (name, N, K, ename, od), od == nb.F32)
+
+
+# the same where every workgroup walks several tiles and hands its ring to the next one, which may be the partly empty
+# column's or the last row's; both ring widths (K = 192 is whole stages of 64, K = 160 is not), bias in LDS and none
+@pytest.mark.parametrize("name,rows,resident", [("t32x128", 32, 512), ("t64x128", 64, 512), ("t128x128", 128, 512), ("t256x128", 256, 256),
+                                                ("t256x256", 256, 256)])
+@pytest.mark.parametrize("K", [192, 160])
+def test_ring_kernels_walk_tiles_past_a_partly_empty_column(nb, name, rows, resident, K):
+    from paper_2006_03031_amd import runtime as rt
+    variant = [i for i in range(7) if nb.variant_name(i) == name][0]
+    width = 256 if name == "t256x256" else 128
+    N = 3 * width - 56
+    M = (2 * resident // 3 + 3) * rows + 1
+    assert -(-M // rows) * 3 > 2 * resident
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K + rows)
+    x = torch.empty((M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    w = torch.empty((N, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    b = torch.empty((N,), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    ref = x.double() @ w.double().T.contiguous()
+    print(f"ring walk {name} {M} {N} {K}", flush=True)
+    for epi, od in ((nb.EPI_BIAS, nb.BF16), (nb.EPI_NONE, nb.BF16), (nb.EPI_BIAS, nb.F32)):
+        buf, out = _guarded((M, N), torch.float32 if od == nb.F32 else torch.bfloat16)
+        rt.dense(x, w, b if epi == nb.EPI_BIAS else None, epi, od, force_variant=variant, out=out)
+        assert bool((buf[M * N:] == 768.0).all()), "wrote past the output"
+        want = ref + b.double() if epi == nb.EPI_BIAS else ref
+        err = ((out.double() - want).abs() / (want.abs() + want.abs().mean())).max().item()
+        assert err <= (GATE_F32 if od == nb.F32 else 2.0 ** -8), (name, K, epi, od, err)   # summation order; one rounding

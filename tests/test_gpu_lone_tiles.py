@@ -17,7 +17,7 @@ def nb():
 
 # K: one stage, fewer stages than slots, as many, more; the line between three and four slots (2048); the line
 # between eight and four waves of the 64-row tile (K > 2048: 224 tiles); one tile, 256, 257; a last row alone, a
-# last column tile partly empty (above the size at which any_kernel takes it); K not in 64-wide stages; three slices
+# last column tile partly empty; K not in 64-wide stages; three slices
 @pytest.mark.parametrize("variant,M,N,K,split", [
     (T32, 1, 128, 64, 1), (T32, 33, 256, 128, 1), (T32, 256, 4096, 192, 1), (T32, 257, 4096, 256, 1), (T32, 95, 384, 1056, 1),
     (T64, 64, 128, 64, 1), (T64, 65, 128, 128, 1), (T64, 127, 384, 192, 1), (T64, 512, 4096, 256, 1), (T64, 513, 4096, 256, 1),

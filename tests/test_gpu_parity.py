@@ -763,9 +763,10 @@ def test_batch_matmul_general_shapes(rt, nb):
 
 
 def test_batch_matmul_nn_on_the_tiled_kernels_and_without_workspace(rt, nb):
-    """b [T,K,N] with K a multiple of 8: the plan is the NT launch on b transposed into the workspace
-    (config 4's P.V at L = 128..512 among the shapes); a caller that brings no workspace gets the
-    bounds-checked kernel and the same result to within rounding."""
+    """b [T,K,N] with K a multiple of 8: the plan is a tiled one and asks for the workspace of b transposed
+    (config 4's P.V at L = 128..512 among the shapes), with or without which a caller gets the same result to
+    within rounding.  (Products as short as these read b as it is either way: test_gpu_unaligned_tiles has those
+    that are launched on b transposed.)"""
     to_dev, _, from_dev, _ = _dev()
     rng = np.random.default_rng(10)
     none = torch.empty(0, dtype=torch.uint8, device="cuda")
