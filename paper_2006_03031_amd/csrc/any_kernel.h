@@ -42,10 +42,8 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
   const int wm = wave >> 1, wn = wave & 1;
   const int z = blockIdx.z;
   const int M = g.M, N = g.N, K = g.K;
-  const int tile = blockIdx.y * gridDim.x + blockIdx.x;  // (a launch holds less than 2^32 threads along x)
-  if (tile >= tiles_m * tiles_n) return;
   int tm, tn;
-  tile_of_block(tile, tiles_m * tiles_n, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4, tm, tn);
+  tile_of_block(blockIdx.x, tiles_m * tiles_n, tiles_m, tiles_n, tiles_m < 4 ? tiles_m : 4, tm, tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const u16* __restrict__ A = (const u16*)g.a + (long long)z * g.sa;
   const u16* __restrict__ B = (const u16*)g.b + (long long)z * g.sb;

@@ -368,14 +368,20 @@ static void fill_tiled(nimble_plan* p, int variant, int split_k, int64_t batch, 
 
 // Makes `p` a launch of any_kernel: 64 x 64 tiles.
 static void fill_any(nimble_plan* p, int64_t batch, int64_t M, int64_t N, int64_t K) {
-  const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 64);
+  const int64_t tiles_m = ceil_div(M, 64), tiles_n = ceil_div(N, 64), tiles = tiles_m * tiles_n;
   p->bm = p->bn = p->bk = 64;
   p->k = M / 64;
   p->r = (int32_t)(M % 64);
   p->residue_copy = 1;
   p->split_k = 1;
-  p->grid[0] = (uint32_t)(tiles < kAnyTilesAlongX ? tiles : kAnyTilesAlongX);
-  p->grid[1] = (uint32_t)(tiles > 0 ? ceil_div(tiles, kAnyTilesAlongX) : 1);
+  p->grid[0] = (uint32_t)tiles;
+  p->grid[1] = 1;
+  if (tiles > 0) {
+    int64_t tm, tn;
+    any_launch_tiles(tiles_m, tiles_n, &tm, &tn);
+    p->grid[0] = (uint32_t)(tm * tn);
+    p->grid[1] = (uint32_t)(ceil_div(tiles_m, tm) * ceil_div(tiles_n, tn));  // launches, 1 but for outputs of over 17 G elements
+  }
   p->grid[2] = (uint32_t)batch;
   p->block = any_four_groups(tiles * batch, K) ? 1024u : 256u;
 }

@@ -85,8 +85,13 @@ inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, i
 // K = 1000 two groups already took 14.0 -> 15.1).
 inline bool any_four_groups(int64_t tiles, int64_t K) { return K >= 512 && tiles <= kComputeUnits; }
 
-// Tiles of any_kernel along the first dimension of the grid, which holds less than 2^32 threads; the rest go to the second.
-constexpr int64_t kAnyTilesAlongX = 1 << 22;
+// Tiles of one launch of any_kernel (a launch holds less than 2^32 threads); larger outputs take several, each of at most
+// `tm` x `tn` tiles.  (With the rest in the second grid dimension every launch paid 0.1 to 0.2 us for finding its tile.)
+inline void any_launch_tiles(int64_t tiles_m, int64_t tiles_n, int64_t* tm, int64_t* tn) {
+  constexpr int64_t most = 1 << 22;
+  *tn = tiles_n < most ? tiles_n : most;
+  *tm = tiles_m * *tn <= most ? tiles_m : most / *tn;
+}
 
 // Whether a weight-streaming launch of 16-row blocks over an [N, K] weight can run the LDS-staged
 // streaming kernel (the LSTM cell needs Ix % 64 == 0 besides).

@@ -175,23 +175,36 @@ static SkinnyArgs skinny_args(const GemmArgs& g) {
 
 // Operands of any alignment in 64 x 64 tiles.
 static int launch_any(const GemmArgs& g, hipStream_t st) {
-  const int tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
-  const int64_t tiles = (int64_t)tiles_m * tiles_n;
-  const dim3 grid((unsigned)(tiles < kAnyTilesAlongX ? tiles : kAnyTilesAlongX),
-                  (unsigned)((tiles + kAnyTilesAlongX - 1) / kAnyTilesAlongX), (unsigned)g.batch);
-  const bool four = any_four_groups(tiles * g.batch, g.K);
-  if (g.b_is_kn) {
-    if (four)
-      hipLaunchKernelGGL((any_kernel<true, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
-    else
-      hipLaunchKernelGGL((any_kernel<true, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
-  } else {
-    if (four)
-      hipLaunchKernelGGL((any_kernel<false, 2, 4>), grid, dim3(1024), 0, st, g, tiles_m, tiles_n);
-    else
-      hipLaunchKernelGGL((any_kernel<false, 4, 1>), grid, dim3(256), 0, st, g, tiles_m, tiles_n);
-  }
-  return check_hip(hipGetLastError(), "any kernel launch");
+  const int64_t tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
+  const bool four = any_four_groups(tiles_m * tiles_n * g.batch, g.K);
+  int64_t tm, tn;
+  any_launch_tiles(tiles_m, tiles_n, &tm, &tn);
+  for (int64_t m0 = 0; m0 < g.M; m0 += tm * 64)
+    for (int64_t n0 = 0; n0 < g.N; n0 += tn * 64) {
+      GemmArgs part = g;
+      part.M = (int)(g.M - m0 < tm * 64 ? g.M - m0 : tm * 64);
+      part.N = (int)(g.N - n0 < tn * 64 ? g.N - n0 : tn * 64);
+      part.a = (const u16*)g.a + m0 * g.lda;
+      part.b = (const u16*)g.b + (g.b_is_kn ? n0 : n0 * g.ldb);
+      if (g.bias) part.bias = (const u16*)g.bias + n0;
+      part.c = g.out_f32 ? (void*)((float*)g.c + m0 * g.ldc + n0) : (void*)((u16*)g.c + m0 * g.ldc + n0);
+      const int pm = (part.M + 63) / 64, pn = (part.N + 63) / 64;
+      const dim3 grid((unsigned)pm * (unsigned)pn, 1, (unsigned)g.batch);
+      if (g.b_is_kn) {
+        if (four)
+          hipLaunchKernelGGL((any_kernel<true, 2, 4>), grid, dim3(1024), 0, st, part, pm, pn);
+        else
+          hipLaunchKernelGGL((any_kernel<true, 4, 1>), grid, dim3(256), 0, st, part, pm, pn);
+      } else {
+        if (four)
+          hipLaunchKernelGGL((any_kernel<false, 2, 4>), grid, dim3(1024), 0, st, part, pm, pn);
+        else
+          hipLaunchKernelGGL((any_kernel<false, 4, 1>), grid, dim3(256), 0, st, part, pm, pn);
+      }
+      const int rc = check_hip(hipGetLastError(), "any kernel launch");
+      if (rc != NIMBLE_OK) return rc;
+    }
+  return NIMBLE_OK;
 }
 
 // The variant's own tiles, every access bounds-checked; as many workgroups as are resident at once walk them.

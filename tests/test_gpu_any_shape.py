@@ -57,8 +57,8 @@ def test_dense_of_any_shape(nb, M, N, K):
                od == nb.F32)
 
 
-def test_more_tiles_than_one_grid_dimension_holds(nb):
-    """4.4 million tiles of 64 x 64 (an output of 36 GB): the second grid dimension takes the rest."""
+def test_more_tiles_than_one_launch_holds(nb):
+    """4.4 million tiles of 64 x 64 (an output of 36 GB): two launches."""
     from paper_2006_03031_amd import runtime as rt
     M, N, K = 400_003, 45_001, 40
     p = nb.dense_plan(M, N, K, nb.EPI_NONE)

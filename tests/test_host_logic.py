@@ -386,7 +386,8 @@ def test_close_estimates_of_streaming_and_tiles():
 
 
 def test_launches_of_very_large_outputs_stay_within_the_grid():
-    # 2^32 threads along the first dimension: an output of 80 G elements (160 GB in bf16) is more tiles of 64 x 64 than that
+    # less than 2^32 threads in a launch: an output of 80 G elements (160 GB in bf16) is more tiles of 64 x 64 than that
+    # (grid[1] of such a plan: launches)
     for M, N, K in ((1_000_000, 80_001, 1003), (80_001, 1_000_000, 8), (1_000_000, 80_001, 64), (300, 400, 7)):
         p = nb.dense_plan(M, N, K)
         tiles = -(-M // p.bm) * -(-N // p.bn)
