@@ -293,8 +293,9 @@ int nimble_lstm_seq_shape(const int64_t* pre_shape, const int64_t* h0_shape, con
  * (at most 64 workgroups, all resident at once); else 0: run the steps one by one. */
 int nimble_lstm_seq_supported(int64_t B, int64_t H);
 
-/* 1 when, besides, the one launch measured faster than one launch per step (H <= 512, or one row up to
- * H = 1024); the hint a caller's dispatch takes. */
+/* 1 when, besides, H <= 512 or B = 1: the hint a caller's dispatch takes.  A fixed rule, not a measurement of the
+ * present loop, which is faster than one launch per step wherever it is supported (H = 1024: 1.7 us per step at 2 rows
+ * and 2.1 at 4 against 3.0). */
 int nimble_lstm_seq_preferred(int64_t B, int64_t H);
 
 /* Bytes of device workspace the call needs: 256 bytes of control words, then two (B,H) planes of

@@ -101,6 +101,7 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
 #pragma unroll
     for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
   float ref = -3.0e38f;                          // in raw-score units; finite: a block of infinitely low scores adds zeros
+                                                 // (while 3e38 a2 is finite: up to alpha = 0.78)
   float sum0 = 0.f, sum1 = 0.f;                  // this lane's share of the row sum
   const float a2 = alpha * 1.4426950408889634f;
 

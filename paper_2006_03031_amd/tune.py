@@ -139,7 +139,7 @@ def ablation(M: int = 128) -> str:
                   for M = 128 would be
       residue     the same tile's r != 0 copy (run at M = 127): the last tile is masked
       big tile    a 256-row tile at M = 128: half of every tile is masked (too few kernels)
-      no dispatch the one kernel that handles everything, bounds-checked per element
+      no dispatch the generic variant, which handles every shape and alignment, bounds-checked
       dispatch    the dispatch function choosing from the whole family at run time"""
     layers = [("768->2304", 768, 2304, nb.EPI_BIAS), ("768->768", 768, 768, nb.EPI_BIAS),
               ("768->3072 gelu", 768, 3072, nb.EPI_BIAS_GELU_ERF)]
