@@ -147,9 +147,9 @@ static double tiled_cost_us(int v, int64_t batch, int64_t rows, int64_t N, int64
   const bool gelu = sk == 1 && epilogue == NIMBLE_EPI_BIAS_GELU_ERF;
   double us;
   // (with K this short the fixed time in the first estimate, which the second leaves out, would decide between them:
-  // it is used only where all three tiles are priced by it)
+  // it is used only where all three tiles are priced by it; and only for shapes that the 64-wide ring runs)
   const bool few = v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && K < kLongestFitted && (K >= 320 || batch * ceil_div(rows, 64) * ceil_div(N, 128) <= kCUs);
-  if (few && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
+  if (few && N % 8 == 0 && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
     us = few_tiles_us(v, tiles, stages, gelu);
   } else {
     const double latency_floor = (double)stages * kStageFloorUs[v] + (gelu ? 0.05 : 0.0);

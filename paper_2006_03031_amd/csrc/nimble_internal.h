@@ -55,28 +55,18 @@ inline bool ring_shape_ok(int64_t N, int64_t K) { return K % 32 == 0 && N % 8 ==
 // tiles with K shared by groups of waves are the better use of it.  Microseconds, tile kernel / any_kernel, to f32:
 // 64- and 128-row tiles: 392 (3130 x 1024 x 904) 18 / 24, 306 (1117 x 4240 x 2648) 53 / 70, 225 (606 x 5760 x 1608) 36 / 39,
 // 190 (2332 x 432 x 712) 11.2 / 9.8; 256-wide tiles: 234 (6421 x 2304 x 2808) 124 / 210, 165 (2771 x 3656 x 4560) 168 / 219,
-// 136 (951 x 8632 x 2256) 85 / 84, 126 (1484 x 2688 x 3416) 79 / 70.  Its lanes write the columns they own, four at a time,
-// where any_kernel writes whole rows: K has to be long enough to make up for that.  6000 x 4096 to f32 25 / 29 at K = 40
-// and 84 / 113 at 1000, to bf16 42 / 34 at 136, 54 / 54 at 328, 79 / 83 at 648; 6000 x 4100 (rows of whole 8-byte pieces)
-// to f32 39 / 38 at 136, 77 / 83 at 648, to bf16 71 / 68 at 456, 106 / 114 at 1000; with N not a multiple of 4 the columns are
-// written one by one: 4434 x 2078 x 2016 104 / 83, 2771 x 3471 x 4560 with GELU 181 / 199.
+// 144 (6000 x 1502 x 6000) 226 / 241, 136 (951 x 8632 x 2256) 85 / 84, 126 (1484 x 2688 x 3416) 79 / 70.  Its lanes write
+// the columns they own, four at a time, where any_kernel writes whole rows: K has to be long enough to make up for
+// that.  6000 x 4096 to f32 25 / 29 at K = 40 and 84 / 113 at 1000, to bf16 42 / 34 at 136, 54 / 54 at 328, 79 / 83 at 648;
+// 6000 x 4100 (rows of whole 8-byte pieces) to f32 39 / 38 at 136, 43 / 45 at 200, to bf16 71 / 68 at 456, 106 / 114 at
+// 1000; 4442 x 6852 x 184 to f32 49 / 55; with N not a multiple of 4 the columns are written one by one: 4434 x 2078 x
+// 2016 104 / 83, 2771 x 3471 x 4560 with GELU 181 / 199.
 inline bool tile_kernel_wins(int variant, int64_t tiles, int64_t N, int64_t K, bool out_f32) {
   if (variant < NIMBLE_VAR_T64x128) return false;
-  if (tiles < (variant <= NIMBLE_VAR_T128x128 ? 256 : 160)) return false;
+  if (tiles < (variant <= NIMBLE_VAR_T128x128 ? 256 : K >= 4096 ? 140 : 160)) return false;
   if (N % 4 != 0) return K >= 4096;
-  if (out_f32) return N % 8 == 0 || K >= 512;
+  if (out_f32) return N % 8 == 0 || K >= 160;
   return K >= (N % 8 == 0 ? 448 : 896);
-}
-
-// Whether a tiled plan the dispatch function made is launched in the 64 x 64 tiles of any_kernel instead (`tiles`: of
-// the variant's own, over all batches; `small`: of 64 x 64).  Where the ring kernels can run, a partly empty last
-// tile column costs them no more than its loads (ring / any_kernel, microseconds: 423 x 2928 x 3648 20 / 37,
-// 12456 x 200 x 1024 12.5 / 19.6, 1240 x 1112 x 512 6.2 / 8.0), but a handful of tiles leaves the chip to few
-// workgroups, and the smaller ones with K shared by four groups of waves are done earlier (953 x 64 x 512, 15 of them,
-// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0).
-inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, int64_t N, int64_t K, bool out_f32) {
-  if (!ring_shape_ok(N, K)) return !tile_kernel_wins(variant, tiles, N, K, out_f32);
-  return N % bn != 0 && small <= 40;
 }
 
 // Whether a launch of any_kernel shares each tile's K among four groups of waves: a workgroup per compute unit is all
@@ -84,6 +74,18 @@ inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, i
 // us, 515 x 1001 10.6 -> 9.4; K = 512: 7.4 -> 7.0; K = 257 7.3 -> 6.8, 256 6.0 -> 6.2, 127 6.4 -> 6.8; with 512 tiles at
 // K = 1000 two groups already took 14.0 -> 15.1).
 inline bool any_four_groups(int64_t tiles, int64_t K) { return K >= 512 && tiles <= kComputeUnits; }
+
+// Whether a tiled plan the dispatch function made is launched in the 64 x 64 tiles of any_kernel instead (`tiles`: of
+// the variant's own, over all batches; `small`: of 64 x 64).  Where the ring kernels can run, a partly empty last
+// tile column costs them no more than its loads (ring / any_kernel, microseconds: 423 x 2928 x 3648 20 / 37,
+// 12456 x 200 x 1024 12.5 / 19.6, 1240 x 1112 x 512 6.2 / 8.0), but a handful of tiles leaves the chip to few
+// workgroups, and the smaller ones with K shared by four groups of waves are done earlier (953 x 64 x 512, 15 of them,
+// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0; without
+// the groups 238 x 264 x 96, 20, 3.9 / 4.4).
+inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, int64_t N, int64_t K, bool out_f32) {
+  if (!ring_shape_ok(N, K)) return !tile_kernel_wins(variant, tiles, N, K, out_f32);
+  return N % bn != 0 && small <= 40 && any_four_groups(small, K);
+}
 
 // Tiles of one launch of any_kernel (a launch holds less than 2^32 threads); larger outputs take several, each of at most
 // `tm` x `tn` tiles.  (With the rest in the second grid dimension every launch paid 0.1 to 0.2 us for finding its tile.)

@@ -419,6 +419,10 @@ def test_plans_describe_the_tiles_that_are_launched():
     for M, N, K in ((4096, 4096, 4104), (8000, 4096, 1000), (8000, 4100, 1000), (2900, 3471, 4568), (423, 2928, 3648)):
         p = nb.dense_plan(M, N, K)
         assert (p.bm, p.bn) == TILED[p.variant], (M, N, K, p)
+    # few tiles but a K too short to share, rows of 8-byte pieces to f32, a long K with 144 tiles of 256 x 256
+    for M, N, K, od in ((238, 264, 96, nb.F32), (4442, 6852, 184, nb.F32), (6000, 1502, 6000, nb.BF16), (2660, 1636, 5056, nb.BF16)):
+        p = nb.dense_plan(M, N, K, nb.EPI_BIAS_GELU_ERF, od)
+        assert (p.bm, p.bn) == TILED[p.variant], (M, N, K, p)
     # any_kernel writes whole rows of bf16, the tile kernel single pieces: a short K does not make up for that
     assert small(nb.dense_plan(6000, 4096, 136, out_dtype=nb.BF16)) and not small(nb.dense_plan(6000, 4096, 136, out_dtype=nb.F32))
     p = nb.batch_matmul_plan(8, 1000, 1000, 1000, True)
