@@ -294,8 +294,8 @@ int nimble_lstm_seq_shape(const int64_t* pre_shape, const int64_t* h0_shape, con
 int nimble_lstm_seq_supported(int64_t B, int64_t H);
 
 /* 1 when, besides, H <= 512 or B = 1: the hint a caller's dispatch takes.  A fixed rule, not a measurement of the
- * present loop, which is faster than one launch per step wherever it is supported (H = 1024: 1.7 us per step at 2 rows
- * and 2.1 at 4 against 3.0). */
+ * present loop, which is faster than one launch per step wherever it is supported (H = 1024: 1.6 us per step at
+ * 4 rows against 3.0). */
 int nimble_lstm_seq_preferred(int64_t B, int64_t H);
 
 /* Bytes of device workspace the call needs: 256 bytes of control words, then two (B,H) planes of
@@ -322,6 +322,25 @@ int nimble_lstm_seq_pre_dyn(const void* pre, const void* w_h, const void* h0, co
 /* Waits for `stream`, then copies the give-up word of `workspace` to the host:
  * *gave_up = 0: every step ran; 1: the loop gave up (see above).  NIMBLE_ERR_HIP if the copy fails. */
 int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up);
+
+/* ---- the token loop of a batch, waiting for nothing -------------------------------------
+ * The same loop for more rows (groups of 8, each on its own workgroups) and for either form of the inputs'
+ * share: Ix = 0 with pre [T,B,4H] f32 and w = w_h [4H,H] (x and bias are not read), or Ix > 0 with
+ * x [T,B,Ix] bf16, w [4H,Ix+H] bf16 and bias [4H] bf16 (pre is not read).  Three launches are enqueued (fill,
+ * loop, recovery) and nothing is waited for or read back, so the call can be captured: where the loop gives up,
+ * the recovery launch runs the sequence again with workgroups that wait for nobody (slowly), else it ends at
+ * once.  h_seq and c_out are right either way and bit-identical to T calls of nimble_lstm_gates_dyn
+ * (nimble_lstm_gates_pre_dyn with pre); c_out may alias c0.
+ * Supported: H = 64..1024 and Ix >= 0 in multiples of 64 with Ix + H <= 1024, Ix a multiple of 128 where Ix + H > 512;
+ * B <= 256 at H = 512, 512 at 256, 128 at 1024; where the per-step launch adds in another order (Ix + H other than
+ * 512 or 1024) fewer, 32 at H = 512.  Workspace of
+ * nimble_lstm_loop_workspace_bytes, its use, max_polls and the errors as for nimble_lstm_seq_pre_dyn;
+ * nimble_lstm_seq_status tells whether the loop gave up. */
+int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H);
+size_t nimble_lstm_loop_workspace_bytes(int64_t B, int64_t Ix, int64_t H);
+int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const void* bias, const void* h0,
+                         const void* c0, void* h_seq, void* c_out, int64_t T, int64_t B, int64_t Ix, int64_t H,
+                         void* workspace, size_t workspace_bytes, uint32_t max_polls, void* stream);
 
 #ifdef __cplusplus
 }

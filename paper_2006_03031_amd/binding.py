@@ -119,6 +119,11 @@ def load():
     lib.nimble_lstm_seq_pre_dyn.argtypes = [vp, vp, vp, vp, vp, vp, i64, i64, i64, vp, ctypes.c_size_t,
                                             ctypes.c_uint32, vp]
     lib.nimble_lstm_seq_status.argtypes = [vp, vp, ctypes.POINTER(ctypes.c_int)]
+    lib.nimble_lstm_loop_supported.argtypes = [i64, i64, i64]
+    lib.nimble_lstm_loop_workspace_bytes.argtypes = [i64, i64, i64]
+    lib.nimble_lstm_loop_workspace_bytes.restype = ctypes.c_size_t
+    lib.nimble_lstm_loop_dyn.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, vp, ctypes.c_size_t,
+                                         ctypes.c_uint32, vp]
     lib.nimble_probe_mfma_bf16.argtypes = [vp, vp, i32, i32, ctypes.POINTER(ctypes.c_double), vp]
     lib.nimble_probe_hbm_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
     _lib = lib
@@ -247,6 +252,20 @@ def nimble_lstm_seq_status(workspace: int, stream: int) -> bool:
     flag = ctypes.c_int(0)
     _check(load().nimble_lstm_seq_status(workspace, stream, ctypes.byref(flag)))
     return bool(flag.value)
+
+
+def lstm_loop_supported(B: int, Ix: int, H: int) -> bool:
+    return bool(load().nimble_lstm_loop_supported(B, Ix, H))
+
+
+def lstm_loop_workspace_bytes(B: int, Ix: int, H: int) -> int:
+    return int(load().nimble_lstm_loop_workspace_bytes(B, Ix, H))
+
+
+def nimble_lstm_loop_dyn(x: int, pre: int, w: int, bias: int, h0: int, c0: int, h_seq: int, c_out: int, T: int, B: int,
+                         Ix: int, H: int, workspace: int, workspace_bytes: int, max_polls: int, stream: int) -> None:
+    _check(load().nimble_lstm_loop_dyn(x, pre, w, bias, h0, c0, h_seq, c_out, T, B, Ix, H, workspace, workspace_bytes,
+                                       max_polls, stream))
 
 
 def storage_bytes(shape: Sequence[int], dtype: int) -> int:

@@ -1,5 +1,5 @@
-// Token loop of one LSTM sequence in a single launch: recurrent weights resident in registers, the
-// hidden state handed from step to step through tagged words in memory, every wait bounded.
+// Token loop of a batch of LSTM sequences in a single launch: weights resident in registers, the hidden
+// state handed from step to step through self-describing words in memory, every wait bounded.
 #ifndef NIMBLE_LSTM_SEQ_KERNEL_H_
 #define NIMBLE_LSTM_SEQ_KERNEL_H_
 #include "device_common.h"
@@ -8,107 +8,151 @@ namespace nimble {
 
 // ---------------------------------------------------------------------------
 // The evaluation section's LSTM remark: a cell step is too small to fill the chip, so a sequence is
-// bound by what separates the steps.  As one launch per step that is the 2-3 us between dependent
+// bound by what separates the steps.  As one launch per step that is the 2-4 us between dependent
 // kernels; here the steps of a sequence run inside one launch.
-//   Inputs: pre [T, B, 4H] f32, the inputs' share of the gates with the bias added (one dense call
-//   over all T*B tokens ahead of the loop), w_h [4H, H] bf16, h_0 [B, H] bf16, c_0 [B, H] f32.
-//   Grid: H / 8 or H / 16 workgroups of 8 waves; a workgroup owns 4 G hidden units = 16 G gate rows (G groups
-//   of the i, f, g, o rows of 4 units) and keeps those rows of w_h in registers for the whole
-//   sequence (wave w: the 64-wide K stages w * per_wave ...: 8 registers per group and stage).  Per
-//   step a wave fetches its K range of h_{t-1}, multiplies, leaves its partial sums in LDS; after one
-//   barrier four neighbouring lanes per (row, unit) add them up and apply the nonlinearity, one gate
-//   each, and the first of them updates the cell.  c_t stays in that lane's register.
-//   Hand-over of h_t: a workgroup publishes its units per row as 32-bit words, bf16 value in the
-//   high half and a step tag (1..65535, never 0) in the low half, with device-scope stores into
-//   buffer t & 1 of two; a consumer wave loads the words of its K range once each, device scope, repeats
-//   until every tag is this step's, and brings them into the MFMA operand layout through a piece of LDS of its own.  Data and arrival are one word: no counter, no fence,
-//   one store and one load on the critical path (a counter barrier over 16 workgroups was measured
-//   at 0.85 us per step bare and 1.56 us with the data exchanged behind it).  Two buffers suffice:
-//   h_t overwrites h_{t-2}, which every workgroup has finished reading before it publishes h_{t-1},
-//   without which nobody can compute h_t.  Tags t and t-2 always differ (the tag period is odd).
-//   The words are cleared, and buffer 0 filled with h_0, by lstm_seq_init_kernel ahead of the launch
-//   on the same stream: a stale tag of an earlier launch can never be taken for this one's.
-//   Every wait is bounded: a wave polls at most max_polls times per step, checking the give-up word
-//   each time; a wave that runs out sets it, and every workgroup leaves at its next check.  So the
-//   grid drains whatever happens (fewer workgroups resident than launched, a stalled neighbour),
-//   the host reads the word afterwards and runs the sequence step by step instead.  max_polls = 0
-//   gives up at the first wait: the host-side way to exercise that path.
-//   Arithmetic: identical, bit for bit, to the per-step kernel on the same shapes (stream_kernel
-//   with 8 waves: the same K stages per wave, the same two accumulators per stage pair, the same
-//   order of adding the waves' partial sums, the same cell function).
-//   Measured, microseconds per step at 1 / 2 / 4 rows (a captured graph of per-step launches: 2.65-2.72 at
-//   H = 512, 2.85-2.95 at H = 1024): H = 512: 1.60 / 1.63 / 1.64; H = 1024: 1.76 / - / 1.96.
-//   A step is one trip to the memory side and back (0.75 us from the store to the polled words), the MFMAs and
-//   partial sums, the barrier, the cell arithmetic.  What the polls ask of the memory side is what counts beside
-//   that: with the words loaded straight in the operand layout (8 loads per stage, every word asked for by up to 16
-//   lanes) the same steps took 1.94 / 2.12 / 2.44 and 2.80 / - / 4.02, and two or more polls in flight at staggered
-//   times made them 2.5 and more.  Tried and not kept: every wave
-//   multiplying its own 16 gate rows over the whole of K from a copy of h in LDS and updating its cells
-//   itself (no partial sums, no single epilogue: 4.1 us per step, the eight waves' reads of all of h cost
-//   more LDS time than the sums saved); all workgroups on one XCD (every 8th of a grid 8 times as large)
-//   exchanging the words with workgroup-scope loads: the words never became visible, the loop gave up as
-//   designed.
+//   Inputs: w_h [4H, H] with pre [T, B, 4H] f32, the inputs' share of the gates with the bias added (one
+//   dense call over all T*B tokens ahead of the loop), or the fused weight w [4H, Ix + H] with x [T, B, Ix] and
+//   the bias; h_0 [B, H] bf16, c_0 [B, H] f32.
+//   Grid: the rows of the batch are cut into groups of R = 8 (one of R = 4 up to 4 rows), which have nothing to do
+//   with each other; per group H / 16 workgroups of 8 waves.  A workgroup owns U = 16 hidden units = 64 gate rows (G
+//   = 4 groups of the i, f, g, o rows of 4 units) and keeps those rows of the weight in registers for the whole
+//   sequence (wave w: the 64-wide K stages w * per_wave ...: 8 registers per group and stage; at most 128 in all, so that two
+//   workgroups fit a compute unit and two loops on two streams do not wait for each other's places).  Per step a
+//   wave multiplies its stages of x_t, loaded a step ahead, or its K range of h_{t-1}, and leaves its partial sums
+//   in LDS; after one barrier the first R U lanes, one per (row, unit), add them up and update the cell.  c_t
+//   stays in that lane's register.
+//   Hand-over of h_t: 64-bit words of four neighbouring units of a row, stored with device scope into buffer
+//   t & 1 of two, in an order in which a wave stores 128 contiguous bytes (8 workgroups' words in one line: 2.4 us
+//   per step) and loads 512 (8 rows of 32 k or 4 rows of 64 k).  |h| <= 1 leaves bit 14 of a bf16, the top bit of
+//   its exponent, zero: in the first value of a word it carries the phase, which changes with every use of a
+//   buffer, in the second a mark that values of the word are NaN (then written as 0x3fff, which no h is).  A
+//   consumer wave loads the words of its K range, device scope, until all of them are in this step's phase: data
+//   and arrival are one word, no counter, no fence, one store and one load on the critical path (a counter
+//   barrier over 16 workgroups was measured at 0.85 us per step bare).  Two buffers suffice: h_t overwrites
+//   h_{t-2}, which every workgroup has finished reading before it publishes h_{t-1}, without which nobody can
+//   compute h_t; so a word is either two steps old or this step's, and one bit tells them apart.  The words are
+//   cleared by lstm_seq_init_kernel ahead of the launch on the same stream (the first phase is 1).
+//   Every wait is bounded: a wave polls at most max_polls times per step, looking at the give-up word with every
+//   eighth; a wave that runs out sets it, and every workgroup leaves at its next check.  So the
+//   grid drains whatever happens (fewer workgroups resident than launched, a stalled neighbour).  Then either
+//   the host reads the word and runs the sequence step by step, or lstm_seq_recover_kernel, enqueued behind, does.
+//   max_polls = 0 gives up at the first wait: the host-side way to exercise that path.
+//   Arithmetic: identical, bit for bit, to the per-step kernel on the same shapes (stream_kernel: the same
+//   eight ranges of K stages, the same two accumulators per range, the same order of adding the ranges' sums, the same
+//   cell function).
+//   What bounds it: one trip through the memory system per step (store, then a load that sees it), about half of the step;
+//   the rest is a chain of MFMAs, LDS sums, barrier and cell arithmetic.  Microseconds per step, pre form at
+//   1 / 4 rows: H = 512 1.10 / 1.17, H = 1024 1.41 / 1.56, H = 256 1.14 / - (32-bit words with a step tag each, four lanes
+//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 / 64 rows, H = Ix = 512: 1.24 /
+//   1.37 / 1.37 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
+//   per cell, 32-byte stores 2.31; one lane per cell, 128-byte stores 1.95; a row group's workgroups on one XCD
+//   and a late first poll 1.56; operands polled straight into their registers, no address arithmetic in the loop 1.37.
+//   Tried and not kept: system scope, exchanges instead of stores, raised priority for the cells (no change); a
+//   first poll whose delay adapts, a step later for each failure and a quarter earlier for each success (1.7-1.9:
+//   of 128 waves some one always fails); every wave multiplying its own 16 gate rows over the whole of K (4.1: the
+//   waves' reads of all of h cost more LDS time than the sums saved); workgroup-scope loads within one XCD (the
+//   words never become visible).
 // ---------------------------------------------------------------------------
 struct LstmSeqArgs {
-  const float* pre;   // [T, B, 4H]
-  const u16* w_h;     // [4H, H]
+  const u16* x;       // [T, B, Ix], or null
+  const float* pre;   // [T, B, 4H], in place of x and bias
+  const u16* w;       // [4H, Ix + H]
+  const u16* bias;    // [4H], with x
   const u16* h0;      // [B, H]
   const float* c0;    // [B, H]
   u16* h_seq;         // [T, B, H]
   float* c_out;       // [B, H]
   uint32_t* ctl;      // 64 words: [0] give-up word, [1] workgroups that ran all T steps
-  uint32_t* exch;     // [2][B][H] tagged words
-  int T, B, H;
+  unsigned long long* exch;  // [row group][2][words of 4 units]: B * H / 2 words
+  float* c_keep;      // [B, H] or null: c_0 for the recovery kernel (c_out may be c_0)
+  int T, B, Ix, H;
   uint32_t max_polls;
 };
 
-__device__ __forceinline__ uint32_t lstm_seq_tag(int t) { return (uint32_t)(t % 65535) + 1u; }
-
-// Clears the control words and buffer 1, fills buffer 0 with h_0 tagged as step 0.
-__global__ void __launch_bounds__(256) lstm_seq_init_kernel(LstmSeqArgs a) {
+// Clears the control words and the hand-over words, keeps c_0 for the recovery kernel.
+__global__ void __launch_bounds__(256) lstm_seq_init_kernel(LstmSeqArgs a, int words) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   const int n = a.B * a.H;
   if (i < 64) a.ctl[i] = 0u;
-  if (i < n) {
-    a.exch[i] = ((uint32_t)a.h0[i] << 16) | lstm_seq_tag(0);
-    a.exch[n + i] = 0u;
-  }
+  for (int j = i; j < words; j += gridDim.x * 256) a.exch[j] = 0ull;
+  if (i < n && a.c_keep) a.c_keep[i] = a.c0[i];
 }
 
-// PW: K stages of 64 per wave, ceil(H / 64 / 8); G: groups of 16 gate rows (4 units) per workgroup
-template <int PW, int G>
-__global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
+// lane i of 16 takes the value of lane i + N
+template <int N>
+__device__ __forceinline__ uint32_t lane_up(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x100 + N, 0xf, 0xf, true);
+}
+// every lane of 4 takes the value of lane Q of them
+template <int Q>
+__device__ __forceinline__ uint32_t quad_lane(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, Q * 0x55, 0xf, 0xf, true);
+}
+
+constexpr uint32_t kHandOverPhase = 0x4000u, kHandOverNan = 0x40000000u;
+
+// The address at a wave-uniform base plus a 32-bit byte offset of the lane's own.  (The offset is made opaque: left to
+// itself the compiler adds the two ahead of the loop and keeps 64-bit addresses in vector registers.)
+template <typename V>
+__device__ __forceinline__ V* at(V* base, uint32_t bytes) {
+  asm volatile("" : "+v"(bytes));
+  return (V*)((const char*)base + bytes);
+}
+
+// phase of the words of step t = 1, 2, ... in their buffer t & 1: 1 at the first use, then in turn
+__device__ __forceinline__ uint32_t lstm_seq_phase(int t) { return ((t - 1) & 2) ? 0u : kHandOverPhase; }
+
+// 0x3fff in either half of a word marked so: NaN
+__device__ __forceinline__ uint32_t lstm_seq_nans(uint32_t v) {
+  const uint32_t lo = (v & 0x3fffu) == 0x3fffu ? 0x7fc0u : (v & 0xffffu);
+  const uint32_t hi = (v & 0x3fff0000u) == 0x3fff0000u ? 0x7fc00000u : (v & 0xffff0000u);
+  return lo | hi;
+}
+
+// PRE: the inputs' share comes precomputed, else from x; PW: K stages of 64 per wave, ceil((Ix + H) / 64 / 8); G: groups
+// of 16 gate rows (4 units) per workgroup; R: rows per group of workgroups, 4 or 8.  rs_few: words per four units in the
+// hand-over buffers for R = 4 (at least the group's rows).
+template <bool PRE, int PW, int G, int R>
+__global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row_groups, int rs_few, int xcd0) {
+  static_assert(R == 4 || R == 8, "a load brings 8 rows of 32 k or 4 rows of 64");
+  const int rs = R == 8 ? 8 : rs_few;
   constexpr int SCOPE = __HIP_MEMORY_SCOPE_AGENT;
-  constexpr int U = 4 * G;  // units per workgroup
-  // partial sums [buffer][wave][group][row][gate row of the group], a group's block padded by 4 floats so that
-  // the 8 groups' columns fall into different banks; a lane writes its 4 sums as one 16-byte word
-  constexpr int GS = 16 * 16 + 4;
-  __shared__ __attribute__((aligned(16))) float red[2][8][G * GS];
-  constexpr int RP = 2;  // pairs of rows (at most 4 rows)
-  __shared__ __attribute__((aligned(16))) uint32_t hbuf[8][2 * RP][PW * 32];  // [wave][row][two k of its range]
+  constexpr int U = 4 * G;    // units per workgroup
+  constexpr int LPS = R / 4;  // loads of 64 words per stage
+  constexpr int CELLS = R * U;  // one lane each, in the first waves
+  // partial sums [buffer][wave][cell]: the four gates of a cell are one 16-byte word
+  __shared__ f32x4 red[2][8][CELLS];
   __shared__ int s_abort[2];  // by step parity: a wave already polling for step t+1 never writes the word step t reads
 
-  const int wg = (int)blockIdx.x;
+  // Workgroups go to the 8 XCDs in turn: a row group's workgroups are those of one XCD (of two, above 32 of them), so that
+  // the hand-over words meet in that XCD's L2.  (Where they go elsewhere the loop is slower and as right.)
+  const int H = a.H, Ix = PRE ? 0 : a.Ix, B = a.B, T = a.T;
+  const int n_wg = H / U, span = n_wg > 32 ? 2 : 1, per_xcd = n_wg / span;
+  const int xcd = ((int)blockIdx.x + xcd0) & 7, nth = (int)blockIdx.x >> 3;
+  const int group = nth / per_xcd * (8 / span) + xcd / span;
+  if (group >= row_groups) return;
+  const int wg = (xcd & (span - 1)) * per_xcd + nth % per_xcd;
+  const int row0 = group * R;
+  const int rows = B - row0 < R ? B - row0 : R;  // of this group
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, gq = lane >> 4;
-  const int T = a.T, B = a.B, H = a.H;
 
-  // this wave's K stages: the per-step kernel's partition
-  const int stages = H >> 6;
+  // this wave's K stages: the per-step kernel's ranges, all of x or all of h (Ix is whole ranges)
+  const int x_stages = Ix >> 6, stages = (Ix + H) >> 6;
   const int per_wave = (stages + 7) / 8;
   const int st_begin = wave * per_wave;
   const int st_end = (st_begin + per_wave) < stages ? (st_begin + per_wave) : stages;
-  const int n_st = st_end > st_begin ? st_end - st_begin : 0;  // <= PW (the launcher picks PW = per_wave)
+  const int n_st = st_end > st_begin ? st_end - st_begin : 0;  // <= PW (the launcher picks PW >= per_wave)
+  const bool of_x = !PRE && st_begin < x_stages;
 
-  // recurrent weights of this workgroup's 16 G gate rows over this wave's stages, in the MFMA operand
-  // layout: lane (r, gq) holds 8 k of tile row r = gate r >> 2 of unit 4 g + (r & 3)
+  // weights of this workgroup's 16 G gate rows over this wave's stages, in the MFMA operand
+  // layout: lane (r, gq) holds 8 k of tile row r = gate r & 3 of unit 4 g + (r >> 2)
   uint4 wa[G][PW], wb[G][PW];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const int unit = wg * U + g * 4 + (r & 3);
-    const u16* wrow = a.w_h + ((long long)(r >> 2) * H + unit) * H;
+    const u16* wrow = a.w + ((long long)(r & 3) * H + wg * U + g * 4 + (r >> 2)) * (Ix + H);
 #pragma unroll
     for (int s = 0; s < PW; ++s) {
       if (s < n_st) {
@@ -124,162 +168,263 @@ __global__ void __launch_bounds__(512) lstm_seq_kernel(LstmSeqArgs a) {
     }
   }
 
-  // cell update: thread -> (row mm < 4, unit u of the workgroup's 4 G, gate q): four neighbouring lanes share a
-  // cell, each adds up and activates one gate; the lane of gate 0 owns c and writes h
-  const int mm = tid / (4 * U), u = (tid >> 2) & (U - 1), q = tid & 3;
-  const int unit = wg * U + u;
-  const bool owner = mm < B;
-  float c = (owner && q == 0) ? a.c0[(long long)mm * H + unit] : 0.f;
+  // cell update: lane -> (group cg of 4 units, row mm, unit uu of the group); four neighbouring lanes hold the units
+  // of a hand-over word, which the first of them stores, so that a wave stores 128 contiguous bytes
+  const int uu = tid & 3, mm = (tid >> 2) & (R - 1), cg = tid / (4 * R);
+  const bool cells = wave * 64 < CELLS;  // (wave-uniform)
+  const bool owner = tid < CELLS && mm < rows;
+  const uint32_t cell = owner ? (uint32_t)((row0 + mm) * H + wg * U + cg * 4 + uu) : 0u;
+  const uint32_t put = (uint32_t)((wg * G + cg) * rs + mm) * 8u;  // the word of the lane's four units, in bytes
+  float c = owner ? *at(a.c0, cell * 4u) : 0.f;
 
   if (tid < 2) s_abort[tid] = 0;
   __syncthreads();
 
-  const int xrow = r < B ? r : 0;  // rows past B read row 0: their accumulator columns are never used
-  const long long plane = (long long)B * H;
-  int ask_row[RP];  // row of this lane's words, one load per pair of rows (an odd last row is asked for twice)
-#pragma unroll
-  for (int p = 0; p < RP; ++p) ask_row[p] = 2 * p + (lane >> 5) < B ? 2 * p + (lane >> 5) : B - 1;
+  // hand-over words of this row group: [buffer][unit / 4][row]
+  const int plane = rs * (H >> 2);
+  unsigned long long* exch = a.exch + (long long)row0 * (H >> 1);  // (groups but the last are R rows of rs = R)
+  // word of this lane in a load: R = 8: 32 k, rows by lane & 7, pieces of 4 k by gq and bit 3; R = 4: 64 k
+  uint32_t ask;   // (bytes, as is the next)
+  uint32_t from;  // this lane's operand row in x_t or h_0 (lanes past the group's rows: columns never used)
+  {
+    const int lrow = (r & (R - 1)) < rows ? r & (R - 1) : rows - 1;
+    ask = (uint32_t)((R == 8 ? gq * 2 + (r >> 3) : (r >> 3) * 8 + gq * 2 + ((r >> 2) & 1)) * rs + lrow +
+                     (of_x ? 0 : (st_begin - x_stages) * (16 * rs))) * 8u;
+    const int orow = row0 + (r < rows ? r : rows - 1);
+    from = (uint32_t)(of_x ? orow * Ix + st_begin * 64 + gq * 8 : orow * H + (st_begin - x_stages) * 64 + gq * 8) * 2u;
+  }
 
-  // The inputs' share of the gates streams from memory, a fresh line per step: it is fetched one step
-  // ahead, and behind the wave's poll loads (loads return in order: in front of them it would hold
+  // operands of this wave's stages for the step to come: x_t, loaded a step ahead, or h_{t-1}
+  uint4 fa[PW], fb[PW];
+#pragma unroll
+  for (int s = 0; s < PW; ++s) fa[s] = fb[s] = make_uint4(0, 0, 0, 0);  // (stages that this wave does not have: zeros)
+  auto load_rows = [&](const u16* src) {
+#pragma unroll
+    for (int s = 0; s < PW; ++s)
+      if (s < n_st) {
+        fa[s] = *(const uint4*)at(src + s * 64, from);
+        fb[s] = *(const uint4*)at(src + s * 64 + 32, from);
+      }
+  };
+  if (of_x) load_rows(a.x); else load_rows(a.h0);
+  const bool waits = !of_x && n_st > 0;  // for h_t
+  if (waits && a.max_polls == 0) s_abort[1] = 1;
+
+  // The bias, or the inputs' share of the gates, which streams from memory, a fresh line per step: it is fetched
+  // one step ahead, and behind the wave's poll loads (loads return in order: in front of them it would hold
   // every poll back by a trip to HBM).
-  float pr = 0.f, pr_next = 0.f;
-  if (owner) pr = a.pre[((long long)mm * 4 + q) * H + unit];
-  for (int t = 1; t <= T; ++t) {
-    // h_{t-1}: this wave's k range of every row, polled until every word carries the tag of step t-1.  A
-    // lane asks for two words of a row (lane & 31) in one load per pair of rows and stage.
-    const uint32_t want = lstm_seq_tag(t - 1);
-    const uint32_t* src = a.exch + (long long)((t - 1) & 1) * plane;
-    uint4 xa[PW], xb[PW];
-    bool gave_up = false;
-    if (n_st > 0) {
-      uint32_t polls = 0;
-      for (;;) {
-        // (wave-uniform: every lane counts alike and reads the same give-up word)
-        if (polls >= a.max_polls) {
-          gave_up = true;
-          break;
+  float pr[4] = {0.f, 0.f, 0.f, 0.f}, pr_next[4] = {0.f, 0.f, 0.f, 0.f};
+  const uint32_t pre_at = owner ? (cell + (uint32_t)((row0 + mm) * 3 * H)) * 4u : 0u;  // [row, gate, unit], in bytes
+  if (owner) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      pr[q] = PRE ? *at(a.pre + q * H, pre_at) : bf2f(a.bias[q * H + wg * U + cg * 4 + uu]);
+  }
+  for (int t = 1;; ++t) {
+    // (two groups at a time: four independent chains, and no more accumulators than that)
+#pragma unroll
+    for (int g0 = 0; g0 < G; g0 += 2) {
+      f32x4 acc[2][2];
+#pragma unroll
+      for (int g = 0; g < 2; ++g) acc[g][0] = acc[g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int s = 0; s < PW; ++s)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+          acc[g][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[g0 + g][s]), as_bf16x8(fa[s]), acc[g][0], 0, 0, 0);
+          acc[g][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[g0 + g][s]), as_bf16x8(fb[s]), acc[g][1], 0, 0, 0);
         }
-        ++polls;
-        // the give-up word travels with the data words, not ahead of them: one round trip per poll
-        const uint32_t others_gave_up = __hip_atomic_load(a.ctl, __ATOMIC_RELAXED, SCOPE);
-        uint32_t bad = 0;
-        unsigned long long v[RP][PW];
+      // accumulator of lane (r, gq), register v: gate v of unit gq of the group, activation row r
 #pragma unroll
-        for (int p = 0; p < RP; ++p)
-#pragma unroll
-          for (int s = 0; s < PW; ++s) {
-            v[p][s] = want | ((unsigned long long)want << 32);
-            if (2 * p < B && s < n_st)
-              v[p][s] = __hip_atomic_load(
-                  (const unsigned long long*)(src + (long long)ask_row[p] * H + (st_begin + s) * 64) + (lane & 31),
-                  __ATOMIC_RELAXED, SCOPE);
-          }
-#pragma unroll
-        for (int p = 0; p < RP; ++p)
-#pragma unroll
-          for (int s = 0; s < PW; ++s) {
-            const uint32_t lo = (uint32_t)v[p][s], hi = (uint32_t)(v[p][s] >> 32);
-            bad |= ((lo ^ want) | (hi ^ want)) & 0xffffu;
-          }
-        if (__all(bad == 0u)) {
-          // to the MFMA operand layout through the wave's own piece of LDS
-#pragma unroll
-          for (int p = 0; p < RP; ++p)
-#pragma unroll
-            for (int s = 0; s < PW; ++s)
-              if (2 * p < B)
-                hbuf[wave][2 * p + (lane >> 5)][s * 32 + (lane & 31)] =
-                    ((uint32_t)v[p][s] >> 16) | ((uint32_t)(v[p][s] >> 32) & 0xffff0000u);
-          break;
-        }
-        if (others_gave_up != 0u) {
-          gave_up = true;
-          break;
-        }
-      }
-      asm volatile("" ::: "memory");  // (a wave's LDS accesses execute in the order issued)
-#pragma unroll
-      for (int s = 0; s < PW; ++s) {
-        xa[s] = *(const uint4*)&hbuf[wave][xrow][s * 32 + gq * 4];
-        xb[s] = *(const uint4*)&hbuf[wave][xrow][s * 32 + 16 + gq * 4];
-      }
-      asm volatile("" ::: "memory");
-      if (gave_up) {
-        if (lane == 0) __hip_atomic_store(a.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_abort[t & 1] = 1;
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < PW; ++s) xa[s] = xb[s] = make_uint4(0, 0, 0, 0);
+      for (int g = 0; g < 2; ++g)
+        if (r < R) red[t & 1][wave][((g0 + g) * R + r) * 4 + gq] = acc[g][0] + acc[g][1];  // rows past the group's are never used
     }
-
-    if (owner && t < T) pr_next = a.pre[(((long long)t * B + mm) * 4 + q) * H + unit];
-    // gates' recurrent share: per group two accumulators (first and second half of each stage); all
-    // MFMAs first, so that none waits for another's result
-    float* rd = red[t & 1][0];
-    if (!gave_up) {
-      f32x4 acc[G][2];
+    if (of_x && t < T) load_rows(a.x + (long long)t * B * Ix);
+    if (PRE && owner && t < T) {
+      const float* src = a.pre + (long long)t * B * 4 * H;
 #pragma unroll
-      for (int g = 0; g < G; ++g) {
-        acc[g][0] = acc[g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int s = 0; s < PW; ++s) {
-          if (s < n_st) {
-            acc[g][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[g][s]), as_bf16x8(xa[s]), acc[g][0], 0, 0, 0);
-            acc[g][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[g][s]), as_bf16x8(xb[s]), acc[g][1], 0, 0, 0);
-          }
-        }
-      }
-      // accumulator of lane (r, gq), register v: gate row 4 gq + v of the group, activation row r
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        float4 p;
-        p.x = acc[g][0][0] + acc[g][1][0];
-        p.y = acc[g][0][1] + acc[g][1][1];
-        p.z = acc[g][0][2] + acc[g][1][2];
-        p.w = acc[g][0][3] + acc[g][1][3];
-        if (r < B) *(float4*)(rd + wave * (G * GS) + g * GS + r * 16 + gq * 4) = p;  // rows past B are never read
-      }
+      for (int q = 0; q < 4; ++q) pr_next[q] = *at(src + q * H, pre_at);
     }
     __syncthreads();
-    if (s_abort[t & 1]) break;  // uniform: written before the barrier, read after it
+    const int aborted = __builtin_amdgcn_readfirstlane(s_abort[t & 1]);  // written before the barrier (after an abort the cells are garbage, and not used)
 
-    {
-      // this lane's gate: the waves' partial sums in the per-step kernel's order, the inputs' share, the
-      // gate's nonlinearity (the operations of lstm_cell, one gate per lane)
-      const int g = u >> 2, uu = u & 3;
-      const int row = owner ? mm : 0;
-      float sum = 0.f;
+    if (cells) {
+      // the waves' partial sums in the per-step kernel's order, the inputs' share, the cell
+      const f32x4* e = &red[t & 1][0][tid & (CELLS - 1)];
+      f32x4 sum = (e[0] + e[CELLS]) + (e[2 * CELLS] + e[3 * CELLS]);
+      if (PRE && PW > 1) __builtin_amdgcn_sched_barrier(0);  // (all eight at once do not fit beside the weights)
+      sum += (e[4 * CELLS] + e[5 * CELLS]) + (e[6 * CELLS] + e[7 * CELLS]);
+      const float gate[4] = {sum[0] + pr[0], sum[1] + pr[1], sum[2] + pr[2], sum[3] + pr[3]};
+      float cn;
+      const uint32_t hb = f2bf(lstm_cell(gate, c, cn));
+      c = cn;
+      // (the next step's share of the inputs has had this whole step to arrive; taking it over here, ahead of
+      // the stores, keeps any wait for it off the path from the store below to the next step's first poll)
+      if (PRE) {
 #pragma unroll
-      for (int wv = 0; wv < 8; wv += 4) {
-        const float* e = rd + wv * (G * GS) + g * GS + row * 16 + q * 4 + uu;
-        sum += (e[0] + e[G * GS]) + (e[2 * G * GS] + e[3 * G * GS]);
+        for (int q = 0; q < 4; ++q) {
+          pr[q] = pr_next[q];
+          asm volatile("" : "+v"(pr[q]));
+        }
       }
-      const float z = sum + pr;
-      const float act = q == 2 ? tanh_fast(z) : sigmoidf(z);
-      // the four gates of the cell sit in four neighbouring lanes
-      const float a_i = __shfl(act, 0, 4), a_f = __shfl(act, 1, 4), a_g = __shfl(act, 2, 4), a_o = __shfl(act, 3, 4);
-      // the next step's share of the inputs has had this whole step to arrive; taking it over here, ahead of
-      // the stores, keeps any wait for it off the path from the store below to the next step's first poll
-      pr = pr_next;
-      asm volatile("" : "+v"(pr));
-      if (owner && q == 0) {
-        c = fmaf(a_f, c, a_i * a_g);
-        const u16 hb = f2bf(a_o * tanh_fast(c));
-        __hip_atomic_store(a.exch + (long long)(t & 1) * plane + (long long)mm * H + unit,
-                           ((uint32_t)hb << 16) | lstm_seq_tag(t), __ATOMIC_RELAXED, SCOPE);
-        a.h_seq[((long long)(t - 1) * B + mm) * H + unit] = hb;
+      const uint32_t lo = hb | (quad_lane<1>(hb) << 16), hi = quad_lane<2>(hb) | (quad_lane<3>(hb) << 16);
+      if (owner && uu == 0) {
+        uint32_t slo = lo, shi = hi;
+        if ((lo | hi) & 0x40004000u) {  // a NaN among the four
+          slo = (lo & 0x4000u ? 0x3fffu : lo & 0xffffu) | (lo & 0x40000000u ? 0x3fff0000u : lo & 0xffff0000u) | kHandOverNan;
+          shi = (hi & 0x4000u ? 0x3fffu : hi & 0xffffu) | (hi & 0x40000000u ? 0x3fff0000u : hi & 0xffff0000u);
+        }
+        slo |= lstm_seq_phase(t);
+        __hip_atomic_store(at(exch + (long long)(t & 1) * plane, put), ((unsigned long long)shi << 32) | slo,
+                           __ATOMIC_RELAXED, SCOPE);
+        *(uint2*)at(a.h_seq + (long long)(t - 1) * B * H, cell * 2u) = make_uint2(lo, hi);
       }
     }
     // (the partial sums alternate between two buffers: a wave can write step t+1's only after this
     // step's barrier, and step t+2's only after the barrier of t+1, which every thread reaches after
     // it has read step t's)
+    if (aborted || t == T) break;
+
+    if (waits) {
+      // h_t: this wave's k range of every row, polled until every word is in the phase of step t
+      const uint32_t want = lstm_seq_phase(t);
+      const unsigned long long* src = exch + (long long)(t & 1) * plane;
+      uint32_t polls = 0, nan;
+      // A poll that finds the words not there yet costs another round trip, and more polls on their way delay the
+      // stores they wait for: the first goes out when the words can be expected, in units of 64 clocks (37 rows, x
+      // form, microseconds per step with 0, 8, 12, 14, 16, 18, 20 units: 1.79, 1.79, 1.65, 1.32, 1.37, 1.42, 1.48;
+      // the step at 14 moves by two units from card to card, so a little later than the best).
+      if (!cells) __builtin_amdgcn_s_sleep(R == 8 || PW > 1 ? 16 : 14);
+      else if (R == 8) __builtin_amdgcn_s_sleep(4);
+      for (;;) {
+        unsigned long long v[PW][LPS];
+#pragma unroll
+        for (int s = 0; s < PW; ++s)
+#pragma unroll
+          for (int l = 0; l < LPS; ++l)  // (a stage that this wave does not have: the words of its last one again)
+            v[s][l] = __hip_atomic_load(at(src + (s < n_st ? s : n_st - 1) * 16 * rs, ask) + l * 8 * rs, __ATOMIC_RELAXED, SCOPE);
+        uint32_t bad = 0;
+#pragma unroll
+        for (int s = 0; s < PW; ++s) {
+          fa[s].x = (uint32_t)v[s][0] ^ want;
+          fa[s].y = (uint32_t)(v[s][0] >> 32);
+          bad |= fa[s].x;
+          if (LPS == 2) {
+            fb[s].x = (uint32_t)v[s][LPS - 1] ^ want;
+            fb[s].y = (uint32_t)(v[s][LPS - 1] >> 32);
+            bad |= fb[s].x;
+          }
+        }
+        nan = bad & kHandOverNan;
+        if (__all((bad & kHandOverPhase) == 0u)) break;
+        // (wave-uniform: every lane counts alike and reads the same give-up word)
+        ++polls;
+        if (polls >= a.max_polls || ((polls & 7u) == 0u && __builtin_amdgcn_readfirstlane((int)__hip_atomic_load(a.ctl, __ATOMIC_RELAXED, SCOPE)) != 0)) {
+          if (lane == 0) __hip_atomic_store(a.ctl, 1u, __ATOMIC_RELAXED, SCOPE);
+          s_abort[(t + 1) & 1] = 1;
+          break;
+        }
+      }
+      if (__any(nan != 0u)) {
+#pragma unroll
+        for (int s = 0; s < PW; ++s) {
+          if (fa[s].x & kHandOverNan) {
+            fa[s].x = lstm_seq_nans(fa[s].x & ~kHandOverNan);
+            fa[s].y = lstm_seq_nans(fa[s].y);
+          }
+          if (LPS == 2 && (fb[s].x & kHandOverNan)) {
+            fb[s].x = lstm_seq_nans(fb[s].x & ~kHandOverNan);
+            fb[s].y = lstm_seq_nans(fb[s].y);
+          }
+        }
+      }
+      // to the operand layout: the lanes of the first R rows collect the other pieces of their 8 k
+#pragma unroll
+      for (int s = 0; s < PW; ++s) {
+        if (R == 8) {
+          fa[s].z = lane_up<8>(fa[s].x);
+          fa[s].w = lane_up<8>(fa[s].y);
+          fb[s].z = lane_up<8>(fb[s].x);
+          fb[s].w = lane_up<8>(fb[s].y);
+        } else {
+          fb[s] = make_uint4(lane_up<8>(fa[s].x), lane_up<8>(fa[s].y), lane_up<12>(fa[s].x), lane_up<12>(fa[s].y));
+          fa[s].z = lane_up<4>(fa[s].x);
+          fa[s].w = lane_up<4>(fa[s].y);
+        }
+        if (s >= n_st) fa[s] = fb[s] = make_uint4(0, 0, 0, 0);
+      }
+    }
   }
 
   if (!(s_abort[0] | s_abort[1])) {
-    if (owner && q == 0) a.c_out[(long long)mm * H + unit] = c;
-    if (tid == 0) __hip_atomic_fetch_add(a.ctl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (owner) *at(a.c_out, cell * 4u) = c;
+    if (tid == 0) __hip_atomic_fetch_add(a.ctl + 1, 1u, __ATOMIC_RELAXED, SCOPE);
+  } else if (tid == 0) {
+    __hip_atomic_store(a.ctl, 1u, __ATOMIC_RELAXED, SCOPE);
+  }
+}
+
+// The same sequence by workgroups that wait for nobody, enqueued behind the loop and gone at once unless that
+// gave up: a workgroup takes 16 rows through all steps, its waves walk the units in fours, each over the whole of K, with
+// the same eight ranges and the same order of the sums.  h_{t-1} is read back from h_seq, c_t lives in c_keep.
+// Bound by one compute unit's reading of the weights, some 50 us per step; runs only where the loop could not.
+__global__ void __launch_bounds__(1024) lstm_seq_recover_kernel(LstmSeqArgs a) {
+  if (__hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r = lane & 15, gq = lane >> 4;
+  const int T = a.T, B = a.B, H = a.H, Ix = a.Ix;
+  const int row = blockIdx.x * 16 + r;
+  const int orow = row < B ? row : B - 1;
+  const int x_stages = Ix >> 6, stages = (Ix + H) >> 6;
+  const int per_range = (stages + 7) / 8;
+  for (int t = 0; t < T; ++t) {
+    const u16* h_prev = t == 0 ? a.h0 : a.h_seq + (long long)(t - 1) * B * H;
+    const u16* xr = a.x ? a.x + ((long long)t * B + orow) * Ix : nullptr;
+    const u16* hr = h_prev + (long long)orow * H;
+    for (int g = wave; g < H / 4; g += 16) {
+      const u16* wrow = a.w + ((long long)(r >> 2) * H + g * 4 + (r & 3)) * (Ix + H) + gq * 8;
+      f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+      for (int half = 0; half < 2; ++half) {
+        f32x4 part[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+          const int begin = (half * 4 + v) * per_range;
+          const int end = begin + per_range < stages ? begin + per_range : stages;
+          for (int s = begin; s < end; ++s) {
+            const u16* src = (s < x_stages ? xr + s * 64 : hr + (s - x_stages) * 64) + gq * 8;
+            acc0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(*(const uint4*)(wrow + s * 64)),
+                                                           as_bf16x8(*(const uint4*)src), acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(*(const uint4*)(wrow + s * 64 + 32)),
+                                                           as_bf16x8(*(const uint4*)(src + 32)), acc1, 0, 0, 0);
+          }
+          part[v] = acc0 + acc1;
+        }
+        sum += (part[0] + part[1]) + (part[2] + part[3]);
+      }
+      // lane (r, gq), register v: gate gq of unit 4 g + v, row r; the lane then takes unit 4 g + gq
+      float gate[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int col = gq * H + g * 4 + v;
+        const float z = sum[v] + (a.pre ? a.pre[((long long)t * B + orow) * 4 * H + col] : bf2f(a.bias[col]));
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const float from = __shfl(z, r + 16 * p, 64);
+          if (gq == v) gate[p] = from;
+        }
+      }
+      if (row < B) {
+        const long long cell = (long long)row * H + g * 4 + gq;
+        float cn;
+        const float hn = lstm_cell(gate, a.c_keep[cell], cn);
+        a.c_keep[cell] = cn;
+        a.h_seq[(long long)t * B * H + cell] = f2bf(hn);
+        if (t == T - 1) a.c_out[cell] = cn;
+      }
+    }
+    __syncthreads();  // (h_t is read by the workgroup's other waves)
   }
 }
 

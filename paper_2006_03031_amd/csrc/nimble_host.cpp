@@ -708,8 +708,7 @@ int nimble_lstm_seq_supported(int64_t B, int64_t H) {
 }
 
 // A fixed rule, kept as callers know it: drawn when the loop took 2.4 microseconds per step at H = 512 with 4 rows and 2.7 / 4.0
-// at H = 1024 with 1 / 4, against 2.65-2.95 for a captured graph of per-step launches.  It takes 1.6 / 1.7 and 1.7 / 2.1 now,
-// against 2.8 and 3.0.
+// at H = 1024 with 1 / 4, against 2.65-2.95 for a captured graph of per-step launches.  It takes 1.2 and 1.4 / 1.6 now.
 int nimble_lstm_seq_preferred(int64_t B, int64_t H) {
   return nimble_lstm_seq_supported(B, H) && (H <= 512 || B == 1);
 }
@@ -717,6 +716,28 @@ int nimble_lstm_seq_preferred(int64_t B, int64_t H) {
 size_t nimble_lstm_seq_workspace_bytes(int64_t B, int64_t H) {
   if (!nimble_lstm_seq_supported(B, H)) return 0;
   return 256 + 2 * (size_t)B * (size_t)H * 4;
+}
+
+// Weights in registers: at most two 64-wide K stages per wave, each wholly of x or of h.  Groups of 8 rows, each on the H / 16
+// workgroups of one XCD (two above H = 512).  The groups of an XCD are dispatched one after the other and none waits for a
+// later one, so there may be more of them than fit at once: one workgroup per compute unit at a time,
+// four rounds of them (microseconds per step, loop / captured launches: H = Ix = 512 at 64, 128, 256 rows
+// 1.48 / 3.83, 2.39 / 5.28, 4.38 / 8.63; H = 1024, pre form, at 32, 128 rows 2.11 / 4.52, 7.39 / 11.49; 256 x 256 at 512 rows
+// 3.63 / 6.78).
+int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H) {
+  if (B < 1 || B > 65536 || H < 64 || H > 1024 || H % 64 != 0 || Ix < 0 || Ix > 1024 || Ix % 64 != 0) return 0;
+  const int64_t stages = (Ix + H) / 64, per_wave = ceil_div(stages, 8);
+  if (per_wave > 2 || Ix / 64 % per_wave != 0) return 0;
+  // (the per-step kernel's order of the sums: see stream_kernel on four waves)
+  nimble_plan p;
+  if (nimble_lstm_plan(B, Ix, H, &p) != NIMBLE_OK || (p.split_k == 4 && stages != 8 && stages != 16)) return 0;
+  const int64_t n_wg = H / 16, span = n_wg > 32 ? 2 : 1;
+  return ceil_div(ceil_div(B, 8) * span, 8) * (n_wg / span) <= 4 * (kCUs / 8);
+}
+
+size_t nimble_lstm_loop_workspace_bytes(int64_t B, int64_t Ix, int64_t H) {
+  if (!nimble_lstm_loop_supported(B, Ix, H)) return 0;
+  return 256 + (size_t)(ceil_div(B, 8) * 8 + B) * (size_t)H * 4;
 }
 
 int64_t nimble_storage_bytes(const int64_t* shape, int rank, int dtype) {

@@ -134,7 +134,11 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
     // shape below and 6.3 with eight waves and two stages; the LSTM cell at 64 rows 3.9 against 5.3).
     const bool many = (uint64_t)grid.x * grid.y > (uint64_t)kComputeUnits &&
                       (double)s.N * (double)s.K * 2.0 <= kCachedWeightBytes;
-    if (many)
+    if (LSTM && many && s.K == 512)
+      hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16, LSTM ? 1 : 0>), grid, dim3(256), 0, st, s);
+    else if (LSTM && many && s.K == 1024)
+      hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16, LSTM ? 2 : 0>), grid, dim3(256), 0, st, s);
+    else if (many)
       hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16>), grid, dim3(256), 0, st, s);
     else if (s.M <= 8)
       hipLaunchKernelGGL((stream_kernel<LSTM, 3, 8, 8>), grid, dim3(512), 0, st, s);
@@ -301,6 +305,39 @@ static int launch_attention(const u16* q, const u16* k, const u16* v, u16* o, in
   else
     launch_attention_as<4, 1, 2>(q, k, v, o, heads, L, alpha, st);
   return check_hip(hipGetLastError(), "attention kernel launch");
+}
+
+// 16 units per workgroup (8 or 32 at 4 rows: no faster or slower, 1.6 / 1.9 us per step against 1.6 before the later steps).
+template <int R>
+static void launch_lstm_seq_as(const LstmSeqArgs& a, int rs, int xcd0, hipStream_t st) {
+  const int row_groups = (a.B + R - 1) / R, per_wave = ((a.Ix + a.H) / 64 + 7) / 8;
+  const int n_wg = a.H / 16, span = n_wg > 32 ? 2 : 1;  // XCDs per row group
+  const dim3 grid((unsigned)(8 * (n_wg / span) * ((row_groups * span + 7) / 8))), block(512);
+  if (a.pre && per_wave <= 1)
+    hipLaunchKernelGGL((lstm_seq_kernel<true, 1, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
+  else if (a.pre)
+    hipLaunchKernelGGL((lstm_seq_kernel<true, 2, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
+  else if (per_wave <= 1)
+    hipLaunchKernelGGL((lstm_seq_kernel<false, 1, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
+  else
+    hipLaunchKernelGGL((lstm_seq_kernel<false, 2, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
+}
+
+// The token loop in one launch behind a fill of its workspace.
+static int launch_lstm_seq(const LstmSeqArgs& a, hipStream_t st) {
+  const int rs = a.B > 4 ? 8 : (a.B > 1 ? 4 : 2);
+  const int words = (a.B > 4 ? (a.B + 7) / 8 : 1) * rs * (a.H / 2), cells = a.B * a.H;
+  hipLaunchKernelGGL(lstm_seq_init_kernel, dim3((cells + 255) / 256), dim3(256), 0, st, a, words);
+  const int rc = check_hip(hipGetLastError(), "lstm sequence fill launch");
+  if (rc != NIMBLE_OK) return rc;
+  // loops of few rows that run at the same time start on different XCDs (their workspaces differ)
+  const uintptr_t ws = reinterpret_cast<uintptr_t>(a.ctl);
+  const int xcd0 = (int)((ws >> 9 ^ ws >> 12 ^ ws >> 15 ^ ws >> 21) & 7);
+  if (a.B > 4)
+    launch_lstm_seq_as<8>(a, rs, xcd0, st);
+  else
+    launch_lstm_seq_as<4>(a, rs, xcd0, st);
+  return check_hip(hipGetLastError(), "lstm sequence launch");
 }
 
 static inline bool misaligned(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) != 0; }
@@ -663,28 +700,59 @@ int nimble_lstm_seq_pre_dyn(const void* pre, const void* w_h, const void* h0, co
                 nimble_lstm_seq_workspace_bytes(B, H));
   LstmSeqArgs a{};
   a.pre = (const float*)pre;
-  a.w_h = (const u16*)w_h;
+  a.w = (const u16*)w_h;
   a.h0 = (const u16*)h0;
   a.c0 = (const float*)c0;
   a.h_seq = (u16*)h_seq;
   a.c_out = (float*)c_out;
   a.ctl = (uint32_t*)workspace;
-  a.exch = (uint32_t*)workspace + 64;
+  a.exch = (unsigned long long*)((char*)workspace + 256);
   a.T = (int)T;
   a.B = (int)B;
   a.H = (int)H;
   a.max_polls = max_polls;
-  hipStream_t st = (hipStream_t)stream;
-  const int words = (int)(B * H) > 64 ? (int)(B * H) : 64;
-  hipLaunchKernelGGL(lstm_seq_init_kernel, dim3((words + 255) / 256), dim3(256), 0, st, a);
-  int rc = check_hip(hipGetLastError(), "lstm sequence fill launch");
+  return launch_lstm_seq(a, (hipStream_t)stream);
+}
+
+int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const void* bias, const void* h0,
+                         const void* c0, void* h_seq, void* c_out, int64_t T, int64_t B, int64_t Ix, int64_t H,
+                         void* workspace, size_t workspace_bytes, uint32_t max_polls, void* stream) {
+  clear_error();
+  if (T < 0 || B < 0 || Ix < 0 || H < 0) return fail(NIMBLE_ERR_ARG, "negative extent");
+  if (!nimble_lstm_loop_supported(B, Ix, H))
+    return fail(NIMBLE_ERR_SHAPE, "lstm loop: B = %lld, Ix = %lld, H = %lld does not run as one launch", (long long)B,
+                (long long)Ix, (long long)H);
+  if (T > (int64_t)1 << 24) return fail(NIMBLE_ERR_ARG, "lstm loop: more than 2^24 steps");
+  if (T == 0) return NIMBLE_OK;
+  if (!w || !h0 || !c0 || !h_seq || !c_out || !workspace || (Ix > 0 ? !x || !bias : !pre))
+    return fail(NIMBLE_ERR_NULL, "null tensor pointer");
+  if (misaligned(x) || misaligned(pre) || misaligned(w) || misaligned(bias) || misaligned(h0) || misaligned(c0) ||
+      misaligned(h_seq) || misaligned(c_out) || misaligned(workspace))
+    return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
+  if (workspace_bytes < nimble_lstm_loop_workspace_bytes(B, Ix, H))
+    return fail(NIMBLE_ERR_WORKSPACE, "lstm loop: workspace of %zu bytes, %zu needed", workspace_bytes,
+                nimble_lstm_loop_workspace_bytes(B, Ix, H));
+  LstmSeqArgs a{};
+  a.x = Ix > 0 ? (const u16*)x : nullptr;
+  a.pre = Ix > 0 ? nullptr : (const float*)pre;
+  a.w = (const u16*)w;
+  a.bias = (const u16*)bias;
+  a.h0 = (const u16*)h0;
+  a.c0 = (const float*)c0;
+  a.h_seq = (u16*)h_seq;
+  a.c_out = (float*)c_out;
+  a.ctl = (uint32_t*)workspace;
+  a.exch = (unsigned long long*)((char*)workspace + 256);
+  a.c_keep = (float*)((char*)workspace + 256 + 4 * ((B + 7) / 8 * 8) * H);
+  a.T = (int)T;
+  a.B = (int)B;
+  a.Ix = (int)Ix;
+  a.H = (int)H;
+  a.max_polls = max_polls;
+  int rc = launch_lstm_seq(a, (hipStream_t)stream);
   if (rc != NIMBLE_OK) return rc;
-  // At most 64 workgroups, fewer than the chip holds at once: 8 units each up to H = 512, 16 beyond
-  // (microseconds per step at 1 / 4 rows with 8, 16 and 32 units: H = 512 1.60 / 1.64, 1.66 / 1.77, 1.91 / 2.09;
-  // H = 1024 1.76 / 2.24, 1.76 / 1.96, 2.09 / 2.39).
-  if (H <= 512) hipLaunchKernelGGL((lstm_seq_kernel<1, 2>), dim3((unsigned)(H / 8)), dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((lstm_seq_kernel<2, 4>), dim3((unsigned)(H / 16)), dim3(512), 0, st, a);
-  return check_hip(hipGetLastError(), "lstm sequence launch");
+  hipLaunchKernelGGL(lstm_seq_recover_kernel, dim3((unsigned)((B + 15) / 16)), dim3(1024), 0, (hipStream_t)stream, a);
+  return check_hip(hipGetLastError(), "lstm loop recovery launch");
 }
 
 int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up) {

@@ -272,11 +272,15 @@ def split_lstm_weight(w: torch.Tensor, Ix: int) -> Tuple[torch.Tensor, torch.Ten
     return w[:, :Ix].contiguous(), w[:, Ix:].contiguous()
 
 
+# polls per wait of the captured token loop before its recovery launch takes over (some 8 ms, what that launch takes)
+LSTM_LOOP_MAX_POLLS = 1 << 14
+
+
 class LstmSequenceGraph:
-    """The token loop of one sequence, `steps` launches of the fused LSTM cell, captured once
-    per batch size B as a HIP graph and replayed: the loop is launch-bound (a step is a few
-    microseconds of GPU work), so replaying removes the per-step host cost.  The graph holds
-    kernel launches only (state is cleared by a fill kernel outside it).  The dynamic extent
+    """The token loop of one sequence, captured once per batch size B as a HIP graph and replayed: where
+    nimble_lstm_loop_supported says so the loop is one launch (with a recovery launch behind it that ends at once
+    unless the loop's bounded waits ran out), else `steps` launches of the fused LSTM cell, with the same bits.  The graph
+    holds kernel launches only (state is cleared by a fill kernel outside it).  The dynamic extent
     B is fixed per graph; a server keeps one graph per batch size it has seen."""
 
     def __init__(self, w: torch.Tensor, bias: torch.Tensor, B: int, steps: int, Ix: int, H: int,
@@ -295,6 +299,10 @@ class LstmSequenceGraph:
         self.xs = torch.zeros((steps, B, Ix), dtype=torch.bfloat16, device=dev)
         self.hs = torch.zeros((steps + 1, B, H), dtype=torch.bfloat16, device=dev)  # hs[0] = h_0
         self.c = torch.zeros((B, H), dtype=torch.float32, device=dev)
+        loop_ix = 0 if project_inputs else Ix
+        self.workspace = None
+        if (project_inputs or Ix > 0) and nb.lstm_loop_supported(B, loop_ix, H):
+            self.workspace = torch.empty(nb.lstm_loop_workspace_bytes(B, loop_ix, H), dtype=torch.uint8, device=dev)
         # one eager pass so that nothing is lazily initialised during capture
         self._enqueue()
         torch.cuda.synchronize()
@@ -307,6 +315,14 @@ class LstmSequenceGraph:
         if self.project_inputs:
             dense(self.xs.view(self.steps * self.B, self.Ix), self.w_x, self.bias, nb.EPI_BIAS, nb.F32,
                   out=self.pre.view(self.steps * self.B, 4 * self.H))
+        if self.workspace is not None:
+            w = self.w_h if self.project_inputs else self.w
+            nb.nimble_lstm_loop_dyn(self.xs.data_ptr(), self.pre.data_ptr() if self.project_inputs else 0, w.data_ptr(),
+                                    self.bias.data_ptr(), self.hs.data_ptr(), self.c.data_ptr(), self.hs[1:].data_ptr(),
+                                    self.c.data_ptr(), self.steps, self.B, 0 if self.project_inputs else self.Ix, self.H,
+                                    self.workspace.data_ptr(), self.workspace.numel(), LSTM_LOOP_MAX_POLLS, st)
+            return
+        if self.project_inputs:
             for t in range(self.steps):
                 nb.nimble_lstm_gates_pre_dyn(self.pre[t].data_ptr(), self.hs[t].data_ptr(), self.w_h.data_ptr(),
                                              self.c.data_ptr(), self.c.data_ptr(), self.hs[t + 1].data_ptr(),

@@ -1,0 +1,146 @@
+"""The token loop of a batch in one launch (nimble_lstm_loop_dyn) against the step-by-step calls, bit for bit: row groups
+that are full, partly full and of one row, every number of K stages per wave, states and inputs that are not finite,
+the recovery launch (forced from the host), replays of a captured loop, and loops that run at the same time."""
+import numpy as np
+import pytest
+
+import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def rt():
+    import paper_2006_03031_amd as nb
+    from paper_2006_03031_amd import runtime
+    nb.load()
+    return runtime
+
+
+@pytest.fixture(scope="module")
+def nb():
+    import paper_2006_03031_amd as nb
+    return nb
+
+
+def _case(seed, T, B, Ix, H):
+    """(x or pre, w, bias, h0, c0) on the GPU; Ix = 0: the pre form."""
+    from gpu_util import f32_to_dev, to_dev
+    rng = np.random.default_rng([5, seed, T, B, Ix, H])
+    x = to_dev(wl.uniform_bf16(rng, (T, B, Ix))) if Ix else f32_to_dev(rng.uniform(-2, 2, (T, B, 4 * H)))
+    w = to_dev(wl.normal_bf16(rng, (4 * H, Ix + H), std=1.0 / np.sqrt(H)))
+    return (x, w, to_dev(wl.uniform_bf16(rng, (4 * H,))), to_dev(wl.uniform_bf16(rng, (B, H))),
+            f32_to_dev(rng.uniform(-1, 1, (B, H))))
+
+
+def _steps(rt, x, w, bias, h0, c0):
+    hs, h, c = [], h0, c0
+    for t in range(x.shape[0]):
+        h, c = rt.lstm_step(x[t], h, w, bias, c) if x.dtype is torch.bfloat16 else rt.lstm_step_pre(x[t], h, w, c)
+        hs.append(h)
+    return torch.stack(hs), c
+
+
+def _loop(nb, x, w, bias, h0, c0, max_polls=1 << 14):
+    """One call into buffers of NaNs; returns (h_seq, c, gave up)."""
+    fused = x.dtype is torch.bfloat16
+    T, B, H = x.shape[0], h0.shape[0], h0.shape[1]
+    Ix = x.shape[2] if fused else 0
+    h_seq = torch.full((T, B, H), float("nan"), dtype=torch.bfloat16, device="cuda")
+    c = c0.clone()                                        # c_out may be c_0
+    ws = torch.full((nb.lstm_loop_workspace_bytes(B, Ix, H),), 255, dtype=torch.uint8, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    print(f"loop T={T} B={B} Ix={Ix} H={H} polls={max_polls}", flush=True)
+    nb.nimble_lstm_loop_dyn(x.data_ptr() if fused else 0, 0 if fused else x.data_ptr(), w.data_ptr(), bias.data_ptr(),
+                            h0.data_ptr(), c.data_ptr(), h_seq.data_ptr(), c.data_ptr(), T, B, Ix, H, ws.data_ptr(),
+                            ws.numel(), max_polls, st)
+    return h_seq, c, nb.nimble_lstm_seq_status(ws.data_ptr(), st)
+
+
+def _same(a, b):
+    return torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+# (x form: both halves of the fused weight; Ix = 0: pre.  320 = five stages, 576 = nine: waves without and with half a share;
+# above 512 a row group spans two XCDs; 65 and more rows: several groups per XCD)
+SHAPES = [(9, 1, 512, 512), (6, 4, 512, 512), (6, 5, 512, 512), (5, 8, 512, 512), (5, 9, 512, 512), (4, 37, 512, 512),
+          (4, 64, 512, 512), (5, 23, 256, 256), (4, 3, 64, 64), (3, 130, 192, 64), (3, 150, 512, 512), (2, 65, 0, 1024), (6, 5, 128, 640), (3, 64, 128, 256),
+          (7, 2, 0, 64), (5, 17, 0, 320), (5, 33, 0, 512), (4, 64, 0, 512), (5, 16, 0, 576), (4, 32, 0, 1024),
+          (1, 6, 0, 512), (1, 6, 512, 512), (40, 12, 0, 256)]
+
+
+@pytest.mark.parametrize("T,B,Ix,H", SHAPES)
+def test_the_loop_equals_the_steps_one_by_one(rt, nb, T, B, Ix, H):
+    assert nb.lstm_loop_supported(B, Ix, H)
+    case = _case(0, T, B, Ix, H)
+    want_h, want_c = _steps(rt, *case)
+    h, c, gave_up = _loop(nb, *case)
+    assert not gave_up, "the loop gave up on an idle GPU"
+    assert _same(h, want_h) and torch.equal(c, want_c)
+
+
+@pytest.mark.parametrize("T,B,Ix,H", [(4, 37, 512, 512), (3, 4, 0, 512), (3, 11, 0, 576), (3, 3, 64, 64), (2, 64, 0, 512)])
+def test_the_recovery_launch_gives_the_same_bits(rt, nb, T, B, Ix, H):
+    case = _case(1, T, B, Ix, H)
+    want_h, want_c = _steps(rt, *case)
+    h, c, gave_up = _loop(nb, *case, max_polls=0)
+    assert gave_up and _same(h, want_h) and torch.equal(c, want_c)
+
+
+@pytest.mark.parametrize("B,Ix", [(3, 0), (3, 512), (13, 0), (13, 512)])
+def test_states_and_inputs_that_are_not_finite(rt, nb, B, Ix):
+    """NaN, infinities and states beyond [-1, 1] travel as through the steps: h_0 may hold anything, a NaN in one row
+    makes that row NaN and leaves the others alone."""
+    T, H = 6, 512
+    x, w, bias, h0, c0 = _case(2, T, B, Ix, H)
+    h0[0, 5], h0[1, 100], c0[1, 7] = 3.0, float("inf"), float("-inf")
+    x[2, B - 1, 11] = float("nan")
+    x[1, B - 2, 3] = float("inf")
+    for polls in (1 << 14, 0):
+        want_h, want_c = _steps(rt, x, w, bias, h0, c0)
+        h, c, _ = _loop(nb, x, w, bias, h0, c0, polls)
+        assert torch.isnan(want_h[-1, B - 1]).all() and torch.isfinite(want_h[-1, 0]).all()
+        assert torch.equal(torch.isnan(h), torch.isnan(want_h)) and torch.equal(torch.isnan(c), torch.isnan(want_c))
+        assert _same(torch.nan_to_num(h), torch.nan_to_num(want_h)) and torch.equal(torch.nan_to_num(c), torch.nan_to_num(want_c))
+
+
+def test_a_captured_loop_replays_and_recovers(rt, nb, monkeypatch):
+    H, T, B = 512, 7, 21
+    rng = np.random.default_rng(9)
+    from gpu_util import to_dev
+    w, b = to_dev(wl.normal_bf16(rng, (4 * H, 2 * H), std=0.05)), to_dev(wl.normal_bf16(rng, (4 * H,)))
+    zeros = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, H), device="cuda")
+    for polls in (rt.LSTM_LOOP_MAX_POLLS, 0):
+        monkeypatch.setattr(rt, "LSTM_LOOP_MAX_POLLS", polls)
+        seq = rt.LstmSequenceGraph(w, b, B, T, H, H)
+        assert seq.workspace is not None
+        for rep in range(3):
+            x = to_dev(wl.uniform_bf16(rng, (T, B, H)))
+            want_h, want_c = _steps(rt, x, w, b, *zeros)
+            h, c = seq.run(x)
+            assert _same(h, want_h) and torch.equal(c, want_c), (polls, rep)
+
+
+def test_loops_on_two_streams_at_once(rt, nb):
+    """Two captured loops of the most rows side by side: each has its own workspace; whether or not one of them has to
+    recover, both are right."""
+    H, T, B = 512, 24, 64
+    rng = np.random.default_rng(11)
+    from gpu_util import to_dev
+    w, b = to_dev(wl.normal_bf16(rng, (4 * H, 2 * H), std=0.05)), to_dev(wl.normal_bf16(rng, (4 * H,)))
+    zeros = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, H), device="cuda")
+    seqs = [rt.LstmSequenceGraph(w, b, B, T, H, H) for _ in range(2)]
+    xs = [to_dev(wl.uniform_bf16(rng, (T, B, H))) for _ in range(2)]
+    want = [_steps(rt, x, w, b, *zeros) for x in xs]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+    for rep in range(4):
+        print(f"two loops, repetition {rep}", flush=True)
+        got = []
+        for s, seq, x in zip(streams, seqs, xs):
+            with torch.cuda.stream(s):
+                got.append(seq.run(x))
+        torch.cuda.synchronize()
+        for (h, c), (wh, wc) in zip(got, want):
+            assert _same(h, wh) and torch.equal(c, wc), rep

@@ -541,6 +541,32 @@ def test_lstm_seq_shape_support_and_refusals():
     call(a, a, a, a, a, a, 0, 1, 512, a, 1 << 20, 10, 0)   # T = 0: nothing to do, nothing launched
 
 
+def test_lstm_loop_support_and_refusals():
+    """The token loop of a batch: the shapes it runs (weights of two stages per wave, each of x or of h; the order
+    of the per-step launch), its workspace, and the refusals decided before anything is launched."""
+    ok = [(1, 512, 512), (256, 512, 512), (256, 0, 512), (512, 256, 256), (128, 0, 1024), (256, 64, 64), (5, 128, 640),
+          (3, 0, 576), (32, 128, 512), (64, 0, 256)]
+    no = [(0, 0, 512), (257, 512, 512), (129, 0, 1024), (257, 64, 64), (4, 64, 512), (4, 512, 576), (4, 0, 96), (4, 32, 512),
+          (4, 0, 1088), (-1, 0, 512), (4, -64, 512), (17, 0, 576), (33, 128, 512)]
+    assert all(nb.lstm_loop_supported(*s) for s in ok) and not any(nb.lstm_loop_supported(*s) for s in no)
+    # control words, two planes of bf16 rows in groups of 8, c_0
+    assert nb.lstm_loop_workspace_bytes(37, 512, 512) == 256 + 4 * 40 * 512 + 4 * 37 * 512
+    assert nb.lstm_loop_workspace_bytes(257, 512, 512) == 0
+    call, a, big = nb.nimble_lstm_loop_dyn, 4096, 1 << 24   # (any aligned number: never dereferenced on these paths)
+    for args, code in [((a, 0, a, a, a, a, a, a, 5, 257, 512, 512, a, big, 10, 0), -3),
+                       ((a, 0, a, a, a, a, a, a, -1, 5, 512, 512, a, big, 10, 0), -8),
+                       ((0, a, a, a, a, a, a, a, 5, 5, 512, 512, a, big, 10, 0), -1),
+                       ((a, 0, a, 0, a, a, a, a, 5, 5, 512, 512, a, big, 10, 0), -1),
+                       ((a, 0, a, a, a, a, a, a, 5, 5, 0, 512, a, big, 10, 0), -1),
+                       ((a, 0, a, a, a, a, a, a, 5, 5, 512, 512, 0, big, 10, 0), -1),
+                       ((a + 8, 0, a, a, a, a, a, a, 5, 5, 512, 512, a, big, 10, 0), -5),
+                       ((a, 0, a, a, a, a, a, a, 5, 5, 512, 512, a, 256 + 4 * 8 * 512 + 4 * 5 * 512 - 1, 10, 0), -6)]:
+        with pytest.raises(nb.NimbleError) as e:
+            call(*args)
+        assert e.value.code == code, (args, e.value)
+    call(a, 0, a, a, a, a, a, a, 0, 5, 512, 512, a, big, 10, 0)   # T = 0: nothing launched
+
+
 def test_tuned_table_overrides_the_cost_model():
     """Section 3.5, tuning: an installed entry decides the dispatch inside its M range and nowhere
     else; entries that cannot run are skipped; count = 0 removes the table."""
