@@ -8,6 +8,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libnimble_hip.so")
+HOST_CALLS = os.path.join(PKG, "_host_calls.so")
 SOURCES = ["nimble_host.cpp", "nimble_vm.cpp", "nimble_kernels.hip"]  # the .h files under csrc/ hold the kernels
 
 
@@ -22,7 +23,31 @@ def hipcc_command(out: str = LIB):
     ]
 
 
+def host_calls_command(out: str = HOST_CALLS):
+    """The native caller-side sequences: host code only, against the installed torch's headers."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    lib = cpp_extension.library_paths()[0]
+    return [
+        "g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+        f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+        *["-isystem" + d for d in cpp_extension.include_paths()], "-I" + sysconfig.get_paths()["include"],
+        "-I" + os.path.join(ROOT, "include"), os.path.join(CSRC, "host_calls.cpp"),
+        "-L" + lib, "-Wl,-rpath," + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-o", out,
+    ]
+
+
+def build_host_calls() -> str:
+    proc = subprocess.run(host_calls_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if proc.returncode != 0:
+        raise RuntimeError("g++ failed:\n" + proc.stdout[-4000:])
+    return HOST_CALLS
+
+
 def build_library(verbose: bool = False) -> str:
+    build_host_calls()
     proc = subprocess.run(hipcc_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     noise = "is not a recognized feature for this target"
     log = "\n".join(l for l in proc.stdout.splitlines() if noise not in l)
@@ -141,9 +166,9 @@ def asm_mfma_findings(asm: str, wait_states: int = 18):
 
 
 def stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(HOST_CALLS):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(HOST_CALLS))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(ROOT, "include", "nimble.h"), os.path.join(ROOT, "include", "nimble_vm.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 

@@ -11,9 +11,17 @@ from __future__ import annotations
 
 from typing import Optional, Tuple
 
+import ctypes
+
 import torch
 
 from . import binding as nb
+
+try:
+    from . import _host_calls
+except ImportError as e:
+    raise ImportError("the native host calls are not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
+                      "first") from e
 
 _TORCH_DTYPE = {nb.BF16: torch.bfloat16, nb.F32: torch.float32}
 
@@ -22,6 +30,22 @@ try:  # raw handle of torch's current stream without building a Stream object (s
     _raw_stream = torch._C._cuda_getCurrentRawStream
 except AttributeError:  # pragma: no cover - older torch
     _raw_stream = None
+
+
+_bound = False
+
+
+def _bind_host_calls(device) -> None:
+    """Gives the native calls the entry points of the library that binding.py loads, on the first call that went
+    through on a GPU; until then they leave every call to the steps below."""
+    global _bound
+    if _bound or _raw_stream is None or device.type != "cuda" or torch.overrides._get_current_function_mode() is not None:
+        return
+    lib = nb.load()
+    addresses = [ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
+                 for f in ("nimble_dense_dyn", "nimble_attention_dyn", "nimble_attention_chain_dyn", "nimble_vm_run")]
+    _host_calls.bind(*addresses, torch._C._cuda_getDevice, _raw_stream, device.index or 0)
+    _bound = True
 
 
 def _stream() -> int:
@@ -83,6 +107,9 @@ def default_workspace(device) -> torch.Tensor:
     if ws is None:
         ws = torch.empty(WORKSPACE_BYTES, dtype=torch.uint8, device=device)
         _WORKSPACE[key] = ws
+        if type(ws) is torch.Tensor and ws.is_cuda:  # from here on the native calls serve this device
+            _bind_host_calls(ws.device)
+            _host_calls.set_workspace(ws.device.index, ws)
     return ws
 
 
@@ -111,6 +138,10 @@ def dense(x: torch.Tensor, w: torch.Tensor, bias: Optional[torch.Tensor], epilog
           out_dtype: int = nb.BF16, force_variant: int = nb.VAR_AUTO,
           out: Optional[torch.Tensor] = None, arena: Optional[StorageArena] = None,
           workspace: Optional[torch.Tensor] = None) -> torch.Tensor:
+    if out is None and arena is None and workspace is None and force_variant == nb.VAR_AUTO:
+        y = _host_calls.dense(x, w, bias, epilogue, out_dtype)
+        if y is not None:
+            return y
     M, N = nb.nimble_dense_shape(tuple(x.shape), tuple(w.shape))
     K = x.shape[1]
     if out is not None:
@@ -160,6 +191,9 @@ def attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor,
               alpha: float = 0.125) -> Tuple[torch.Tensor, torch.Tensor, torch.Tensor]:
     """S = alpha Q.K^T (f32), P = softmax rows (bf16), O = P.V (bf16), through one entry point: one launch
     for head dimension 64 and up to 512 tokens, the three calls otherwise."""
+    r = _host_calls.attention(q, k, v, alpha)
+    if r is not None:
+        return r
     T, M, N = nb.batch_matmul_shape(tuple(q.shape), tuple(k.shape), True)
     _, _, Dv = nb.batch_matmul_shape((T, M, N), tuple(v.shape), False)
     s, p = _alloc((T, M, N), nb.F32, q.device), _alloc((T, M, N), nb.BF16, q.device)
@@ -175,11 +209,17 @@ def fused_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, alpha: fl
                     out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """O = softmax(alpha Q.K^T).V in one launch.  The composite's shape function is the two
     batch_matmul shape functions connected: (T,L,D)x(T,L,D)^T -> (T,L,L), then x(T,L,D) -> (T,L,D)."""
+    if out is None:
+        o = _host_calls.fused_attention(q, k, v, alpha)
+        if o is not None:
+            return o
     s_shape = nb.batch_matmul_shape(tuple(q.shape), tuple(k.shape), True)
     T, L, D = nb.batch_matmul_shape(s_shape, tuple(v.shape), False)
     o = out if out is not None else _alloc((T, L, D), nb.BF16, q.device)
     nb.nimble_attention_dyn(_ptr(q, _BF, "q"), _ptr(k, _BF, "k"), _ptr(v, _BF, "v"), _ptr(o, _BF, "o"), T, L, D, alpha,
                             _stream())
+    if not _bound:
+        _bind_host_calls(q.device)
     return o
 
 

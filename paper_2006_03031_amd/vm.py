@@ -318,6 +318,12 @@ class Executable:
         AllocStorage instructions carve up (None for programs that allocate nothing on the GPU);
         tensor results are views into it (or the input/constant they alias) and stay valid until the
         next run with the same pool.  Integers come back as int, shape tensors as lists of int."""
+        if workspace is None:  # plain tensors throughout: one native call
+            r = rt._host_calls.vm_run(self._handle.value, inputs, pool, self._constants, max_instructions)
+            if r is not None:
+                if isinstance(r, int):
+                    raise nb.NimbleError(r, nb.last_error())
+                return r
         ins = (_CVmTensor * max(len(inputs), 1))(*[_describe(t) for t in inputs])
         on_gpu = isinstance(pool, torch.Tensor) or any(isinstance(t, torch.Tensor) for t in inputs)
         if isinstance(pool, TensorDesc):  # address arithmetic only (programs that launch nothing)
