@@ -255,6 +255,8 @@ def lstm_step_pre(pre: torch.Tensor, h: torch.Tensor, w_h: torch.Tensor, c: torc
 # polls per wait of the one-launch token loop before it gives up (a poll is a round trip to memory, 0.5-1 us:
 # a quarter of a second at the very most)
 LSTM_SEQ_MAX_POLLS = 1 << 18
+# polls per wait of the loop with a recovery launch behind it before that takes over (some 8 ms, about what it takes itself)
+LSTM_LOOP_MAX_POLLS = 1 << 14
 
 
 def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0: torch.Tensor,
@@ -264,10 +266,12 @@ def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0
     returns (h_seq [T,B,H] bf16, c_T [B,H] f32, ran_in_one_launch).
 
     one_launch=None: shapes for which nimble_lstm_seq_preferred says so run as one launch
-    (nimble_lstm_seq_pre_dyn); True: every shape nimble_lstm_seq_supported accepts does (others raise);
+    (nimble_lstm_seq_pre_dyn), other shapes that nimble_lstm_loop_supported accepts through nimble_lstm_loop_dyn, whose
+    own recovery launch stands behind it, so that nothing is waited for and the third value is False as for
+    steps; True: every shape nimble_lstm_seq_supported accepts runs as one launch (others raise);
     False: none.  After a one-launch run the call waits for the stream and reads the loop's give-up word;
-    if the loop gave up, or one launch was not taken, the steps run one by one through
-    nimble_lstm_gates_pre_dyn, which gives the same bits."""
+    if the loop gave up, or neither was taken, the steps run one by one through
+    nimble_lstm_gates_pre_dyn.  All three give the same bits."""
     (T, B, H), _ = nb.lstm_seq_shape(tuple(pre.shape), tuple(h0.shape), tuple(c0.shape), tuple(w_h.shape))
     dev = h0.device
     h_seq = _alloc((T, B, H), nb.BF16, dev)
@@ -281,6 +285,12 @@ def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0
         raise nb.NimbleError(-3, f"the one-launch token loop does not run B={B}, H={H}")
     if one_launch is None:
         one_launch = nb.lstm_seq_preferred(B, H)
+        # 128 steps of 3 rows at H = 1024 took 748 us as eager steps (projection included), 215 in the loop
+        if not one_launch and nb.lstm_loop_supported(B, 0, H):
+            ws = torch.empty(nb.lstm_loop_workspace_bytes(B, 0, H), dtype=torch.uint8, device=dev)
+            nb.nimble_lstm_loop_dyn(0, pp, wp, 0, hp, cp, h_seq.data_ptr(), c_out.data_ptr(), T, B, 0, H, ws.data_ptr(),
+                                    ws.numel(), min(max_polls, LSTM_LOOP_MAX_POLLS), _stream())
+            return h_seq, c_out, False
     if supported and one_launch:
         need = nb.lstm_seq_workspace_bytes(B, H)
         if workspace is None:
@@ -310,10 +320,6 @@ def lstm_sequence(xs: torch.Tensor, w_x: torch.Tensor, w_h: torch.Tensor, bias: 
 def split_lstm_weight(w: torch.Tensor, Ix: int) -> Tuple[torch.Tensor, torch.Tensor]:
     """One-time split of the fused weight [4H, Ix+H] into contiguous input and recurrent halves."""
     return w[:, :Ix].contiguous(), w[:, Ix:].contiguous()
-
-
-# polls per wait of the captured token loop before its recovery launch takes over (some 8 ms, what that launch takes)
-LSTM_LOOP_MAX_POLLS = 1 << 14
 
 
 class LstmSequenceGraph:

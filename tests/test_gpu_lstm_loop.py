@@ -122,6 +122,16 @@ def test_a_captured_loop_replays_and_recovers(rt, nb, monkeypatch):
             assert _same(h, want_h) and torch.equal(c, want_c), (polls, rep)
 
 
+@pytest.mark.parametrize("B,H", [(2, 1024), (20, 512), (5, 320), (300, 512)])
+def test_sequences_beyond_the_preferred_shapes(rt, nb, B, H):
+    """lstm_sequence_pre by default: the loop where it runs (300 rows: the steps), the bits of the steps either way."""
+    x, w, _, h0, c0 = _case(6, 5, B, 0, H)
+    assert not nb.lstm_seq_preferred(B, H) and nb.lstm_loop_supported(B, 0, H) == (B < 300)
+    h, c, one = rt.lstm_sequence_pre(x, w, h0, c0)
+    want_h, want_c, _ = rt.lstm_sequence_pre(x, w, h0, c0, one_launch=False)
+    assert not one and _same(h, want_h) and torch.equal(c, want_c)
+
+
 def test_loops_on_two_streams_at_once(rt, nb):
     """Two captured loops of the most rows side by side: each has its own workspace; whether or not one of them has to
     recover, both are right."""
