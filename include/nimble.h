@@ -103,7 +103,9 @@ typedef struct nimble_plan {
   int32_t split_k;        /* K is cut into this many slices (1 = none); with > 1  */
                           /* the slices write f32 partial sums to the workspace   */
                           /* and a second kernel adds them and applies the epilogue */
-  uint32_t grid[3];       /* launch grid                                          */
+  uint32_t grid[3];       /* launch grid (grid[1] = 2 with split_k = 1 in a tiled plan of */
+                          /* bm = 192, bn = 256: two workgroups share each tile, half  */
+                          /* its columns each)                                         */
   uint32_t block;         /* threads per workgroup                                */
   uint64_t workspace_bytes; /* device scratch the launch needs                    */
   int64_t split_rows;     /* > 0: two launches.  Rows [0, split_rows), a whole number  */

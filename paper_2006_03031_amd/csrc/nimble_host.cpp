@@ -68,6 +68,9 @@ static double tile_cost(int variant, int64_t K, int epilogue, int bm = 0) {
 // Heights the 256-wide tile is built at: 2 wave rows of 4..10 MFMA tiles of 16 rows.
 static const int kTileRows256[] = {320, 288, 256, 224, 192, 160, 128};
 
+// The height of the 256-wide tile that may be shared by two workgroups, 128 columns each.
+static const int kHalvedRows = 192;
+
 bool tile_rows_ok(int variant, int bm, int64_t N, int64_t K) {
   if (bm == 0 || bm == kVariants[variant].bm) return true;
   if (variant != NIMBLE_VAR_T256x256) return false;
@@ -123,6 +126,17 @@ static double few_tiles_us(int v, int64_t tiles, int64_t stages, bool gelu) {
   return tiles <= kCUs ? us : us * (shared + more * (double)(tiles - kCUs) / (double)kCUs);
 }
 
+// 192-row tiles of the 256-wide variant in two halves, a compute unit each: between what 128 rows hold in one round and what 256 do, which then
+// leave a quarter to half of the chip idle.  Fixed time plus the walk over stages of 32 k, fitted (to 3 %) over
+// K = 768 .. 4096 and 96 .. 256 halves.  Measured, microseconds, halves / the choice without them: 1100 x 4096 x 1024
+// (GELU) 16.4 / 19.3, 1530 18.1 / 20.1; 4600 x 1024 x 4096 40.0 / 47.4, 6100 45.6 / 50.7; 2500 x 2304 x 768 13.9 / 15.6;
+// 6000 x 768 x 3072 31.4 / 40.5.  Where 128-row tiles are one round they stay: 3500 x 1024 x 4096 38.3 / 34.5; so do two
+// workgroups of 64-row tiles on short K: 1300 x 3072 x 768 (GELU) 13.9 / 13.5.
+static double halved_us(int64_t halves, int64_t stages, bool gelu) {
+  const double crowded = halves > 128 ? 0.00043 * (double)(halves - 128) : 0.0;
+  return 3.0 + (gelu ? 2.0 : 0.0) + (0.244 + crowded) * (double)stages;
+}
+
 // Estimated time of one launch of tiled variant v over `rows` rows with K cut into `sk`
 // slices, microseconds.  The tiles run in rounds of one per compute unit.  A full round runs
 // at the chip's power-limited rate; the last, partial round runs faster per tile the fewer
@@ -151,6 +165,8 @@ static double tiled_cost_us(int v, int64_t batch, int64_t rows, int64_t N, int64
   const bool few = v <= NIMBLE_VAR_T128x128 && tiles <= 2 * kCUs && K < kLongestFitted && (K >= 320 || batch * ceil_div(rows, 64) * ceil_div(N, 128) <= kCUs);
   if (few && N % 8 == 0 && wide_stages_ok(K, sk) && (double)N * (double)K * 2.0 <= kCachedWeightBytes) {
     us = few_tiles_us(v, tiles, stages, gelu);
+  } else if (v == NIMBLE_VAR_T256x128 && bm == kHalvedRows) {  // (how the halves are priced)
+    us = halved_us(tiles, stages, gelu);
   } else {
     const double latency_floor = (double)stages * kStageFloorUs[v] + (gelu ? 0.05 : 0.0);
     const double t_full = tile_cost(v, k_slice, sk > 1 ? NIMBLE_EPI_NONE : epilogue, bm) * kUsPerUnit;
@@ -280,13 +296,14 @@ struct Launch {
   int variant = -1;
   int split_k = 1;
   int bm = 0;  // tile height when it differs from the variant's own
+  bool halved = false;  // each tile is shared by two workgroups
   double us = 0;
 };
 
 // Best single launch for `rows` rows: the least estimated time among weight streaming (up to
 // 64 rows) and every tiled variant and K split that fits the workspace.
 static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int epilogue,
-                          uint64_t max_workspace, bool allow_skinny) {
+                          uint64_t max_workspace, bool allow_skinny, bool allow_halved = true) {
   Launch best;
   double skinny_us = -1.0, least_tiled_us = 1e30;
   // weight streaming: up to 64 rows, and beyond that in 16-row blocks of the streaming kernel while
@@ -317,12 +334,32 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
         best.variant = v;
         best.split_k = sk;
         best.bm = 0;
+        best.halved = false;
         best.us = us;
       }
     }
     // the same tile at a reduced height: with the run-time M known, pick the height at which
     // the tile rows fill whole rounds of the chip instead of leaving a mostly empty last round
     static const bool heights_on = !(std::getenv("NIMBLE_TILE_ROWS") && std::atoi(std::getenv("NIMBLE_TILE_ROWS")) == 0);
+    if (v == NIMBLE_VAR_T256x128 && allow_halved && batch == 1 && heights_on && K >= 320 && K < kLongestFitted &&
+        ceil_div(rows, kHalvedRows) * (N / 128) <= kCUs && tile_rows_ok(NIMBLE_VAR_T256x256, kHalvedRows, N, K) &&
+        wide_stages_ok(K, 1)) {
+      const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, 1, kHalvedRows);
+      // (not in place of K in two or three, however the estimates compare: 360 x 9216 x 11072 91.7 us, 82.3 in 128-row
+      // tiles with K in two; 386 x 7424 x 4416 43.4 / 41.4.  In place of K in four: 327 x 11008 x 11584 110.8 / 138.4.  Nor
+      // in place of 64-row tiles whose weights come from HBM, which are priced too high: 234 x 12288 x 2688 28.2 / 25.8;
+      // nor of fewer tile rows of 256 there: 429 x 9984 x 11328 115.5 / 111.4)
+      const bool from_hbm = (double)N * (double)K * 2.0 > kCachedWeightBytes;
+      const bool kept = best.split_k == 2 || best.split_k == 3 || (from_hbm && best.variant == NIMBLE_VAR_T64x128) ||
+                        (from_hbm && best.variant == v && best.split_k == 1 && ceil_div(rows, kHalvedRows) > ceil_div(rows, kVariants[v].bm));
+      if (us < best.us && !kept) {
+        best.variant = NIMBLE_VAR_T256x256;
+        best.split_k = 1;
+        best.bm = kHalvedRows;
+        best.halved = true;
+        best.us = us;
+      }
+    }
     if (v == NIMBLE_VAR_T256x256 && batch == 1 && heights_on)
       for (int bm : kTileRows256) {
         if (bm == kVariants[v].bm || rows <= bm || !tile_rows_ok(v, bm, N, K)) continue;
@@ -331,6 +368,7 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
           best.variant = v;
           best.split_k = 1;
           best.bm = bm;
+          best.halved = false;
           best.us = us;
         }
       }
@@ -420,6 +458,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
   int64_t split_rows = 0;
   int residue_variant = NIMBLE_VAR_AUTO;
   int split_k = 1;
+  bool halved = false;
   bool chosen = forced;  // by the caller or a tuned entry: launched as named
   if (variant == NIMBLE_VAR_AUTO) {
     if (!aligned_k || M == 0 || N == 0) {
@@ -437,6 +476,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
       variant = single.variant < 0 ? NIMBLE_VAR_GENERIC : single.variant;
       split_k = single.split_k;
       tile_rows = single.bm;
+      halved = single.halved;
       // Alternative: two launches.  Whole tile rows (all k of them, or as many as fill whole
       // rounds of the chip) run the r = 0 copy of a big-tile variant: no bounds code, no
       // partial round.  The remaining rows, residue included, run whatever suits their
@@ -458,14 +498,20 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
             if (head <= 0 || rest <= 0 || (c == 1 && head == cuts[0])) continue;
             const double head_us = tiled_cost_us(v, 1, head, N, K, epilogue) + kLaunchGapUs;
             if (head_us >= best_us) continue;  // (the tail's search is most of what a plan costs)
-            const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true);
+            // (priced without halved tiles: two launches picked for their sake took 1 to 2 % longer than one:
+            // 4751 x 8192 x 7552 426.9 us, 417.7 in 320-row tiles)
+            const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true, false);
             if (tail.variant < 0) continue;
-            const double us = head_us + tail.us;
+            // (a streamed tail's estimate and the gap both count its launch, which decides against halved tiles at
+            // K > 2048: 4154 x 1024 x 3648 with GELU 36.6 us in two launches, 38.8 in halves)
+            const bool twice = halved && tail.variant == NIMBLE_VAR_SKINNY16 && K > 2048;
+            const double us = head_us + tail.us - (twice ? kLaunchUs + 1.0 : 0.0);
             if (us < best_us) {
               best_us = us;
               variant = v;
               split_k = 1;
               tile_rows = 0;
+              halved = false;
               split_rows = head;
               residue_variant = tail.variant;
             }
@@ -537,6 +583,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
     split_k = forced_sk;
   }
   fill_tiled(p, variant, split_k, batch, split_rows > 0 ? split_rows : M, N, K, tile_rows);
+  if (halved) p->grid[1] = 2;
   if (!chosen && split_rows == 0 &&
       small_tiles_win(variant, (int64_t)p->grid[0] * batch, batch * ceil_div(M, 64) * ceil_div(N, 64), p->bn, N, K, opt.out_f32))
     fill_any(p, batch, M, N, K);

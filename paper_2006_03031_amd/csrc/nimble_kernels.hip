@@ -113,6 +113,19 @@ static int launch_lone(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
   return check_hip(hipGetLastError(), "ring kernel launch");
 }
 
+// Tiles of 256 columns shared by two workgroups, half the columns and a compute unit each, on the 64-wide ring.
+template <int BM>
+static int launch_halves(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
+  const int tiles_m = (g.M + BM - 1) / BM, tiles_n = g.N / 128;
+  const dim3 grid(p.grid[0] * 2), block(512);
+  const int group_m = tiles_m < 4 ? tiles_m : 4;
+  if (p.residue_copy)
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, 128, 4, 2, true, 3, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
+  else
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, 128, 4, 2, false, 3, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
+  return check_hip(hipGetLastError(), "ring kernel launch");
+}
+
 // Whether the LDS-staged streaming kernel can run a weight-streaming launch: one 16-row tile per
 // workgroup, K in whole 64-wide stages (the LSTM cell: its x | h boundary too), 32-bit lane offsets.
 static bool stream_kernel_ok(bool lstm, int rows_per_block, int64_t N, int64_t K, int64_t Ix) {
@@ -260,7 +273,9 @@ static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
         case 288: return launch_ring<288, 256, 2, 4, 0>(g, p, st);
         case 256: return launch_ring<256, 256, 2, 4>(g, p, st);
         case 224: return launch_ring<224, 256, 2, 4>(g, p, st);
-        case 192: return launch_ring<192, 256, 2, 4>(g, p, st);
+        case 192:
+          if (p.split_k == 1 && p.grid[1] == 2) return launch_halves<192>(g, p, st);
+          return launch_ring<192, 256, 2, 4>(g, p, st);
         case 160: return launch_ring<160, 256, 2, 4>(g, p, st);
         case 128: return launch_ring<128, 256, 2, 4>(g, p, st);
         default: return fail(NIMBLE_ERR_ARG, "t256x256 is not built with tiles of %d rows", p.bm);
