@@ -33,6 +33,12 @@ namespace nimble {
 //   instructions alone 84-96 at 2.1-2.4 GHz.  The kernel before it (16 rows per wave, V transposed through
 //   registers with 2-byte LDS writes): 216 us; 12 heads of 512 keys 9.8 -> 5.8.  Without the overlap of
 //   two blocks 140; eight row waves per workgroup 123, two 152.
+//   The workgroups of a compute unit share its vector units: a wave that has its maxima runs at higher priority until
+//   its last product is issued, so the matrix core is fed while the others look for theirs.  Raised from the rescaling
+//   or the first score product on, over the maxima, or lowered a quarter earlier it gives less or nothing.  With it, with
+//   the maximum starting from the reference and the loads' offsets kept, before -> now: 96 x 2048 123.0 -> 119.6 us,
+//   96 x 1000 36.5 -> 34.9, 24 x 2048 41.1 -> 38.0, 48 x 777 19.6 -> 18.1; 12 x 2048 (two key groups, the maximum
+//   alone) 22.3 -> 22.1.
 // ---------------------------------------------------------------------------
 template <int RW, int KG, int S>
 __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_eu(2, 4)))
@@ -69,12 +75,27 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
   // chunk lane & 7
   const int rr = lane >> 3;
   const uint32_t ring_lds = __builtin_amdgcn_readfirstlane(lds_addr_of(&ring[kg][0][0][0]));
+  // offsets of this lane's pieces of a K and of a V tile whose rows all exist.  Kept, like the priority below, only
+  // without key groups: they save 8 instructions per block, but with groups 12 x 2048 took 22.2 -> 23.0 us.
+  constexpr bool WHOLE = KG == 1;
+  uint32_t off[2][LD];
+#pragma unroll
+  for (int n = 0; n < LD; ++n) {
+    const int row = (rw * LD + n) * 8 + rr;
+    off[0][n] = (uint32_t)(row * D + ((lane & 7) ^ ((row >> 1) & 7)) * 8) * 2u;
+    off[1][n] = (uint32_t)(row * D + ((lane & 7) ^ (4 * ((row >> 1) & 1))) * 8) * 2u;
+  }
   auto issue = [&](auto is_v, int i) {  // K or V tile of block i of this group
     constexpr bool V = decltype(is_v)::value;
     const int j0 = (i * KG + kg) * BJ;
     const u16* base = (V ? v : k) + head + (long long)j0 * D;
     const uint32_t dst = ring_lds + ((V ? S : 0) + (S == 1 ? 0 : (i & 1))) * (TILE * 16);
     const int last = L - 1 - j0;                 // rows past the head's last one repeat it
+    if (WHOLE && last >= BJ - 1) {  // uniform
+#pragma unroll
+      for (int n = 0; n < LD; ++n) dma16_so(off[V][n], base, dst + (rw * LD + n) * 1024);
+      return;
+    }
 #pragma unroll
     for (int n = 0; n < LD; ++n) {
       const int j = rw * LD + n;
@@ -136,15 +157,14 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
       qk(sn[0], KN, 0, 0);
       qk(sn[1], KN, 1, 0);
     }
-    float bmax = fmaxf(s[0][0], s[1][0]);
+    float nref = ref;  // (from here the maximum is one v_max3 per two scores and nothing has to be quieted first)
 #pragma unroll
-    for (int e = 1; e < 16; ++e) bmax = fmaxf(fmaxf(bmax, s[0][e]), s[1][e]);
+    for (int e = 0; e < 16; ++e) nref = fmaxf(fmaxf(nref, s[0][e]), s[1][e]);
     {  // the row's other half
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bmax), __float_as_uint(bmax), false, false);
-      bmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(nref), __float_as_uint(nref), false, false);
+      nref = fmaxf(fmaxf(ref, __uint_as_float(sw[0])), __uint_as_float(sw[1]));
     }
-    if (__any(bmax > ref)) {
-      const float nref = fmaxf(ref, bmax);
+    if (__any(nref > ref)) {
       const float rescale = __builtin_amdgcn_exp2f((ref - nref) * a2);  // (of zeros in the first block)
       sum0 *= rescale;
       sum1 *= rescale;
@@ -156,6 +176,7 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
     }
     const float nm2 = -ref * a2;
     const uint32_t vs0 = lds_addr_of(&ring[kg][1][S == 1 ? 0 : SL][0]) + v_off, vs1 = vs0 ^ 64;  // d 0..31, 32..63
+    if (KG == 1) __builtin_amdgcn_s_setprio(1);  // (see the kernel's comment)
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (NEXT && u < 3) {
@@ -178,6 +199,7 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
         oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)), pf, oacc[t], 0, 0, 0);
       }
     }
+    if (KG == 1) __builtin_amdgcn_s_setprio(0);
   };
   auto arrive = [&](int i) {  // K of block i + 1 and V of block i are there; the tiles read before are refilled
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
