@@ -334,8 +334,9 @@ int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up);
  * once.  h_seq and c_out are right either way and bit-identical to T calls of nimble_lstm_gates_dyn
  * (nimble_lstm_gates_pre_dyn with pre); c_out may alias c0.
  * Supported: H = 64..1024 and Ix >= 0 in multiples of 64 with Ix + H <= 1024, Ix a multiple of 128 where Ix + H > 512;
- * B <= 256 at H = 512, 512 at 256, 128 at 1024; where the per-step launch adds in another order (Ix + H other than
- * 512 or 1024) fewer, 32 at H = 512.  Workspace of
+ * B <= 256 at H = 512, 512 at 256, 128 at 1024; with Ix + H other than 512 or 1024 fewer, 32 at H = 512: as many as
+ * the per-step launch serves with up to 256 workgroups, whose sums run over eight ranges of Ix + H and beyond over
+ * four.  Workspace of
  * nimble_lstm_loop_workspace_bytes, its use, max_polls and the errors as for nimble_lstm_seq_pre_dyn;
  * nimble_lstm_seq_status tells whether the loop gave up. */
 int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H);

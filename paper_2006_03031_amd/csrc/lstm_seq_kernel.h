@@ -38,8 +38,8 @@ namespace nimble {
 //   the host reads the word and runs the sequence step by step, or lstm_seq_recover_kernel, enqueued behind, does.
 //   max_polls = 0 gives up at the first wait: the host-side way to exercise that path.
 //   Arithmetic: identical, bit for bit, to the per-step kernel on the same shapes (stream_kernel: the same
-//   eight ranges of K stages, the same two accumulators per range, the same order of adding the ranges' sums, the same
-//   cell function).
+//   eight or four ranges of K stages, the same two accumulators per range, the same order of adding the ranges' sums,
+//   the same cell function).
 //   What bounds it: one trip through the memory system per step (store, then a load that sees it), about half of the step;
 //   the rest is a chain of MFMAs, LDS sums, barrier and cell arithmetic.  Microseconds per step, pre form at
 //   1 / 4 rows: H = 512 1.10 / 1.17, H = 1024 1.41 / 1.56, H = 256 1.14 / - (32-bit words with a step tag each, four lanes
@@ -66,6 +66,7 @@ struct LstmSeqArgs {
   unsigned long long* exch;  // [row group][2][words of 4 units]: B * H / 2 words
   float* c_keep;      // [B, H] or null: c_0 for the recovery kernel (c_out may be c_0)
   int T, B, Ix, H;
+  int ranges;         // of K stages with a sum of their own: 8, or 4 where the per-step launch runs four waves
   uint32_t max_polls;
 };
 
@@ -112,9 +113,18 @@ __device__ __forceinline__ uint32_t lstm_seq_nans(uint32_t v) {
 // PRE: the inputs' share comes precomputed, else from x; PW: K stages of 64 per wave, ceil((Ix + H) / 64 / 8); G: groups
 // of 16 gate rows (4 units) per workgroup; R: rows per group of workgroups, 4 or 8.  rs_few: words per four units in the
 // hand-over buffers for R = 4 (at least the group's rows).
-template <bool PRE, int PW, int G, int R>
+// A wave's share of K is 2 PW units of 32 k.  ORDER 0, eight ranges: wave w has the units of range w one after the other,
+// in two chains, as the per-step launch on eight waves.  ORDER 1, four ranges of 2 PW whole stages: that launch has four
+// waves, each with the first halves of its stages in one chain and the second halves in the other; here waves 2 w and
+// 2 w + 1 have one of these chains each, which gives the same sums without a wave doing more.  ORDER 2: as 1 where a
+// range holds stages of x and of h (in place of 1 it takes 128 steps of 37 rows, H = Ix = 512, from 188 us to 204).
+template <bool PRE, int PW, int G, int R, int ORDER>
 __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row_groups, int rs_few, int xcd0) {
   static_assert(R == 4 || R == 8, "a load brings 8 rows of 32 k or 4 rows of 64");
+  static_assert(ORDER == 0 || R == 8, "up to 4 rows the per-step launch runs eight waves");
+  constexpr bool MIX = ORDER == 2;
+  constexpr int NU = 2 * PW;               // units of 32 k per wave
+  constexpr int STEP = ORDER == 0 ? 32 : 64;  // k from one of them to the next
   const int rs = R == 8 ? 8 : rs_few;
   constexpr int SCOPE = __HIP_MEMORY_SCOPE_AGENT;
   constexpr int U = 4 * G;    // units per workgroup
@@ -139,32 +149,35 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r = lane & 15, gq = lane >> 4;
 
-  // this wave's K stages: the per-step kernel's ranges, all of x or all of h (Ix is whole ranges)
+  // this wave's units: of the per-step kernel's ranges (ORDER < 2: all of x or all of h, Ix is whole ranges)
   const int x_stages = Ix >> 6, stages = (Ix + H) >> 6;
-  const int per_wave = (stages + 7) / 8;
-  const int st_begin = wave * per_wave;
-  const int st_end = (st_begin + per_wave) < stages ? (st_begin + per_wave) : stages;
-  const int n_st = st_end > st_begin ? st_end - st_begin : 0;  // <= PW (the launcher picks PW >= per_wave)
-  const bool of_x = !PRE && st_begin < x_stages;
+  int st_begin, n_units, k_begin;  // first stage, units <= NU, first k
+  if (ORDER == 0) {
+    const int per_wave = (stages + 7) / 8;  // <= PW (the launcher picks PW >= per_wave)
+    st_begin = wave * per_wave;
+    const int st_end = (st_begin + per_wave) < stages ? (st_begin + per_wave) : stages;
+    n_units = st_end > st_begin ? 2 * (st_end - st_begin) : 0;
+    k_begin = st_begin * 64;
+  } else {
+    st_begin = (wave >> 1) * NU;  // (the launcher: stages = 4 NU)
+    n_units = NU;
+    k_begin = st_begin * 64 + (wave & 1) * 32;
+  }
+  const bool of_x = !PRE && st_begin < x_stages;  // (MIX: its first units)
+  int x_units = of_x ? n_units : 0;
+  if (MIX && of_x) x_units = x_stages - st_begin < NU ? x_stages - st_begin : NU;
 
-  // weights of this workgroup's 16 G gate rows over this wave's stages, in the MFMA operand
+  // weights of this workgroup's 16 G gate rows over this wave's units, in the MFMA operand
   // layout: lane (r, gq) holds 8 k of tile row r = gate r & 3 of unit 4 g + (r >> 2)
-  uint4 wa[G][PW], wb[G][PW];
+  uint4 wt[G][NU];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const u16* wrow = a.w + ((long long)(r & 3) * H + wg * U + g * 4 + (r >> 2)) * (Ix + H);
+    const u16* wrow = a.w + ((long long)(r & 3) * H + wg * U + g * 4 + (r >> 2)) * (Ix + H) + k_begin + gq * 8;
 #pragma unroll
-    for (int s = 0; s < PW; ++s) {
-      if (s < n_st) {
-        const int k = (st_begin + s) * 64 + gq * 8;
-        wa[g][s] = *(const uint4*)(wrow + k);
-        wb[g][s] = *(const uint4*)(wrow + k + 32);
-      } else {
-        wa[g][s] = wb[g][s] = make_uint4(0, 0, 0, 0);
-      }
+    for (int j = 0; j < NU; ++j) {
+      wt[g][j] = ORDER != 0 || j < n_units ? *(const uint4*)(wrow + j * STEP) : make_uint4(0, 0, 0, 0);
       // (left to itself the compiler loads the weights anew in every step instead of keeping them)
-      keep_in_registers(wa[g][s]);
-      keep_in_registers(wb[g][s]);
+      keep_in_registers(wt[g][j]);
     }
   }
 
@@ -186,28 +199,34 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
   // word of this lane in a load: R = 8: 32 k, rows by lane & 7, pieces of 4 k by gq and bit 3; R = 4: 64 k
   uint32_t ask;   // (bytes, as is the next)
   uint32_t from;  // this lane's operand row in x_t or h_0 (lanes past the group's rows: columns never used)
+  // first k of this wave within h (MIX: can be below 0, its first units are of x)
+  const int h_begin = k_begin - x_stages * 64;
   {
     const int lrow = (r & (R - 1)) < rows ? r & (R - 1) : rows - 1;
     ask = (uint32_t)((R == 8 ? gq * 2 + (r >> 3) : (r >> 3) * 8 + gq * 2 + ((r >> 2) & 1)) * rs + lrow +
-                     (of_x ? 0 : (st_begin - x_stages) * (16 * rs))) * 8u;
+                     (MIX || of_x ? 0 : (h_begin >> 2) * rs)) * 8u;
     const int orow = row0 + (r < rows ? r : rows - 1);
-    from = (uint32_t)(of_x ? orow * Ix + st_begin * 64 + gq * 8 : orow * H + (st_begin - x_stages) * 64 + gq * 8) * 2u;
+    from = (uint32_t)(of_x ? orow * Ix + k_begin + gq * 8 : orow * H + h_begin + gq * 8) * 2u;
   }
 
-  // operands of this wave's stages for the step to come: x_t, loaded a step ahead, or h_{t-1}
-  uint4 fa[PW], fb[PW];
+  // operands of this wave's units for the step to come: x_t, loaded a step ahead, or h_{t-1}
+  uint4 f[NU];
 #pragma unroll
-  for (int s = 0; s < PW; ++s) fa[s] = fb[s] = make_uint4(0, 0, 0, 0);  // (stages that this wave does not have: zeros)
+  for (int j = 0; j < NU; ++j) f[j] = make_uint4(0, 0, 0, 0);  // (units that this wave does not have: zeros)
   auto load_rows = [&](const u16* src) {
 #pragma unroll
-    for (int s = 0; s < PW; ++s)
-      if (s < n_st) {
-        fa[s] = *(const uint4*)at(src + s * 64, from);
-        fb[s] = *(const uint4*)at(src + s * 64 + 32, from);
-      }
+    for (int j = 0; j < NU; ++j)
+      if (ORDER == 1 || j < (MIX ? x_units : n_units)) f[j] = *(const uint4*)at(src + j * STEP, from);
   };
-  if (of_x) load_rows(a.x); else load_rows(a.h0);
-  const bool waits = !of_x && n_st > 0;  // for h_t
+  if (MIX) {
+    const int orow = row0 + (r < rows ? r : rows - 1);
+#pragma unroll
+    for (int j = 0; j < NU; ++j)
+      f[j] = *(const uint4*)((j < x_units ? a.x + orow * Ix + k_begin : a.h0 + orow * H + h_begin) + j * STEP + gq * 8);
+  } else {
+    load_rows(of_x ? a.x : a.h0);
+  }
+  const bool waits = MIX ? x_units < NU : !of_x && n_units > 0;  // for h_t
   if (waits && a.max_polls == 0) s_abort[1] = 1;
 
   // The bias, or the inputs' share of the gates, which streams from memory, a fresh line per step: it is fetched
@@ -228,16 +247,16 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
 #pragma unroll
       for (int g = 0; g < 2; ++g) acc[g][0] = acc[g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int s = 0; s < PW; ++s)
+      for (int j = 0; j < NU; ++j)
 #pragma unroll
         for (int g = 0; g < 2; ++g) {
-          acc[g][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[g0 + g][s]), as_bf16x8(fa[s]), acc[g][0], 0, 0, 0);
-          acc[g][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[g0 + g][s]), as_bf16x8(fb[s]), acc[g][1], 0, 0, 0);
+          const int chain = ORDER == 0 ? j & 1 : 0;
+          acc[g][chain] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wt[g0 + g][j]), as_bf16x8(f[j]), acc[g][chain], 0, 0, 0);
         }
       // accumulator of lane (r, gq), register v: gate v of unit gq of the group, activation row r
 #pragma unroll
       for (int g = 0; g < 2; ++g)
-        if (r < R) red[t & 1][wave][((g0 + g) * R + r) * 4 + gq] = acc[g][0] + acc[g][1];  // rows past the group's are never used
+        if (r < R) red[t & 1][wave][((g0 + g) * R + r) * 4 + gq] = ORDER == 0 ? acc[g][0] + acc[g][1] : acc[g][0];  // rows past the group's are never used
     }
     if (of_x && t < T) load_rows(a.x + (long long)t * B * Ix);
     if (PRE && owner && t < T) {
@@ -249,7 +268,8 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
     const int aborted = __builtin_amdgcn_readfirstlane(s_abort[t & 1]);  // written before the barrier (after an abort the cells are garbage, and not used)
 
     if (cells) {
-      // the waves' partial sums in the per-step kernel's order, the inputs' share, the cell
+      // the waves' partial sums in the per-step kernel's order (ORDER > 0: neighbours are its waves' two chains), the
+      // inputs' share, the cell
       const f32x4* e = &red[t & 1][0][tid & (CELLS - 1)];
       f32x4 sum = (e[0] + e[CELLS]) + (e[2 * CELLS] + e[3 * CELLS]);
       if (PRE && PW > 1) __builtin_amdgcn_sched_barrier(0);  // (all eight at once do not fit beside the weights)
@@ -297,23 +317,27 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
       if (!cells) __builtin_amdgcn_s_sleep(R == 8 || PW > 1 ? 16 : 14);
       else if (R == 8) __builtin_amdgcn_s_sleep(4);
       for (;;) {
-        unsigned long long v[PW][LPS];
+        // R = 8: a unit per load; R = 4: two of them, the lanes of the upper 8 rows hold the second
+        constexpr int UPL = 2 / LPS;
+        unsigned long long v[NU / UPL];
 #pragma unroll
-        for (int s = 0; s < PW; ++s)
-#pragma unroll
-          for (int l = 0; l < LPS; ++l)  // (a stage that this wave does not have: the words of its last one again)
-            v[s][l] = __hip_atomic_load(at(src + (s < n_st ? s : n_st - 1) * 16 * rs, ask) + l * 8 * rs, __ATOMIC_RELAXED, SCOPE);
+        for (int i = 0; i < NU / UPL; ++i) {
+          const unsigned long long* word;
+          if (ORDER == 0)  // (units that this wave does not have: the words of its last stage again)
+            word = at(src + (2 * (i / LPS) < n_units ? i / LPS : n_units / 2 - 1) * 16 * rs, ask) + (i % LPS) * 8 * rs;
+          else if (MIX)  // (units of x: the words of its first unit of h)
+            word = at(src + (long long)((h_begin >> 2) + (i < x_units ? x_units : i) * 16) * rs, ask);
+          else
+            word = at(src + i * 16 * rs, ask);
+          v[i] = __hip_atomic_load(word, __ATOMIC_RELAXED, SCOPE);
+        }
         uint32_t bad = 0;
 #pragma unroll
-        for (int s = 0; s < PW; ++s) {
-          fa[s].x = (uint32_t)v[s][0] ^ want;
-          fa[s].y = (uint32_t)(v[s][0] >> 32);
-          bad |= fa[s].x;
-          if (LPS == 2) {
-            fb[s].x = (uint32_t)v[s][LPS - 1] ^ want;
-            fb[s].y = (uint32_t)(v[s][LPS - 1] >> 32);
-            bad |= fb[s].x;
-          }
+        for (int i = 0; i < NU / UPL; ++i) {
+          const uint32_t lo = (uint32_t)v[i] ^ want;
+          bad |= lo;
+          f[i * UPL].x = MIX && i < x_units ? f[i * UPL].x : lo;
+          f[i * UPL].y = MIX && i < x_units ? f[i * UPL].y : (uint32_t)(v[i] >> 32);
         }
         nan = bad & kHandOverNan;
         if (__all((bad & kHandOverPhase) == 0u)) break;
@@ -327,31 +351,23 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
       }
       if (__any(nan != 0u)) {
 #pragma unroll
-        for (int s = 0; s < PW; ++s) {
-          if (fa[s].x & kHandOverNan) {
-            fa[s].x = lstm_seq_nans(fa[s].x & ~kHandOverNan);
-            fa[s].y = lstm_seq_nans(fa[s].y);
+        for (int j = 0; j < NU; j += 2 / LPS)
+          if (f[j].x & (MIX && j < x_units ? 0u : kHandOverNan)) {
+            f[j].x = lstm_seq_nans(f[j].x & ~kHandOverNan);
+            f[j].y = lstm_seq_nans(f[j].y);
           }
-          if (LPS == 2 && (fb[s].x & kHandOverNan)) {
-            fb[s].x = lstm_seq_nans(fb[s].x & ~kHandOverNan);
-            fb[s].y = lstm_seq_nans(fb[s].y);
-          }
-        }
       }
       // to the operand layout: the lanes of the first R rows collect the other pieces of their 8 k
 #pragma unroll
-      for (int s = 0; s < PW; ++s) {
-        if (R == 8) {
-          fa[s].z = lane_up<8>(fa[s].x);
-          fa[s].w = lane_up<8>(fa[s].y);
-          fb[s].z = lane_up<8>(fb[s].x);
-          fb[s].w = lane_up<8>(fb[s].y);
-        } else {
-          fb[s] = make_uint4(lane_up<8>(fa[s].x), lane_up<8>(fa[s].y), lane_up<12>(fa[s].x), lane_up<12>(fa[s].y));
-          fa[s].z = lane_up<4>(fa[s].x);
-          fa[s].w = lane_up<4>(fa[s].y);
-        }
-        if (s >= n_st) fa[s] = fb[s] = make_uint4(0, 0, 0, 0);
+      for (int j = 0; j < NU; j += 2 / LPS) {
+        if (R == 4) f[j + 1] = make_uint4(lane_up<8>(f[j].x), lane_up<8>(f[j].y), lane_up<12>(f[j].x), lane_up<12>(f[j].y));
+        f[j].z = MIX && j < x_units ? f[j].z : lane_up<R == 8 ? 8 : 4>(f[j].x);
+        f[j].w = MIX && j < x_units ? f[j].w : lane_up<R == 8 ? 8 : 4>(f[j].y);
+      }
+      if (ORDER == 0) {
+#pragma unroll
+        for (int j = 0; j < NU; ++j)
+          if (j >= n_units) f[j] = make_uint4(0, 0, 0, 0);
       }
     }
   }
@@ -366,7 +382,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
 
 // The same sequence by workgroups that wait for nobody, enqueued behind the loop and gone at once unless that
 // gave up: a workgroup takes 16 rows through all steps, its waves walk the units in fours, each over the whole of K, with
-// the same eight ranges and the same order of the sums.  h_{t-1} is read back from h_seq, c_t lives in c_keep.
+// the same ranges and the same order of the sums.  h_{t-1} is read back from h_seq, c_t lives in c_keep.
 // Bound by one compute unit's reading of the weights, some 50 us per step; runs only where the loop could not.
 __global__ void __launch_bounds__(1024) lstm_seq_recover_kernel(LstmSeqArgs a) {
   if (__hip_atomic_load(a.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) return;
@@ -377,7 +393,7 @@ __global__ void __launch_bounds__(1024) lstm_seq_recover_kernel(LstmSeqArgs a) {
   const int row = blockIdx.x * 16 + r;
   const int orow = row < B ? row : B - 1;
   const int x_stages = Ix >> 6, stages = (Ix + H) >> 6;
-  const int per_range = (stages + 7) / 8;
+  const int per_range = (stages + a.ranges - 1) / a.ranges;
   for (int t = 0; t < T; ++t) {
     const u16* h_prev = t == 0 ? a.h0 : a.h_seq + (long long)(t - 1) * B * H;
     const u16* xr = a.x ? a.x + ((long long)t * B + orow) * Ix : nullptr;
@@ -385,12 +401,12 @@ __global__ void __launch_bounds__(1024) lstm_seq_recover_kernel(LstmSeqArgs a) {
     for (int g = wave; g < H / 4; g += 16) {
       const u16* wrow = a.w + ((long long)(r >> 2) * H + g * 4 + (r & 3)) * (Ix + H) + gq * 8;
       f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-      for (int half = 0; half < 2; ++half) {
+      for (int four = 0; four < a.ranges; four += 4) {
         f32x4 part[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-          const int begin = (half * 4 + v) * per_range;
+          const int begin = (four + v) * per_range;
           const int end = begin + per_range < stages ? begin + per_range : stages;
           for (int s = begin; s < end; ++s) {
             const u16* src = (s < x_stages ? xr + s * 64 : hr + (s - x_stages) * 64) + gq * 8;

@@ -775,7 +775,7 @@ int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H) {
   if (B < 1 || B > 65536 || H < 64 || H > 1024 || H % 64 != 0 || Ix < 0 || Ix > 1024 || Ix % 64 != 0) return 0;
   const int64_t stages = (Ix + H) / 64, per_wave = ceil_div(stages, 8);
   if (per_wave > 2 || Ix / 64 % per_wave != 0) return 0;
-  // (the per-step kernel's order of the sums: see stream_kernel on four waves)
+  // (where the per-step launch runs four waves the loop takes the sums over four ranges, of two or four whole stages)
   nimble_plan p;
   if (nimble_lstm_plan(B, Ix, H, &p) != NIMBLE_OK || (p.split_k == 4 && stages != 8 && stages != 16)) return 0;
   const int64_t n_wg = H / 16, span = n_wg > 32 ? 2 : 1;

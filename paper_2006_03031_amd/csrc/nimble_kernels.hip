@@ -147,11 +147,7 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
     // shape below and 6.3 with eight waves and two stages; the LSTM cell at 64 rows 3.9 against 5.3).
     const bool many = (uint64_t)grid.x * grid.y > (uint64_t)kComputeUnits &&
                       (double)s.N * (double)s.K * 2.0 <= kCachedWeightBytes;
-    if (LSTM && many && s.K == 512)
-      hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16, LSTM ? 1 : 0>), grid, dim3(256), 0, st, s);
-    else if (LSTM && many && s.K == 1024)
-      hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16, LSTM ? 2 : 0>), grid, dim3(256), 0, st, s);
-    else if (many)
+    if (many)
       hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16>), grid, dim3(256), 0, st, s);
     else if (s.M <= 8)
       hipLaunchKernelGGL((stream_kernel<LSTM, 3, 8, 8>), grid, dim3(512), 0, st, s);
@@ -323,19 +319,31 @@ static int launch_attention(const u16* q, const u16* k, const u16* v, u16* o, in
 }
 
 // 16 units per workgroup (8 or 32 at 4 rows: no faster or slower, 1.6 / 1.9 us per step against 1.6 before the later steps).
+template <int N>
+using Int = std::integral_constant<int, N>;
+
 template <int R>
 static void launch_lstm_seq_as(const LstmSeqArgs& a, int rs, int xcd0, hipStream_t st) {
   const int row_groups = (a.B + R - 1) / R, per_wave = ((a.Ix + a.H) / 64 + 7) / 8;
   const int n_wg = a.H / 16, span = n_wg > 32 ? 2 : 1;  // XCDs per row group
   const dim3 grid((unsigned)(8 * (n_wg / span) * ((row_groups * span + 7) / 8))), block(512);
-  if (a.pre && per_wave <= 1)
-    hipLaunchKernelGGL((lstm_seq_kernel<true, 1, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
-  else if (a.pre)
-    hipLaunchKernelGGL((lstm_seq_kernel<true, 2, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
-  else if (per_wave <= 1)
-    hipLaunchKernelGGL((lstm_seq_kernel<false, 1, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
-  else
-    hipLaunchKernelGGL((lstm_seq_kernel<false, 2, 4, R>), grid, block, 0, st, a, row_groups, rs, xcd0);
+  // (four ranges: whole ranges of 2 per_wave stages, see nimble_lstm_loop_supported)
+  const bool mixed = a.ranges == 4 && a.Ix / 64 % (2 * per_wave) != 0;
+  const int order = a.ranges != 4 ? 0 : mixed ? 2 : 1;
+  auto launch = [&](auto pre, auto pw, auto ord) {
+    constexpr int ORDER = R == 8 ? decltype(ord)::value : 0;
+    hipLaunchKernelGGL((lstm_seq_kernel<decltype(pre)::value, decltype(pw)::value, 4, R, ORDER>), grid, block, 0, st, a,
+                       row_groups, rs, xcd0);
+  };
+  auto pick = [&](auto pw) {
+    if (a.pre && order == 0) launch(std::true_type(), pw, Int<0>());
+    else if (a.pre) launch(std::true_type(), pw, Int<1>());
+    else if (order == 0) launch(std::false_type(), pw, Int<0>());
+    else if (order == 1) launch(std::false_type(), pw, Int<1>());
+    else launch(std::false_type(), pw, Int<2>());
+  };
+  if (per_wave <= 1) pick(Int<1>());
+  else pick(Int<2>());
 }
 
 // The token loop in one launch behind a fill of its workspace.
@@ -725,6 +733,7 @@ int nimble_lstm_seq_pre_dyn(const void* pre, const void* w_h, const void* h0, co
   a.T = (int)T;
   a.B = (int)B;
   a.H = (int)H;
+  a.ranges = 8;
   a.max_polls = max_polls;
   return launch_lstm_seq(a, (hipStream_t)stream);
 }
@@ -763,8 +772,12 @@ int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const vo
   a.B = (int)B;
   a.Ix = (int)Ix;
   a.H = (int)H;
+  nimble_plan step;
+  int rc = nimble_lstm_plan(B, Ix, H, &step);
+  if (rc != NIMBLE_OK) return rc;
+  a.ranges = step.split_k;
   a.max_polls = max_polls;
-  int rc = launch_lstm_seq(a, (hipStream_t)stream);
+  rc = launch_lstm_seq(a, (hipStream_t)stream);
   if (rc != NIMBLE_OK) return rc;
   hipLaunchKernelGGL(lstm_seq_recover_kernel, dim3((unsigned)((B + 15) / 16)), dim3(1024), 0, (hipStream_t)stream, a);
   return check_hip(hipGetLastError(), "lstm loop recovery launch");

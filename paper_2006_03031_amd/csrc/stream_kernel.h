@@ -2,8 +2,6 @@
 // direct global->LDS loads of whole 128-byte lines.
 #ifndef NIMBLE_STREAM_KERNEL_H_
 #define NIMBLE_STREAM_KERNEL_H_
-#include <type_traits>
-
 #include "device_common.h"
 #include "skinny_kernel.h"
 
@@ -51,14 +49,8 @@ __device__ __forceinline__ void wait_vmcnt_of(int n) {  // n is a constant after
 // NW = 8 with S = 2, 3, 4: 24.7, 24.5, 24.4 / 27.6, 28.0, 27.9; NW = 8, XR = 8, S = 3: 23.9 (four rows:
 // 25.0).  Two groups of 16 weight rows per workgroup sharing one activation tile (half the activation
 // traffic, but one workgroup per compute unit): 25.9-27.4 / 27.5-28.8, not kept.
-// SR > 0: four waves of exactly 2 SR stages (K = 512 SR), as two neighbouring ranges of SR with accumulators of their own.
-// The eight waves' partial sums are added as ((0 + 1) + (2 + 3)) + ((4 + 5) + (6 + 7)); four waves that add their two
-// sums give that order too, so that a row's result does not depend on the batch it came in, and the token loop in one launch
-// gives the same bits.  Written out stage by stage: telling the ranges apart in the loop cost it 3 %.
-template <bool LSTM, int S, int NW = 8, int XR = 16, int SR = 0>
+template <bool LSTM, int S, int NW = 8, int XR = 16>
 __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
-  constexpr int VW = SR > 0 ? 2 : 1;                // ranges per wave
-  static_assert(SR == 0 || (SR <= 2 && NW == 4 && S == 2), "two ranges per wave: eight in all, two slots");
   static_assert(XR == 8 || XR == 16, "the activation tile is one or two loads of 8 rows");
   constexpr int RG = 1;                             // groups of 16 weight rows per workgroup
   constexpr int LD = 2 * RG + XR / 8;               // direct loads per stage and wave
@@ -161,15 +153,10 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
   const int f0 = r * 8 + (gq ^ sw), f1 = r * 8 + ((gq + 4) ^ sw);
   const int xr = r & (XR - 1), xsw = (xr >> 1) & 7;
   const int g0 = RG * 128 + xr * 8 + (gq ^ xsw), g1 = RG * 128 + xr * 8 + ((gq + 4) ^ xsw);
-  f32x4 acc[VW][RG][2];
+  f32x4 acc[RG][2];
 #pragma unroll
-  for (int g = 0; g < RG; ++g)
-#pragma unroll
-    for (int u = 0; u < VW; ++u) acc[u][g][0] = acc[u][g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  using First = std::integral_constant<int, 0>;
-  using Second = std::integral_constant<int, VW - 1>;
-  auto compute = [&](int slot, auto range) {
-    constexpr int V = decltype(range)::value;
+  for (int g = 0; g < RG; ++g) acc[g][0] = acc[g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int slot) {
     const uint4* t = &ring[wave][slot][0];
     const uint4 xa = t[g0], xb = t[g1];
     uint4 wa[RG], wb[RG];
@@ -177,29 +164,14 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
     for (int g = 0; g < RG; ++g) wa[g] = t[g * 128 + f0], wb[g] = t[g * 128 + f1];
 #pragma unroll
     for (int g = 0; g < RG; ++g) {
-      acc[V][g][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[g]), as_bf16x8(xa), acc[V][g][0], 0, 0, 0);
-      acc[V][g][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[g]), as_bf16x8(xb), acc[V][g][1], 0, 0, 0);
+      acc[g][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wa[g]), as_bf16x8(xa), acc[g][0], 0, 0, 0);
+      acc[g][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wb[g]), as_bf16x8(xb), acc[g][1], 0, 0, 0);
     }
     // the slot is refilled only after these reads have returned
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   };
 
-  if constexpr (SR > 0) {
-    issue(st_begin, 0);
-    issue(st_begin + 1, 1);
-#pragma unroll
-    for (int i = 0; i < 2 * SR; ++i) {
-      if (i + 1 < 2 * SR)
-        wait_vmcnt<LD>();
-      else
-        wait_vmcnt<0>();
-      if (i < SR)
-        compute(i & 1, First{});
-      else
-        compute(i & 1, Second{});
-      if (i + 2 < 2 * SR) issue(st_begin + i + 2, i & 1);
-    }
-  } else if (n_st >= S - 1) {
+  if (n_st >= S - 1) {
     // S-1 stages in flight; stage i of this wave lives in slot i % S
 #pragma unroll
     for (int i = 0; i < S - 1; ++i) issue(st_begin + i, i);
@@ -207,7 +179,7 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
     for (int i = 0; i + (S - 1) < n_st; ++i) {
       issue(st_begin + i + S - 1, fill);       // the slot of stage i - 1, whose reads have returned
       wait_vmcnt<(S - 1) * LD>();                // stage i has landed
-      compute(slot, First{});
+      compute(slot);
       slot = slot + 1 == S ? 0 : slot + 1;
       fill = fill + 1 == S ? 0 : fill + 1;
     }
@@ -215,13 +187,13 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
 #pragma unroll
     for (int j = S - 2; j >= 0; --j) {
       wait_vmcnt_of(j * LD);
-      compute(slot, First{});
+      compute(slot);
       slot = slot + 1 == S ? 0 : slot + 1;
     }
   } else {
     for (int i = 0; i < n_st; ++i) issue(st_begin + i, i);
     wait_vmcnt<0>();
-    for (int i = 0; i < n_st; ++i) compute(i, First{});
+    for (int i = 0; i < n_st; ++i) compute(i);
   }
 
   // accumulator of lane (r, gq), register v: weight row i = 4 gq + v, activation row j = r
@@ -229,11 +201,7 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
 #pragma unroll
   for (int g = 0; g < RG; ++g)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      float sum = acc[0][g][0][v] + acc[0][g][1][v];
-      if (VW == 2) sum += acc[VW - 1][g][0][v] + acc[VW - 1][g][1][v];
-      red[wave][g][r][gq * 4 + v] = sum;
-    }
+    for (int v = 0; v < 4; ++v) red[wave][g][r][gq * 4 + v] = acc[g][0][v] + acc[g][1][v];
   __syncthreads();
 
   if (LSTM) {
@@ -249,9 +217,8 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
           const int col = q * 4 + u;
           float sum = 0.f;
 #pragma unroll
-          for (int wv = 0; wv < NW; wv += 4 / VW)  // (VW = 2: a wave's sum is already that of two ranges)
-            sum += VW == 2 ? red[wv][0][mm][col] + red[wv + 1][0][mm][col] :
-                             (red[wv][0][mm][col] + red[wv + 1][0][mm][col]) + (red[wv + 2][0][mm][col] + red[wv + 3][0][mm][col]);
+          for (int wv = 0; wv < NW; wv += 4)
+            sum += (red[wv][0][mm][col] + red[wv + 1][0][mm][col]) + (red[wv + 2][0][mm][col] + red[wv + 3][0][mm][col]);
           gate[q] = sum + pre_bias[q];
         }
         const long long o = (long long)m * s.H + unit;

@@ -67,7 +67,9 @@ def _same(a, b):
 SHAPES = [(9, 1, 512, 512), (6, 4, 512, 512), (6, 5, 512, 512), (5, 8, 512, 512), (5, 9, 512, 512), (4, 37, 512, 512),
           (4, 64, 512, 512), (5, 23, 256, 256), (4, 3, 64, 64), (3, 130, 192, 64), (3, 150, 512, 512), (2, 65, 0, 1024), (6, 5, 128, 640), (3, 64, 128, 256),
           (7, 2, 0, 64), (5, 17, 0, 320), (5, 33, 0, 512), (4, 64, 0, 512), (5, 16, 0, 576), (4, 32, 0, 1024),
-          (1, 6, 0, 512), (1, 6, 512, 512), (40, 12, 0, 256)]
+          (1, 6, 0, 512), (1, 6, 512, 512), (40, 12, 0, 256),
+          # four ranges that hold stages of x and of h: of four stages, and of two
+          (4, 37, 640, 384), (3, 41, 128, 896), (3, 33, 384, 640), (3, 97, 192, 320), (2, 278, 448, 64)]
 
 
 @pytest.mark.parametrize("T,B,Ix,H", SHAPES)
@@ -80,7 +82,8 @@ def test_the_loop_equals_the_steps_one_by_one(rt, nb, T, B, Ix, H):
     assert _same(h, want_h) and torch.equal(c, want_c)
 
 
-@pytest.mark.parametrize("T,B,Ix,H", [(4, 37, 512, 512), (3, 4, 0, 512), (3, 11, 0, 576), (3, 3, 64, 64), (2, 64, 0, 512)])
+@pytest.mark.parametrize("T,B,Ix,H", [(4, 37, 512, 512), (3, 4, 0, 512), (3, 11, 0, 576), (3, 3, 64, 64), (2, 64, 0, 512),
+                                       (3, 37, 640, 384), (2, 97, 192, 320)])
 def test_the_recovery_launch_gives_the_same_bits(rt, nb, T, B, Ix, H):
     case = _case(1, T, B, Ix, H)
     want_h, want_c = _steps(rt, *case)
@@ -88,7 +91,7 @@ def test_the_recovery_launch_gives_the_same_bits(rt, nb, T, B, Ix, H):
     assert gave_up and _same(h, want_h) and torch.equal(c, want_c)
 
 
-@pytest.mark.parametrize("B,Ix", [(3, 0), (3, 512), (13, 0), (13, 512)])
+@pytest.mark.parametrize("B,Ix", [(3, 0), (3, 512), (13, 0), (13, 512), (37, 0), (37, 512)])
 def test_states_and_inputs_that_are_not_finite(rt, nb, B, Ix):
     """NaN, infinities and states beyond [-1, 1] travel as through the steps: h_0 may hold anything, a NaN in one row
     makes that row NaN and leaves the others alone."""
@@ -103,6 +106,24 @@ def test_states_and_inputs_that_are_not_finite(rt, nb, B, Ix):
         assert torch.isnan(want_h[-1, B - 1]).all() and torch.isfinite(want_h[-1, 0]).all()
         assert torch.equal(torch.isnan(h), torch.isnan(want_h)) and torch.equal(torch.isnan(c), torch.isnan(want_c))
         assert _same(torch.nan_to_num(h), torch.nan_to_num(want_h)) and torch.equal(torch.nan_to_num(c), torch.nan_to_num(want_c))
+
+
+def test_the_order_of_the_sums(rt, nb):
+    """The per-step launch adds a gate's products in eight ranges of K up to 256 workgroups and in four beyond, and the
+    loop and its recovery do the same.  Gates of 2^24, 1 and 1 in the stages 0, 2 and 3 and -2^24 in stage 4: one range of
+    four stages loses both ones to rounding (2^24 + 1 is 2^24 in f32), which leaves 0; ranges of two stages keep them."""
+    H = Ix = 512
+    for B, gate in ((5, 2.0), (32, 2.0), (33, 0.0), (37, 0.0), (64, 0.0)):
+        x = torch.zeros((1, B, Ix), dtype=torch.bfloat16, device="cuda")
+        w = torch.zeros((4 * H, Ix + H), dtype=torch.bfloat16, device="cuda")
+        for stage, a, b in ((0, 4096.0, 4096.0), (2, 1.0, 1.0), (3, 1.0, 1.0), (4, 4096.0, -4096.0)):
+            x[..., stage * 64], w[:, stage * 64] = a, b
+        state = (torch.zeros((B, H), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, H), device="cuda"))
+        case = (x, w, torch.zeros(4 * H, dtype=torch.bfloat16, device="cuda"), *state)
+        c = np.tanh(gate) / (1 + np.exp(-gate))          # all four gates are the same
+        for h_seq, c_out in (_steps(rt, *case), _loop(nb, *case)[:2], _loop(nb, *case, max_polls=0)[:2]):
+            assert float((c_out - c).abs().max()) < 1e-5, (B, c_out[0, 0].item())
+            assert bool((h_seq == 0).all()) == (gate == 0), B
 
 
 def test_a_captured_loop_replays_and_recovers(rt, nb, monkeypatch):
