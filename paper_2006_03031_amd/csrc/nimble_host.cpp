@@ -304,7 +304,7 @@ struct Launch {
 // 64 rows) and every tiled variant and K split that fits the workspace.
 static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int epilogue,
                           uint64_t max_workspace, bool allow_skinny, bool allow_halved = true) {
-  Launch best;
+  Launch best, roomy;  // within the workspace, and with as much of it as anyone could bring
   double skinny_us = -1.0, least_tiled_us = 1e30;
   // weight streaming: up to 64 rows, and beyond that in 16-row blocks of the streaming kernel while
   // the layer is small enough for the blocks' re-reads to come from L2
@@ -317,26 +317,30 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
     if (v > NIMBLE_VAR_T32x128 && rows <= kVariants[v - 1].bm) break;  // tile taller than needed
     for (int sk : kSplits) {
       if (!split_k_ok(v, batch, N, K, sk)) continue;
-      if (sk > 1 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > max_workspace) continue;
       // (three slices only within the built-in scratch, so that the entry point that lives on it keeps taking
       // the calls it took when K was cut by powers of two)
       if (sk == 3 && K >= kLongestFitted) continue;
       if (sk == 3 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > (uint64_t)NIMBLE_NOALLOC_SCRATCH_BYTES) continue;
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, sk);
-      if (us < least_tiled_us) least_tiled_us = us;
       // (a finer cut takes more workspace and more of the memory's time: of the same tile, or of one of up to 128 rows
       // against a smaller tile, it has to win by more than the estimates are good for: 879 x 1024 x 6528 in 128-row
       // tiles with K in four 29.9 us, in 64-row tiles with K in two 23.1; 149 x 3712 x 6272 the same, 26.5 and 21.1)
-      const bool finer = best.split_k > 1 && K < kLongestFitted &&
-                         (best.variant == v || (sk > best.split_k && v <= NIMBLE_VAR_T128x128));
-      const double bar = finer ? 0.95 * best.us : best.us;
-      if (best.variant < 0 || us < bar) {
-        best.variant = v;
-        best.split_k = sk;
-        best.bm = 0;
-        best.halved = false;
-        best.us = us;
-      }
+      auto consider = [&](Launch* l) {
+        const bool finer = l->split_k > 1 && K < kLongestFitted &&
+                           (l->variant == v || (sk > l->split_k && v <= NIMBLE_VAR_T128x128));
+        const double bar = finer ? 0.95 * l->us : l->us;
+        if (l->variant < 0 || us < bar) {
+          l->variant = v;
+          l->split_k = sk;
+          l->bm = 0;
+          l->halved = false;
+          l->us = us;
+        }
+      };
+      consider(&roomy);
+      if (sk > 1 && (uint64_t)sk * (uint64_t)rows * (uint64_t)N * 4u > max_workspace) continue;
+      if (us < least_tiled_us) least_tiled_us = us;
+      consider(&best);
     }
     // the same tile at a reduced height: with the run-time M known, pick the height at which
     // the tile rows fill whole rounds of the chip instead of leaving a mostly empty last round
@@ -346,13 +350,21 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
         wide_stages_ok(K, 1)) {
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, 1, kHalvedRows);
       // (not in place of K in two or three, however the estimates compare: 360 x 9216 x 11072 91.7 us, 82.3 in 128-row
-      // tiles with K in two; 386 x 7424 x 4416 43.4 / 41.4.  In place of K in four: 327 x 11008 x 11584 110.8 / 138.4.  Nor
-      // in place of 64-row tiles whose weights come from HBM, which are priced too high: 234 x 12288 x 2688 28.2 / 25.8;
-      // nor of fewer tile rows of 256 there: 429 x 9984 x 11328 115.5 / 111.4)
+      // tiles with K in two; 386 x 7424 x 4416 43.4 / 41.4.  Nor in place of 64-row tiles whose weights come from HBM, which
+      // are priced too high: 234 x 12288 x 2688 28.2 / 25.8; nor of fewer tile rows of 256 there: 429 x 9984 x 11328 115.5 /
+      // 111.4.  In place of K in four they are faster than that and than any whole tile: 268 x 11008 x 8832 with GELU 92.7 us,
+      // 113.5 in four, 115.2 in 64-row tiles; 414 x 8448 x 12096 126.7, 142.9, 136.3 in 256-row tiles; 584 x 6656 x 11072
+      // 117.0, 143.7, 118.1: the least of 25 such shapes gained 1 % on whole tiles)
       const bool from_hbm = (double)N * (double)K * 2.0 > kCachedWeightBytes;
-      const bool kept = best.split_k == 2 || best.split_k == 3 || (from_hbm && best.variant == NIMBLE_VAR_T64x128) ||
-                        (from_hbm && best.variant == v && best.split_k == 1 && ceil_div(rows, kHalvedRows) > ceil_div(rows, kVariants[v].bm));
-      if (us < best.us && !kept) {
+      auto kept = [&](const Launch& l) {
+        return l.split_k == 2 || l.split_k == 3 || (from_hbm && l.variant == NIMBLE_VAR_T64x128) ||
+               (from_hbm && l.variant == v && l.split_k == 1 && ceil_div(rows, kHalvedRows) > ceil_div(rows, kVariants[v].bm));
+      };
+      // Halves need no workspace, so they are taken or not whatever there is of it, by what they stand in place of where it
+      // is plenty: the plan that is reported runs then in any workspace.  (Where that is a cut of K, they may still
+      // serve callers who lack the workspace for it.)
+      const Launch& instead = kept(roomy) ? best : roomy;
+      if (us < instead.us && !kept(instead)) {
         best.variant = NIMBLE_VAR_T256x256;
         best.split_k = 1;
         best.bm = kHalvedRows;

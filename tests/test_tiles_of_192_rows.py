@@ -1,14 +1,23 @@
 """Tiles of 192 x 256 shared by two workgroups, half the columns each: what the plan says (CPU) and the results
 against float64 (GPU) at the edges of tiles, K stages and the chip."""
+import ctypes
+import os
+import random
+import subprocess
+
 import pytest
 
 torch = pytest.importorskip("torch")
 import paper_2006_03031_amd as nb
+from paper_2006_03031_amd import binding, build
+
+
+def is_halved(p):
+    return (p.variant, p.bm, p.bn, p.split_k, p.grid[1]) == (6, 192, 256, 1, 2)
 
 
 def halved(M, N, K):
-    p = nb.dense_plan(M, N, K)
-    return (p.variant, p.bm, p.bn, p.split_k, p.grid[1]) == (6, 192, 256, 1, 2)
+    return is_halved(nb.dense_plan(M, N, K))
 
 
 def test_the_plan():
@@ -21,6 +30,53 @@ def test_the_plan():
                     (1100, 4096 + 128, 1024)):
         assert not halved(M, N, K), (M, N, K)
     assert nb.dense_plan(1100, 4096, 1024, force_variant=6 | (12 << 16)).grid[1] == 1
+
+
+PLAN_WITHIN = """
+#include "nimble_internal.h"
+extern "C" int plan_within(int64_t M, int64_t N, int64_t K, int epilogue, uint64_t workspace, nimble_plan* p) {
+  nimble::PlanOptions opt;
+  opt.max_workspace = workspace;
+  return nimble::plan_dense(1, M, N, K, epilogue, NIMBLE_VAR_AUTO, opt, p);
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan_within(tmp_path_factory):
+    """The dispatch function as the entry points call it: within the scratch that the caller brought."""
+    d = tmp_path_factory.mktemp("plan")
+    (d / "plan_within.cpp").write_text(PLAN_WITHIN)
+    lib = str(d / "plan_within.so")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-fPIC", "-shared", "-I" + os.path.join(build.ROOT, "include"), "-I" + build.CSRC,
+                    str(d / "plan_within.cpp"), os.path.join(build.CSRC, "nimble_host.cpp"), "-o", lib], check=True)
+    fn = ctypes.CDLL(lib).plan_within
+    fn.argtypes = [ctypes.c_int64] * 3 + [ctypes.c_int, ctypes.c_uint64, ctypes.POINTER(binding._CPlan)]
+
+    def plan(M, N, K, epilogue, workspace):
+        c = binding._CPlan()
+        assert fn(M, N, K, epilogue, workspace, ctypes.byref(c)) == 0
+        return binding._plan(c)
+    return plan
+
+
+def test_halves_run_in_any_workspace(plan_within):
+    """Halves need no workspace: where the plan names them they run with none and with the built-in scratch.  The shapes
+    are those whose best launch without halves would cut K in four, and random ones with weights beyond the caches."""
+    rng = random.Random(3)
+    shapes = [(262, 11008, 11136), (280, 11008, 10432), (392, 8960, 12160), (616, 6656, 10752)]
+    shapes += [(rng.randint(200, 1000), 256 * rng.randint(16, 48), 64 * rng.randint(100, 191)) for _ in range(20000)]
+    n = 0
+    for M, N, K in shapes:
+        for epilogue in (nb.EPI_NONE, nb.EPI_BIAS_GELU_ERF):
+            want = nb.dense_plan(M, N, K, epilogue)
+            if is_halved(want):
+                n += 1
+                for workspace in (0, binding.NOALLOC_SCRATCH_BYTES, 64 << 20):
+                    assert plan_within(M, N, K, epilogue, workspace) == want, (M, N, K, epilogue, workspace)
+    assert n > 1000
+    for M, N, K in shapes[:4]:
+        assert halved(M, N, K)
 
 
 @pytest.mark.gpu
