@@ -643,13 +643,16 @@ static double any_cost_us(int64_t batch, int64_t M, int64_t N, int64_t K, bool b
 // shapes that the ring kernels cannot run takes twice their time.  Checked on 290 products of 30 M to 40 G
 // multiply-adds, 1 .. 96 batches: the choice costs 0.6 % over the better one of each.  any_kernel / transposed, microseconds:
 // 12 x 512 x 64 x 512 6.1 / 13.2, 1 x 1000^3 9.9 / 20.4, 96 x 512 x 64 x 512 20 / 27, 24 x 1151 x 320 x 256 19 / 23;
-// 1 x 4096 x 1024 x 512 15.5 / 13.0, 8 x 1000^3 56 / 48, 1 x 2048 x 2048 x 2040 62 / 51, 4 x 1905 x 2048 x 1408 123 / 62.
+// 1 x 4096 x 1024 x 512 15.5 / 13.0, 8 x 1000^3 56 / 48, 1 x 2048 x 2048 x 2040 62 / 51, 4 x 1905 x 2048 x 1408 123 / 62; in
+// halved tiles 1 x 480 x 8448 x 1344 41 / 33, 1 x 661 x 6400 x 768 26 / 22, 1 x 370 x 10240 x 6400 205 / 178.
 bool nn_transposes(const nimble_plan& p, int64_t batch, int64_t M, int64_t N, int64_t K) {
   double us = 8.0 + 0.3e-6 * (double)(batch * N * K * 2);
   if (p.bn == 64) {
     us += any_cost_us(batch, M, N, K, false) - 2.5;
   } else {
-    const double tiled = tiled_cost_us(p.variant, batch, M, N, K, NIMBLE_EPI_NONE, 1, p.bm);
+    // (tiles that two workgroups share have a price of their own, which is under the variant of half the width)
+    const bool halved = p.variant == NIMBLE_VAR_T256x256 && p.bm == kHalvedRows && p.split_k == 1 && p.grid[1] == 2;
+    const double tiled = tiled_cost_us(halved ? (int)NIMBLE_VAR_T256x128 : p.variant, batch, M, N, K, NIMBLE_EPI_NONE, 1, p.bm);
     us += (ring_shape_ok(N, K) ? tiled : 2.0 * tiled) + 0.12e-6 * (double)(batch * (M * K + N * K + M * N) * 2);
   }
   return us < any_cost_us(batch, M, N, K, true);

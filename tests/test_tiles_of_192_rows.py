@@ -79,6 +79,33 @@ def test_halves_run_in_any_workspace(plan_within):
         assert halved(M, N, K)
 
 
+def test_products_with_b_kn_take_the_halves_by_their_own_price():
+    """A.B with b [K, N] runs on b transposed where the launch found for that, here halves, is estimated to be done
+    sooner than 64 x 64 tiles on b as it is.  Both estimates written out once more, in microseconds."""
+    def halves(M, N, K):
+        tiles, stages = -(-M // 192) * (N // 128), K // 32
+        us = 3.0 + (0.244 + 0.00043 * max(0, tiles - 128)) * stages
+        return us + 8.0 + 0.3e-6 * (N * K * 2) + 0.12e-6 * (M * K + N * K + M * N) * 2
+
+    def any_kernel(M, N, K):
+        tiles, stages = -(-M // 64) * (N // 64), -(-K // 64)
+        four = K >= 512 and tiles <= 256
+        lone = 3.5 + 1.14 * -(-stages // 4) if four else 3.0 + 0.67 * stages
+        per_cu = tiles / 256 if tiles <= 256 else max(2.0, tiles / 256)
+        return max(lone, 3.0 + per_cu * (0.6 + 0.42 * stages))
+
+    rng = random.Random(4)
+    shapes = [(rng.randint(200, 2000), 256 * rng.randint(1, 48), 64 * rng.randint(5, 190)) for _ in range(30000)]
+    seen = {True: 0, False: 0}
+    # (the first five were given to the 64 x 64 tiles by the price of whole tiles)
+    for M, N, K in [(480, 8448, 1344), (661, 6400, 768), (370, 10240, 6400), (375, 10496, 5120), (624, 6656, 832)] + shapes:
+        if is_halved(nb.batch_matmul_plan(1, M, N, K, True)) and M * N * K >= 32e6:
+            p, transposed = nb.batch_matmul_plan(1, M, N, K, False), halves(M, N, K) < any_kernel(M, N, K)
+            assert (p.bn == 256) == is_halved(p) == transposed, (M, N, K, p, halves(M, N, K), any_kernel(M, N, K))
+            seen[transposed] += 1
+    assert seen[True] > 500, seen
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [(1035, 4096, 768), (1152, 4096, 832), (1153, 4096, 896), (1536, 4096, 768), (2115, 2304, 768),
                                    (4225, 1024, 2112), (5569, 768, 768), (12001, 512, 640)])
