@@ -170,7 +170,7 @@ const at::Tensor* plain_vm_tensor(PyObject* o) {
 }
 
 // A result of the interpreter: an integer, a host shape, or the part of the pool, an input or a constant that it names.
-PyObject* vm_result(const nimble_vm_tensor& r, const std::vector<const at::Tensor*>& owners) {
+PyObject* vm_result(const nimble_vm_tensor& r, const std::vector<at::Tensor>& owners) {
   if (r.dtype == NIMBLE_I64) {
     if (r.rank == 0) return PyLong_FromLongLong(r.shape[0]);
     const int64_t n = r.shape[0];
@@ -182,10 +182,10 @@ PyObject* vm_result(const nimble_vm_tensor& r, const std::vector<const at::Tenso
   int64_t bytes = r.dtype == NIMBLE_F32 ? 4 : 2;
   for (int i = 0; i < r.rank; ++i) bytes *= r.shape[i];
   const char* at_ = (const char*)r.data;
-  for (const at::Tensor* owner : owners) {
-    const char* lo = (const char*)owner->data_ptr();
-    if (lo <= at_ && at_ + bytes <= lo + owner->nbytes()) {
-      at::Tensor flat = owner->dim() == 1 ? *owner : owner->view(-1);
+  for (const at::Tensor& owner : owners) {
+    const char* lo = (const char*)owner.data_ptr();
+    if (lo <= at_ && at_ + bytes <= lo + owner.nbytes()) {
+      at::Tensor flat = owner.dim() == 1 ? owner : owner.view(-1);
       if (flat.scalar_type() != at::kByte) flat = flat.view(at::kByte);
       at::Tensor t = flat.narrow(0, at_ - lo, bytes).view(dtype).view(at::IntArrayRef(r.shape, r.rank));
       return THPVariable_Wrap(std::move(t));
@@ -207,8 +207,10 @@ PyObject* vm_run(PyObject*, PyObject* const* args, Py_ssize_t n) {
   const Workspace* ws = workspace_of(*pool);
   if (!ws) Py_RETURN_NONE;
   nimble_vm_tensor in[kMaxInputs], out[kMaxResults];
-  std::vector<const at::Tensor*> owners{pool};
+  // (tensors of our own: the lists are the caller's, and another thread may change them while the lock is released)
+  std::vector<at::Tensor> owners;
   owners.reserve(1 + n_in + PyList_GET_SIZE(args[3]));
+  owners.push_back(*pool);
   for (Py_ssize_t i = 0; i < n_in; ++i) {
     const at::Tensor* t = plain_vm_tensor(PySequence_Fast_GET_ITEM(args[1], i));
     if (!t) Py_RETURN_NONE;
@@ -216,12 +218,12 @@ PyObject* vm_run(PyObject*, PyObject* const* args, Py_ssize_t n) {
     in[i].dtype = t->scalar_type() == at::kFloat ? NIMBLE_F32 : NIMBLE_BF16;
     in[i].rank = (int32_t)t->dim();
     for (int d = 0; d < 4; ++d) in[i].shape[d] = d < t->dim() ? t->size(d) : 0;
-    owners.push_back(t);
+    owners.push_back(*t);
   }
   for (Py_ssize_t i = 0; i < PyList_GET_SIZE(args[3]); ++i) {
     const at::Tensor* t = plain_vm_tensor(PyList_GET_ITEM(args[3], i));
     if (!t) Py_RETURN_NONE;
-    owners.push_back(t);
+    owners.push_back(*t);
   }
   nimble_vm* vm = (nimble_vm*)PyLong_AsVoidPtr(args[0]);
   const long long max_instructions = PyLong_AsLongLong(args[4]);

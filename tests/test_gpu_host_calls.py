@@ -119,3 +119,31 @@ def test_the_interpreter_through_one_native_call(rt, nb, monkeypatch):
     want = exe.run([x], pool)
     assert codes[0] == codes[1]
     assert all(p == t.data_ptr() and s == t.shape and torch.equal(c, t) for (p, s, c), t in zip(got, want)) and len(got) == len(want)
+
+
+def test_the_interpreter_keeps_what_it_runs_on(rt, nb, monkeypatch):
+    """The lists of inputs and constants are the caller's: another thread may empty them while the interpreter runs. Here
+    that happens once the operands have been read, in place of the question for the current stream."""
+    from paper_2006_03031_amd import vm
+    a = vm.Assembler(1)
+    a.ret(a.alloc_adt(0, [0, a.load_const(0)]))
+    want = torch.arange(6, dtype=torch.float32, device="cuda").view(2, 3)
+    inputs, pool = [want.clone()], torch.empty(1 << 16, dtype=torch.uint8, device="cuda")
+    exe = vm.Executable.from_assembler(a, [want + 6])
+    constants, real, dropped = exe._constants, rt._raw_stream, []
+
+    def drop_and_answer(device):
+        inputs.clear(), constants.clear()
+        dropped.append([torch.zeros((2, 3), device="cuda") for _ in range(4)])   # where their memory was, had it been freed
+        return real(device)
+    monkeypatch.setattr(rt, "_raw_stream", drop_and_answer)
+    monkeypatch.setattr(rt, "_bound", False)
+    rt._bind_host_calls(pool.device)
+    try:
+        got = rt._host_calls.vm_run(exe._handle.value, inputs, pool, constants, 0)
+    finally:
+        monkeypatch.undo()
+        rt._bound = False
+        rt._bind_host_calls(pool.device)
+    assert len(dropped) == 1 and not inputs and not constants
+    assert torch.equal(got[0], want) and torch.equal(got[1], want + 6)
