@@ -9,19 +9,33 @@ and the stream; all arithmetic runs in the HIP library.
 """
 from __future__ import annotations
 
-from typing import Optional, Tuple
-
 import ctypes
+import warnings
+from typing import Optional, Tuple
 
 import torch
 
 from . import binding as nb
 
+
+class _StepsOnly:
+    """In place of the native one-call sequences where they cannot be loaded (not built, or built for another torch):
+    leaves every call to the steps, which give the same results, and says so on the first call on a GPU."""
+    dense = attention = fused_attention = vm_run = set_workspace = staticmethod(lambda *a: None)
+
+    def __init__(self, why: ImportError):
+        self.why = why
+
+    def bind(self, *a) -> None:
+        warnings.warn(f"the native host calls do not load ({self.why}): calls go through Python step by step, which takes "
+                      "some microseconds more each; to build them run "
+                      "`python -c 'import __graft_entry__ as g; g.build()'`", RuntimeWarning, stacklevel=2)
+
+
 try:
     from . import _host_calls
 except ImportError as e:
-    raise ImportError("the native host calls are not built; run `python -c 'import __graft_entry__ as g; g.build()'` "
-                      "first") from e
+    _host_calls = _StepsOnly(e)
 
 _TORCH_DTYPE = {nb.BF16: torch.bfloat16, nb.F32: torch.float32}
 

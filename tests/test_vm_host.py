@@ -209,3 +209,34 @@ def test_load_time_verification(words, what):
 def test_library_programs_assemble_and_load():
     for prog, n_const in ((vm.lstm_sequence_program(), 2), (vm.ffn_block_program(), 4), (vm.attention_program(), 0)):
         vm.Executable.from_assembler(prog, [vm.TensorDesc(FAKE, (8, 8), nb.BF16)] * n_const)
+
+
+def test_programs_run_without_the_native_host_calls():
+    """Importing the runtime and running programs of descriptors needs no more than the HIP library; what hinders the
+    native calls (here another torch than they were built for) is told when a GPU call would have used them."""
+    import subprocess
+    import sys
+    import textwrap
+    code = textwrap.dedent("""
+        import importlib.abc, sys, warnings
+        class NoHostCalls(importlib.abc.MetaPathFinder):
+            def find_spec(self, name, path=None, target=None):
+                if name.endswith("._host_calls"):
+                    raise ImportError("undefined symbol: of another torch")
+        sys.meta_path.insert(0, NoHostCalls())
+        import paper_2006_03031_amd as nb
+        from paper_2006_03031_amd import vm, runtime as rt
+        a = vm.Assembler(1)
+        a.ret(a.shape_of(0))
+        x = vm.TensorDesc(0x7F0000000000, (37, 64), nb.BF16)
+        assert vm.Executable.from_assembler(a).run([x], None) == [[37, 64]]
+        with warnings.catch_warnings(record=True) as seen:
+            warnings.simplefilter("always")
+            for _ in range(2):
+                rt._bind_host_calls(rt.torch.device("cuda", 0))
+        assert len(seen) == 1 and "of another torch" in str(seen[0].message), seen
+        assert rt._host_calls.dense(None, None, None, 0, 0) is None
+    """)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
