@@ -151,33 +151,39 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
 
   // this wave's units: of the per-step kernel's ranges (ORDER < 2: all of x or all of h, Ix is whole ranges)
   const int x_stages = Ix >> 6, stages = (Ix + H) >> 6;
-  int st_begin, n_units, k_begin;  // first stage, units <= NU, first k
+  int st_begin, n_st, k_begin;  // first stage, stages (ORDER > 0: pairs of units) <= PW, first k
   if (ORDER == 0) {
     const int per_wave = (stages + 7) / 8;  // <= PW (the launcher picks PW >= per_wave)
     st_begin = wave * per_wave;
     const int st_end = (st_begin + per_wave) < stages ? (st_begin + per_wave) : stages;
-    n_units = st_end > st_begin ? 2 * (st_end - st_begin) : 0;
+    n_st = st_end > st_begin ? st_end - st_begin : 0;
     k_begin = st_begin * 64;
   } else {
     st_begin = (wave >> 1) * NU;  // (the launcher: stages = 4 NU)
-    n_units = NU;
+    n_st = PW;
     k_begin = st_begin * 64 + (wave & 1) * 32;
   }
   const bool of_x = !PRE && st_begin < x_stages;  // (MIX: its first units)
-  int x_units = of_x ? n_units : 0;
-  if (MIX && of_x) x_units = x_stages - st_begin < NU ? x_stages - st_begin : NU;
+  const int x_units = !of_x ? 0 : x_stages - st_begin < NU ? x_stages - st_begin : NU;  // (MIX)
 
   // weights of this workgroup's 16 G gate rows over this wave's units, in the MFMA operand
   // layout: lane (r, gq) holds 8 k of tile row r = gate r & 3 of unit 4 g + (r >> 2)
   uint4 wt[G][NU];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const u16* wrow = a.w + ((long long)(r & 3) * H + wg * U + g * 4 + (r >> 2)) * (Ix + H) + k_begin + gq * 8;
+    const u16* wrow = a.w + ((long long)(r & 3) * H + wg * U + g * 4 + (r >> 2)) * (Ix + H);
 #pragma unroll
-    for (int j = 0; j < NU; ++j) {
-      wt[g][j] = ORDER != 0 || j < n_units ? *(const uint4*)(wrow + j * STEP) : make_uint4(0, 0, 0, 0);
+    for (int s = 0; s < PW; ++s) {
+      if (ORDER != 0 || s < n_st) {
+        const int k = k_begin + 2 * s * STEP + gq * 8;
+        wt[g][2 * s] = *(const uint4*)(wrow + k);
+        wt[g][2 * s + 1] = *(const uint4*)(wrow + k + STEP);
+      } else {
+        wt[g][2 * s] = wt[g][2 * s + 1] = make_uint4(0, 0, 0, 0);
+      }
       // (left to itself the compiler loads the weights anew in every step instead of keeping them)
-      keep_in_registers(wt[g][j]);
+      keep_in_registers(wt[g][2 * s]);
+      keep_in_registers(wt[g][2 * s + 1]);
     }
   }
 
@@ -215,8 +221,10 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
   for (int j = 0; j < NU; ++j) f[j] = make_uint4(0, 0, 0, 0);  // (units that this wave does not have: zeros)
   auto load_rows = [&](const u16* src) {
 #pragma unroll
-    for (int j = 0; j < NU; ++j)
-      if (ORDER == 1 || j < (MIX ? x_units : n_units)) f[j] = *(const uint4*)at(src + j * STEP, from);
+    for (int s = 0; s < PW; ++s) {
+      if (MIX ? 2 * s < x_units : ORDER != 0 || s < n_st) f[2 * s] = *(const uint4*)at(src + 2 * s * STEP, from);
+      if (MIX ? 2 * s + 1 < x_units : ORDER != 0 || s < n_st) f[2 * s + 1] = *(const uint4*)at(src + (2 * s + 1) * STEP, from);
+    }
   };
   if (MIX) {
     const int orow = row0 + (r < rows ? r : rows - 1);
@@ -226,7 +234,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
   } else {
     load_rows(of_x ? a.x : a.h0);
   }
-  const bool waits = MIX ? x_units < NU : !of_x && n_units > 0;  // for h_t
+  const bool waits = MIX ? x_units < NU : !of_x && n_st > 0;  // for h_t
   if (waits && a.max_polls == 0) s_abort[1] = 1;
 
   // The bias, or the inputs' share of the gates, which streams from memory, a fresh line per step: it is fetched
@@ -246,13 +254,15 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
       f32x4 acc[2][2];
 #pragma unroll
       for (int g = 0; g < 2; ++g) acc[g][0] = acc[g][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      auto product = [&](int j, int g) {
+        const int chain = ORDER == 0 ? j & 1 : 0;
+        acc[g][chain] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wt[g0 + g][j]), as_bf16x8(f[j]), acc[g][chain], 0, 0, 0);
+      };
 #pragma unroll
-      for (int j = 0; j < NU; ++j)
+      for (int j = 0; j < NU; j += 2)
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {
-          const int chain = ORDER == 0 ? j & 1 : 0;
-          acc[g][chain] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(wt[g0 + g][j]), as_bf16x8(f[j]), acc[g][chain], 0, 0, 0);
-        }
+        for (int i = 0; i < 4; ++i)
+          if (ORDER == 0) product(j + (i & 1), i >> 1); else product(j + (i >> 1), i & 1);  // (ORDER > 0: one chain per group)
       // accumulator of lane (r, gq), register v: gate v of unit gq of the group, activation row r
 #pragma unroll
       for (int g = 0; g < 2; ++g)
@@ -317,28 +327,31 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
       if (!cells) __builtin_amdgcn_s_sleep(R == 8 || PW > 1 ? 16 : 14);
       else if (R == 8) __builtin_amdgcn_s_sleep(4);
       for (;;) {
-        // R = 8: a unit per load; R = 4: two of them, the lanes of the upper 8 rows hold the second
-        constexpr int UPL = 2 / LPS;
-        unsigned long long v[NU / UPL];
+        unsigned long long v[PW][LPS];  // R = 8: a unit per load; R = 4: two, the lanes of the upper 8 rows hold the second
 #pragma unroll
-        for (int i = 0; i < NU / UPL; ++i) {
-          const unsigned long long* word;
-          if (ORDER == 0)  // (units that this wave does not have: the words of its last stage again)
-            word = at(src + (2 * (i / LPS) < n_units ? i / LPS : n_units / 2 - 1) * 16 * rs, ask) + (i % LPS) * 8 * rs;
-          else if (MIX)  // (units of x: the words of its first unit of h)
-            word = at(src + (long long)((h_begin >> 2) + (i < x_units ? x_units : i) * 16) * rs, ask);
-          else
-            word = at(src + i * 16 * rs, ask);
-          v[i] = __hip_atomic_load(word, __ATOMIC_RELAXED, SCOPE);
-        }
+        for (int s = 0; s < PW; ++s)
+#pragma unroll
+          for (int l = 0; l < LPS; ++l) {
+            const int j = 2 * s + l;
+            if (ORDER == 0)  // (a stage that this wave does not have: the words of its last one again)
+              v[s][l] = __hip_atomic_load(at(src + (s < n_st ? s : n_st - 1) * 16 * rs, ask) + l * 8 * rs, __ATOMIC_RELAXED, SCOPE);
+            else if (!MIX)
+              v[s][l] = __hip_atomic_load(at(src + j * 16 * rs, ask), __ATOMIC_RELAXED, SCOPE);
+            else  // (units of x: the words of its first unit of h)
+              v[s][l] = __hip_atomic_load(at(src + (long long)((h_begin >> 2) + (j < x_units ? x_units : j) * 16) * rs, ask),
+                                          __ATOMIC_RELAXED, SCOPE);
+          }
         uint32_t bad = 0;
 #pragma unroll
-        for (int i = 0; i < NU / UPL; ++i) {
-          const uint32_t lo = (uint32_t)v[i] ^ want;
-          bad |= lo;
-          f[i * UPL].x = MIX && i < x_units ? f[i * UPL].x : lo;
-          f[i * UPL].y = MIX && i < x_units ? f[i * UPL].y : (uint32_t)(v[i] >> 32);
-        }
+        for (int s = 0; s < PW; ++s)
+#pragma unroll
+          for (int l = 0; l < LPS; ++l) {
+            const int j = 2 * s + l;
+            const uint32_t lo = (uint32_t)v[s][l] ^ want;
+            f[j].x = MIX && j < x_units ? f[j].x : lo;
+            f[j].y = MIX && j < x_units ? f[j].y : (uint32_t)(v[s][l] >> 32);
+            bad |= lo;
+          }
         nan = bad & kHandOverNan;
         if (__all((bad & kHandOverPhase) == 0u)) break;
         // (wave-uniform: every lane counts alike and reads the same give-up word)
@@ -351,23 +364,24 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int row
       }
       if (__any(nan != 0u)) {
 #pragma unroll
-        for (int j = 0; j < NU; j += 2 / LPS)
-          if (f[j].x & (MIX && j < x_units ? 0u : kHandOverNan)) {
-            f[j].x = lstm_seq_nans(f[j].x & ~kHandOverNan);
-            f[j].y = lstm_seq_nans(f[j].y);
-          }
+        for (int s = 0; s < PW; ++s)
+#pragma unroll
+          for (int j = 2 * s; j < 2 * s + LPS; ++j)
+            if (f[j].x & (MIX && j < x_units ? 0u : kHandOverNan)) {
+              f[j].x = lstm_seq_nans(f[j].x & ~kHandOverNan);
+              f[j].y = lstm_seq_nans(f[j].y);
+            }
       }
       // to the operand layout: the lanes of the first R rows collect the other pieces of their 8 k
 #pragma unroll
-      for (int j = 0; j < NU; j += 2 / LPS) {
-        if (R == 4) f[j + 1] = make_uint4(lane_up<8>(f[j].x), lane_up<8>(f[j].y), lane_up<12>(f[j].x), lane_up<12>(f[j].y));
-        f[j].z = MIX && j < x_units ? f[j].z : lane_up<R == 8 ? 8 : 4>(f[j].x);
-        f[j].w = MIX && j < x_units ? f[j].w : lane_up<R == 8 ? 8 : 4>(f[j].y);
-      }
-      if (ORDER == 0) {
+      for (int s = 0; s < PW; ++s) {
+        if (R == 4) f[2 * s + 1] = make_uint4(lane_up<8>(f[2 * s].x), lane_up<8>(f[2 * s].y), lane_up<12>(f[2 * s].x), lane_up<12>(f[2 * s].y));
 #pragma unroll
-        for (int j = 0; j < NU; ++j)
-          if (j >= n_units) f[j] = make_uint4(0, 0, 0, 0);
+        for (int j = 2 * s; j < 2 * s + LPS; ++j) {
+          f[j].z = MIX && j < x_units ? f[j].z : lane_up<R == 8 ? 8 : 4>(f[j].x);
+          f[j].w = MIX && j < x_units ? f[j].w : lane_up<R == 8 ? 8 : 4>(f[j].y);
+        }
+        if (ORDER == 0 && s > 0 && n_st <= s) f[2 * s] = make_uint4(0, 0, 0, 0), f[2 * s + 1] = make_uint4(0, 0, 0, 0);
       }
     }
   }
