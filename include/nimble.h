@@ -328,17 +328,20 @@ int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up);
 /* ---- the token loop of a batch, waiting for nothing -------------------------------------
  * The same loop for more rows (groups of 8, each on its own workgroups) and for either form of the inputs'
  * share: Ix = 0 with pre [T,B,4H] f32 and w = w_h [4H,H] (x and bias are not read), or Ix > 0 with
- * x [T,B,Ix] bf16, w [4H,Ix+H] bf16 and bias [4H] bf16 (pre is not read).  Three launches are enqueued (fill,
- * loop, recovery) and nothing is waited for or read back, so the call can be captured: where the loop gives up,
- * the recovery launch runs the sequence again with workgroups that wait for nobody (slowly), else it ends at
- * once.  h_seq and c_out are right either way and bit-identical to T calls of nimble_lstm_gates_dyn
+ * x [T,B,Ix] bf16, w [4H,Ix+H] bf16 and bias [4H] bf16 (pre is not read).  Launches are enqueued (a fill,
+ * the loop, one launch per 64 rows, per 32 above H = 512, a recovery) and nothing is waited for or read back, so
+ * the call can be captured: where the loop gives up, the recovery launch runs the sequence again with workgroups
+ * that wait for nobody (slowly, some 50 us per step), else it ends at once.  h_seq and c_out are right either way and bit-identical to T calls of nimble_lstm_gates_dyn
  * (nimble_lstm_gates_pre_dyn with pre); c_out may alias c0.
  * Supported: H = 64..1024 and Ix >= 0 in multiples of 64 with Ix + H <= 1024, Ix a multiple of 128 where Ix + H > 512;
  * B <= 256 at H = 512, 512 at 256, 128 at 1024; with Ix + H other than 512 or 1024 fewer, 32 at H = 512: as many as
  * the per-step launch serves with up to 256 workgroups, whose sums run over eight ranges of Ix + H and beyond over
  * four.  Workspace of
  * nimble_lstm_loop_workspace_bytes, its use, max_polls and the errors as for nimble_lstm_seq_pre_dyn;
- * nimble_lstm_seq_status tells whether the loop gave up. */
+ * nimble_lstm_seq_status tells whether the loop gave up.
+ * At the same time: two loops, of this or of the call above, always find their places on the GPU beside each other.  Three or
+ * more (other streams, other processes) can each hold places that the others lack; then some give up after max_polls
+ * polls.  Programs that run so many at once call nimble_lstm_gates_dyn per step instead. */
 int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H);
 size_t nimble_lstm_loop_workspace_bytes(int64_t B, int64_t Ix, int64_t H);
 int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const void* bias, const void* h0,

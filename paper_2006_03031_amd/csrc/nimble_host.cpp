@@ -781,11 +781,9 @@ size_t nimble_lstm_seq_workspace_bytes(int64_t B, int64_t H) {
 }
 
 // Weights in registers: at most two 64-wide K stages per wave, each wholly of x or of h.  Groups of 8 rows, each on the H / 16
-// workgroups of one XCD (two above H = 512).  The groups of an XCD are dispatched one after the other and none waits for a
-// later one, so there may be more of them than fit at once: one workgroup per compute unit at a time,
-// four rounds of them (microseconds per step, loop / captured launches: H = Ix = 512 at 64, 128, 256 rows
-// 1.48 / 3.83, 2.39 / 5.28, 4.38 / 8.63; H = 1024, pre form, at 32, 128 rows 2.11 / 4.52, 7.39 / 11.49; 256 x 256 at 512 rows
-// 3.63 / 6.78).
+// workgroups of one XCD (two above H = 512), one workgroup per compute unit at a time and four rounds of them
+// (microseconds for 64 steps, loop / captured launches: H = Ix = 512 at 64, 128, 256 rows 119 / 241, 196 / 338, 369 / 556;
+// H = 1024 with the inputs' product ahead at 40, 128 rows 262 / 355, 533 / 701).
 int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H) {
   if (B < 1 || B > 65536 || H < 64 || H > 1024 || H % 64 != 0 || Ix < 0 || Ix > 1024 || Ix % 64 != 0) return 0;
   const int64_t stages = (Ix + H) / 64, per_wave = ceil_div(stages, 8);

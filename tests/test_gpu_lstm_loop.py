@@ -175,3 +175,29 @@ def test_loops_on_two_streams_at_once(rt, nb):
         torch.cuda.synchronize()
         for (h, c), (wh, wc) in zip(got, want):
             assert _same(h, wh) and torch.equal(c, wc), rep
+
+
+def test_two_loops_of_many_rows_always_find_their_places(rt, nb):
+    """Loops of four row groups per XCD on two streams, replayed back to back: neither ever waits for places that the other
+    holds, so none gives up (with nothing else on the GPU), and all are right."""
+    H, T, B, reps = 512, 16, 256, 30
+    rng = np.random.default_rng(12)
+    from gpu_util import to_dev
+    w, b = to_dev(wl.normal_bf16(rng, (4 * H, 2 * H), std=0.05)), to_dev(wl.normal_bf16(rng, (4 * H,)))
+    zeros = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, H), device="cuda")
+    seqs = [rt.LstmSequenceGraph(w, b, B, T, H, H) for _ in range(2)]
+    xs = [to_dev(wl.uniform_bf16(rng, (T, B, H))) for _ in range(2)]
+    want = [_steps(rt, x, w, b, *zeros) for x in xs]
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    gave_up = [torch.zeros(1, dtype=torch.int32, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    print("two loops of 256 rows", flush=True)
+    for _ in range(reps):
+        for s, seq, x, g in zip(streams, seqs, xs, gave_up):
+            with torch.cuda.stream(s):
+                seq.run(x)
+                g += (seq.workspace[:4].view(torch.int32) != 0).int()
+    torch.cuda.synchronize()
+    assert [int(g) for g in gave_up] == [0, 0]
+    for seq, (wh, wc) in zip(seqs, want):
+        assert _same(seq.hs[1:], wh) and torch.equal(seq.c, wc)
