@@ -281,11 +281,13 @@ def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0
 
     one_launch=None: shapes for which nimble_lstm_seq_preferred says so run as one launch
     (nimble_lstm_seq_pre_dyn), other shapes that nimble_lstm_loop_supported accepts through nimble_lstm_loop_dyn, whose
-    own recovery launch stands behind it, so that nothing is waited for and the third value is False as for
-    steps; True: every shape nimble_lstm_seq_supported accepts runs as one launch (others raise);
-    False: none.  After a one-launch run the call waits for the stream and reads the loop's give-up word;
+    own recovery launch stands behind it, so that nothing is waited for and the third value is False (it is
+    not known then) as for steps; True: every shape nimble_lstm_seq_supported accepts runs as one launch (others
+    raise); False: none.  After a one-launch run the call waits for the stream and reads the loop's give-up word;
     if the loop gave up, or neither was taken, the steps run one by one through
-    nimble_lstm_gates_pre_dyn.  All three give the same bits."""
+    nimble_lstm_gates_pre_dyn.  All three give the same bits.
+    workspace: of the one-launch run; the others need none or bring their own.
+    Two loops find their places on the GPU beside each other; programs that run more at once ask for steps (False)."""
     (T, B, H), _ = nb.lstm_seq_shape(tuple(pre.shape), tuple(h0.shape), tuple(c0.shape), tuple(w_h.shape))
     dev = h0.device
     h_seq = _alloc((T, B, H), nb.BF16, dev)
@@ -341,13 +343,19 @@ class LstmSequenceGraph:
     nimble_lstm_loop_supported says so the loop is one launch (with a recovery launch behind it that ends at once
     unless the loop's bounded waits ran out), else `steps` launches of the fused LSTM cell, with the same bits.  The graph
     holds kernel launches only (state is cleared by a fill kernel outside it).  The dynamic extent
-    B is fixed per graph; a server keeps one graph per batch size it has seen."""
+    B is fixed per graph; a server keeps one graph per batch size it has seen.
+
+    Two such loops find their places on the GPU beside each other.  Of three or more that replay at the same time some
+    can run out of their waits, which costs milliseconds: four of 64 rows at H = 512 took 0.4 ms for 64 steps, and 17 in
+    the one round of 17 where that happened; as launches per step (one_launch=False) 0.5."""
 
     def __init__(self, w: torch.Tensor, bias: torch.Tensor, B: int, steps: int, Ix: int, H: int,
-                 project_inputs: bool = False):
+                 project_inputs: bool = False, one_launch: Optional[bool] = None):
         """project_inputs: compute the inputs' share of the gates for all tokens in one dense
         call (M = steps * B) ahead of the loop, so each step streams only the recurrent half
-        of the weight."""
+        of the weight.
+        one_launch: None: the loop in one launch where it is supported; True: the same, other shapes raise;
+        False: a launch per step, for programs that replay three or more of these graphs at once."""
         dev = w.device
         (self.B, self.H), _ = nb.lstm_shape((B, Ix), (B, H), (B, H), tuple(w.shape))
         self.steps, self.Ix = steps, Ix
@@ -361,7 +369,10 @@ class LstmSequenceGraph:
         self.c = torch.zeros((B, H), dtype=torch.float32, device=dev)
         loop_ix = 0 if project_inputs else Ix
         self.workspace = None
-        if (project_inputs or Ix > 0) and nb.lstm_loop_supported(B, loop_ix, H):
+        supported = (project_inputs or Ix > 0) and nb.lstm_loop_supported(B, loop_ix, H)
+        if one_launch and not supported:
+            raise nb.NimbleError(-3, f"the one-launch token loop does not run B={B}, Ix={loop_ix}, H={H}")
+        if supported and one_launch is not False:
             self.workspace = torch.empty(nb.lstm_loop_workspace_bytes(B, loop_ix, H), dtype=torch.uint8, device=dev)
         # one eager pass so that nothing is lazily initialised during capture
         self._enqueue()

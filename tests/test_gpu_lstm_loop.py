@@ -143,6 +143,37 @@ def test_a_captured_loop_replays_and_recovers(rt, nb, monkeypatch):
             assert _same(h, want_h) and torch.equal(c, want_c), (polls, rep)
 
 
+@pytest.mark.parametrize("B,Ix,H,project,one_launch", [
+    (17, 64, 576, True, None), (17, 64, 576, False, None), (3, 72, 64, False, None),   # shapes that the loop does not run
+    (21, 512, 512, False, False), (3, 64, 512, True, False)])                          # a launch per step asked for
+def test_captured_launches_per_step(rt, nb, B, Ix, H, project, one_launch):
+    assert nb.lstm_loop_supported(B, 0 if project else Ix, H) == (one_launch is False)
+    T = 5
+    rng = np.random.default_rng([13, B, Ix, H])
+    from gpu_util import to_dev
+    w, b = to_dev(wl.normal_bf16(rng, (4 * H, Ix + H), std=0.05)), to_dev(wl.normal_bf16(rng, (4 * H,)))
+    zeros = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, H), device="cuda")
+    seq = rt.LstmSequenceGraph(w, b, B, T, Ix, H, project_inputs=project, one_launch=one_launch)
+    assert seq.workspace is None
+    for rep in range(3):
+        x = to_dev(wl.uniform_bf16(rng, (T, B, Ix)))
+        if project:
+            w_x, w_h = rt.split_lstm_weight(w, Ix)
+            pre = rt.dense(x.view(T * B, Ix), w_x, b, nb.EPI_BIAS, nb.F32).view(T, B, 4 * H)
+            want_h, want_c = _steps(rt, pre, w_h, b, *zeros)
+        else:
+            want_h, want_c = _steps(rt, x, w, b, *zeros)
+        h, c = seq.run(x)
+        assert _same(h, want_h) and torch.equal(c, want_c), rep
+    if one_launch is None:
+        with pytest.raises(nb.NimbleError) as e:
+            rt.LstmSequenceGraph(w, b, B, T, Ix, H, project_inputs=project, one_launch=True)
+        assert e.value.code == -3
+    else:
+        h1, c1 = rt.LstmSequenceGraph(w, b, B, T, Ix, H, project_inputs=project, one_launch=True).run(x)
+        assert _same(h1, h) and torch.equal(c1, c)
+
+
 @pytest.mark.parametrize("B,H", [(2, 1024), (20, 512), (5, 320), (300, 512)])
 def test_sequences_beyond_the_preferred_shapes(rt, nb, B, H):
     """lstm_sequence_pre by default: the loop where it runs (300 rows: the steps), the bits of the steps either way."""
