@@ -144,7 +144,8 @@ def test_unsupported_shapes_run_step_by_step_or_raise(rt, nb):
 
 def test_whole_sequence_with_projected_inputs_equals_the_captured_graph(rt, nb):
     """config 2's cell (2048 x 1024): the inputs' product for all tokens in one dense call, then the loop in one
-    launch; the same bits as the captured graph of per-step launches, which test_gpu_parity holds to the oracle."""
+    launch; the same bits as the steps one by one, which test_gpu_parity holds to the oracle, as the loop captured in a
+    graph and as a captured graph of per-step launches."""
     from gpu_util import to_dev
     lw = wl.config2_weights()
     dw, db = to_dev(lw.w), to_dev(lw.b)
@@ -157,15 +158,23 @@ def test_whole_sequence_with_projected_inputs_equals_the_captured_graph(rt, nb):
         print(f"sequence B={B}", flush=True)
         h_seq, c_T, one = rt.lstm_sequence(xs, w_x, w_h, db, h0, c0)
         assert one == nb.lstm_seq_preferred(B, H) and one
-        graph = rt.LstmSequenceGraph(dw, db, B, T, Ix, H, project_inputs=True)
-        hs, c = graph.run(xs)
-        assert torch.equal(hs, h_seq) and torch.equal(c, c_T)
+        pre = rt.dense(xs.view(T * B, Ix), w_x, db, nb.EPI_BIAS, nb.F32).view(T, B, 4 * H)
+        h, c = h0, c0
+        for t in range(T):
+            h, c = rt.lstm_step_pre(pre[t], h, w_h, c)
+            assert torch.equal(h, h_seq[t]), (B, t)
+        assert torch.equal(c, c_T)
+        for one_launch in (None, False):
+            graph = rt.LstmSequenceGraph(dw, db, B, T, Ix, H, project_inputs=True, one_launch=one_launch)
+            assert (graph.workspace is None) == (one_launch is False)
+            hs, c = graph.run(xs)
+            assert torch.equal(hs, h_seq) and torch.equal(c, c_T)
 
 
 def test_step_tags_wrap_after_65535_steps(rt, nb):
-    """The hand-over words carry a 16-bit step tag with period 65535: a sequence longer than that must still give
-    the bits of the step-by-step path (checked on the last steps and the final cell state) and match the oracle
-    on its last step."""
+    """A sequence of more steps than 16 bits can number (the hand-over words tell the step by one bit, which comes
+    round every fourth) must still give the bits of the step-by-step path (checked on the last steps and the final cell
+    state) and match the oracle on its last step."""
     from gpu_util import bits_from_dev, f32_to_dev, from_dev, to_dev
     T, B, H = 65535 + 700, 1, 64
     rng = np.random.default_rng([2, 99])

@@ -110,9 +110,10 @@ def test_products_with_b_kn_take_the_halves_by_their_own_price():
 @pytest.mark.parametrize("M,N,K", [(1035, 4096, 768), (1152, 4096, 832), (1153, 4096, 896), (1536, 4096, 768), (2115, 2304, 768),
                                    (4225, 1024, 2112), (5569, 768, 768), (12001, 512, 640)])
 @pytest.mark.parametrize("out", ["bf16", "f32"])
-def test_results(M, N, K, out):
+@pytest.mark.parametrize("epilogue", [nb.EPI_NONE, nb.EPI_BIAS, nb.EPI_BIAS_GELU_ERF])
+def test_results(M, N, K, out, epilogue):
     from paper_2006_03031_amd import runtime as rt
-    assert halved(M, N, K)
+    assert is_halved(nb.dense_plan(M, N, K, epilogue))
     gen = torch.Generator(device="cuda")
     gen.manual_seed(M * N + K)
     x = torch.empty((M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
@@ -120,10 +121,33 @@ def test_results(M, N, K, out):
     b = torch.empty((N,), device="cuda").normal_(0, 1, generator=gen).to(torch.bfloat16)
     dt = torch.float32 if out == "f32" else torch.bfloat16
     buf = torch.full((M * N + 256,), 768.0, dtype=dt, device="cuda")
-    y = rt.dense(x, w, b, nb.EPI_BIAS, nb.F32 if out == "f32" else nb.BF16, out=buf[:M * N].view(M, N))
-    ref = torch.matmul(x.double(), w.double().t().contiguous()) + b.double()
+    y = rt.dense(x, w, None if epilogue == nb.EPI_NONE else b, epilogue, nb.F32 if out == "f32" else nb.BF16,
+                 out=buf[:M * N].view(M, N))
+    bias = b.double() * (epilogue != nb.EPI_NONE)
+    ref = torch.matmul(x.double(), w.double().t().contiguous()) + bias
     # f32 sums of K products: K eps of the sum of magnitudes at the very most; bf16: half a unit in the last place more
-    mag = torch.matmul(x.double().abs(), w.double().abs().t().contiguous()) + b.double().abs()
-    bound = mag * (K + 1) * 2.0 ** -24 + (ref.abs() * 2.0 ** -8 if out == "bf16" else 0)
+    bound = (torch.matmul(x.double().abs(), w.double().abs().t().contiguous()) + bias.abs()) * (K + 1) * 2.0 ** -24
+    if epilogue == nb.EPI_BIAS_GELU_ERF:
+        # its slope is at most 1.13, its fit 2.5e-5 off, its exponential and reciprocal a few units in the last place
+        ref = torch.nn.functional.gelu(ref)
+        bound = 1.13 * bound + 2.5e-5 + ref.abs() * 2.0 ** -20
+    bound += ref.abs() * 2.0 ** -8 if out == "bf16" else 0
     assert bool(((y.double() - ref).abs() <= bound).all())
     assert bool((buf[M * N:] == 768.0).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("trans_b", [True, False])
+@pytest.mark.parametrize("M,N,K", [(1035, 4096, 768), (1153, 4096, 896), (4225, 1024, 2112)])
+def test_single_products(M, N, K, trans_b):
+    """A product of one batch, scaled, with b [N, K] or transposed into the workspace."""
+    from paper_2006_03031_amd import runtime as rt
+    assert is_halved(nb.batch_matmul_plan(1, M, N, K, trans_b, nb.F32))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    a = torch.empty((1, M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    b = torch.empty((1, N, K), device="cuda").normal_(0, 0.05, generator=gen).to(torch.bfloat16)
+    y = rt.batch_matmul(a, b if trans_b else b.transpose(1, 2).contiguous(), trans_b, 0.375, nb.F32)
+    ref = torch.matmul(a[0].double(), b[0].double().t().contiguous()) * 0.375
+    mag = torch.matmul(a[0].double().abs(), b[0].double().abs().t().contiguous()) * 0.375
+    assert bool(((y[0].double() - ref).abs() <= mag * (K + 1) * 2.0 ** -24).all())
