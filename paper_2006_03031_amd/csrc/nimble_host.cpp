@@ -351,13 +351,15 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
       const double us = tiled_cost_us(v, batch, rows, N, K, epilogue, 1, kHalvedRows);
       // (not in place of K in two or three, however the estimates compare: 360 x 9216 x 11072 91.7 us, 82.3 in 128-row
       // tiles with K in two; 386 x 7424 x 4416 43.4 / 41.4.  Nor in place of 64-row tiles whose weights come from HBM, which
-      // are priced too high: 234 x 12288 x 2688 28.2 / 25.8; nor of fewer tile rows of 256 there: 429 x 9984 x 11328 115.5 /
-      // 111.4.  In place of K in four they are faster than that and than any whole tile: 268 x 11008 x 8832 with GELU 92.7 us,
+      // are priced too high: 234 x 12288 x 2688 28.2 / 25.8; nor of one round of 128-row tiles there: 378 x 10240 x 4288 51.6 /
+      // 46.8, 336 x 9984 x 3456 with GELU 43.6 / 37.1 (8 to 17 % on 50 such shapes; of two rounds they are done in three
+      // quarters of the time); nor of fewer tile rows of 256 there: 429 x 9984 x 11328 115.5 / 111.4.  In place of K in four they are faster than that and than any whole tile: 268 x 11008 x 8832 with GELU 92.7 us,
       // 113.5 in four, 115.2 in 64-row tiles; 414 x 8448 x 12096 126.7, 142.9, 136.3 in 256-row tiles; 584 x 6656 x 11072
       // 117.0, 143.7, 118.1: the least of 25 such shapes gained 1 % on whole tiles)
       const bool from_hbm = (double)N * (double)K * 2.0 > kCachedWeightBytes;
       auto kept = [&](const Launch& l) {
         return l.split_k == 2 || l.split_k == 3 || (from_hbm && l.variant == NIMBLE_VAR_T64x128) ||
+               (from_hbm && l.variant == NIMBLE_VAR_T128x128 && l.split_k == 1 && ceil_div(rows, 128) * ceil_div(N, 128) <= kCUs) ||
                (from_hbm && l.variant == v && l.split_k == 1 && ceil_div(rows, kHalvedRows) > ceil_div(rows, kVariants[v].bm));
       };
       // Halves need no workspace, so they are taken or not whatever there is of it, by what they stand in place of where it
