@@ -329,7 +329,7 @@ int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up);
  * The same loop for more rows (groups of 8, each on its own workgroups) and for either form of the inputs'
  * share: Ix = 0 with pre [T,B,4H] f32 and w = w_h [4H,H] (x and bias are not read), or Ix > 0 with
  * x [T,B,Ix] bf16, w [4H,Ix+H] bf16 and bias [4H] bf16 (pre is not read).  Launches are enqueued (a fill,
- * the loop, one launch per 64 rows, per 32 above H = 512, a recovery) and nothing is waited for or read back, so
+ * the loop, one launch per 64 rows at H = 512, 128 at 256, 32 at 1024, a recovery) and nothing is waited for or read back, so
  * the call can be captured: where the loop gives up, the recovery launch runs the sequence again with workgroups
  * that wait for nobody (slowly, some 50 us per step), else it ends at once.  h_seq and c_out are right either way and bit-identical to T calls of nimble_lstm_gates_dyn
  * (nimble_lstm_gates_pre_dyn with pre); c_out may alias c0.
@@ -343,6 +343,9 @@ int nimble_lstm_seq_status(const void* workspace, void* stream, int* gave_up);
  * more (other streams, other processes) can each hold places that the others lack; then some give up after max_polls
  * polls.  Programs that run so many at once call nimble_lstm_gates_dyn per step instead. */
 int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H);
+/* 1 when, besides, T steps are enough to be done sooner than T captured launches of nimble_lstm_gates_dyn: 7, or where the
+ * loop takes several launches 8 and two more for each of them. */
+int nimble_lstm_loop_preferred(int64_t T, int64_t B, int64_t Ix, int64_t H);
 size_t nimble_lstm_loop_workspace_bytes(int64_t B, int64_t Ix, int64_t H);
 int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const void* bias, const void* h0,
                          const void* c0, void* h_seq, void* c_out, int64_t T, int64_t B, int64_t Ix, int64_t H,

@@ -120,6 +120,7 @@ def load():
                                             ctypes.c_uint32, vp]
     lib.nimble_lstm_seq_status.argtypes = [vp, vp, ctypes.POINTER(ctypes.c_int)]
     lib.nimble_lstm_loop_supported.argtypes = [i64, i64, i64]
+    lib.nimble_lstm_loop_preferred.argtypes = [i64, i64, i64, i64]
     lib.nimble_lstm_loop_workspace_bytes.argtypes = [i64, i64, i64]
     lib.nimble_lstm_loop_workspace_bytes.restype = ctypes.c_size_t
     lib.nimble_lstm_loop_dyn.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, vp, ctypes.c_size_t,
@@ -256,6 +257,10 @@ def nimble_lstm_seq_status(workspace: int, stream: int) -> bool:
 
 def lstm_loop_supported(B: int, Ix: int, H: int) -> bool:
     return bool(load().nimble_lstm_loop_supported(B, Ix, H))
+
+
+def lstm_loop_preferred(T: int, B: int, Ix: int, H: int) -> bool:
+    return bool(load().nimble_lstm_loop_preferred(T, B, Ix, H))
 
 
 def lstm_loop_workspace_bytes(B: int, Ix: int, H: int) -> int:

@@ -17,9 +17,9 @@ namespace nimble {
 //   with each other; per group H / 16 workgroups of 8 waves.  A workgroup owns U = 16 hidden units = 64 gate rows (G
 //   = 4 groups of the i, f, g, o rows of 4 units) and keeps those rows of the weight in registers for the whole
 //   sequence (wave w: the 64-wide K stages w * per_wave ...: 8 registers per group and stage; at most 128 in all, so that two
-//   workgroups fit a compute unit).  A launch has one row group per XCD (or pair of XCDs), more rows take several launches one
-//   after the other: a loop then has at most half of the chip's places, and two loops on two streams never wait for
-//   each other's.  (With all groups in one launch, two to an XCD at a time, 64 steps of 128 / 256 rows, H = Ix = 512, took 165 /
+//   workgroups fit a compute unit).  A launch has as many row groups as give a compute unit one workgroup at most, more rows
+//   take several launches one after the other: a loop then has at most half of the chip's places, and two loops on two
+//   streams never wait for each other's.  (With all groups in one launch, two to an XCD at a time, 64 steps of 128 / 256 rows, H = Ix = 512, took 165 /
 //   302 us instead of 196 / 369; but two such loops could each hold places that the other's next group lacked, and 4 in
 //   70 gave up.  Captured launches per step 338 / 556.)  Per step a
 //   wave multiplies its stages of x_t, loaded a step ahead, or its K range of h_{t-1}, and leaves its partial sums
@@ -116,7 +116,7 @@ __device__ __forceinline__ uint32_t lstm_seq_nans(uint32_t v) {
 
 // PRE: the inputs' share comes precomputed, else from x; PW: K stages of 64 per wave, ceil((Ix + H) / 64 / 8); G: groups
 // of 16 gate rows (4 units) per workgroup; R: rows per group of workgroups, 4 or 8.  rs_few: words per four units in the
-// hand-over buffers for R = 4 (at least the group's rows).  group0: first of this launch's row groups, one per XCD (or pair).
+// hand-over buffers for R = 4 (at least the group's rows).  group0: first of this launch's row groups.
 // A wave's share of K is 2 PW units of 32 k.  ORDER 0, eight ranges: wave w has the units of range w one after the other,
 // in two chains, as the per-step launch on eight waves.  ORDER 1, four ranges of 2 PW whole stages: that launch has four
 // waves, each with the first halves of its stages in one chain and the second halves in the other; here waves 2 w and
@@ -143,9 +143,9 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   const int H = a.H, Ix = PRE ? 0 : a.Ix, B = a.B, T = a.T;
   const int n_wg = H / U, span = n_wg > 32 ? 2 : 1, per_xcd = n_wg / span;
   const int xcd = ((int)blockIdx.x + xcd0) & 7, nth = (int)blockIdx.x >> 3;
-  const int group = group0 + xcd / span;
+  const int group = group0 + nth / per_xcd * (8 / span) + xcd / span;
   if (group >= row_groups) return;
-  const int wg = (xcd & (span - 1)) * per_xcd + nth;
+  const int wg = (xcd & (span - 1)) * per_xcd + nth % per_xcd;
   const int row0 = group * R;
   const int rows = B - row0 < R ? B - row0 : R;  // of this group
   const int tid = threadIdx.x;

@@ -785,7 +785,7 @@ size_t nimble_lstm_seq_workspace_bytes(int64_t B, int64_t H) {
 // Weights in registers: at most two 64-wide K stages per wave, each wholly of x or of h.  Groups of 8 rows, each on the H / 16
 // workgroups of one XCD (two above H = 512), one workgroup per compute unit at a time and four rounds of them
 // (microseconds for 64 steps, loop / captured launches: H = Ix = 512 at 64, 128, 256 rows 119 / 241, 196 / 338, 369 / 556;
-// H = 1024 with the inputs' product ahead at 40, 128 rows 262 / 355, 533 / 701).
+// H = 1024 with the inputs' product ahead at 40, 128 rows 262 / 355, 533 / 701; 32 steps of 512 rows at 256 175 / 218).
 int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H) {
   if (B < 1 || B > 65536 || H < 64 || H > 1024 || H % 64 != 0 || Ix < 0 || Ix > 1024 || Ix % 64 != 0) return 0;
   const int64_t stages = (Ix + H) / 64, per_wave = ceil_div(stages, 8);
@@ -795,6 +795,17 @@ int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H) {
   if (nimble_lstm_plan(B, Ix, H, &p) != NIMBLE_OK || (p.split_k == 4 && stages != 8 && stages != 16)) return 0;
   const int64_t n_wg = H / 16, span = n_wg > 32 ? 2 : 1;
   return ceil_div(ceil_div(B, 8) * span, 8) * (n_wg / span) <= 4 * (kCUs / 8);
+}
+
+// What the loop costs before its first step, some 15 us and 8 for each further launch, has to be earned.  Microseconds for 4, 6,
+// 8, 12, 16 steps, loop / captured launches: H = Ix = 512, 1 row 22.7 / 18.2, 24.8 / 23.9, 27.4 / 29.3, 30.8 / 40.4, -; 64 rows
+// 25.0 / 21.0, 27.1 / 28.4, 29.8 / 35.8, 34.5 / 50.9, -; two launches: 65 rows -, 40.8 / 31.9, 45.8 / 40.4, 55.2 / 57.9, 65.9 / 75.5,
+// H = 1024 33 rows -, 51.9 / 43.5, 58.1 / 54.0, 72.7 / 73.1, 89.7 / 96.5; four: 256 rows -, -, 84.9 / 73.9, 104 / 108, 124 / 143,
+// 512 of 256 -, -, 71.2 / 59.4, 88.0 / 84.6, 106 / 111.
+int nimble_lstm_loop_preferred(int64_t T, int64_t B, int64_t Ix, int64_t H) {
+  if (!nimble_lstm_loop_supported(B, Ix, H)) return 0;
+  const int64_t launches = ceil_div(ceil_div(B, 8), lstm_groups_per_launch(H));
+  return T >= (launches == 1 ? 7 : 8 + 2 * launches);
 }
 
 size_t nimble_lstm_loop_workspace_bytes(int64_t B, int64_t Ix, int64_t H) {

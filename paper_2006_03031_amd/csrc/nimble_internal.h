@@ -95,6 +95,13 @@ inline void any_launch_tiles(int64_t tiles_m, int64_t tiles_n, int64_t* tm, int6
   *tm = tiles_m * *tn <= most ? tiles_m : most / *tn;
 }
 
+// Row groups (of 8) in one launch of the LSTM token loop: of H / 16 workgroups each on one XCD (two above H = 512), as many
+// as give each of its compute units one workgroup at most.
+inline int lstm_groups_per_launch(int64_t H) {
+  const int n_wg = (int)(H / 16), span = n_wg > 32 ? 2 : 1, per_xcd = n_wg / span;
+  return 8 / span * (per_xcd < kComputeUnits / 8 ? kComputeUnits / 8 / per_xcd : 1);
+}
+
 // Whether a weight-streaming launch of 16-row blocks over an [N, K] weight can run the LDS-staged
 // streaming kernel (the LSTM cell needs Ix % 64 == 0 besides).
 bool stream_kernel_shape_ok(int64_t N, int64_t K);

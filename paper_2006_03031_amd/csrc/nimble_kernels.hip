@@ -326,13 +326,14 @@ template <int R>
 static void launch_lstm_seq_as(const LstmSeqArgs& a, int rs, int xcd0, hipStream_t st) {
   const int row_groups = (a.B + R - 1) / R, per_wave = ((a.Ix + a.H) / 64 + 7) / 8;
   const int n_wg = a.H / 16, span = n_wg > 32 ? 2 : 1;  // XCDs per row group
-  const dim3 grid((unsigned)(8 * (n_wg / span))), block(512);
+  const int wide = 8 / span, per_launch = lstm_groups_per_launch(a.H), groups = row_groups < per_launch ? row_groups : per_launch;
+  const dim3 grid((unsigned)(8 * (n_wg / span) * ((groups + wide - 1) / wide))), block(512);
   // (four ranges: whole ranges of 2 per_wave stages, see nimble_lstm_loop_supported)
   const bool mixed = a.ranges == 4 && a.Ix / 64 % (2 * per_wave) != 0;
   const int order = a.ranges != 4 ? 0 : mixed ? 2 : 1;
   auto launch = [&](auto pre, auto pw, auto ord) {
     constexpr int ORDER = R == 8 ? decltype(ord)::value : 0;
-    for (int group0 = 0; group0 < row_groups; group0 += 8 / span)
+    for (int group0 = 0; group0 < row_groups; group0 += per_launch)
       hipLaunchKernelGGL((lstm_seq_kernel<decltype(pre)::value, decltype(pw)::value, 4, R, ORDER>), grid, block, 0, st, a,
                          group0, row_groups, rs, xcd0);
   };

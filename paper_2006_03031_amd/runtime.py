@@ -280,7 +280,7 @@ def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0
     returns (h_seq [T,B,H] bf16, c_T [B,H] f32, ran_in_one_launch).
 
     one_launch=None: shapes for which nimble_lstm_seq_preferred says so run as one launch
-    (nimble_lstm_seq_pre_dyn), other shapes that nimble_lstm_loop_supported accepts through nimble_lstm_loop_dyn, whose
+    (nimble_lstm_seq_pre_dyn), others by nimble_lstm_loop_preferred through nimble_lstm_loop_dyn, whose
     own recovery launch stands behind it, so that nothing is waited for and the third value is False (it is
     not known then) as for steps; True: every shape nimble_lstm_seq_supported accepts runs as one launch (others
     raise); False: none.  After a one-launch run the call waits for the stream and reads the loop's give-up word;
@@ -301,8 +301,10 @@ def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0
         raise nb.NimbleError(-3, f"the one-launch token loop does not run B={B}, H={H}")
     if one_launch is None:
         one_launch = nb.lstm_seq_preferred(B, H)
-        # 128 steps of 3 rows at H = 1024 took 748 us as eager steps (projection included), 215 in the loop
-        if not one_launch and nb.lstm_loop_supported(B, 0, H):
+        # 128 steps of 3 rows at H = 1024 took 748 us as eager steps (projection included), 215 in the loop.  An eager step
+        # takes its caller 5 us: 2 steps of 20 rows at H = 512 22.6 us, 20.0 in the loop (one 17.4 / 20.1); 12 of 256 96.9 / 87.4
+        # (8 65.5 / 68.2)
+        if not one_launch and nb.lstm_loop_preferred(T + 5, B, 0, H):
             ws = torch.empty(nb.lstm_loop_workspace_bytes(B, 0, H), dtype=torch.uint8, device=dev)
             nb.nimble_lstm_loop_dyn(0, pp, wp, 0, hp, cp, h_seq.data_ptr(), c_out.data_ptr(), T, B, 0, H, ws.data_ptr(),
                                     ws.numel(), min(max_polls, LSTM_LOOP_MAX_POLLS), _stream())
@@ -340,7 +342,7 @@ def split_lstm_weight(w: torch.Tensor, Ix: int) -> Tuple[torch.Tensor, torch.Ten
 
 class LstmSequenceGraph:
     """The token loop of one sequence, captured once per batch size B as a HIP graph and replayed: where
-    nimble_lstm_loop_supported says so the loop is one launch (with a recovery launch behind it that ends at once
+    nimble_lstm_loop_preferred says so the loop is one launch (with a recovery launch behind it that ends at once
     unless the loop's bounded waits ran out), else `steps` launches of the fused LSTM cell, with the same bits.  The graph
     holds kernel launches only (state is cleared by a fill kernel outside it).  The dynamic extent
     B is fixed per graph; a server keeps one graph per batch size it has seen.
@@ -354,7 +356,8 @@ class LstmSequenceGraph:
         """project_inputs: compute the inputs' share of the gates for all tokens in one dense
         call (M = steps * B) ahead of the loop, so each step streams only the recurrent half
         of the weight.
-        one_launch: None: the loop in one launch where it is supported; True: the same, other shapes raise;
+        one_launch: None: the loop in one launch where that is preferred (nimble_lstm_loop_preferred); True: where it is
+        supported, other shapes raise;
         False: a launch per step, for programs that replay three or more of these graphs at once."""
         dev = w.device
         (self.B, self.H), _ = nb.lstm_shape((B, Ix), (B, H), (B, H), tuple(w.shape))
@@ -372,7 +375,7 @@ class LstmSequenceGraph:
         supported = (project_inputs or Ix > 0) and nb.lstm_loop_supported(B, loop_ix, H)
         if one_launch and not supported:
             raise nb.NimbleError(-3, f"the one-launch token loop does not run B={B}, Ix={loop_ix}, H={H}")
-        if supported and one_launch is not False:
+        if one_launch or (one_launch is None and supported and nb.lstm_loop_preferred(steps, B, loop_ix, H)):
             self.workspace = torch.empty(nb.lstm_loop_workspace_bytes(B, loop_ix, H), dtype=torch.uint8, device=dev)
         # one eager pass so that nothing is lazily initialised during capture
         self._enqueue()

@@ -208,6 +208,28 @@ def test_loops_on_two_streams_at_once(rt, nb):
             assert _same(h, wh) and torch.equal(c, wc), rep
 
 
+@pytest.mark.parametrize("B,H,least", [(3, 512, 7), (70, 512, 12), (130, 256, 12)])
+def test_few_steps_run_one_by_one(rt, nb, B, H, least):
+    """What the loop costs before its first step is more than a few launches: the captured sequence takes it from `least`
+    steps on, the eager one some steps earlier, with the same bits."""
+    from gpu_util import to_dev
+    rng = np.random.default_rng([14, B, H])
+    w, b = to_dev(wl.normal_bf16(rng, (4 * H, 2 * H), std=0.05)), to_dev(wl.normal_bf16(rng, (4 * H,)))
+    zeros = torch.zeros((B, H), dtype=torch.bfloat16, device="cuda"), torch.zeros((B, H), device="cuda")
+    for T in (1, least - 1, least):
+        x = to_dev(wl.uniform_bf16(rng, (T, B, H)))
+        seq = rt.LstmSequenceGraph(w, b, B, T, H, H)
+        assert (seq.workspace is None) == (T < least)
+        want_h, want_c = _steps(rt, x, w, b, *zeros)
+        h, c = seq.run(x)
+        assert _same(h, want_h) and torch.equal(c, want_c), T
+    for T in (1, least - 6, least - 5):
+        x, w_h, _, h0, c0 = _case(7, T, B, 0, H)
+        want_h, want_c, _ = rt.lstm_sequence_pre(x, w_h, h0, c0, one_launch=False)
+        h, c, _ = rt.lstm_sequence_pre(x, w_h, h0, c0)
+        assert _same(h, want_h) and torch.equal(c, want_c), T
+
+
 def test_two_loops_of_many_rows_always_find_their_places(rt, nb):
     """Loops of four row groups per XCD on two streams, replayed back to back: neither ever waits for places that the other
     holds, so none gives up (with nothing else on the GPU), and all are right."""

@@ -552,6 +552,11 @@ def test_lstm_loop_support_and_refusals():
     # control words, two planes of bf16 rows in groups of 8, c_0
     assert nb.lstm_loop_workspace_bytes(37, 512, 512) == 256 + 4 * 40 * 512 + 4 * 37 * 512
     assert nb.lstm_loop_workspace_bytes(257, 512, 512) == 0
+    # the least number of steps for which it is preferred: one launch, and two to four of them
+    for (B, Ix, H), least in {(1, 512, 512): 7, (64, 0, 512): 7, (65, 512, 512): 12, (192, 512, 512): 14, (256, 0, 512): 16,
+                              (128, 256, 256): 7, (512, 256, 256): 16, (32, 0, 1024): 7, (33, 0, 1024): 12, (3, 64, 64): 7}.items():
+        assert [nb.lstm_loop_preferred(T, B, Ix, H) for T in (0, 1, least - 1, least, 128)] == [False, False, False, True, True]
+    assert not any(nb.lstm_loop_preferred(128, *s) for s in no)
     call, a, big = nb.nimble_lstm_loop_dyn, 4096, 1 << 24   # (any aligned number: never dereferenced on these paths)
     for args, code in [((a, 0, a, a, a, a, a, a, 5, 257, 512, 512, a, big, 10, 0), -3),
                        ((a, 0, a, a, a, a, a, a, -1, 5, 512, 512, a, big, 10, 0), -8),
