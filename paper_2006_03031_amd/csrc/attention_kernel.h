@@ -29,14 +29,14 @@ namespace nimble {
 //   some row's maximum moved.  (Rescaling only once a maximum has grown by 2^8 saves a tenth of the time, but then the
 //   largest probabilities are no longer exactly 1 and the error against 64 bits grows from 2.19e-3 to 2.3e-3.)
 //   What bounds it: per block of 64 keys and 32 rows about 1050 clocks of vector instructions, half of them the
-//   exponentials, under which 512 clocks of MFMA run; 96 heads of 2048 keys: 118 us (870 TFLOP/s), the vector
+//   exponentials, under which 512 clocks of MFMA run; 96 heads of 2048 keys: 118-120 us (860-870 TFLOP/s), the vector
 //   instructions alone 84-96 at 2.1-2.4 GHz.  The kernel before it (16 rows per wave, V transposed through
 //   registers with 2-byte LDS writes): 216 us; 12 heads of 512 keys 9.8 -> 5.8.  Without the overlap of
 //   two blocks 140; eight row waves per workgroup 123, two 152.
 //   The workgroups of a compute unit share its vector units: a wave that has its maxima runs at higher priority until
 //   its last product is issued, so the matrix core is fed while the others look for theirs.  Raised from the rescaling
 //   or the first score product on, over the maxima, or lowered a quarter earlier it gives less or nothing.  With it, with
-//   the maximum starting from the reference and the loads' offsets kept, before -> now: 96 x 2048 123.0 -> 119.6 us,
+//   the maximum starting from the reference and the loads' offsets kept, before -> now on one card: 96 x 2048 123.0 -> 119.6 us,
 //   96 x 1000 36.5 -> 34.9, 24 x 2048 41.1 -> 38.0, 48 x 777 19.6 -> 18.1; 12 x 2048 (two key groups, the maximum
 //   alone) 22.3 -> 22.1.
 // ---------------------------------------------------------------------------

@@ -58,8 +58,6 @@ __device__ __forceinline__ float tanh_fast(float z) {
 // One cell update from the four gate pre-activations (i, f, g, o): returns h, writes c.  Every LSTM
 // kernel goes through this one function, with the fused multiply-add spelled out, so that they agree
 // bit for bit.
-// (The one-launch token loop spreads the four gates of a cell over four lanes and then does exactly
-// these operations on the gathered values.)
 __device__ __forceinline__ float lstm_cell(const float (&gate)[4], float c_prev, float& c_new) {
   const float a_i = sigmoidf(gate[0]), a_f = sigmoidf(gate[1]), a_g = tanh_fast(gate[2]), a_o = sigmoidf(gate[3]);
   c_new = fmaf(a_f, c_prev, a_i * a_g);

@@ -34,7 +34,9 @@ namespace nimble {
 //   and arrival are one word, no counter, no fence, one store and one load on the critical path (a counter
 //   barrier over 16 workgroups was measured at 0.85 us per step bare).  Two buffers suffice: h_t overwrites
 //   h_{t-2}, which every workgroup has finished reading before it publishes h_{t-1}, without which nobody can
-//   compute h_t; so a word is either two steps old or this step's, and one bit tells them apart.  The words are
+//   compute h_t; and a wave polls the same words in every step, so it has seen a word's value of two steps ago when it
+//   looks for this step's, and loads of one address never go back: the word it finds is one of these two, and one bit
+//   tells them apart.  The words are
 //   cleared by lstm_seq_init_kernel ahead of the launch on the same stream (the first phase is 1).
 //   Every wait is bounded: a wave polls at most max_polls times per step, looking at the give-up word with every
 //   eighth; a wave that runs out sets it, and every workgroup leaves at its next check.  So the
@@ -48,7 +50,7 @@ namespace nimble {
 //   the rest is a chain of MFMAs, LDS sums, barrier and cell arithmetic.  Microseconds per step, pre form at
 //   1 / 4 rows: H = 512 1.10 / 1.17, H = 1024 1.41 / 1.56, H = 256 1.14 / - (32-bit words with a step tag each, four lanes
 //   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 / 64 rows, H = Ix = 512: 1.24 /
-//   1.37 / 1.37 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
+//   1.34 / 1.34 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
 //   per cell, 32-byte stores 2.31; one lane per cell, 128-byte stores 1.95; a row group's workgroups on one XCD
 //   and a late first poll 1.56; operands polled straight into their registers, no address arithmetic in the loop 1.37.
 //   Tried and not kept: system scope, exchanges instead of stores, raised priority for the cells (no change); a
@@ -325,9 +327,12 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       const unsigned long long* src = exch + (long long)(t & 1) * plane;
       uint32_t polls = 0, nan;
       // A poll that finds the words not there yet costs another round trip, and more polls on their way delay the
-      // stores they wait for: the first goes out when the words can be expected, in units of 64 clocks (37 rows, x
-      // form, microseconds per step with 0, 8, 12, 14, 16, 18, 20 units: 1.79, 1.79, 1.65, 1.32, 1.37, 1.42, 1.48;
-      // the step at 14 moves by two units from card to card, so a little later than the best).
+      // stores they wait for: the first goes out when the words can be expected, in units of 64 clocks.  Microseconds for
+      // 128 steps with 12, 14, 16, 18, 20 units, x form of H = 512, 37 rows: 235, 205, 178, 183, 190 (on another card 14 was
+      // the best: the edge moves by two units, so a little later); pre form, H = 512, 16 rows 207, 188, 185, 187, 192; 24 rows
+      // of 256 198, 183, 179, 176, 181, of 1024 271, 257, 252, 255, 247.  Up to 4 rows, pre form, with 12, 13, 14, 15, 16 units,
+      // means over the XCD it starts on: H = 512, 1 row 175, 163, 159, 165, 167, H = 256 175, 163, 148, 153, 157; two stages
+      // per wave, H = 1024, with 14 to 18: 221, 215, 213, 213, 213.
       if (!cells) __builtin_amdgcn_s_sleep(R == 8 || PW > 1 ? 16 : 14);
       else if (R == 8) __builtin_amdgcn_s_sleep(4);
       for (;;) {
