@@ -803,7 +803,7 @@ int nimble_lstm_loop_supported(int64_t B, int64_t Ix, int64_t H) {
 // H = 1024 33 rows -, 51.9 / 43.5, 58.1 / 54.0, 72.7 / 73.1, 89.7 / 96.5; four: 256 rows -, -, 84.9 / 73.9, 104 / 108, 124 / 143,
 // 512 of 256 -, -, 71.2 / 59.4, 88.0 / 84.6, 106 / 111.
 int nimble_lstm_loop_preferred(int64_t T, int64_t B, int64_t Ix, int64_t H) {
-  if (!nimble_lstm_loop_supported(B, Ix, H)) return 0;
+  if (!nimble_lstm_loop_supported(B, Ix, H) || T > (int64_t)1 << 24) return 0;  // (nimble_lstm_loop_dyn takes no more steps)
   const int64_t launches = ceil_div(ceil_div(B, 8), lstm_groups_per_launch(H));
   return T >= (launches == 1 ? 7 : 8 + 2 * launches);
 }

@@ -306,6 +306,9 @@ def lstm_sequence_pre(pre: torch.Tensor, w_h: torch.Tensor, h0: torch.Tensor, c0
         # (8 65.5 / 68.2)
         if not one_launch and nb.lstm_loop_preferred(T + 5, B, 0, H):
             ws = torch.empty(nb.lstm_loop_workspace_bytes(B, 0, H), dtype=torch.uint8, device=dev)
+            if cp % 16:  # (any alignment of c0 will do here, as for steps)
+                c_out.copy_(c0)
+                cp = c_out.data_ptr()
             nb.nimble_lstm_loop_dyn(0, pp, wp, 0, hp, cp, h_seq.data_ptr(), c_out.data_ptr(), T, B, 0, H, ws.data_ptr(),
                                     ws.numel(), min(max_polls, LSTM_LOOP_MAX_POLLS), _stream())
             return h_seq, c_out, False

@@ -184,6 +184,18 @@ def test_sequences_beyond_the_preferred_shapes(rt, nb, B, H):
     assert not one and _same(h, want_h) and torch.equal(c, want_c)
 
 
+@pytest.mark.parametrize("T", [1, 9])
+def test_a_first_state_of_any_alignment(rt, nb, T):
+    """lstm_sequence_pre copies c_0 for the steps, so that it may lie anywhere; the loop takes it from there too."""
+    x, w, _, h0, c0 = _case(8, T, 20, 0, 512)
+    buf = torch.empty(c0.numel() + 1, device="cuda")
+    odd = buf[1:].view_as(c0).copy_(c0)
+    assert odd.data_ptr() % 16 == 4 and nb.lstm_loop_preferred(T + 5, 20, 0, 512) == (T > 1)
+    want_h, want_c, _ = rt.lstm_sequence_pre(x, w, h0, odd, one_launch=False)
+    h, c, _ = rt.lstm_sequence_pre(x, w, h0, odd)
+    assert _same(h, want_h) and torch.equal(c, want_c) and torch.equal(odd, c0)
+
+
 def test_loops_on_two_streams_at_once(rt, nb):
     """Two captured loops of the most rows side by side: each has its own workspace; whether or not one of them has to
     recover, both are right."""

@@ -557,6 +557,7 @@ def test_lstm_loop_support_and_refusals():
                               (128, 256, 256): 7, (512, 256, 256): 16, (32, 0, 1024): 7, (33, 0, 1024): 12, (3, 64, 64): 7}.items():
         assert [nb.lstm_loop_preferred(T, B, Ix, H) for T in (0, 1, least - 1, least, 128)] == [False, False, False, True, True]
     assert not any(nb.lstm_loop_preferred(128, *s) for s in no)
+    assert nb.lstm_loop_preferred(1 << 24, 5, 512, 512) and not nb.lstm_loop_preferred((1 << 24) + 1, 5, 512, 512)
     call, a, big = nb.nimble_lstm_loop_dyn, 4096, 1 << 24   # (any aligned number: never dereferenced on these paths)
     for args, code in [((a, 0, a, a, a, a, a, a, 5, 257, 512, 512, a, big, 10, 0), -3),
                        ((a, 0, a, a, a, a, a, a, -1, 5, 512, 512, a, big, 10, 0), -8),
