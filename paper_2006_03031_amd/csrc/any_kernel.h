@@ -238,7 +238,7 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
         const int row = p * RP + lane / WN, col = lane % WN;
         const int m = m0 + wm * WM + j * 16 + row, n = n_base + col;
         const float v = out_lds[row * ELD + col];
-        if (m < M && n < N) C[(long long)m * g.ldc + n] = v;
+        if (m < M && n < N) store_through(&C[(long long)m * g.ldc + n], v);  // (515 x 1001 x 1003 10.75 -> 10.5 us; bf16 no faster)
       }
     } else {
       constexpr int LW = WN / 2, RP = 64 / LW;  // lanes per row (two columns each), rows per store

@@ -443,7 +443,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
         o.y = epilogue(acc[i][j][1], alpha, bias4[i][1], epi);
         o.z = epilogue(acc[i][j][2], alpha, bias4[i][2], epi);
         o.w = epilogue(acc[i][j][3], alpha, bias4[i][3], epi);
-        *(float4*)(C + (long long)m * g.ldc + n) = o;
+        store_through(C + (long long)m * g.ldc + n, __builtin_bit_cast(uint4, o));
       }
     }
     return -1;
@@ -476,7 +476,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
           const int c = lane & 7;
           const uint4 v = *(const uint4*)(region + h * (16 * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
           if (EDGE && (m0 + wm * WM + j * 16 + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
-          *(uint4*)(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8) = v;
+          store_through(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
         }
     }
     return EDGE ? -1 : NST;
@@ -509,8 +509,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       const int c = lane & 7;
       const uint4 v = *(const uint4*)(region + h * (WM * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
       if (EDGE && (m0 + wm * WM + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
-      uint4* dst = (uint4*)(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8);
-      *dst = v;
+      store_through(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
     }
   return -1;
 }
@@ -609,12 +608,12 @@ __global__ void __launch_bounds__(256)
   const float v0 = epilogue(acc.x, 1.0f, b4[0], epi), v1 = epilogue(acc.y, 1.0f, b4[1], epi);
   const float v2 = epilogue(acc.z, 1.0f, b4[2], epi), v3 = epilogue(acc.w, 1.0f, b4[3], epi);
   if (out_f32) {
-    *(float4*)((float*)out + idx) = make_float4(v0, v1, v2, v3);
+    store_through((float*)out + idx, __builtin_bit_cast(uint4, make_float4(v0, v1, v2, v3)));
   } else {
     uint2 pk;
     pk.x = pack_bf16x2(v0, v1);
     pk.y = pack_bf16x2(v2, v3);
-    *(uint2*)((u16*)out + idx) = pk;
+    store_through((u16*)out + idx, pk);
   }
 }
 
