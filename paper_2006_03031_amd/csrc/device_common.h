@@ -36,11 +36,14 @@ __device__ __forceinline__ u16 f2bf(float f) {
 // cost more still.  Reading the function from a 1024-segment table of chords in LDS (five ordinary
 // instructions and one data-dependent 8-byte read per element) was measured too: 2-6 % slower per
 // kernel, the reads' bank conflicts cost more than the arithmetic they replace.
-__device__ __forceinline__ float gelu_erf(float v) {
+__device__ __forceinline__ float gelu_exponent(float v) {
   const float t = fminf(v * v, 81.0f);
   float p = fmaf(0.0010142630f, t, -0.10677572f);  // -log2(e) (a + b t + c t^2)
   p = fmaf(p, t, -2.3011212f);
-  const float e = __builtin_amdgcn_exp2f(p * v);    // exp(-(a v + b v^3 + c v^5))
+  return p * v;
+}
+__device__ __forceinline__ float gelu_erf(float v) {
+  const float e = __builtin_amdgcn_exp2f(gelu_exponent(v));  // exp(-(a v + b v^3 + c v^5))
   return v * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
@@ -73,6 +76,34 @@ __device__ __forceinline__ void keep_in_registers(uint4& v) {
 __device__ __forceinline__ float epilogue(float acc, float alpha, float bias, int epi) {
   const float v = fmaf(alpha, acc, bias);
   return epi == NIMBLE_EPI_BIAS_GELU_ERF ? gelu_erf(v) : v;
+}
+// The same for N values at a time with the choice made outside.  With a choice per value there is a branch per value, and
+// left to itself the compiler computes one or two values at a time, each a chain of a dozen dependent instructions; here
+// N chains go side by side (the empty statements keep the N results of a step together).  Eight at a time, with their
+// choice outside: the feed-forward pair of 4500 / 8069 / 16129 tokens 82.2 / 123.1 / 227.4 -> 79.9 / 120.6 / 222 us,
+// 800 x 3072 x 768 with GELU 9.97 -> 9.77.
+template <bool GELU, int N>
+__device__ __forceinline__ void epilogue_of(float (&v)[N]) {
+  if (!GELU) return;
+  float e[N];
+  auto together = [&](float (&x)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+  };
+#pragma unroll
+  for (int i = 0; i < N; ++i) e[i] = gelu_exponent(v[i]);
+  together(e);
+#pragma unroll
+  for (int i = 0; i < N; ++i) e[i] = __builtin_amdgcn_exp2f(e[i]);
+  together(e);
+#pragma unroll
+  for (int i = 0; i < N; ++i) e[i] = 1.0f + e[i];
+  together(e);
+#pragma unroll
+  for (int i = 0; i < N; ++i) e[i] = __builtin_amdgcn_rcpf(e[i]);
+  together(e);
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] *= e[i];
 }
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }

@@ -428,90 +428,101 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       bias4[i][3] = bf2f((u16)(bb.y >> 16));
     }
   }
-  if (g.out_f32) {
-    float* C = (float*)g.c + (long long)z * g.sc + (long long)blockIdx.y * g.M * g.ldc;
+  // (one copy of what follows per kind of epilogue: see epilogue_of)
+  auto finish = [&](auto gelu_tag) -> int {
+    constexpr bool GELU = decltype(gelu_tag)::value;
+    if (g.out_f32) {
+      float* C = (float*)g.c + (long long)z * g.sc + (long long)blockIdx.y * g.M * g.ldc;
 #pragma unroll
-    for (int j = 0; j < TM; ++j) {
-      const int m = m0 + wm * WM + j * 16 + fr_row;
-      if (EDGE && m >= g.M) continue;
+      for (int j = 0; j < TM; ++j) {
+        const int m = m0 + wm * WM + j * 16 + fr_row;
+        if (EDGE && m >= g.M) continue;
 #pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int n = n0 + wn * WN + i * 16 + fr_q * 4;
-        if (EDGE && n >= g.N) continue;
-        float4 o;
-        o.x = epilogue(acc[i][j][0], alpha, bias4[i][0], epi);
-        o.y = epilogue(acc[i][j][1], alpha, bias4[i][1], epi);
-        o.z = epilogue(acc[i][j][2], alpha, bias4[i][2], epi);
-        o.w = epilogue(acc[i][j][3], alpha, bias4[i][3], epi);
-        store_through(C + (long long)m * g.ldc + n, __builtin_bit_cast(uint4, o));
-      }
-    }
-    return -1;
-  }
-  u16* C = (u16*)g.c + (long long)z * g.sc;
-  constexpr int NH = WN / 64;
-  if constexpr (PF) {
-    // bf16 through the wave's own staging area, 16 rows at a time: [NH][16 rows][128 bytes], chunk c of
-    // row r at slot c ^ ((r >> 1) & 7), written back out as full 128-byte lines.  (Wave-private: no
-    // workgroup barrier; a wave's LDS accesses execute in order.)
-    unsigned char* region = (unsigned char*)(smem + S * (BMP + BN) * CH) + 2 * BN * 2 + wave * (16 * WN * 2);
+        for (int i = 0; i < TN; ++i) {
+          const int n = n0 + wn * WN + i * 16 + fr_q * 4;
+          if (EDGE && n >= g.N) continue;
+          float v[4];
 #pragma unroll
-    for (int j = 0; j < TM; ++j) {
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int col = (i & 3) * 16 + fr_q * 4;
-        const int chunk = (col >> 3) ^ ((fr_row >> 1) & 7);
-        uint2 pk;
-        pk.x = pack_bf16x2(epilogue(acc[i][j][0], alpha, bias4[i][0], epi),
-                           epilogue(acc[i][j][1], alpha, bias4[i][1], epi));
-        pk.y = pack_bf16x2(epilogue(acc[i][j][2], alpha, bias4[i][2], epi),
-                           epilogue(acc[i][j][3], alpha, bias4[i][3], epi));
-        *(uint2*)(region + (i >> 2) * (16 * 128) + fr_row * 128 + chunk * 16 + (col & 4) * 2) = pk;
-      }
-#pragma unroll
-      for (int h = 0; h < NH; ++h)
-#pragma unroll
-        for (int p = 0; p < 2; ++p) {
-          const int row = p * 8 + (lane >> 3);
-          const int c = lane & 7;
-          const uint4 v = *(const uint4*)(region + h * (16 * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
-          if (EDGE && (m0 + wm * WM + j * 16 + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
-          store_through(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
+          for (int e = 0; e < 4; ++e) v[e] = fmaf(alpha, acc[i][j][e], bias4[i][e]);
+          epilogue_of<GELU>(v);
+          const float4 o = make_float4(v[0], v[1], v[2], v[3]);
+          store_through(C + (long long)m * g.ldc + n, __builtin_bit_cast(uint4, o));
         }
+      }
+      return -1;
     }
-    return EDGE ? -1 : NST;
-  }
-  // bf16: every wave stages its [WM][WN] block in LDS as WN/64 blocks of [WM][64] (rows of 128
-  // bytes, chunk c of row r at slot c ^ ((r >> 1) & 7)) and writes it back out as full 128-byte lines
-  __syncthreads();  // all fragment reads of the ring are done
-  unsigned char* region = (unsigned char*)smem + wave * (WM * WN * 2);
+    u16* C = (u16*)g.c + (long long)z * g.sc;
+    constexpr int NH = WN / 64;
+    if constexpr (PF) {
+      // bf16 through the wave's own staging area, 16 rows at a time: [NH][16 rows][128 bytes], chunk c of
+      // row r at slot c ^ ((r >> 1) & 7), written back out as full 128-byte lines.  (Wave-private: no
+      // workgroup barrier; a wave's LDS accesses execute in order.)
+      unsigned char* region = (unsigned char*)(smem + S * (BMP + BN) * CH) + 2 * BN * 2 + wave * (16 * WN * 2);
 #pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int row = j * 16 + fr_row;
+      for (int j = 0; j < TM; ++j) {
 #pragma unroll
-    for (int i = 0; i < TN; ++i) {
-      const int col = (i & 3) * 16 + fr_q * 4;
-      const int chunk = (col >> 3) ^ ((row >> 1) & 7);
-      uint2 pk;
-      pk.x = pack_bf16x2(epilogue(acc[i][j][0], alpha, bias4[i][0], epi),
-                         epilogue(acc[i][j][1], alpha, bias4[i][1], epi));
-      pk.y = pack_bf16x2(epilogue(acc[i][j][2], alpha, bias4[i][2], epi),
-                         epilogue(acc[i][j][3], alpha, bias4[i][3], epi));
-      *(uint2*)(region + (i >> 2) * (WM * 128) + row * 128 + chunk * 16 + (col & 4) * 2) = pk;
+        for (int i = 0; i < TN; i += 2) {
+          float v[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = fmaf(alpha, acc[i + (e >> 2)][j][e & 3], bias4[i + (e >> 2)][e & 3]);
+          epilogue_of<GELU>(v);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            const int col = ((i + x) & 3) * 16 + fr_q * 4;
+            const int chunk = (col >> 3) ^ ((fr_row >> 1) & 7);
+            *(uint2*)(region + ((i + x) >> 2) * (16 * 128) + fr_row * 128 + chunk * 16 + (col & 4) * 2) =
+                make_uint2(pack_bf16x2(v[4 * x], v[4 * x + 1]), pack_bf16x2(v[4 * x + 2], v[4 * x + 3]));
+          }
+        }
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            const int row = p * 8 + (lane >> 3);
+            const int c = lane & 7;
+            const uint4 v = *(const uint4*)(region + h * (16 * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
+            if (EDGE && (m0 + wm * WM + j * 16 + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
+            store_through(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
+          }
+      }
+      return EDGE ? -1 : NST;
     }
-  }
-  // the region is private to the wave: no workgroup barrier, the compiler orders the LDS accesses
+    // bf16: every wave stages its [WM][WN] block in LDS as WN/64 blocks of [WM][64] (rows of 128
+    // bytes, chunk c of row r at slot c ^ ((r >> 1) & 7)) and writes it back out as full 128-byte lines
+    __syncthreads();  // all fragment reads of the ring are done
+    unsigned char* region = (unsigned char*)smem + wave * (WM * WN * 2);
 #pragma unroll
-  for (int h = 0; h < NH; ++h)
+    for (int j = 0; j < TM; ++j) {
+      const int row = j * 16 + fr_row;
 #pragma unroll
-    for (int p = 0; p < WM / 8; ++p) {
-      const int row = p * 8 + (lane >> 3);
-      const int c = lane & 7;
-      const uint4 v = *(const uint4*)(region + h * (WM * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
-      if (EDGE && (m0 + wm * WM + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
-      store_through(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
+      for (int i = 0; i < TN; i += 2) {
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = fmaf(alpha, acc[i + (e >> 2)][j][e & 3], bias4[i + (e >> 2)][e & 3]);
+        epilogue_of<GELU>(v);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const int col = ((i + x) & 3) * 16 + fr_q * 4;
+          const int chunk = (col >> 3) ^ ((row >> 1) & 7);
+          *(uint2*)(region + ((i + x) >> 2) * (WM * 128) + row * 128 + chunk * 16 + (col & 4) * 2) =
+              make_uint2(pack_bf16x2(v[4 * x], v[4 * x + 1]), pack_bf16x2(v[4 * x + 2], v[4 * x + 3]));
+        }
+      }
     }
-  return -1;
+    // the region is private to the wave: no workgroup barrier, the compiler orders the LDS accesses
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+#pragma unroll
+      for (int p = 0; p < WM / 8; ++p) {
+        const int row = p * 8 + (lane >> 3);
+        const int c = lane & 7;
+        const uint4 v = *(const uint4*)(region + h * (WM * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
+        if (EDGE && (m0 + wm * WM + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
+        store_through(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
+      }
+    return -1;
+  };
+  return epi == NIMBLE_EPI_BIAS_GELU_ERF ? finish(std::true_type{}) : finish(std::false_type{});
 }
 
 // S = number of ring stages.  4 keeps two workgroups of the 128x128 tile on a compute unit.  A
