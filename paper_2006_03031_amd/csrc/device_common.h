@@ -205,6 +205,18 @@ __device__ __forceinline__ void dma16_so(uint32_t voff, const void* sbase, uint3
                "s"(lds_addr)
                : "memory", "m0");
 }
+// A matrix product with a direct global -> LDS load behind it, at LDS byte lds_base + lds_off (the product is also the
+// wait state between writing M0 and the load).
+__device__ __forceinline__ void mfma_acc_load(f32x4& acc, const bf16x8& a, const bf16x8& b, uint32_t voff, const void* sbase,
+                                              uint32_t lds_base, uint32_t lds_off) {
+  asm volatile(
+      "s_add_u32 m0, %5, %6\n\t"
+      "v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0\n\t"
+      "global_load_lds_dwordx4 %3, %4"
+      : "+a"(acc)
+      : "v"(a), "v"(b), "v"(voff), "s"(sbase), "s"(lds_base), "s"(lds_off)
+      : "memory", "m0", "scc");
+}
 // One dword per lane: a wave instruction fills 256 contiguous bytes of LDS.
 __device__ __forceinline__ void dma4_so(uint32_t voff, const void* sbase, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1\n" ::"v"(voff), "s"(sbase),

@@ -414,7 +414,11 @@ static void fill_tiled(nimble_plan* p, int variant, int split_k, int64_t batch, 
   p->grid[0] = (uint32_t)(ceil_div(M, v.bm) * ceil_div(N, v.bn));
   p->grid[1] = (uint32_t)split_k;
   p->grid[2] = (uint32_t)batch;
-  p->block = eight_waves(variant, (uint64_t)p->grid[0] * p->grid[1] * p->grid[2], K, split_k) ? 512u : (uint32_t)v.threads;
+  const int64_t tiles = (int64_t)p->grid[0] * batch;
+  if (ring_shape_ok(N, K) && quarter_kernel_wins(v.bm, v.bn, tiles, K, split_k, batch))
+    p->block = 256;
+  else
+    p->block = eight_waves(variant, (uint64_t)tiles * p->grid[1], K, split_k) ? 512u : (uint32_t)v.threads;
   p->workspace_bytes = split_k > 1 ? (uint64_t)split_k * (uint64_t)M * (uint64_t)N * 4u : 0;
 }
 
@@ -597,7 +601,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
     split_k = forced_sk;
   }
   fill_tiled(p, variant, split_k, batch, split_rows > 0 ? split_rows : M, N, K, tile_rows);
-  if (halved) p->grid[1] = 2;
+  if (halved) p->grid[1] = 2, p->block = 512;
   if (!chosen && split_rows == 0 &&
       small_tiles_win(variant, (int64_t)p->grid[0] * batch, batch * ceil_div(M, 64) * ceil_div(N, 64), p->bn, N, K, opt.out_f32))
     fill_any(p, batch, M, N, K);

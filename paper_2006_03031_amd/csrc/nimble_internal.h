@@ -47,6 +47,31 @@ inline bool eight_waves(int variant, uint64_t tiles, int64_t K, int64_t slices) 
   return variant == NIMBLE_VAR_T128x128;
 }
 
+// Slots of gemm_quarter_kernel's ring, 0: not built for these tiles.
+constexpr int quarter_slots(int bm, int bn) {
+  if (bn == 256) return bm <= 256 ? 2 : 0;
+  return bn != 128 ? 0 : bm == 256 ? 3 : bm == 128 ? 4 : 0;
+}
+
+// Whether a launch of `tiles` whole tiles (over all batches) runs four waves in place of eight, one per SIMD
+// (gemm_quarter_kernel).  They walk a K stage 4 to 7 % faster, but have no second wave under the epilogue, the fill and the
+// first loads: a workgroup has to walk enough stages, over all its tiles.  Microseconds, eight waves / four: 256-wide
+// tiles, stages walked: 4 (2113 x 4096 x 256) 9.2 / 10.4, 12 (3500 x 4096 x 768) 23.4 / 23.9, 16 (3500 x 4096 x 1024 with GELU)
+// 29.8 / 31.0, 24 (8192 x 4096 x 768 with GELU) 53.4 / 54.9, 24 (4096 x 4096 x 1536) 43.1 / 42.3, 32 (16129 x 4096 x 512 with
+// GELU) 98.0 / 93.4, (5000 x 4096 x 1024) 40.5 / 39.7, (4096 x 4096 x 2048) 53.7 / 52.6, 64 (9000, 10240 and 16384 x 1024 x 4096)
+// 62.6 / 58.5, 66.4 / 62.8, 95.7 / 91.3; 256 x 128: 24 (8192 x 1024 x 1536 with GELU) 27.2 / 27.6, 32 (x 2048) 32.2 / 31.8, 64
+// 56.7 / 54.3; 128 x 128, alone on their compute units: 32 (2113 x 1024 x 2048) 17.0 / 17.2, 48 23.7 / 23.3, 64 29.9 / 29.1.
+// (Tiles of 64 rows are slower throughout, two workgroups of 128 x 128 to a compute unit too: 6000 x 768 x 768 11.0 / 11.3.)
+inline bool quarter_kernel_wins(int bm, int bn, int64_t tiles, int64_t K, int64_t slices, int64_t batch) {
+  const int slots = quarter_slots(bm, bn);
+  if (slots == 0 || !wide_stages_ok(K, slices)) return false;
+  const int64_t stages = K >> 6, per = (stages + slices - 1) / slices;
+  if (stages - (slices - 1) * per < slots) return false;  // (the first stages are loaded unconditionally)
+  if (bm == 128 && bn == 128) return slices == 1 && tiles <= kComputeUnits && per >= 48;
+  const int64_t walked = slices == 1 && batch == 1 ? (tiles + kComputeUnits - 1) / kComputeUnits : 1;
+  return per * walked >= 32;
+}
+
 // Whether the ring kernels can run an [M, N] output over K: whole 32-wide stages, output rows of whole 16-byte pieces.
 inline bool ring_shape_ok(int64_t N, int64_t K) { return K % 32 == 0 && N % 8 == 0; }
 

@@ -10,6 +10,8 @@
 //       copy for r = 0: no bounds code at all.  RESIDUE=true is the copy for r != 0: decided
 //       once per tile, tiles past the last row or column run the same pipeline with clamped loads
 //       and masked stores.  Also the split-K reduction kernel.
+//   gemm_quarter_kernel.h  gemm_quarter_kernel<BM,BN,S>: the larger of these tiles by four waves, one per SIMD, where a
+//       workgroup walks many stages.
 //   gemm_tile_kernel.h   gemm_tile_kernel: the same tiles register-staged and bounds-checked throughout,
 //       for K that is not whole stages and output rows of any alignment, where these fill the chip.
 //   any_kernel.h         any_kernel: 64x64 tiles for operands and outputs of any shape, alignment
@@ -37,6 +39,7 @@
 #include "attention_kernel.h"
 #include "device_common.h"
 #include "gemm_ring_kernel.h"
+#include "gemm_quarter_kernel.h"
 #include "gemm_tile_kernel.h"
 #include "misc_kernels.h"
 #include "nimble_internal.h"
@@ -82,6 +85,12 @@ static int launch_ring(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
   dim3 grid(wgs, slices, p.grid[2]), block(WGM * WGN * 64);
   if constexpr (WS > 0) {
     if (wide_stages_ok(g.K, slices)) {
+      if constexpr (quarter_slots(BM, BN) > 0) {
+        if (quarter_kernel_wins(BM, BN, (int64_t)p.grid[0] * p.grid[2], g.K, slices, p.grid[2])) {
+          hipLaunchKernelGGL((gemm_quarter_kernel<BM, BN, quarter_slots(BM, BN)>), grid, dim3(256), 0, st, g, tiles_m, tiles_n, group_m);
+          return check_hip(hipGetLastError(), "quarter kernel launch");
+        }
+      }
       if (p.residue_copy)
         hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, WS, true>), grid, block, 0, st, g, tiles_m,
                            tiles_n, group_m);
@@ -106,6 +115,12 @@ static int launch_lone(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const dim3 grid(p.grid[0], p.split_k > 1 ? p.split_k : 1, p.grid[2]), block(WGM * WGN * 64);
   const int group_m = tiles_m < 4 ? tiles_m : 4;
+  if constexpr (quarter_slots(BM, BN) > 0) {
+    if (quarter_kernel_wins(BM, BN, (int64_t)p.grid[0] * p.grid[2], g.K, grid.y, p.grid[2])) {
+      hipLaunchKernelGGL((gemm_quarter_kernel<BM, BN, quarter_slots(BM, BN)>), grid, dim3(256), 0, st, g, tiles_m, tiles_n, group_m);
+      return check_hip(hipGetLastError(), "quarter kernel launch");
+    }
+  }
   if (p.residue_copy)
     hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, WS, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
   else
