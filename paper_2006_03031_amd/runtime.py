@@ -21,7 +21,7 @@ from . import binding as nb
 class _StepsOnly:
     """In place of the native one-call sequences where they cannot be loaded (not built, or built for another torch):
     leaves every call to the steps, which give the same results, and says so on the first call on a GPU."""
-    dense = attention = fused_attention = vm_run = set_workspace = staticmethod(lambda *a: None)
+    dense = attention = fused_attention = lstm_sequence = vm_run = set_workspace = staticmethod(lambda *a: None)
 
     def __init__(self, why: ImportError):
         self.why = why
@@ -57,7 +57,9 @@ def _bind_host_calls(device) -> None:
         return
     lib = nb.load()
     addresses = [ctypes.cast(getattr(lib, f), ctypes.c_void_p).value
-                 for f in ("nimble_dense_dyn", "nimble_attention_dyn", "nimble_attention_chain_dyn", "nimble_vm_run")]
+                 for f in ("nimble_dense_dyn", "nimble_attention_dyn", "nimble_attention_chain_dyn", "nimble_vm_run",
+                           "nimble_lstm_seq_preferred", "nimble_lstm_seq_workspace_bytes", "nimble_lstm_seq_pre_dyn",
+                           "nimble_lstm_seq_status")]
     _host_calls.bind(*addresses, torch._C._cuda_getDevice, _raw_stream, device.index or 0)
     _bound = True
 
@@ -333,6 +335,12 @@ def lstm_sequence(xs: torch.Tensor, w_x: torch.Tensor, w_h: torch.Tensor, bias: 
     """A whole sequence xs [T, B, Ix] through the cell: the inputs' share of the gates for all T*B tokens in one
     dense call (M = T*B dynamic, f32 output), then the token loop (lstm_sequence_pre).  w_x [4H, Ix] and
     w_h [4H, H] are the two halves of the fused weight (split_lstm_weight)."""
+    if not kw:
+        r = _host_calls.lstm_sequence(xs, w_x, w_h, bias, h0, c0, LSTM_SEQ_MAX_POLLS)
+        if isinstance(r, tuple):
+            return r
+        if r is not None:  # the loop gave up
+            return lstm_sequence_pre(r, w_h, h0, c0, one_launch=False)
     T, B, Ix = xs.shape
     pre = dense(xs.view(T * B, Ix), w_x, bias, nb.EPI_BIAS, nb.F32)
     return lstm_sequence_pre(pre.view(T, B, w_x.shape[0]), w_h, h0, c0, **kw)
