@@ -246,17 +246,31 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
 
   if constexpr (KG == 1) {
     const float inv = 1.0f / sum;
-    if (m_row < L) {
-      // accumulator element e of tile t: d = 32 t + 8 (e >> 2) + 4 h + (e & 3)
+    // Whole rows of 128 bytes through the ring's memory, so that they can go through the L2: chunk c of row r at slot
+    // c ^ (r & 7) of the wave's 4 KiB.  96 x 2048 118.1 -> 115.8 us, 48 x 512 9.9 -> 9.25.  A lone wave of one key block stores
+    // its 8-byte pieces as they are: the trip through LDS is on its critical path (12 x 23 3.38 us, 3.51 with it).
+    constexpr bool ROWS_WHOLE = RW > 1;
+    static_assert(RW * 256 <= KG * 2 * S * TILE, "the waves' rows reuse the ring");
+    if (ROWS_WHOLE) __syncthreads();  // (every wave has read its last tile)
+    uint4* stage = &ring[0][0][0][0] + rw * 256;
+    // accumulator element e of tile t: d = 32 t + 8 (e >> 2) + 4 h + (e & 3)
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          uint2 pk;
-          pk.x = pack_bf16x2(oacc[t][4 * b] * inv, oacc[t][4 * b + 1] * inv);
-          pk.y = pack_bf16x2(oacc[t][4 * b + 2] * inv, oacc[t][4 * b + 3] * inv);
+      for (int b = 0; b < 4; ++b) {
+        const uint2 pk = make_uint2(pack_bf16x2(oacc[t][4 * b] * inv, oacc[t][4 * b + 1] * inv),
+                                    pack_bf16x2(oacc[t][4 * b + 2] * inv, oacc[t][4 * b + 3] * inv));
+        if (ROWS_WHOLE)
+          *((uint2*)&stage[r32 * 8 + ((t * 4 + b) ^ (r32 & 7))] + h) = pk;
+        else if (m_row < L)
           *(uint2*)(o + head + (long long)m_row * D + t * 32 + b * 8 + h * 4) = pk;
-        }
+      }
+    asm volatile("" ::: "memory");  // (the wave's own accesses execute in order)
+#pragma unroll
+    for (int x = 0; ROWS_WHOLE && x < 4; ++x) {
+      const int row = x * 8 + (lane >> 3), c = lane & 7, m = m_row - r32 + row;
+      const uint4 v = stage[row * 8 + (c ^ (row & 7))];
+      if (m < L) store_through(o + head + (long long)m * D + c * 8, v);
     }
   } else {
     // the groups' outputs [group][row][64 d] (a row's 16-byte pieces spread over the banks) and their
@@ -298,8 +312,8 @@ __global__ void __launch_bounds__(RW* KG * 64) __attribute__((amdgpu_waves_per_e
       }
       const float inv = 1.0f / total;
       if (m < L)
-        *(uint2*)(o + head + (long long)m * D + c * 4) =
-            make_uint2(pack_bf16x2(a.x * inv, a.y * inv), pack_bf16x2(a.z * inv, a.w * inv));
+        store_through(o + head + (long long)m * D + c * 4,
+                      make_uint2(pack_bf16x2(a.x * inv, a.y * inv), pack_bf16x2(a.z * inv, a.w * inv)));
     }
   }
 }

@@ -147,8 +147,8 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // while the rest of the kernel runs, and the next kernel still finds them in the memory-side cache (non-temporal stores,
 // which do not stay there, cost it as much as they gain).  4096 x 4096 bf16 at K = 64 13.3 -> 10.7 us, at K = 1024 34.0 ->
 // 31.9; the feed-forward pair 2113 / 16129 x (1024 -> 4096 -> 1024) 54.1 / 235 -> 52.8 / 230.  For kernels whose wave
-// instructions write whole 128-byte lines: pieces of lines do not meet in the L2 any more (attention's 8-byte pieces:
-// 48 heads of 512 10.0 -> 10.9; the streaming kernel's 2-byte ones, 509 x 768 x 768, 5.65 -> 5.95).
+// instructions write whole 128-byte lines: pieces of lines do not meet in the L2 any more (attention from registers, 16
+// bytes of a row at a time: 48 heads of 512 10.0 -> 10.9; the streaming kernel's 2-byte ones, 509 x 768 x 768, 5.65 -> 5.95).
 // (The two wait states keep the next vector instruction, which the compiler does not know to be near a store, off the
 // data registers until the store has read them.)
 __device__ __forceinline__ void store_through(void* p, uint4 v) {
