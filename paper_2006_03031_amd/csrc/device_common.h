@@ -164,6 +164,14 @@ __device__ __forceinline__ void store_through(void* p, uint2 v) {
   store_through((unsigned long long*)p, ((unsigned long long)v.y << 32) | v.x);
 }
 
+// Whether the partial sums of a K-split launch stay in the L2s for the reduction behind it (plain stores).  Beside weights
+// that come from memory, which are the bound then, they do better there: layers of 5120 and 8192 columns, several in turn,
+// 50 / 100 / 128 rows 217 / 166 / 251 us a pass, 222 / 173 / 264 with the sums through the L2; small layers do not: 400 x 1024 x
+// 4096 13.4 / 12.9, 509 x 768 x 3072 12.7 / 11.9.  The line is what the L2s hold together.
+__device__ __forceinline__ bool partial_sums_stay(const GemmArgs& g, unsigned slices) {
+  return slices > 1 && (long long)g.N * g.K * 2 >= (32ll << 20);
+}
+
 // Direct global -> LDS load of 16 bytes per lane: lane i's data lands at LDS byte
 // address lds_addr + 16 i (lds_addr is wave-uniform and goes through M0).  It is
 // tracked by vmcnt only; the caller waits with s_waitcnt vmcnt before a barrier

@@ -433,6 +433,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
     constexpr bool GELU = decltype(gelu_tag)::value;
     if (g.out_f32) {
       float* C = (float*)g.c + (long long)z * g.sc + (long long)blockIdx.y * g.M * g.ldc;
+      const bool keep = partial_sums_stay(g, gridDim.y);
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
         const int m = m0 + wm * WM + j * 16 + fr_row;
@@ -446,7 +447,10 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
           for (int e = 0; e < 4; ++e) v[e] = fmaf(alpha, acc[i][j][e], bias4[i][e]);
           epilogue_of<GELU>(v);
           const float4 o = make_float4(v[0], v[1], v[2], v[3]);
-          store_through(C + (long long)m * g.ldc + n, __builtin_bit_cast(uint4, o));
+          if (keep)
+            *(float4*)(C + (long long)m * g.ldc + n) = o;
+          else
+            store_through(C + (long long)m * g.ldc + n, __builtin_bit_cast(uint4, o));
         }
       }
       return -1;
