@@ -355,8 +355,11 @@ class LstmSequenceGraph:
     """The token loop of one sequence, captured once per batch size B as a HIP graph and replayed: where
     nimble_lstm_loop_preferred says so the loop is one launch (with a recovery launch behind it that ends at once
     unless the loop's bounded waits ran out), else `steps` launches of the fused LSTM cell, with the same bits.  The graph
-    holds kernel launches only (where steps run in place, state is cleared by a fill kernel outside it).  The dynamic extent
+    holds kernel launches only (state is cleared by a fill kernel outside it).  The dynamic extent
     B is fixed per graph; a server keeps one graph per batch size it has seen.
+
+    run() starts from zero.  `graph` itself goes on from what hs[0] and c hold, so that a program which takes a long sequence
+    in parts puts the last h into hs[0], leaves c as it is and replays it.
 
     Two such loops find their places on the GPU beside each other.  Of three or more that replay at the same time some
     can run out of their waits, which costs milliseconds: four of 64 rows at H = 512 took 0.4 ms for 64 steps, and 17 in
@@ -381,6 +384,9 @@ class LstmSequenceGraph:
         self.xs = torch.zeros((steps, B, Ix), dtype=torch.bfloat16, device=dev)
         self.hs = torch.zeros((steps + 1, B, H), dtype=torch.bfloat16, device=dev)  # hs[0] = h_0
         self.c = torch.zeros((B, H), dtype=torch.float32, device=dev)
+        # one fill clears both (c seen as bf16: all of one type): 128 steps of 37 rows at H = 512 186.1 -> 184.5 us, 32 of one
+        # row 57.8 -> 56.5
+        self._first_state = [self.hs[0], self.c.view(torch.bfloat16)]
         loop_ix = 0 if project_inputs else Ix
         self.workspace = None
         supported = (project_inputs or Ix > 0) and nb.lstm_loop_supported(B, loop_ix, H)
@@ -388,9 +394,6 @@ class LstmSequenceGraph:
             raise nb.NimbleError(-3, f"the one-launch token loop does not run B={B}, Ix={loop_ix}, H={H}")
         if one_launch or (one_launch is None and supported and nb.lstm_loop_preferred(steps, B, loop_ix, H)):
             self.workspace = torch.empty(nb.lstm_loop_workspace_bytes(B, loop_ix, H), dtype=torch.uint8, device=dev)
-            # the loop reads its first state from here and writes it nowhere, so that no run has to clear anything
-            # (two launches a run: 128 steps of 37 rows at H = 512 189 -> 182.5 us)
-            self._zeros = torch.zeros((B, H), dtype=torch.float32, device=dev)
         # one eager pass so that nothing is lazily initialised during capture
         self._enqueue()
         torch.cuda.synchronize()
@@ -406,7 +409,7 @@ class LstmSequenceGraph:
         if self.workspace is not None:
             w = self.w_h if self.project_inputs else self.w
             nb.nimble_lstm_loop_dyn(self.xs.data_ptr(), self.pre.data_ptr() if self.project_inputs else 0, w.data_ptr(),
-                                    self.bias.data_ptr(), self._zeros.data_ptr(), self._zeros.data_ptr(), self.hs[1:].data_ptr(),
+                                    self.bias.data_ptr(), self.hs.data_ptr(), self.c.data_ptr(), self.hs[1:].data_ptr(),
                                     self.c.data_ptr(), self.steps, self.B, 0 if self.project_inputs else self.Ix, self.H,
                                     self.workspace.data_ptr(), self.workspace.numel(), LSTM_LOOP_MAX_POLLS, st)
             return
@@ -425,8 +428,6 @@ class LstmSequenceGraph:
         """Run the sequence from h_0 = c_0 = 0; returns (all h_t [steps,B,H], final c)."""
         if xs is not None:
             self.xs.copy_(xs)
-        if self.workspace is None:   # (the steps run on hs and c in place)
-            self.hs[0].zero_()
-            self.c.zero_()
+        torch._foreach_zero_(self._first_state)
         self.graph.replay()
         return self.hs[1:], self.c
