@@ -25,8 +25,9 @@ namespace nimble {
 //   groups, two register sets each; with four 12.7), the same with K = 1000 9.4; 500 x 500 x 2003 20.6 -> 18.0 -> 16.8;
 //   12 x 333 x 64 x 333 as A.B 88 -> 6.6 us.  128 x 128 tiles were measured too: no faster even at
 //   8000 x 1001 x 1003 (54 us against 51), half the speed on small grids.
+//   THROUGH: f32 outputs are written through the L2s (see any_output_stays).
 // ---------------------------------------------------------------------------
-template <bool KN, int P, int KG>
+template <bool KN, int P, int KG, bool THROUGH>
 __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, int tiles_n) {
   constexpr int BM = 64, BN = 64;
   constexpr int A_CH = BM * 8 / 256, B_CH = BN * 8 / 256;  // 16-byte chunks per thread and stage
@@ -238,7 +239,12 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
         const int row = p * RP + lane / WN, col = lane % WN;
         const int m = m0 + wm * WM + j * 16 + row, n = n_base + col;
         const float v = out_lds[row * ELD + col];
-        if (m < M && n < N) store_through(&C[(long long)m * g.ldc + n], v);  // (515 x 1001 x 1003 10.75 -> 10.5 us; bf16 no faster)
+        if (m < M && n < N) {
+          if (THROUGH)
+            store_through(&C[(long long)m * g.ldc + n], v);
+          else
+            C[(long long)m * g.ldc + n] = v;
+        }
       }
     } else {
       constexpr int LW = WN / 2, RP = 64 / LW;  // lanes per row (two columns each), rows per store

@@ -112,6 +112,18 @@ inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, i
   return N % bn != 0 && small <= 40 && any_four_groups(small, K);
 }
 
+// Whether a launch of any_kernel in `tiles` tiles, over all batches, leaves its output in the L2s.  Its rows start anywhere,
+// so that nearly all of the 128-byte runs which a wave writes fall into two lines.  Where every workgroup stores at about the
+// same time, the launch's end, f32 outputs gain by being written through all the same, since the next launch waits for it: one
+// round of workgroups, or two of a short K.  Otherwise the pieces that go to memory are what counts.  Microseconds, left / written
+// through: 144 tiles (515 x 1001 x 1003) 10.7 / 10.45, 230 (1433 x 635 x 322) 7.2 / 6.8, 256 (1000 x 1000 x 500) 8.0 / 7.5, 292 (4610 x
+// 212 x 52) 5.8 / 5.4, 504 (1287 x 1517 x 111) 7.0 / 6.4; 285 (1187 x 941 x 473, GELU) 11.6 / 12.1, 384 (3038 x 470 x 339, GELU) 10.7 /
+// 11.0, 573 (12205 x 147 x 138) 8.3 / 8.7, 752 (3000 x 1001 x 129) 9.7 / 10.0, 5250 (11134 x 1861 x 277) 52 / 79, 5922 (6000 x 4001 x 33)
+// 32 / 61.  bf16 is no faster in one round either.
+inline bool any_output_stays(int64_t tiles, int64_t K, bool out_f32) {
+  return !out_f32 || tiles > (K <= 128 ? 2 : 1) * kComputeUnits;
+}
+
 // Tiles of one launch of any_kernel (a launch holds less than 2^32 threads); larger outputs take several, each of at most
 // `tm` x `tn` tiles.  (With the rest in the second grid dimension every launch paid 0.1 to 0.2 us for finding its tile.)
 inline void any_launch_tiles(int64_t tiles_m, int64_t tiles_n, int64_t* tm, int64_t* tn) {

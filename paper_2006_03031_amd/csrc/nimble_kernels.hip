@@ -218,17 +218,18 @@ static int launch_any(const GemmArgs& g, hipStream_t st) {
       part.c = g.out_f32 ? (void*)((float*)g.c + m0 * g.ldc + n0) : (void*)((u16*)g.c + m0 * g.ldc + n0);
       const int pm = (part.M + 63) / 64, pn = (part.N + 63) / 64;
       const dim3 grid((unsigned)pm * (unsigned)pn, 1, (unsigned)g.batch);
-      if (g.b_is_kn) {
-        if (four)
-          hipLaunchKernelGGL((any_kernel<true, 2, 4>), grid, dim3(1024), 0, st, part, pm, pn);
+      auto launch = [&](auto kn, auto through) {
+        constexpr bool KN = decltype(kn)::value, THROUGH = decltype(through)::value;
+        if (four)  // (one round of workgroups)
+          hipLaunchKernelGGL((any_kernel<KN, 2, 4, true>), grid, dim3(1024), 0, st, part, pm, pn);
         else
-          hipLaunchKernelGGL((any_kernel<true, 4, 1>), grid, dim3(256), 0, st, part, pm, pn);
-      } else {
-        if (four)
-          hipLaunchKernelGGL((any_kernel<false, 2, 4>), grid, dim3(1024), 0, st, part, pm, pn);
-        else
-          hipLaunchKernelGGL((any_kernel<false, 4, 1>), grid, dim3(256), 0, st, part, pm, pn);
-      }
+          hipLaunchKernelGGL((any_kernel<KN, 4, 1, THROUGH>), grid, dim3(256), 0, st, part, pm, pn);
+      };
+      const bool through = !any_output_stays((int64_t)pm * pn * g.batch, g.K, g.out_f32 != 0);
+      if (g.b_is_kn)
+        through ? launch(std::true_type(), std::true_type()) : launch(std::true_type(), std::false_type());
+      else
+        through ? launch(std::false_type(), std::true_type()) : launch(std::false_type(), std::false_type());
       const int rc = check_hip(hipGetLastError(), "any kernel launch");
       if (rc != NIMBLE_OK) return rc;
     }
