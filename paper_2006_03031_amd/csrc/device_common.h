@@ -146,9 +146,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 // in the L2s, which are written back when the kernel ends, in front of whatever waits for it; these are on their way
 // while the rest of the kernel runs, and the next kernel still finds them in the memory-side cache (non-temporal stores,
 // which do not stay there, cost it as much as they gain).  4096 x 4096 bf16 at K = 64 13.3 -> 10.7 us, at K = 1024 34.0 ->
-// 31.9; the feed-forward pair 2113 / 16129 x (1024 -> 4096 -> 1024) 54.1 / 235 -> 52.8 / 230.  For kernels whose wave
-// instructions write whole 128-byte lines: pieces of lines do not meet in the L2 any more (attention from registers, 16
-// bytes of a row at a time: 48 heads of 512 10.0 -> 10.9; the streaming kernel's 2-byte ones, 509 x 768 x 768, 5.65 -> 5.95).
+// 31.9; the feed-forward pair 2113 / 16129 x (1024 -> 4096 -> 1024) 54.1 / 235 -> 52.8 / 230.  What goes to memory this way has to be
+// whole 64-byte pieces, better whole lines: pieces do not meet in the L2 any more (attention from registers, 16 bytes of a row
+// at a time: 48 heads of 512 10.0 -> 10.9; the streaming kernel's 2-byte ones, 509 x 768 x 768, 5.65 -> 5.95; rows that start
+// anywhere, see output_stays and any_output_stays).
 // (The two wait states keep the next vector instruction, which the compiler does not know to be near a store, off the
 // data registers until the store has read them.)
 __device__ __forceinline__ void store_through(void* p, uint4 v) {
@@ -170,6 +171,15 @@ __device__ __forceinline__ void store_through(void* p, uint2 v) {
 // 4096 13.4 / 12.9, 509 x 768 x 3072 12.7 / 11.9.  The line is what the L2s hold together.
 __device__ __forceinline__ bool partial_sums_stay(const GemmArgs& g, unsigned slices) {
   return slices > 1 && (long long)g.N * g.K * 2 >= (32ll << 20);
+}
+
+// An output store, plain or through the L2 (see output_stays).
+template <bool STAYS>
+__device__ __forceinline__ void store_out(void* p, uint4 v) {
+  if (STAYS)
+    *(uint4*)p = v;
+  else
+    store_through(p, v);
 }
 
 // Direct global -> LDS load of 16 bytes per lane: lane i's data lands at LDS byte

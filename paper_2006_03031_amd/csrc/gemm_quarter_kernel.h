@@ -40,7 +40,7 @@ struct QuarterLink {
   int parity = 0;       // its bias slot
 };
 
-template <int BM, int BN, int S>
+template <int BM, int BN, int S, bool STAYS>
 __device__ __forceinline__ int gemm_quarter_body(const GemmArgs& g, const int m0, const int n0, uint4* smem,
                                                  const QuarterLink& lk) {
   constexpr int WM = BM / 2, WN = BN / 2;
@@ -247,7 +247,7 @@ __device__ __forceinline__ int gemm_quarter_body(const GemmArgs& g, const int m0
     const bool edge = decltype(edge_tag)::value;
     if (g.out_f32) {
       float* C = (float*)g.c + (long long)z * g.sc + (long long)blockIdx.y * g.M * g.ldc;
-      const bool keep = partial_sums_stay(g, gridDim.y);
+      const bool keep = STAYS || partial_sums_stay(g, gridDim.y);
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
         const int m = m0 + wm * WM + j * 16 + fr_row;
@@ -280,7 +280,7 @@ __device__ __forceinline__ int gemm_quarter_body(const GemmArgs& g, const int m0
         const int row = (x & 1) * 8 + (lane >> 3), c = lane & 7;
         const int m = m0 + wm * WM + j * 16 + row, n = n0 + wn * WN + (x >> 1) * 64 + c * 8;
         if (edge && (m >= g.M || n >= g.N)) continue;
-        store_through(C + (long long)m * g.ldc + n, line[x]);
+        store_out<STAYS>(C + (long long)m * g.ldc + n, line[x]);
       }
     };
 #pragma unroll
@@ -317,7 +317,7 @@ __device__ __forceinline__ int gemm_quarter_body(const GemmArgs& g, const int m0
   return epi == NIMBLE_EPI_BIAS_GELU_ERF ? finish(std::true_type{}, std::false_type{}) : finish(std::false_type{}, std::false_type{});
 }
 
-template <int BM, int BN, int S>
+template <int BM, int BN, int S, bool STAYS>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
     gemm_quarter_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
   constexpr int kUint4 = S * (BM + BN) * 8 + 2 * (BN / 8) + 4 * 16 * (BN / 2) * 2 / 16;
@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))
       lk.next_m0 = tile_m * BM;
       lk.next_n0 = tile_n * BN;
     }
-    lk.stores = gemm_quarter_body<BM, BN, S>(g, m0, n0, smem, lk);
+    lk.stores = gemm_quarter_body<BM, BN, S, STAYS>(g, m0, n0, smem, lk);
     lk.filled = true;
     lk.slot = (lk.slot + turn) % S;
     lk.parity ^= 1;

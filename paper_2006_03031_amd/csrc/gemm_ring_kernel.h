@@ -56,7 +56,8 @@ struct RingLink {
 // past N-1 are fetched from the last one, so every load stays in bounds and the pipeline is the interior
 // one; their products land in rows and columns the epilogue does not store (N is a multiple of 8 here, so
 // a 16-byte piece of an output row is stored whole or not at all).
-template <int BM, int BN, int WGM, int WGN, int S, bool EDGE, int MODE, bool PF = false>
+// STAYS: the output is left in the L2s (output_stays).
+template <int BM, int BN, int WGM, int WGN, int S, bool EDGE, int MODE, bool PF, bool STAYS>
 __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, const int n0,
                                               uint4* smem, const RingLink lk = RingLink{}) {
   constexpr bool WIDE = MODE == RING_WIDE;
@@ -433,7 +434,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
     constexpr bool GELU = decltype(gelu_tag)::value;
     if (g.out_f32) {
       float* C = (float*)g.c + (long long)z * g.sc + (long long)blockIdx.y * g.M * g.ldc;
-      const bool keep = partial_sums_stay(g, gridDim.y);
+      const bool keep = STAYS || partial_sums_stay(g, gridDim.y);
 #pragma unroll
       for (int j = 0; j < TM; ++j) {
         const int m = m0 + wm * WM + j * 16 + fr_row;
@@ -486,7 +487,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
             const int c = lane & 7;
             const uint4 v = *(const uint4*)(region + h * (16 * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
             if (EDGE && (m0 + wm * WM + j * 16 + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
-            store_through(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
+            store_out<STAYS>(C + (long long)(m0 + wm * WM + j * 16 + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
           }
       }
       return EDGE ? -1 : NST;
@@ -522,7 +523,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
         const int c = lane & 7;
         const uint4 v = *(const uint4*)(region + h * (WM * 128) + row * 128 + ((c ^ ((row >> 1) & 7)) * 16));
         if (EDGE && (m0 + wm * WM + row >= g.M || n0 + wn * WN + h * 64 + c * 8 >= g.N)) continue;
-        store_through(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
+        store_out<STAYS>(C + (long long)(m0 + wm * WM + row) * g.ldc + n0 + wn * WN + h * 64 + c * 8, v);
       }
     return -1;
   };
@@ -537,7 +538,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
 // the 8-wave ping-pong, slower at whole rounds, so that shape is not built.
 // BM may be any multiple of 16 * WGM: the 256-wide tile is built at 128..256 rows so that the
 // dispatch function can pick the height at which the run-time M fills whole rounds of the chip.
-template <int BM, int BN, int WGM, int WGN, bool RESIDUE, int S = 4, bool WIDE = false>
+template <int BM, int BN, int WGM, int WGN, bool RESIDUE, int S, bool WIDE, bool STAYS>
 __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
   // WIDE: stages of 64 k (K must be a multiple of 64; the launcher sees to that), S = 2 to 4.
@@ -584,12 +585,12 @@ __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per
       }
     }
     if (RESIDUE && (m0 + BM > g.M || n0 + BN > g.N)) {  // same pipeline, clamped loads, masked stores
-      lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, true, kMode, kPF>(g, m0, n0, smem, lk);
+      lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, true, kMode, kPF, STAYS>(g, m0, n0, smem, lk);
       lk.filled = kPF && lk.next;
       lk.parity ^= 1;
       continue;
     }
-    lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, false, kMode, kPF>(g, m0, n0, smem, lk);
+    lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, false, kMode, kPF, STAYS>(g, m0, n0, smem, lk);
     lk.filled = kPF && lk.next;
     lk.parity ^= 1;
   }

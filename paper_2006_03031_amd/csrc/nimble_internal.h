@@ -2,6 +2,8 @@
 #ifndef NIMBLE_INTERNAL_H_
 #define NIMBLE_INTERNAL_H_
 
+#include <cstdint>
+
 #include "nimble.h"
 
 namespace nimble {
@@ -177,6 +179,29 @@ struct GemmArgs {
   int b_is_kn;
   int batch;
 };
+
+// Whether the tiled kernels leave their output in the L2s (plain stores) instead of writing it through them as it is made
+// (store_through in device_common.h).  What goes to memory by itself has to be whole 64-byte pieces: rows that do not start on
+// one cost about twice the writes.  Microseconds, left / written through.
+//   Rows of whole pieces: bf16 leaves as whole lines and is written through whatever its size, 4096 x 4096 x 64 12.1 / 10.1, 20000 x
+//   10240 x 128 130 / 123 (of 100 shapes none lost more than 1 %).  f32 leaves as half lines, which is as good while the output stays in
+//   the caches: 4736 x 2048 x 512 18.8 / 16.0, 4096 x 4096 x 256 21.6 / 18.7, 385 x 5760 x 1280 15.5 / 13.2; but 24 x 1024 x 1024 x 64 22.9 /
+//   23.5, 12 x 2048 x 2048 x 64 39.3 / 41.7, and from 32 MB on, beside weights that do not, 2000 x 12000 x 1536 85.7 / 92.2, 700 x 12288 x
+//   1536 44.6 / 46.7, 466 x 19520 x 320 (50 layers in turn) 25.4 / 30.1 (512 x 32000 x 1024 gains there, 43.6 / 42.1).
+//   Other rows: f32 loses mostly, 3000 x 4104 x 256 20.1 / 21.4, 10201 x 3864 x 64 48 / 86 (1605 x 840 x 192 with GELU gains, 5.8 / 5.5).  bf16
+//   gains where the output is large enough for its write-back at the kernel's end to show, 8658 x 696 x 128 9.6 / 8.0, 835 x 8336 x 480
+//   16.1 / 14.6, 4096 x 4104 x 64 14.4 / 12.8, and loses below 1 MB, 706 x 328 x 288 4.56 / 4.65, and when there is too much of it,
+//   3767 x 4616 x 1024 (60 layers in turn) 50 / 53, 12869 x 2488 x 960 64 / 73, 10201 x 7736 x 64 54 / 90.
+inline bool output_stays(const GemmArgs& g, int64_t slices) {
+  constexpr int64_t MB = 1 << 20;
+  if (slices > 1) return false;  // (partial_sums_stay)
+  const int64_t width = g.out_f32 ? 4 : 2, out = (int64_t)g.batch * g.M * g.N * width;
+  const bool few_weights = (int64_t)g.batch * g.N * g.K * 2 <= 8 * MB;
+  const uint64_t starts = (uint64_t)reinterpret_cast<uintptr_t>(g.c) | (uint64_t)(g.ldc * width) | (g.batch > 1 ? (uint64_t)(g.sc * width) : 0);
+  const bool whole = starts % 64 == 0;
+  if (g.out_f32) return !whole || out > (few_weights ? 64 : 32) * MB;
+  return !whole && (out < MB || out > (few_weights ? 36 : 24) * MB);
+}
 
 }  // namespace nimble
 #endif

@@ -59,6 +59,32 @@ static int check_hip(hipError_t e, const char* what) {
   return fail(NIMBLE_ERR_HIP, "%s: %s", what, hipGetErrorString(e));
 }
 
+// The copy of a ring kernel for this residue that stores the output the way that is better for it (output_stays).
+template <int BM, int BN, int WGM, int WGN, int S, bool WIDE>
+static int launch_ring_copy(const GemmArgs& g, const nimble_plan& p, dim3 grid, int tiles_m, int tiles_n, int group_m, hipStream_t st) {
+  auto launch = [&](auto residue, auto stays) {
+    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, residue, S, WIDE, stays>), grid, dim3(WGM * WGN * 64), 0, st, g, tiles_m,
+                       tiles_n, group_m);
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  if (output_stays(g, grid.y))
+    p.residue_copy ? launch(Yes(), Yes()) : launch(No(), Yes());
+  else
+    p.residue_copy ? launch(Yes(), No()) : launch(No(), No());
+  return check_hip(hipGetLastError(), "ring kernel launch");
+}
+
+template <int BM, int BN>
+static int launch_quarter(const GemmArgs& g, dim3 grid, int tiles_m, int tiles_n, int group_m, hipStream_t st) {
+  constexpr int S = quarter_slots(BM, BN);
+  if (output_stays(g, grid.y))
+    hipLaunchKernelGGL((gemm_quarter_kernel<BM, BN, S, true>), grid, dim3(256), 0, st, g, tiles_m, tiles_n, group_m);
+  else
+    hipLaunchKernelGGL((gemm_quarter_kernel<BM, BN, S, false>), grid, dim3(256), 0, st, g, tiles_m, tiles_n, group_m);
+  return check_hip(hipGetLastError(), "quarter kernel launch");
+}
+
 // WS: slots of the 64-wide ring (0: the tile is only built on the 32-wide ring).  The 64-wide
 // ring runs whenever K is whole 64-wide stages and every K slice gets at least one of them.
 template <int BM, int BN, int WGM, int WGN, int WS = 2, int S = 4>
@@ -82,63 +108,37 @@ static int launch_ring(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
     const unsigned resident = (unsigned)(kComputeUnits * kTilesPerCU[p.variant]);
     if (!one_tile_each && slices == 1 && p.grid[2] == 1 && wgs > resident) wgs = resident;
   }
-  dim3 grid(wgs, slices, p.grid[2]), block(WGM * WGN * 64);
+  const dim3 grid(wgs, slices, p.grid[2]);
   if constexpr (WS > 0) {
     if (wide_stages_ok(g.K, slices)) {
-      if constexpr (quarter_slots(BM, BN) > 0) {
-        if (quarter_kernel_wins(BM, BN, (int64_t)p.grid[0] * p.grid[2], g.K, slices, p.grid[2])) {
-          hipLaunchKernelGGL((gemm_quarter_kernel<BM, BN, quarter_slots(BM, BN)>), grid, dim3(256), 0, st, g, tiles_m, tiles_n, group_m);
-          return check_hip(hipGetLastError(), "quarter kernel launch");
-        }
-      }
-      if (p.residue_copy)
-        hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, WS, true>), grid, block, 0, st, g, tiles_m,
-                           tiles_n, group_m);
-      else
-        hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, false, WS, true>), grid, block, 0, st, g, tiles_m,
-                           tiles_n, group_m);
-      return check_hip(hipGetLastError(), "ring kernel launch");
+      if constexpr (quarter_slots(BM, BN) > 0)
+        if (quarter_kernel_wins(BM, BN, (int64_t)p.grid[0] * p.grid[2], g.K, slices, p.grid[2]))
+          return launch_quarter<BM, BN>(g, grid, tiles_m, tiles_n, group_m, st);
+      return launch_ring_copy<BM, BN, WGM, WGN, WS, true>(g, p, grid, tiles_m, tiles_n, group_m, st);
     }
   }
-  if (p.residue_copy)
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, S>), grid, block, 0, st, g, tiles_m,
-                       tiles_n, group_m);
-  else
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, false, S>), grid, block, 0, st, g, tiles_m,
-                       tiles_n, group_m);
-  return check_hip(hipGetLastError(), "ring kernel launch");
+  return launch_ring_copy<BM, BN, WGM, WGN, S, false>(g, p, grid, tiles_m, tiles_n, group_m, st);
 }
 
 // One tile per workgroup on the 64-wide ring only (the caller has checked that K fits it).
 template <int BM, int BN, int WGM, int WGN, int WS>
 static int launch_lone(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const dim3 grid(p.grid[0], p.split_k > 1 ? p.split_k : 1, p.grid[2]), block(WGM * WGN * 64);
+  const dim3 grid(p.grid[0], p.split_k > 1 ? p.split_k : 1, p.grid[2]);
   const int group_m = tiles_m < 4 ? tiles_m : 4;
-  if constexpr (quarter_slots(BM, BN) > 0) {
-    if (quarter_kernel_wins(BM, BN, (int64_t)p.grid[0] * p.grid[2], g.K, grid.y, p.grid[2])) {
-      hipLaunchKernelGGL((gemm_quarter_kernel<BM, BN, quarter_slots(BM, BN)>), grid, dim3(256), 0, st, g, tiles_m, tiles_n, group_m);
-      return check_hip(hipGetLastError(), "quarter kernel launch");
-    }
-  }
-  if (p.residue_copy)
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, WS, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
-  else
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, false, WS, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
-  return check_hip(hipGetLastError(), "ring kernel launch");
+  if constexpr (quarter_slots(BM, BN) > 0)
+    if (quarter_kernel_wins(BM, BN, (int64_t)p.grid[0] * p.grid[2], g.K, grid.y, p.grid[2]))
+      return launch_quarter<BM, BN>(g, grid, tiles_m, tiles_n, group_m, st);
+  return launch_ring_copy<BM, BN, WGM, WGN, WS, true>(g, p, grid, tiles_m, tiles_n, group_m, st);
 }
 
 // Tiles of 256 columns shared by two workgroups, half the columns and a compute unit each, on the 64-wide ring.
 template <int BM>
 static int launch_halves(const GemmArgs& g, const nimble_plan& p, hipStream_t st) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = g.N / 128;
-  const dim3 grid(p.grid[0] * 2), block(512);
+  const dim3 grid(p.grid[0] * 2);
   const int group_m = tiles_m < 4 ? tiles_m : 4;
-  if (p.residue_copy)
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, 128, 4, 2, true, 3, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
-  else
-    hipLaunchKernelGGL((gemm_ring_kernel<BM, 128, 4, 2, false, 3, true>), grid, block, 0, st, g, tiles_m, tiles_n, group_m);
-  return check_hip(hipGetLastError(), "ring kernel launch");
+  return launch_ring_copy<BM, 128, 4, 2, 3, true>(g, p, grid, tiles_m, tiles_n, group_m, st);
 }
 
 // Whether the LDS-staged streaming kernel can run a weight-streaming launch: one 16-row tile per
