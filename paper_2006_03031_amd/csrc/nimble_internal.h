@@ -117,11 +117,11 @@ inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, i
 // Whether a launch of any_kernel in `tiles` tiles, over all batches, leaves its output in the L2s.  Its rows start anywhere,
 // so that nearly all of the 128-byte runs which a wave writes fall into two lines.  Where every workgroup stores at about the
 // same time, the launch's end, f32 outputs gain by being written through all the same, since the next launch waits for it: one
-// round of workgroups, or two of a short K.  Otherwise the pieces that go to memory are what counts.  Microseconds, left / written
-// through: 144 tiles (515 x 1001 x 1003) 10.7 / 10.45, 230 (1433 x 635 x 322) 7.2 / 6.8, 256 (1000 x 1000 x 500) 8.0 / 7.5, 292 (4610 x
-// 212 x 52) 5.8 / 5.4, 504 (1287 x 1517 x 111) 7.0 / 6.4; 285 (1187 x 941 x 473, GELU) 11.6 / 12.1, 384 (3038 x 470 x 339, GELU) 10.7 /
-// 11.0, 573 (12205 x 147 x 138) 8.3 / 8.7, 752 (3000 x 1001 x 129) 9.7 / 10.0, 5250 (11134 x 1861 x 277) 52 / 79, 5922 (6000 x 4001 x 33)
-// 32 / 61.  bf16 is no faster in one round either.
+// round of workgroups, or two of a short K.  Otherwise the pieces that go to memory are what counts.  Microseconds, left /
+// written through: 144 tiles (515 x 1001 x 1003) 10.7 / 10.45, 230 (1433 x 635 x 322) 7.2 / 6.8, 256 (1000 x 1000 x 500) 8.0 / 7.5,
+// 292 (4610 x 212 x 52) 5.8 / 5.4, 504 (1287 x 1517 x 111) 7.0 / 6.4; 285 (1187 x 941 x 473, GELU) 11.6 / 12.1, 384 (3038 x 470 x
+// 339, GELU) 10.7 / 11.0, 573 (12205 x 147 x 138) 8.3 / 8.7, 752 (3000 x 1001 x 129) 9.7 / 10.0, 5250 (11134 x 1861 x 277)
+// 52 / 79, 5922 (6000 x 4001 x 33) 32 / 61.  bf16 is no faster in one round either.
 inline bool any_output_stays(int64_t tiles, int64_t K, bool out_f32) {
   return !out_f32 || tiles > (K <= 128 ? 2 : 1) * kComputeUnits;
 }
@@ -183,15 +183,17 @@ struct GemmArgs {
 // Whether the tiled kernels leave their output in the L2s (plain stores) instead of writing it through them as it is made
 // (store_through in device_common.h).  What goes to memory by itself has to be whole 64-byte pieces: rows that do not start on
 // one cost about twice the writes.  Microseconds, left / written through.
-//   Rows of whole pieces: bf16 leaves as whole lines and is written through whatever its size, 4096 x 4096 x 64 12.1 / 10.1, 20000 x
-//   10240 x 128 130 / 123 (of 100 shapes none lost more than 1 %).  f32 leaves as half lines, which is as good while the output stays in
-//   the caches: 4736 x 2048 x 512 18.8 / 16.0, 4096 x 4096 x 256 21.6 / 18.7, 385 x 5760 x 1280 15.5 / 13.2; but 24 x 1024 x 1024 x 64 22.9 /
-//   23.5, 12 x 2048 x 2048 x 64 39.3 / 41.7, and from 32 MB on, beside weights that do not, 2000 x 12000 x 1536 85.7 / 92.2, 700 x 12288 x
-//   1536 44.6 / 46.7, 466 x 19520 x 320 (50 layers in turn) 25.4 / 30.1 (512 x 32000 x 1024 gains there, 43.6 / 42.1).
-//   Other rows: f32 loses mostly, 3000 x 4104 x 256 20.1 / 21.4, 10201 x 3864 x 64 48 / 86 (1605 x 840 x 192 with GELU gains, 5.8 / 5.5).  bf16
-//   gains where the output is large enough for its write-back at the kernel's end to show, 8658 x 696 x 128 9.6 / 8.0, 835 x 8336 x 480
-//   16.1 / 14.6, 4096 x 4104 x 64 14.4 / 12.8, and loses below 1 MB, 706 x 328 x 288 4.56 / 4.65, and when there is too much of it,
-//   3767 x 4616 x 1024 (60 layers in turn) 50 / 53, 12869 x 2488 x 960 64 / 73, 10201 x 7736 x 64 54 / 90.
+//   Rows of whole pieces: bf16 leaves as whole lines and is written through whatever its size, 4096 x 4096 x 64 12.1 / 10.1,
+//   20000 x 10240 x 128 130 / 123 (82 shapes: 4 % less in the mean, none lost more than 1.4 %).  f32 leaves as half lines, which is
+//   as good while the output stays in the caches: 4736 x 2048 x 512 18.8 / 16.0, 4096 x 4096 x 256 21.6 / 18.7, 385 x 5760 x 1280
+//   15.5 / 13.2; but 24 x 1024 x 1024 x 64 22.9 / 23.5, 12 x 2048 x 2048 x 64 39.3 / 41.7, and beside more weights from 32 MB on:
+//   2000 x 12000 x 1536 85.7 / 92.2, 700 x 12288 x 1536 44.6 / 46.7, 466 x 19520 x 320 (50 layers in turn) 25.4 / 30.1 (512 x 32000 x
+//   1024 would gain, 43.6 / 42.1).
+//   Other rows: f32 loses mostly, 3000 x 4104 x 256 20.1 / 21.4, 10201 x 3864 x 64 48 / 86 (1605 x 840 x 192 with GELU would gain,
+//   5.8 / 5.5).  bf16 gains where the output is large enough for its write-back at the kernel's end to show, 8658 x 696 x 128
+//   9.6 / 8.0, 835 x 8336 x 480 16.1 / 14.6, 4096 x 4104 x 64 14.4 / 12.8 (4 of some 90 shapes lose 2 to 4 %, 5022 x 792 x 224
+//   8.2 / 8.5), and loses below 1 MB, 706 x 328 x 288 4.56 / 4.65, and when there is too much of it, 3767 x 4616 x 1024 (60 layers
+//   in turn) 50 / 53, 12869 x 2488 x 960 64 / 73, 10201 x 7736 x 64 54 / 90.
 inline bool output_stays(const GemmArgs& g, int64_t slices) {
   constexpr int64_t MB = 1 << 20;
   if (slices > 1) return false;  // (partial_sums_stay)

@@ -42,12 +42,12 @@ def test_other_operands_are_left_to_the_steps(rt):
     assert native(*operands(5, 3, 64, 1024), polls) is None   # not the one-launch loop's by default
     h, c, one = rt.lstm_sequence(*operands(5, 3, 64, 1024))
     assert h.shape == (5, 3, 1024) and c.shape == (3, 1024)
-    # a cell state at any address, as for the steps
+    # a cell state that does not start on 16 bytes: refused by the loop, as before, taken by the steps
     buf = torch.zeros(2 * 128 + 1, device="cuda")
+    c0 = buf[1:].view(2, 128)
+    assert native(*ops[:5], c0, polls) is None
+    with pytest.raises(rt.nb.NimbleError, match="16-byte aligned"):
+        rt.lstm_sequence(*ops[:5], c0)
     want = rt.lstm_sequence(*ops[:5], torch.zeros((2, 128), device="cuda"))
-    try:
-        got = rt.lstm_sequence(*ops[:5], buf[1:].view(2, 128))
-    except Exception as e:
-        assert "align" in str(e)
-    else:
-        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    got = rt.lstm_sequence(*ops[:5], c0, one_launch=False)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
