@@ -31,6 +31,13 @@ def _to_dev(arr):
     return t.view(torch.bfloat16).cuda()
 
 
+def _kernel_of(plan) -> str:
+    """The kernel that the rows of a tiled plan's first launch run, with its tile."""
+    lone = plan.grid[0] * plan.grid[1] * plan.grid[2] <= 256
+    four_waves = plan.block == 256 and (plan.bn == 256 or plan.bm == 256 or (plan.bm == 128 and lone))
+    return f"{'gemm_quarter_kernel' if four_waves else 'gemm_ring_kernel'} {plan.bm}x{plan.bn}"
+
+
 def _traffic_note():
     """HBM-side bytes per dense launch from two rocprofv3 --pmc runs (FETCH_SIZE, then
     WRITE_SIZE, each scaled by a plain copy of known size); the summary of those runs is
@@ -149,11 +156,11 @@ def bench_config5(steps: int, warmup: int):
     k_ms = statistics.median(kernel_ms)
     launches = 2 * steps
     achieved = total_flops / (k_ms * 1e-3) / 1e12
-    plans = sorted({nb.dense_plan(M, N1, K1).name for M in Ms} | {nb.dense_plan(M, N2, K2).name for M in Ms})
+    plans = sorted({_kernel_of(nb.dense_plan(M, n, k)) for M in Ms for n, k in ((N1, K1), (N2, K2))})
     roofline = _roof("mfma", achieved, "TFLOP/s", traffic=_traffic_note(),
                      traffic_source="profiles/dense_config5_hbm_traffic.txt (rocprofv3 --pmc runs of this "
                                     "command, bytes per dense launch; not measured by this run)",
-                     kernel="gemm_ring_kernel (" + ",".join(plans) + ")", launches=launches,
+                     kernel=", ".join(plans), launches=launches,
                      avg_launch_us=round(k_ms * 1e3 / launches, 2), flops_per_launch=round(total_flops / launches))
     return {
         "value": total_flops / elapsed / 1e12, "ms_per_step": elapsed * 1e3 / steps, "roofline": roofline,
