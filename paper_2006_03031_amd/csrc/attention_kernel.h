@@ -29,7 +29,7 @@ namespace nimble {
 //   some row's maximum moved.  (Rescaling only once a maximum has grown by 2^8 saves a tenth of the time, but then the
 //   largest probabilities are no longer exactly 1 and the error against 64 bits grows from 2.19e-3 to 2.3e-3.)
 //   What bounds it: per block of 64 keys and 32 rows about 1050 clocks of vector instructions, half of them the
-//   exponentials, under which 512 clocks of MFMA run; 96 heads of 2048 keys: 118-120 us (860-870 TFLOP/s), the vector
+//   exponentials, under which 512 clocks of MFMA run; 96 heads of 2048 keys: 115-120 us (860-900 TFLOP/s), the vector
 //   instructions alone 84-96 at 2.1-2.4 GHz.  The kernel before it (16 rows per wave, V transposed through
 //   registers with 2-byte LDS writes): 216 us; 12 heads of 512 keys 9.8 -> 5.8.  Without the overlap of
 //   two blocks 140; eight row waves per workgroup 123, two 152.

@@ -80,8 +80,8 @@ __device__ __forceinline__ float epilogue(float acc, float alpha, float bias, in
 // The same for N values at a time with the choice made outside.  With a choice per value there is a branch per value, and
 // left to itself the compiler computes one or two values at a time, each a chain of a dozen dependent instructions; here
 // N chains go side by side (the empty statements keep the N results of a step together).  Eight at a time, with their
-// choice outside: the feed-forward pair of 4500 / 8069 / 16129 tokens 82.2 / 123.1 / 227.4 -> 79.9 / 120.6 / 222 us,
-// 800 x 3072 x 768 with GELU 9.97 -> 9.77.
+// choice outside, as graph replays on the eight-wave kernels: the feed-forward pair of 4500 / 8069 tokens 83.1 / 124.0 ->
+// 80.2 / 121.6 us (16129 tokens 224 / 223, within the spread of the runs), 800 x 3072 x 768 with GELU 10.05 -> 9.9.
 template <bool GELU, int N>
 __device__ __forceinline__ void epilogue_of(float (&v)[N]) {
   if (!GELU) return;

@@ -24,10 +24,10 @@ namespace nimble {
 //   (1 %: less toggling).
 //   The loads past a tile's last stage are the next tile's first ones, so a walk over several tiles never drains its ring.
 //   Arithmetic: the sums of the ring kernels in the same order, bit for bit.
-//   Measured, eight waves / four: 8192^3 752 / 688 us, 8192 x 4096 x 4096 190 / 179, 16384 x 1024 x 4096 95.7 / 91.3,
-//   10240 x 1024 x 4096 in 160-row tiles 66.4 / 62.8; one 64-wide stage of a 256 x 256 tile 1.39 / 1.31 us.  Without its
-//   barriers and waits it is no faster; without the loads 8192^3 would take 617 us (2.12 GHz instead of 1.90), without the
-//   fragment reads 637, without both 525 (2.40 GHz).  Eight waves on the same ring, and in two groups that multiply and
+//   Measured, eight waves / four: 8192^3 737 / 690 us, 8192 x 4096 x 4096 190 / 179, 16384 x 1024 x 4096 102.6 / 96.0,
+//   10240 x 1024 x 4096 in 160-row tiles 69.6 / 65.6; one 64-wide stage of a 256 x 256 tile 1.39 / 1.31 us.  Without its
+//   barriers and waits it is no faster; on a card where 8192^3 took 708 us as it is (1.90 GHz), 617 without the loads (2.12 GHz),
+//   637 without the fragment reads, 525 without both (2.40 GHz).  Eight waves on the same ring, and in two groups that multiply and
 //   read in turn, were no faster than the ring kernels and 7 % slower.  Where it does not pay: see quarter_kernel_wins.
 // ---------------------------------------------------------------------------
 // What one tile of a workgroup's walk hands to the next.

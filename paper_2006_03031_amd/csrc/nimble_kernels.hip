@@ -2,15 +2,15 @@
 // (Section 3.5).  bf16 operands, f32 accumulation on the matrix cores, f32 epilogue.
 //
 // Kernel family (one header each under csrc/)
-//   gemm_ring_kernel.h   gemm_ring_kernel<BM,BN,WGM,WGN,RESIDUE>: every tiled variant (32x128,
-//       64x128, 128x128, 256x128, and the 256-wide tile at heights 128..320).  A ring of four
-//       32-wide K stages filled by direct global->LDS loads, 16x16x32 MFMA with in-place
+//   gemm_ring_kernel.h   gemm_ring_kernel<BM,BN,WGM,WGN,RESIDUE,S,WIDE,STAYS>: every tiled variant (32x128,
+//       64x128, 128x128, 256x128, and the 256-wide tile at heights 128..320).  A ring of S
+//       64-wide (WIDE) or four 32-wide K stages filled by direct global->LDS loads, 16x16x32 MFMA with in-place
 //       accumulators, the next stage's fragments read in between the MFMAs, an epilogue that
 //       transposes through LDS so every store is a full 128-byte line.  RESIDUE=false is the
 //       copy for r = 0: no bounds code at all.  RESIDUE=true is the copy for r != 0: decided
 //       once per tile, tiles past the last row or column run the same pipeline with clamped loads
-//       and masked stores.  Also the split-K reduction kernel.
-//   gemm_quarter_kernel.h  gemm_quarter_kernel<BM,BN,S>: the larger of these tiles by four waves, one per SIMD, where a
+//       and masked stores.  STAYS: the copy with plain output stores.  Also the split-K reduction kernel.
+//   gemm_quarter_kernel.h  gemm_quarter_kernel<BM,BN,S,STAYS>: the larger of these tiles by four waves, one per SIMD, where a
 //       workgroup walks many stages.
 //   gemm_tile_kernel.h   gemm_tile_kernel: the same tiles register-staged and bounds-checked throughout,
 //       for K that is not whole stages and output rows of any alignment, where these fill the chip.
