@@ -25,8 +25,7 @@ namespace nimble {
 //   wave multiplies its stages of x_t, loaded a step ahead, or its K range of h_{t-1}, and leaves its partial sums
 //   in LDS; after one barrier the first R U lanes, one per (row, unit), add them up and update the cell.  c_t
 //   stays in that lane's register.
-//   Hand-over of h_t: 64-bit words of four neighbouring units of a row, stored with device scope into buffer
-//   t & 1 of two, in an order in which a wave stores 128 contiguous bytes (8 workgroups' words in one line: 2.4 us
+//   Hand-over of h_t: 64-bit words of four neighbouring units of a row, stored into buffer t & 1 of two, in an order in which a wave stores 128 contiguous bytes (8 workgroups' words in one line: 2.4 us
 //   per step) and loads 512 (8 rows of 32 k or 4 rows of 64 k).  |h| <= 1 leaves bit 14 of a bf16, the top bit of
 //   its exponent, zero: in the first value of a word it carries the phase, which changes with every use of a
 //   buffer, in the second a mark that values of the word are NaN (then written as 0x3fff, which no h is).  A
@@ -38,6 +37,19 @@ namespace nimble {
 //   looks for this step's, and loads of one address never go back: the word it finds is one of these two, and one bit
 //   tells them apart.  The words are
 //   cleared by lstm_seq_init_kernel ahead of the launch on the same stream (the first phase is 1).
+//   Scope of the stores.  A store of device scope goes through to the memory side (695 clocks until it is done, where a
+//   plain one takes 273), and a load of device scope finds a plain store of the same XCD in that XCD's L2: one way
+//   between two workgroups of an XCD 957 clocks with stores of device scope, 519 with plain ones (1370 between XCDs).
+//   So each workgroup leaves its XCD's number in the first of its words of buffer 0, which nobody writes before every
+//   workgroup has read them (that takes h_2), without the phase bit; a workgroup that finds all numbers
+//   of its row group equal to its own stores plainly from then on, any other with device scope.  Nobody relies on the
+//   others' choice: all are right, the plain stores are seen by all who can look for them.  128 steps, pre
+//   form of H = 512, 1 / 4 / 16 rows 156 / 150 / 165 -> 122 / 126 / 137 us.
+//   x_t comes from memory, and what a compute unit's waves load returns in order, so that polls queue behind x.  The waves
+//   that multiply x load it straight into LDS, three steps ahead and right behind the barrier, when this step's
+//   polls are over and the next ones are some 900 clocks away (loaded into registers behind the products a step
+//   ahead 4 / 37 rows, H = Ix = 512, took 153 / 175 us, into LDS but behind the products 152 / 162, by the polling waves as their words
+//   had arrived 155 / 179; now 139 / 151; before the plain stores 163 / 169).
 //   Every wait is bounded: a wave polls at most max_polls times per step, looking at the give-up word with every
 //   eighth; a wave that runs out sets it, and every workgroup leaves at its next check.  So the
 //   grid drains whatever happens (fewer workgroups resident than launched, a stalled neighbour).  Then either
@@ -46,18 +58,20 @@ namespace nimble {
 //   Arithmetic: identical, bit for bit, to the per-step kernel on the same shapes (stream_kernel: the same
 //   eight or four ranges of K stages, the same two accumulators per range, the same order of adding the ranges' sums,
 //   the same cell function).
-//   What bounds it: one trip through the memory system per step (store, then a load that sees it), about half of the step;
-//   the rest is a chain of MFMAs, LDS sums, barrier and cell arithmetic.  Microseconds per step, pre form at
-//   1 / 4 rows: H = 512 1.10 / 1.17, H = 1024 1.41 / 1.56, H = 256 1.14 / - (32-bit words with a step tag each, four lanes
-//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 / 64 rows, H = Ix = 512: 1.24 /
-//   1.34 / 1.34 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
+//   What bounds it: a chain of, in clocks by time stamps, products and partial sums to LDS 400, barrier 150, sums 250, cell 600,
+//   and the way through the L2 to the slowest workgroup 700.  Microseconds per step, pre form at
+//   1 / 4 rows: H = 512 0.96 / 0.99, H = 1024 1.41 / 1.56, H = 256 0.95 / - (32-bit words with a step tag each, four lanes
+//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 rows, H = Ix = 512: 1.09 /
+//   1.18 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
 //   per cell, 32-byte stores 2.31; one lane per cell, 128-byte stores 1.95; a row group's workgroups on one XCD
 //   and a late first poll 1.56; operands polled straight into their registers, no address arithmetic in the loop 1.37.
 //   Tried and not kept: system scope, exchanges instead of stores, raised priority for the cells (no change); a
 //   first poll whose delay adapts, a step later for each failure and a quarter earlier for each success (1.7-1.9:
 //   of 128 waves some one always fails); every wave multiplying its own 16 gate rows over the whole of K (4.1: the
-//   waves' reads of all of h cost more LDS time than the sums saved); workgroup-scope loads within one XCD (the
-//   words never become visible).
+//   waves' reads of all of h cost more LDS time than the sums saved); workgroup-scope loads within one XCD (they
+//   hit the compute unit's own cache, and the words never become visible); with plain stores, four lanes per cell, one per gate
+//   (1 / 4 / 37 rows 122 / 127 / 151 -> 120 / 131 / 149), and the products of all four groups ahead of their sums
+//   (122 / 126 -> 125 / 128).
 // ---------------------------------------------------------------------------
 struct LstmSeqArgs {
   const u16* x;       // [T, B, Ix], or null
@@ -95,6 +109,9 @@ template <int Q>
 __device__ __forceinline__ uint32_t quad_lane(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, Q * 0x55, 0xf, 0xf, true);
 }
+
+// the XCD that the wave runs on
+__device__ __forceinline__ uint32_t xcc_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }
 
 constexpr uint32_t kHandOverPhase = 0x4000u, kHandOverNan = 0x40000000u;
 
@@ -138,6 +155,10 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   constexpr int CELLS = R * U;  // one lane each, in the first waves
   // partial sums [buffer][wave][cell]: the four gates of a cell are one 16-byte word
   __shared__ f32x4 red[2][8][CELLS];
+  // operands of the waves that multiply x: three steps' [chunk of 8 k][row] (MIX keeps them in registers)
+  constexpr bool XR = !PRE && !MIX;
+  constexpr int XLOADS = NU * 4 * R > 64 ? NU * 4 * R / 64 : 1;  // of 64 chunks, per step
+  __shared__ uint4 x_ring[XR ? 7 : 1][3][XR ? XLOADS * 64 : 1];
   __shared__ int s_abort[2];  // by step parity: a wave already polling for step t+1 never writes the word step t reads
 
   // Workgroups go to the 8 XCDs in turn: a row group's workgroups are those of one XCD (of two, above 32 of them), so that
@@ -149,6 +170,11 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   if (group >= row_groups) return;
   const int wg = (xcd & (span - 1)) * per_xcd + nth % per_xcd;
   const int row0 = group * R;
+  // hand-over words of this row group: [buffer][unit / 4][row]
+  const int plane = rs * (H >> 2);
+  unsigned long long* exch = a.exch + (long long)row0 * (H >> 1);  // (groups but the last are R rows of rs = R)
+  const unsigned long long here = xcc_id() + 1;  // (1 ... 8: neither phase nor mark)
+  if (span == 1 && threadIdx.x == 0) __hip_atomic_store(exch + wg * G * rs, here, __ATOMIC_RELAXED, SCOPE);
   const int rows = B - row0 < R ? B - row0 : R;  // of this group
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -204,10 +230,18 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
 
   if (tid < 2) s_abort[tid] = 0;
   __syncthreads();
-
-  // hand-over words of this row group: [buffer][unit / 4][row]
-  const int plane = rs * (H >> 2);
-  unsigned long long* exch = a.exch + (long long)row0 * (H >> 1);  // (groups but the last are R rows of rs = R)
+  // whether the row group's workgroups share an XCD, that is an L2
+  bool near = false;
+  if (span == 1) {
+    const unsigned long long* ids = exch + (lane < n_wg ? lane : 0) * G * rs;
+    const uint32_t most = a.max_polls < 256u ? a.max_polls : 256u;
+    unsigned long long v = 0;
+    for (uint32_t polls = 0; polls < most; ++polls) {
+      v = __hip_atomic_load(ids, __ATOMIC_RELAXED, SCOPE);
+      if (__all(v != 0ull)) break;
+    }
+    near = __all(v == here);
+  }
   // word of this lane in a load: R = 8: 32 k, rows by lane & 7, pieces of 4 k by gq and bit 3; R = 4: 64 k
   uint32_t ask;   // (bytes, as is the next)
   uint32_t from;  // this lane's operand row in x_t or h_0 (lanes past the group's rows: columns never used)
@@ -232,12 +266,29 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       if (MIX ? 2 * s + 1 < x_units : ORDER != 0 || s < n_st) f[2 * s + 1] = *(const uint4*)at(src + (2 * s + 1) * STEP, from);
     }
   };
+  uint32_t x_at = 0;  // (bytes) of the lane's chunk in x_t
+  if (XR && of_x) {
+    const int row = lane & (R - 1), chunk = lane / R & (NU * 4 - 1);
+    x_at = (uint32_t)((row0 + (row < rows ? row : rows - 1)) * Ix + k_begin + (chunk >> 2) * STEP + (chunk & 3) * 8) * 2u;
+  }
+  const uint32_t x_lds = lds_addr_of(&x_ring[XR && of_x ? wave : 0][0][0]);
+  auto load_x = [&](int t) {  // x of step t = 1, 2, ... into its slot (past the last step that one's again: the waits count)
+    const u16* src = a.x + (long long)((t < T ? t : T) - 1) * B * Ix;
+#pragma unroll
+    for (int l = 0; l < XLOADS; ++l) dma16_so(x_at, src + l * 2 * STEP, x_lds + (uint32_t)(t % 3 * XLOADS + l) * 1024u);
+  };
+  if (XR && of_x) {
+    load_x(1);
+    load_x(2);
+    load_x(3);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  }
   if (MIX) {
     const int orow = row0 + (r < rows ? r : rows - 1);
 #pragma unroll
     for (int j = 0; j < NU; ++j)
       f[j] = *(const uint4*)((j < x_units ? a.x + orow * Ix + k_begin : a.h0 + orow * H + h_begin) + j * STEP + gq * 8);
-  } else {
+  } else if (!XR || !of_x) {
     load_rows(of_x ? a.x : a.h0);
   }
   const bool waits = MIX ? x_units < NU : !of_x && n_st > 0;  // for h_t
@@ -254,6 +305,17 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       pr[q] = PRE ? *at(a.pre + q * H, pre_at) : bf2f(a.bias[q * H + wg * U + cg * 4 + uu]);
   }
   for (int t = 1;; ++t) {
+    if (XR && of_x) {
+      // this step's loads were issued three steps ago: behind them are those of two more steps and, from the cells' waves,
+      // at least a store per step
+      if (cells)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XLOADS + 3) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XLOADS) : "memory");
+      const uint4* slot = &x_ring[wave][t % 3][0];
+#pragma unroll
+      for (int j = 0; j < NU; ++j) f[j] = slot[(j * 4 + gq) * R + (r & (R - 1))];
+    }
     // (two groups at a time: four independent chains, and no more accumulators than that)
 #pragma unroll
     for (int g0 = 0; g0 < G; g0 += 2) {
@@ -274,13 +336,14 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       for (int g = 0; g < 2; ++g)
         if (r < R) red[t & 1][wave][((g0 + g) * R + r) * 4 + gq] = ORDER == 0 ? acc[g][0] + acc[g][1] : acc[g][0];  // rows past the group's are never used
     }
-    if (of_x && t < T) load_rows(a.x + (long long)t * B * Ix);
+    if (MIX && of_x && t < T) load_rows(a.x + (long long)t * B * Ix);
     if (PRE && owner && t < T) {
       const float* src = a.pre + (long long)t * B * 4 * H;
 #pragma unroll
       for (int q = 0; q < 4; ++q) pr_next[q] = *at(src + q * H, pre_at);
     }
     __syncthreads();
+    if (XR && of_x) load_x(t + 3);  // (into this step's slot, which the wave has read)
     const int aborted = __builtin_amdgcn_readfirstlane(s_abort[t & 1]);  // written before the barrier (after an abort the cells are garbage, and not used)
 
     if (cells) {
@@ -311,8 +374,12 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
           shi = (hi & 0x4000u ? 0x3fffu : hi & 0xffffu) | (hi & 0x40000000u ? 0x3fff0000u : hi & 0xffff0000u);
         }
         slo |= lstm_seq_phase(t);
-        __hip_atomic_store(at(exch + (long long)(t & 1) * plane, put), ((unsigned long long)shi << 32) | slo,
-                           __ATOMIC_RELAXED, SCOPE);
+        unsigned long long* word = at(exch + (long long)(t & 1) * plane, put);
+        const unsigned long long v = ((unsigned long long)shi << 32) | slo;
+        if (near)
+          __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        else
+          __hip_atomic_store(word, v, __ATOMIC_RELAXED, SCOPE);
         *(uint2*)at(a.h_seq + (long long)(t - 1) * B * H, cell * 2u) = make_uint2(lo, hi);
       }
     }
@@ -332,9 +399,16 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       // the best: the edge moves by two units, so a little later); pre form, H = 512, 16 rows 207, 188, 185, 187, 192; 24 rows
       // of 256 198, 183, 179, 176, 181, of 1024 271, 257, 252, 255, 247.  Up to 4 rows, pre form, with 12, 13, 14, 15, 16 units,
       // means over the XCD it starts on: H = 512, 1 row 175, 163, 159, 165, 167, H = 256 175, 163, 148, 153, 157; two stages
-      // per wave, H = 1024, with 14 to 18: 221, 215, 213, 213, 213.
-      if (!cells) __builtin_amdgcn_s_sleep(R == 8 || PW > 1 ? 16 : 14);
-      else if (R == 8) __builtin_amdgcn_s_sleep(4);
+      // per wave, H = 1024, with 14 to 18: 221, 215, 213, 213, 213.  Within an XCD, with plain stores, polls cost little and the
+      // arrival is earlier: pre form of H = 512, 1 row, with 0, 3, 5, 7, 9, 11, 13 units 125, 127, 131, 126, 130, 134, 140 (the period is a
+      // poll's), 16 rows 137, 141, 142, 137, 139, 140, 144; x form, 37 rows 162, 160, 160, 160, 154, 153, 156.
+      if (near) {
+        if (!cells) __builtin_amdgcn_s_sleep(PRE ? 7 : 9);
+      } else if (!cells) {
+        __builtin_amdgcn_s_sleep(R == 8 || PW > 1 ? 16 : 14);
+      } else if (R == 8) {
+        __builtin_amdgcn_s_sleep(4);
+      }
       for (;;) {
         unsigned long long v[PW][LPS];  // R = 8: a unit per load; R = 4: two, the lanes of the upper 8 rows hold the second
 #pragma unroll
@@ -395,6 +469,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
     }
   }
 
+  if (XR && of_x) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // nothing may arrive in LDS after the workgroup's end
   if (!(s_abort[0] | s_abort[1])) {
     if (owner) *at(a.c_out, cell * 4u) = c;
     if (tid == 0) __hip_atomic_fetch_add(a.ctl + 1, 1u, __ATOMIC_RELAXED, SCOPE);

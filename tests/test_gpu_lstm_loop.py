@@ -82,6 +82,19 @@ def test_the_loop_equals_the_steps_one_by_one(rt, nb, T, B, Ix, H):
     assert _same(h, want_h) and torch.equal(c, want_c)
 
 
+@pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 8])
+@pytest.mark.parametrize("B,Ix,H", [(1, 512, 512), (4, 256, 256), (7, 256, 256), (9, 768, 256), (33, 512, 512), (41, 256, 256),
+                                    (3, 896, 128), (8, 448, 64), (12, 64, 448)])
+def test_inputs_that_arrive_three_steps_ahead(rt, nb, T, B, Ix, H):
+    """Fewer steps than the inputs' ring holds, as many, and more; one to seven of the eight waves multiply x, one or two stages
+    each, rows that are not the group's."""
+    assert nb.lstm_loop_supported(B, Ix, H)
+    case = _case(6, T, B, Ix, H)
+    want_h, want_c = _steps(rt, *case)
+    h, c, gave_up = _loop(nb, *case)
+    assert not gave_up and _same(h, want_h) and torch.equal(c, want_c)
+
+
 @pytest.mark.parametrize("T,B,Ix,H", [(4, 37, 512, 512), (3, 4, 0, 512), (3, 11, 0, 576), (3, 3, 64, 64), (2, 64, 0, 512),
                                        (3, 37, 640, 384), (2, 97, 192, 320)])
 def test_the_recovery_launch_gives_the_same_bits(rt, nb, T, B, Ix, H):
