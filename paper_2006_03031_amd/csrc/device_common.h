@@ -134,6 +134,23 @@ __device__ __forceinline__ uint4 load8_tail(const u16* p, int left, int len) {
   return make_uint4((uint32_t)rlo, (uint32_t)(rlo >> 32), (uint32_t)rhi, (uint32_t)(rhi >> 32));
 }
 
+// The first `n` (0 .. 8) elements of a chunk of which the row's last eight have been loaded, the rest zero.
+__device__ __forceinline__ uint4 keep_first8(uint4 v, int n) {
+  const uint64_t lo = ((uint64_t)v.y << 32) | v.x, hi = ((uint64_t)v.w << 32) | v.z;
+  const int sh = 16 * (8 - n);  // 0 .. 128 bits
+  const uint64_t rlo = sh == 0 ? lo : sh < 64 ? (lo >> sh) | (hi << (64 - sh)) : sh < 128 ? hi >> (sh - 64) : 0;
+  const uint64_t rhi = sh < 64 ? hi >> sh : 0;
+  return make_uint4((uint32_t)rlo, (uint32_t)(rlo >> 32), (uint32_t)rhi, (uint32_t)(rhi >> 32));
+}
+// A chunk whose row starts at an odd element, loaded from the element before, moved down by it (sh = 16; 0: left as it is).
+// `next` is the word behind the chunk; where a lane's neighbour holds that chunk (!own) it is taken from there.
+__device__ __forceinline__ uint4 shift8(uint4 v, uint32_t next, uint32_t sh, bool own) {
+  const uint32_t neighbour = (uint32_t)__builtin_amdgcn_mov_dpp((int)v.x, 0x101, 0xf, 0xf, true);
+  next = own ? next : neighbour;
+  return make_uint4(__builtin_amdgcn_alignbit(v.y, v.x, sh), __builtin_amdgcn_alignbit(v.z, v.y, sh),
+                    __builtin_amdgcn_alignbit(v.w, v.z, sh), __builtin_amdgcn_alignbit(next, v.w, sh));
+}
+
 // Two float32 -> two bfloat16 (round to nearest even) in one v_cvt_pk_bf16_f32; lo in bits 0..15.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));

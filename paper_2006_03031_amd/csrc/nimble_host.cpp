@@ -423,7 +423,7 @@ static void fill_tiled(nimble_plan* p, int variant, int split_k, int64_t batch, 
 }
 
 // Makes `p` a launch of any_kernel: 64 x 64 tiles.
-static void fill_any(nimble_plan* p, int64_t batch, int64_t M, int64_t N, int64_t K) {
+static void fill_any(nimble_plan* p, int64_t batch, int64_t M, int64_t N, int64_t K, bool b_is_kn) {
   const int64_t tiles_m = ceil_div(M, 64), tiles_n = ceil_div(N, 64), tiles = tiles_m * tiles_n;
   p->bm = p->bn = p->bk = 64;
   p->k = M / 64;
@@ -439,7 +439,7 @@ static void fill_any(nimble_plan* p, int64_t batch, int64_t M, int64_t N, int64_
     p->grid[1] = (uint32_t)(ceil_div(tiles_m, tm) * ceil_div(tiles_n, tn));  // launches, 1 but for outputs of over 17 G elements
   }
   p->grid[2] = (uint32_t)batch;
-  p->block = any_four_groups(tiles * batch, K) ? 1024u : 256u;
+  p->block = any_four_groups(tiles * batch, K, b_is_kn) ? 1024u : 256u;
 }
 
 int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int force_variant,
@@ -542,13 +542,16 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
   if (variant == NIMBLE_VAR_GENERIC) {
     // Any shape and alignment.  A grid of at most two workgroups per compute unit, or a single block of
     // rows, streams both operands in 16 x 16 blocks whose waves share K; everything else runs in 64 x 64
-    // tiles (any_kernel).  Measured at K = 1003 on N = 1001: 64 rows 6.7 us against 11.4, 128 rows 10.5
-    // against 11.4, 64 rows on N = 4001 13.1 against 11.5; 256 x 256 6.6 against 11.3.
+    // tiles (any_kernel).  With K odd the blocks' loads of rows that start at odd elements take three times as long, and from some
+    // length on the second workgroup of a compute unit is not worth it.  Microseconds, blocks / tiles: K = 1003 on N = 1001,
+    // 64 rows (252 blocks) 6.3 / 8.3, 80 10.0 / 8.3, 128 10.2 / 8.4; K = 1002, 64 rows 3.7 / 7.3, 128 (504) 4.5 / 7.4; K =
+    // 257 on N = 1001, 64 rows 4.0 / 5.5, 80 5.5 / 5.3; 333 columns, K = 1399, 192 rows (252) 8.4 / 9.8, 256 14.6 / 9.8; 517
+    // columns, K = 131, 192 rows (396) 3.5 / 4.9; 250 columns, K = 777, 256 rows (256) 5.5 / 7.4, 320 8.5 / 7.4.
     const int64_t cols16 = ceil_div(N, 16), rows16 = ceil_div(M, 16);
     const bool rows = opt.generic_rows && batch == 1 && K > 0 && rows16 <= 65535 &&
-                      (rows16 <= 1 || cols16 * rows16 <= 2 * kCUs);
+                      (rows16 <= 1 || cols16 * rows16 <= (K % 2 != 0 && K > 256 ? 1 : 2) * kCUs);
     p->variant = variant;
-    fill_any(p, batch, M, N, K);
+    fill_any(p, batch, M, N, K, !opt.generic_rows);
     if (rows) {
       p->bm = p->bn = 16;
       p->bk = 32;
@@ -604,7 +607,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
   if (halved) p->grid[1] = 2, p->block = 512;
   if (!chosen && split_rows == 0 &&
       small_tiles_win(variant, (int64_t)p->grid[0] * batch, batch * ceil_div(M, 64) * ceil_div(N, 64), p->bn, N, K, opt.out_f32))
-    fill_any(p, batch, M, N, K);
+    fill_any(p, batch, M, N, K, !opt.generic_rows);
   if (split_rows > 0) {
     // k and r describe the whole call; grid and residue_copy describe the first launch; the second
     // launch is planned here exactly as the entry point plans it, so that what is reported (its
@@ -629,15 +632,16 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
 // groups of waves share it), or what a compute unit's tiles take one behind the other; b [K, N] takes longer than [N, K].
 static double any_cost_us(int64_t batch, int64_t M, int64_t N, int64_t K, bool b_is_kn) {
   const int64_t tiles = batch * ceil_div(M, 64) * ceil_div(N, 64), stages = ceil_div(K, 64);
-  const double deep = (double)(any_four_groups(tiles, K) ? ceil_div(stages, 4) : stages);
+  const bool four = K >= 512 && tiles <= kCUs;  // (the [N, K] form too: with fewer stages one group's price still holds as an upper bound)
+  const double deep = (double)(four ? ceil_div(stages, 4) : stages);
   double per_cu = (double)tiles / (double)kCUs;
   if (per_cu > 1.0 && per_cu < 2.0) per_cu = 2.0;
   double lone, many;
   if (b_is_kn) {
-    lone = any_four_groups(tiles, K) ? 3.5 + 1.14 * deep : 3.0 + 0.67 * deep;
+    lone = four ? 3.5 + 1.14 * deep : 3.0 + 0.67 * deep;
     many = 3.0 + per_cu * (0.6 + 0.42 * (double)stages);
   } else {
-    lone = any_four_groups(tiles, K) ? 3.2 + 1.28 * deep : 4.0 + 0.56 * deep;
+    lone = four ? 3.2 + 1.28 * deep : 4.0 + 0.56 * deep;
     many = 4.0 + per_cu * (0.69 + 0.27 * (double)stages);
   }
   return lone > many ? lone : many;
@@ -907,7 +911,7 @@ int nimble_batch_matmul_plan(int64_t batch, int64_t M, int64_t N, int64_t K, int
       if (rc != NIMBLE_OK) return rc;
       if (plan->variant >= NIMBLE_VAR_T32x128) {
         plan->workspace_bytes = (uint64_t)batch * (uint64_t)N * (uint64_t)K * 2u;
-        if (!nn_transposes(*plan, batch, M, N, K)) fill_any(plan, batch, M, N, K);
+        if (!nn_transposes(*plan, batch, M, N, K)) fill_any(plan, batch, M, N, K, true);
         return NIMBLE_OK;
       }
     }

@@ -97,21 +97,22 @@ inline bool tile_kernel_wins(int variant, int64_t tiles, int64_t N, int64_t K, b
 }
 
 // Whether a launch of any_kernel shares each tile's K among four groups of waves: a workgroup per compute unit is all
-// there is, and K is long enough to pay for handing the sums over (measured at K = 1000: 1000 x 1000 as A.B 13.2 -> 10.5
-// us, 515 x 1001 10.6 -> 9.4; K = 512: 7.4 -> 7.0; K = 257 7.3 -> 6.8, 256 6.0 -> 6.2, 127 6.4 -> 6.8; with 512 tiles at
-// K = 1000 two groups already took 14.0 -> 15.1).
-inline bool any_four_groups(int64_t tiles, int64_t K) { return K >= 512 && tiles <= kComputeUnits; }
+// there is, and K is long enough to pay for handing the sums over: with b [N, K] two stages.  Microseconds, one group / four: 515 x 1001 to
+// f32, K = 40 4.5 / 4.3, 64 4.3 / 4.3, 127 5.4 / 4.7, 256 5.4 / 4.7, 511 8.6 / 6.6; 1000 x 1000 to bf16, K = 40 4.3 / 4.5, 64
+// 4.2 / 4.5, 128 4.6 / 4.5, 257 7.0 / 5.8; 70 x 130, K = 64 3.9 / 4.1, 128 4.3 / 4.1, 640 7.2 / 5.8.  With b [K, N] from K = 512 on, as
+// measured before the groups shared the end of a tile too.  With 512 tiles at K = 1000 two groups already took 14.0 -> 15.1.
+inline bool any_four_groups(int64_t tiles, int64_t K, bool b_is_kn) { return K >= (b_is_kn ? 512 : 65) && tiles <= kComputeUnits; }
 
 // Whether a tiled plan the dispatch function made is launched in the 64 x 64 tiles of any_kernel instead (`tiles`: of
 // the variant's own, over all batches; `small`: of 64 x 64).  Where the ring kernels can run, a partly empty last
 // tile column costs them no more than its loads (ring / any_kernel, microseconds: 423 x 2928 x 3648 20 / 37,
 // 12456 x 200 x 1024 12.5 / 19.6, 1240 x 1112 x 512 6.2 / 8.0), but a handful of tiles leaves the chip to few
 // workgroups, and the smaller ones with K shared by four groups of waves are done earlier (953 x 64 x 512, 15 of them,
-// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0; without
-// the groups 238 x 264 x 96, 20, 3.9 / 4.4).
+// 5.1 / 2.9, 662 x 184 x 2048, 33, 10.9 / 9.1, 1315 x 112 x 1024, 42, 6.8 / 7.5, 1637 x 112 x 512, 52, 5.2 / 6.0; where one
+// group ran 238 x 264 x 96, 20, 3.9 / 4.4).
 inline bool small_tiles_win(int variant, int64_t tiles, int64_t small, int bn, int64_t N, int64_t K, bool out_f32) {
   if (!ring_shape_ok(N, K)) return !tile_kernel_wins(variant, tiles, N, K, out_f32);
-  return N % bn != 0 && small <= 40 && any_four_groups(small, K);
+  return N % bn != 0 && small <= 40 && K >= 512;
 }
 
 // Whether a launch of any_kernel in `tiles` tiles, over all batches, leaves its output in the L2s.  Its rows start anywhere,

@@ -204,7 +204,7 @@ static SkinnyArgs skinny_args(const GemmArgs& g) {
 // Operands of any alignment in 64 x 64 tiles.
 static int launch_any(const GemmArgs& g, hipStream_t st) {
   const int64_t tiles_m = (g.M + 63) / 64, tiles_n = (g.N + 63) / 64;
-  const bool four = any_four_groups(tiles_m * tiles_n * g.batch, g.K);
+  const bool four = any_four_groups(tiles_m * tiles_n * g.batch, g.K, g.b_is_kn != 0);
   int64_t tm, tn;
   any_launch_tiles(tiles_m, tiles_n, &tm, &tn);
   for (int64_t m0 = 0; m0 < g.M; m0 += tm * 64)
@@ -218,18 +218,20 @@ static int launch_any(const GemmArgs& g, hipStream_t st) {
       part.c = g.out_f32 ? (void*)((float*)g.c + m0 * g.ldc + n0) : (void*)((u16*)g.c + m0 * g.ldc + n0);
       const int pm = (part.M + 63) / 64, pn = (part.N + 63) / 64;
       const dim3 grid((unsigned)pm * (unsigned)pn, 1, (unsigned)g.batch);
-      auto launch = [&](auto kn, auto through) {
-        constexpr bool KN = decltype(kn)::value, THROUGH = decltype(through)::value;
+      auto launch = [&](auto kn, auto through, auto odd) {
+        constexpr bool KN = decltype(kn)::value, THROUGH = decltype(through)::value, ODD = decltype(odd)::value;
         if (four)  // (one round of workgroups)
-          hipLaunchKernelGGL((any_kernel<KN, 2, 4, true>), grid, dim3(1024), 0, st, part, pm, pn);
+          hipLaunchKernelGGL((any_kernel<KN, 2, 4, true, ODD>), grid, dim3(1024), 0, st, part, pm, pn);
         else
-          hipLaunchKernelGGL((any_kernel<KN, 4, 1, THROUGH>), grid, dim3(256), 0, st, part, pm, pn);
+          hipLaunchKernelGGL((any_kernel<KN, 4, 1, THROUGH, ODD>), grid, dim3(256), 0, st, part, pm, pn);
       };
-      const bool through = !any_output_stays((int64_t)pm * pn * g.batch, g.K, g.out_f32 != 0);
-      if (g.b_is_kn)
-        through ? launch(std::true_type(), std::true_type()) : launch(std::true_type(), std::false_type());
-      else
-        through ? launch(std::false_type(), std::true_type()) : launch(std::false_type(), std::false_type());
+      auto pick = [&](auto kn, auto odd) {
+        if (any_output_stays((int64_t)pm * pn * g.batch, g.K, g.out_f32 != 0)) launch(kn, std::false_type(), odd);
+        else launch(kn, std::true_type(), odd);
+      };
+      if (g.b_is_kn) pick(std::true_type(), std::false_type());
+      else if ((g.K & 1) != 0) pick(std::false_type(), std::true_type());  // (rows of K elements, K odd: every other one starts at an odd element)
+      else pick(std::false_type(), std::false_type());
       const int rc = check_hip(hipGetLastError(), "any kernel launch");
       if (rc != NIMBLE_OK) return rc;
     }

@@ -57,6 +57,27 @@ def test_dense_of_any_shape(nb, M, N, K):
                od == nb.F32)
 
 
+# K odd (every other row starts at an odd element) and even at the edges of chunks, of stages and of rounds of four stages; one
+# group of waves (more than 256 tiles, or one stage) and four; the last element of the last row is the end of the buffer
+@pytest.mark.parametrize("K", [5, 7, 8, 9, 57, 63, 64, 65, 66, 71, 72, 73, 127, 129, 191, 193, 255, 256, 257, 263, 321])
+@pytest.mark.parametrize("M,N", [(80, 1001), (129, 1001), (63, 2003), (1100, 1031)])
+def test_rows_that_start_at_odd_elements(nb, M, N, K):
+    from paper_2006_03031_amd import runtime as rt
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K * 10 + M)
+    uniform = lambda *shape: torch.empty(shape, device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    x, w, b = uniform(M, K), uniform(N, K), uniform(N)
+    ref = x.double() @ w.double().T.contiguous()
+    print(f"odd rows {M} x {N} x {K}", flush=True)
+    for epi, od in ((nb.EPI_NONE, nb.F32), (nb.EPI_BIAS, nb.BF16), (nb.EPI_BIAS, nb.F32)):
+        buf, out = _guarded((M, N), torch.float32 if od == nb.F32 else torch.bfloat16)
+        rt.dense(x, w, b if epi == nb.EPI_BIAS else None, epi, od, out=out)
+        assert bool((buf[M * N:] == 768.0).all()), "wrote past the output"
+        want = ref + b.double() if epi == nb.EPI_BIAS else ref
+        err = ((out.double() - want).abs() / (want.abs() + want.abs().mean())).max().item()
+        assert err <= (GATE_F32 if od == nb.F32 else 2.0 ** -8), (M, N, K, epi, od, err)   # summation order; one rounding
+
+
 def test_more_tiles_than_one_launch_holds(nb):
     """4.4 million tiles of 64 x 64 (an output of 36 GB): two launches."""
     from paper_2006_03031_amd import runtime as rt
