@@ -325,26 +325,36 @@ __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 // ---------------------------------------------------------------------------
 // The attention chain with its intermediate results, in one launch: S = alpha Q.K^T (f32), P = softmax rows of S
 // (bf16), O = P.V, for head dimension 64 and up to 64 KG keys.
-//   Workgroup: 32 query rows, KG waves; wave g owns keys 64 g .. 64 g + 63 and keeps their scores in registers,
-//   in the layout of attention_kernel, from the first product to the second: S and P are written out once and never
-//   read back.  The waves' row maxima, row sums and shares of O meet in LDS.  S and P leave through the wave's K
+//   Workgroup: ROWS query rows, KG waves; wave g owns keys 64 g .. 64 g + 63 and keeps their scores in registers
+//   from the first product to the second: S and P are written out once and never read back.  ROWS = 32: MFMA 32x32x16, in the
+//   layout of attention_kernel.  ROWS = 16: MFMA 16x16x32, lane (r, h) holds, for its query row r, keys 16 t + 4 h + (0..3); the
+//   8 k slots of h in MFMA u of the second product are defined as the 4 keys it holds of t = 2 u and the 4 of 2 u + 1.
+//   The waves' row maxima, row sums and shares of O meet in LDS.  S and P leave through the wave's K
 //   tile, which is free by then, so that a store covers whole row segments (their rows start at any element: L is
-//   any number).  The loads of K and V are all issued at the start.
-//   What bounds it: the launch and the chain load, score, reduce, store; with many heads the 6 L^2 bytes per head
-//   that leave.  Graph replays, microseconds, three launches -> one: 12 heads of 23 tokens 10.5 -> 5.4, 333 20.7 -> 8.5,
-//   512 27.9 -> 9.6; 96 heads of 512 99 -> 44 (at 151 MB written 3.5 TB/s).  A last block written element by element
-//   instead of in pieces of 16 bytes cost 2.6 us.
+//   any number).  V loads under the scores.
+//   What bounds it: the launch and one workgroup's chain load, score, reduce, store; with many heads the 6 L^2 bytes per head
+//   that leave.  16 rows make that chain shorter wherever their workgroups still fit the chip at once (attention_chain_rows).
+//   Graph replays, microseconds, three launches / one with 32 rows / with 16: 12 heads of 23 tokens 10.5 / 5.4 / 4.2, of 200
+//   - / 6.4 / 5.1, of 333 20.7 / 8.4 / 6.7, of 512 27.9 / 9.4 / 11.7; 96 heads of 512 99 -> 44 (at 151 MB written 3.5 TB/s).
+//   A last block written element by element instead of in pieces of 16 bytes cost 2.6 us; V's rows past the last key zeroed
+//   a row per lane, all in the same banks, 0.1; waiting for V with K and storing S ahead of the exponentials 0.1 to 0.3.
 // ---------------------------------------------------------------------------
-template <int KG>
+template <int KG, int ROWS>
 __global__ void __launch_bounds__(KG * 64)
     attention_chain_kernel(const u16* __restrict__ q, const u16* __restrict__ k, const u16* __restrict__ v,
                            float* __restrict__ s_out, u16* __restrict__ p_out, u16* __restrict__ o, int L, float alpha) {
+  static_assert(ROWS == 16 || ROWS == 32, "one MFMA of 16 x 16 or of 32 x 32 columns of rows");
   constexpr int D = 64, BJ = 64, TILE = BJ * 8, T = KG * 64;
+  constexpr int NE = ROWS, NP = NE / 4;       // scores of a lane, and pieces of four neighbouring keys of them
+  constexpr int LPR = 64 / ROWS;              // lanes that share a row
+  constexpr bool WIDE = ROWS == 32;
   __shared__ __attribute__((aligned(256))) uint4 tiles[KG][2][TILE];  // K, V
-  __shared__ float red_max[KG][32], red_sum[KG][32];
+  __shared__ float red_max[KG][ROWS], red_sum[KG][ROWS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int kg = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int r32 = lane & 31, h = lane >> 5;
+  const int r = lane & (ROWS - 1), h = lane / ROWS;
+  // piece i of this lane: keys 4 piece(i) .. + 3 of the wave's 64
+  auto piece = [&](int i) { return WIDE ? (i >> 2) * 8 + (i & 3) * 2 + h : i * 4 + h; };
   int qb, head_i;
   {  // contiguous runs of (head, query block) per XCD
     const unsigned nb = gridDim.x * gridDim.y, id = blockIdx.y * gridDim.x + blockIdx.x;
@@ -354,98 +364,84 @@ __global__ void __launch_bounds__(KG * 64)
     qb = (int)(pid % gridDim.x);
   }
   const long long head = (long long)head_i * L * D, plane = (long long)head_i * L * L;
-  const int m0 = qb * 32;
-  const int m_ld = m0 + r32 < L ? m0 + r32 : L - 1;
+  const int m0 = qb * ROWS;
+  const int m_ld = m0 + r < L ? m0 + r : L - 1;
   const int j0 = kg * BJ;
   const int keys = L - j0 < BJ ? (L - j0 < 0 ? 0 : L - j0) : BJ;  // of this wave (uniform)
 
   const int rr = lane >> 3;
   const uint32_t k_lds = __builtin_amdgcn_readfirstlane(lds_addr_of(&tiles[kg][0][0]));
-  if (keys > 0) {
+  auto issue = [&](const u16* src, bool is_v) {  // 8 rows an instruction
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {  // 8 rows each: K, then V
-      int row = (j & 7) * 8 + rr;
-      const int c = (lane & 7) ^ (j >= 8 ? 4 * ((row >> 1) & 1) : ((row >> 1) & 7));
+    for (int j = 0; j < 8; ++j) {
+      int row = j * 8 + rr;
+      const int c = (lane & 7) ^ (is_v ? 4 * ((row >> 1) & 1) : ((row >> 1) & 7));
       row = row < keys ? row : keys - 1;
-      dma16_so((uint32_t)(row * D + c * 8) * 2u, (j >= 8 ? v : k) + head + (long long)j0 * D, k_lds + j * 1024);
+      dma16_so((uint32_t)(row * D + c * 8) * 2u, src + head + (long long)j0 * D, k_lds + (is_v ? 8 + j : j) * 1024);
     }
-  }
-  bf16x8 qf[4];
+  };
+  if (keys > 0) issue(k, false);
+  constexpr int QF = WIDE ? 4 : 2;  // query fragments: d = 64 / QF dd + 8 h .. + 7
+  bf16x8 qf[QF];
 #pragma unroll
-  for (int dd = 0; dd < 4; ++dd)
-    qf[dd] = as_bf16x8(*(const uint4*)(q + head + (long long)m_ld * D + dd * 16 + h * 8));
+  for (int dd = 0; dd < QF; ++dd)
+    qf[dd] = as_bf16x8(*(const uint4*)(q + head + (long long)m_ld * D + dd * (D / QF) + h * 8));
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the tiles are the wave's own: no barrier)
-  if (keys > 0 && keys < BJ && lane < BJ - keys) {
-    // rows of V past the last key are multiplied by zeros: they must be finite
-#pragma unroll
-    for (int c = 0; c < 8; ++c) tiles[kg][1][(keys + lane) * 8 + c] = make_uint4(0, 0, 0, 0);
-  }
+  if (keys > 0) issue(v, true);                     // (needed after the softmax only)
 
-  f32x16 s[2];
+  float s[NE];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s[t][e] = 0.f;
+  for (int e = 0; e < NE; ++e) s[e] = 0.f;
   float mx = -INFINITY;
   uint4* const stage = &tiles[kg][0][0];
   if (keys > 0) {
-    const int ksw = (r32 >> 1) & 7;
+    const int ksw = (r >> 1) & 7;
+    if constexpr (WIDE) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 2; ++t) {
+        f32x16 a;
 #pragma unroll
-      for (int dd = 0; dd < 4; ++dd) {
-        const bf16x8 kf = as_bf16x8(stage[(t * 32 + r32) * 8 + ((2 * dd + h) ^ ksw)]);
-        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[dd], s[t], 0, 0, 0);
+        for (int e = 0; e < 16; ++e) a[e] = 0.f;
+#pragma unroll
+        for (int dd = 0; dd < QF; ++dd)
+          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(stage[(t * 32 + r) * 8 + ((2 * dd + h) ^ ksw)]), qf[dd], a, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) s[t * 16 + e] = a[e];
       }
+    } else {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+      for (int t = 0; t < 4; ++t) {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int e = 0; e < 16; ++e) s[t][e] = fmaf(alpha, s[t][e], 0.f);  // (the products' epilogue)
+        for (int dd = 0; dd < QF; ++dd)
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(stage[(t * 16 + r) * 8 + ((4 * dd + h) ^ ksw)]), qf[dd], a, 0, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[t * 4 + e] = a[e];
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e) s[e] = fmaf(alpha, s[e], 0.f);  // (the products' epilogue)
     lds_order();
-    // S through the K tile: [32 rows][16 chunks of 4 keys], chunk c of row r at c ^ (r & 15)
+    // S through the K tile: [row][16 pieces of 4 keys], piece c of row r at c ^ (r & 15)
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        ((float4*)stage)[r32 * 16 + ((t * 8 + b * 2 + h) ^ (r32 & 15))] =
-            make_float4(s[t][4 * b], s[t][4 * b + 1], s[t][4 * b + 2], s[t][4 * b + 3]);
+    for (int i = 0; i < NP; ++i)
+      ((float4*)stage)[r * 16 + (piece(i) ^ (r & 15))] = make_float4(s[4 * i], s[4 * i + 1], s[4 * i + 2], s[4 * i + 3]);
     if (keys < BJ) {  // uniform
 #pragma unroll
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (t * 32 + (e >> 2) * 8 + h * 4 + (e & 3) >= keys) s[t][e] = -INFINITY;
+      for (int e = 0; e < NE; ++e)
+        if (piece(e >> 2) * 4 + (e & 3) >= keys) s[e] = -INFINITY;
     }
 #pragma unroll
-    for (int e = 0; e < 16; ++e) mx = fmaxf(fmaxf(mx, s[0][e]), s[1][e]);
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    for (int e = 0; e < NE; e += 2) mx = fmaxf(fmaxf(mx, s[e]), s[e + 1]);
+#pragma unroll
+    for (int x = ROWS; x < 64; x *= 2) mx = fmaxf(mx, __shfl_xor(mx, x, 64));
   }
   if (KG > 1) {
-    if (h == 0) red_max[kg][r32] = mx;
+    if (h == 0) red_max[kg][r] = mx;
     __syncthreads();
-    mx = red_max[0][r32];
+    mx = red_max[0][r];
 #pragma unroll
-    for (int g = 1; g < KG; ++g) mx = fmaxf(mx, red_max[g][r32]);
-  }
-  lds_order();
-  if (keys > 0) {
-    float* C = s_out + plane + j0;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = i * 4 + (lane >> 4), c = lane & 15;
-      const float4 w = ((const float4*)stage)[row * 16 + (c ^ (row & 15))];
-      if (m0 + row < L && c * 4 + 4 <= keys) __builtin_memcpy(C + (long long)(m0 + row) * L + c * 4, &w, 16);
-    }
-    if (keys & 3) {  // the piece of a row that the last key ends
-      const int row = r32, c = keys >> 2;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int e = 2 * i + h;
-        const float w = ((const float*)stage)[(row * 16 + (c ^ (row & 15))) * 4 + e];
-        if (m0 + row < L && e < (keys & 3)) C[(long long)(m0 + row) * L + c * 4 + e] = w;
-      }
-    }
+    for (int g = 1; g < KG; ++g) mx = fmaxf(mx, red_max[g][r]);
   }
   // probabilities: 2^((s - max) log2 e), the difference first: with max log2 e rounded on its own (a fused
   // multiply-add per score) the rounding is a factor of 2^(half a last place of the product) on the whole row, which
@@ -455,88 +451,122 @@ __global__ void __launch_bounds__(KG * 64)
   constexpr float kLog2e = 1.4426950408889634f;
   if (keys > 0) {
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        s[t][e] = __builtin_amdgcn_exp2f((s[t][e] - mx) * kLog2e);
-        sum += s[t][e];
-      }
+    for (int e = 0; e < NE; ++e) {
+      s[e] = __builtin_amdgcn_exp2f((s[e] - mx) * kLog2e);
+      sum += s[e];
+    }
   }
-  sum += __shfl_xor(sum, 32, 64);
-  if (KG > 1) {
-    if (h == 0) red_sum[kg][r32] = sum;
-    __syncthreads();
-    sum = red_sum[0][r32];
 #pragma unroll
-    for (int g = 1; g < KG; ++g) sum += red_sum[g][r32];
+  for (int x = ROWS; x < 64; x *= 2) sum += __shfl_xor(sum, x, 64);
+  if (KG > 1 && h == 0) red_sum[kg][r] = sum;
+  // V has had the scores and the probabilities to arrive; its rows past the last key are multiplied by zeros: they must be
+  // finite
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (keys > 0 && keys < BJ)
+    for (int c = keys * 8 + lane; c < TILE; c += 64) tiles[kg][1][c] = make_uint4(0, 0, 0, 0);
+  lds_order();
+  if (keys > 0) {
+    float* C = s_out + plane + j0;
+#pragma unroll
+    for (int i = 0; i < ROWS / 4; ++i) {
+      const int row = i * 4 + (lane >> 4), c = lane & 15;
+      const float4 w = ((const float4*)stage)[row * 16 + (c ^ (row & 15))];
+      if (m0 + row < L && c * 4 + 4 <= keys) __builtin_memcpy(C + (long long)(m0 + row) * L + c * 4, &w, 16);
+    }
+    if (keys & 3) {  // the piece of a row that the last key ends
+      const int row = r, c = keys >> 2;
+#pragma unroll
+      for (int i = 0; i < 4 / LPR; ++i) {
+        const int e = LPR * i + h;
+        const float w = ((const float*)stage)[(row * 16 + (c ^ (row & 15))) * 4 + e];
+        if (m0 + row < L && e < (keys & 3)) C[(long long)(m0 + row) * L + c * 4 + e] = w;
+      }
+    }
+  }
+  if (KG > 1) {
+    __syncthreads();
+    sum = red_sum[0][r];
+#pragma unroll
+    for (int g = 1; g < KG; ++g) sum += red_sum[g][r];
   }
   const float inv = 1.0f / sum;
-  f32x16 oacc[2];
+  float oacc[NE];  // as the scores: pieces of four d
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) oacc[t][e] = 0.f;
+  for (int e = 0; e < NE; ++e) oacc[e] = 0.f;
   if (keys > 0) {
-    uint4 pw[4];  // 16 keys each: the operand of P.V, and what P holds
+    uint2 pw[NP];  // pieces of four keys; two of them are the operand of P.V, and what P holds
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const f32x16& e = s[u >> 1];
-      const int b = (u & 1) * 8;
-      pw[u] = make_uint4(pack_bf16x2(e[b] * inv, e[b + 1] * inv), pack_bf16x2(e[b + 2] * inv, e[b + 3] * inv),
-                         pack_bf16x2(e[b + 4] * inv, e[b + 5] * inv), pack_bf16x2(e[b + 6] * inv, e[b + 7] * inv));
-    }
+    for (int i = 0; i < NP; ++i)
+      pw[i] = make_uint2(pack_bf16x2(s[4 * i] * inv, s[4 * i + 1] * inv), pack_bf16x2(s[4 * i + 2] * inv, s[4 * i + 3] * inv));
     lds_order();
-    // P through the K tile: [32 rows][8 chunks of 8 keys], chunk c of row r at c ^ (r & 7)
+    // P through the K tile: [row][8 chunks of 8 keys], chunk c of row r at c ^ (r & 7)
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      uint2* row = (uint2*)(stage + r32 * 8);
-      row[((2 * u) ^ (r32 & 7)) * 2 + h] = make_uint2(pw[u].x, pw[u].y);
-      row[((2 * u + 1) ^ (r32 & 7)) * 2 + h] = make_uint2(pw[u].z, pw[u].w);
-    }
-    const int i16 = lane & 15, dh = (lane >> 4) & 1;
-    const uint32_t vs0 = lds_addr_of(&tiles[kg][1][0]) +
-                         (uint32_t)((4 * h + (i16 >> 2)) * 128 +
-                                    (((2 * dh + ((i16 & 3) >> 1)) ^ (4 * ((i16 >> 3) & 1))) * 16) + (i16 & 1) * 8);
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int i = 0; i < NP; ++i) ((uint2*)(stage + r * 8))[((piece(i) >> 1) ^ (r & 7)) * 2 + (piece(i) & 1)] = pw[i];
+    // V by transposing reads of four keys by 16 d: MFMA u takes the keys of this lane's pieces 2 u and 2 u + 1
+    const int i16 = lane & 15, swz = 4 * ((i16 >> 3) & 1);
+    const uint32_t v_lds = lds_addr_of(&tiles[kg][1][0]) + (uint32_t)((4 * h + (i16 >> 2)) * 128 + (i16 & 1) * 8);
+    if constexpr (WIDE) {
+      const int dh = (lane >> 4) & 1;
+      const uint32_t vs0 = v_lds + (uint32_t)(((2 * dh + ((i16 & 3) >> 1)) ^ swz) * 16);
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const uint32_t a = (t ? vs0 ^ 64 : vs0) + u * 2048;
-        const uint2 lo = lds_read_tr16(a), hi = lds_read_tr16(a + 1024);
-        oacc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)), as_bf16x8(pw[u]),
-                                                          oacc[t], 0, 0, 0);
+        f32x16 a;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) a[e] = 0.f;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t at = (t ? vs0 ^ 64 : vs0) + u * 2048;
+          const uint2 lo = lds_read_tr16(at), hi = lds_read_tr16(at + 1024);
+          a = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
+                                                      as_bf16x8(make_uint4(pw[2 * u].x, pw[2 * u].y, pw[2 * u + 1].x, pw[2 * u + 1].y)), a, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oacc[t * 16 + e] = a[e];
       }
+    } else {
+      const uint32_t vs0 = v_lds + (uint32_t)((((i16 & 3) >> 1) ^ swz) * 16);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const uint32_t at = (vs0 ^ (t * 32)) + u * 4096;
+          const uint2 lo = lds_read_tr16(at), hi = lds_read_tr16(at + 2048);
+          a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(make_uint4(lo.x, lo.y, hi.x, hi.y)),
+                                                      as_bf16x8(make_uint4(pw[2 * u].x, pw[2 * u].y, pw[2 * u + 1].x, pw[2 * u + 1].y)), a, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) oacc[t * 4 + e] = a[e];
+      }
+    }
     lds_order();
     u16* C = p_out + plane + j0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < ROWS / 8; ++i) {
       const int row = i * 8 + (lane >> 3), c = lane & 7;
       const uint4 w = stage[row * 8 + (c ^ (row & 7))];
       if (m0 + row < L && c * 8 + 8 <= keys) __builtin_memcpy(C + (long long)(m0 + row) * L + c * 8, &w, 16);
     }
     if (keys & 7) {
-      const int row = r32, c = keys >> 3;
+      const int row = r, c = keys >> 3;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int e = 2 * i + h;
+      for (int i = 0; i < 8 / LPR; ++i) {
+        const int e = LPR * i + h;
         const u16 w = ((const u16*)stage)[(row * 8 + (c ^ (row & 7))) * 8 + e];
         if (m0 + row < L && e < (keys & 7)) C[(long long)(m0 + row) * L + c * 8 + e] = w;
       }
     }
   }
-  // the waves' shares of O, 8 KiB each over their own tiles, added in order
+  // the waves' shares of O over their own tiles, added in order: group g at g * 1024, [row][16 pieces of 4 d]
   lds_order();
-  float4* part = (float4*)&tiles[0][0][0];  // group g at g * 1024: [32 rows][16 chunks of 4 d]
+  float4* part = (float4*)&tiles[0][0][0];
 #pragma unroll
-  for (int t = 0; t < 2; ++t)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-      part[kg * 1024 + r32 * 16 + ((t * 8 + b * 2 + h) ^ (r32 & 15))] =
-          make_float4(oacc[t][4 * b], oacc[t][4 * b + 1], oacc[t][4 * b + 2], oacc[t][4 * b + 3]);
+  for (int i = 0; i < NP; ++i)
+    part[kg * 1024 + r * 16 + (piece(i) ^ (r & 15))] = make_float4(oacc[4 * i], oacc[4 * i + 1], oacc[4 * i + 2], oacc[4 * i + 3]);
   if (KG > 1) __syncthreads();
   lds_order();
 #pragma unroll
-  for (int x = tid; x < 32 * 16; x += T) {
+  for (int x = tid; x < ROWS * 16; x += T) {
     const int row = x >> 4, c = x & 15;
     float4 a = part[row * 16 + (c ^ (row & 15))];
 #pragma unroll

@@ -127,6 +127,14 @@ inline bool any_output_stays(int64_t tiles, int64_t K, bool out_f32) {
   return !out_f32 || tiles > (K <= 128 ? 2 : 1) * kComputeUnits;
 }
 
+// Query rows per workgroup of attention_chain_kernel with `waves` waves: 16 where these workgroups all find a place at once (16 KB
+// of LDS per wave, 160 KB and 32 waves per compute unit), else 32.  Microseconds, 32 rows / 16: eight waves, 252 workgroups of 16 rows (12 heads of
+// 333) 8.4 / 6.7, 264 (352) 8.2 / 10.3; four, 512 (32 of 250) 7.8 / 7.3, 624 (48 of 200) 8.9 / 10.0; two, 672 (96 of 100) 7.1 / 5.9,
+// 1600 (200 of 128) 9.5 / 10.8; one, 1800 (600 of 33) 7.7 / 6.1.
+inline int attention_chain_rows(int64_t heads, int64_t L, int waves) {
+  return heads * ((L + 15) / 16) <= 8 * kComputeUnits / waves ? 16 : 32;
+}
+
 // Tiles of one launch of any_kernel (a launch holds less than 2^32 threads); larger outputs take several, each of at most
 // `tm` x `tn` tiles.  (With the rest in the second grid dimension every launch paid 0.1 to 0.2 us for finding its tile.)
 inline void any_launch_tiles(int64_t tiles_m, int64_t tiles_n, int64_t* tm, int64_t* tn) {

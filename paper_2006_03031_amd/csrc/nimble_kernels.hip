@@ -641,18 +641,22 @@ int nimble_attention_chain_dyn(const void* q, const void* k, const void* v, void
       return fail(NIMBLE_ERR_ALIGN, "device pointers must be 16-byte aligned");
     if (workspace_bytes > 0 && !workspace) return fail(NIMBLE_ERR_NULL, "workspace_bytes > 0 with a null workspace");
     if (workspace && misaligned(workspace)) return fail(NIMBLE_ERR_ALIGN, "workspace must be 16-byte aligned");
-    const dim3 grid((unsigned)((N + 31) / 32), (unsigned)heads);
     hipStream_t st = (hipStream_t)stream;
     const u16 *qp = (const u16*)q, *kp = (const u16*)k, *vp = (const u16*)v;
     const int L = (int)N;
-    if (L <= 64)
-      hipLaunchKernelGGL(attention_chain_kernel<1>, grid, dim3(64), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
-    else if (L <= 128)
-      hipLaunchKernelGGL(attention_chain_kernel<2>, grid, dim3(128), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
-    else if (L <= 256)
-      hipLaunchKernelGGL(attention_chain_kernel<4>, grid, dim3(256), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
-    else
-      hipLaunchKernelGGL(attention_chain_kernel<8>, grid, dim3(512), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
+    auto launch = [&](auto waves, auto rows) {
+      constexpr int KG = decltype(waves)::value, ROWS = decltype(rows)::value;
+      const dim3 grid((unsigned)((L + ROWS - 1) / ROWS), (unsigned)heads);
+      hipLaunchKernelGGL((attention_chain_kernel<KG, ROWS>), grid, dim3(KG * 64), 0, st, qp, kp, vp, (float*)s, (u16*)p, (u16*)o, L, alpha);
+    };
+    auto pick = [&](auto waves) {
+      if (attention_chain_rows(heads, L, decltype(waves)::value) == 16) launch(waves, Int<16>());
+      else launch(waves, Int<32>());
+    };
+    if (L <= 64) pick(Int<1>());
+    else if (L <= 128) pick(Int<2>());
+    else if (L <= 256) pick(Int<4>());
+    else pick(Int<8>());
     return check_hip(hipGetLastError(), "attention chain launch");
   }
   int rc = nimble_batch_matmul_dyn(q, k, s, heads, M, N, D, 1, alpha, NIMBLE_F32, workspace, workspace_bytes, stream);

@@ -44,7 +44,10 @@ def test_fused_attention_launch_shapes(rt, heads, L, growing):
 # one, two, four and eight waves; a last wave with 1, 63 and 64 keys and waves without any; a last query tile of one
 # row; odd L (rows of S and P at any alignment); 513: the three calls
 @pytest.mark.parametrize("heads,L", [(1, 1), (3, 31), (2, 33), (5, 63), (3, 64), (2, 65), (2, 127), (3, 128), (2, 129), (1, 193),
-                                     (2, 256), (3, 257), (2, 333), (2, 448), (3, 449), (2, 511), (2, 512), (2, 513)])
+                                     (2, 256), (3, 257), (2, 333), (2, 448), (3, 449), (2, 511), (2, 512), (2, 513),
+                                     # more workgroups of 16 rows than find a place at once: 32 rows; the last such that do
+                                     (2049, 1), (1025, 31), (683, 33), (513, 63), (512, 64), (513, 64), (205, 65), (129, 127), (129, 128),
+                                     (57, 129), (40, 193), (32, 256), (33, 256), (15, 257), (16, 257), (13, 333), (10, 448), (9, 511), (9, 512)])
 @pytest.mark.parametrize("alpha", [0.125, -0.25])
 def test_attention_chain_edges(rt, heads, L, alpha):
     gen = torch.Generator(device="cuda")
