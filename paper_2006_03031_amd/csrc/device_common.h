@@ -240,6 +240,12 @@ __device__ __forceinline__ void dma16_so(uint32_t voff, const void* sbase, uint3
                "s"(lds_addr)
                : "memory", "m0");
 }
+// The same for data that nobody reads again: non-temporal, it passes the caches by.
+__device__ __forceinline__ void dma16_so_once(uint32_t voff, const void* sbase, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt\n" ::"v"(voff), "s"(sbase),
+               "s"(lds_addr)
+               : "memory", "m0");
+}
 // A matrix product with a direct global -> LDS load behind it, at LDS byte lds_base + lds_off (the product is also the
 // wait state between writing M0 and the load).
 __device__ __forceinline__ void mfma_acc_load(f32x4& acc, const bf16x8& a, const bf16x8& b, uint32_t voff, const void* sbase,

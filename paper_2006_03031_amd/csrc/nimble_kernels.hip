@@ -164,7 +164,12 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
                       (double)s.N * (double)s.K * 2.0 <= kCachedWeightBytes;
     if (many)
       hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16>), grid, dim3(256), 0, st, s);
-    else if (s.M <= 8)
+    else if (!LSTM && weights_pass_by(s.N, s.K) && grid.y == 1) {
+      if (s.M <= 8)
+        hipLaunchKernelGGL((stream_kernel<false, 3, 8, 8, true>), grid, dim3(512), 0, st, s);
+      else
+        hipLaunchKernelGGL((stream_kernel<false, 3, 8, 16, true>), grid, dim3(512), 0, st, s);
+    } else if (s.M <= 8)
       hipLaunchKernelGGL((stream_kernel<LSTM, 3, 8, 8>), grid, dim3(512), 0, st, s);
     else
       hipLaunchKernelGGL((stream_kernel<LSTM, 3, 8, 16>), grid, dim3(512), 0, st, s);

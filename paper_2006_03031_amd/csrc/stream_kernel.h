@@ -49,7 +49,8 @@ __device__ __forceinline__ void wait_vmcnt_of(int n) {  // n is a constant after
 // NW = 8 with S = 2, 3, 4: 24.7, 24.5, 24.4 / 27.6, 28.0, 27.9; NW = 8, XR = 8, S = 3: 23.9 (four rows:
 // 25.0).  Two groups of 16 weight rows per workgroup sharing one activation tile (half the activation
 // traffic, but one workgroup per compute unit): 25.9-27.4 / 27.5-28.8, not kept.
-template <bool LSTM, int S, int NW = 8, int XR = 16>
+// ONCE: the weights are loaded non-temporally, past the caches (weights_pass_by).
+template <bool LSTM, int S, int NW = 8, int XR = 16, bool ONCE = false>
 __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
   static_assert(XR == 8 || XR == 16, "the activation tile is one or two loads of 8 rows");
   constexpr int RG = 1;                             // groups of 16 weight rows per workgroup
@@ -132,7 +133,12 @@ __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
     const int k0 = st << 6;
     const uint32_t dst = ring_lds + slot * (SLOT * 16);
 #pragma unroll
-    for (int u = 0; u < 2 * RG; ++u) dma16_so(w_off[u], s.w + k0, dst + u * 1024);
+    for (int u = 0; u < 2 * RG; ++u) {
+      if (ONCE)
+        dma16_so_once(w_off[u], s.w + k0, dst + u * 1024);
+      else
+        dma16_so(w_off[u], s.w + k0, dst + u * 1024);
+    }
     constexpr uint32_t XT = RG * 2048;  // the activation tile follows the weight rows
     if (LSTM) {
       // the stage lies in x (k0 < Ix) or in h: Ix is a multiple of 64

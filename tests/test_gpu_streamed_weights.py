@@ -1,0 +1,30 @@
+"""Layers of more than 64 MB of weights at up to 16 rows, whose weights the streaming kernel loads past the caches, against
+float64: the 8-row and the 16-row activation tile, a partly filled last block of weight rows, the layers just above and just
+below the line, twice in a row with other weights in the same memory."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N,K", [(8192, 4096), (5003, 6400), (4999, 6400), (515, 64000)])
+@pytest.mark.parametrize("M", [1, 7, 8, 9, 16])
+def test_weights_loaded_past_the_caches(M, N, K):
+    import paper_2006_03031_amd as nb
+    from paper_2006_03031_amd import runtime as rt
+    nb.load()
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M * 7 + N)
+    x = torch.empty((M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    b = torch.empty((N,), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    w = torch.empty((N, K), dtype=torch.bfloat16, device="cuda")
+    for rep in range(2):
+        w.normal_(0, 0.02, generator=gen)
+        print(f"streamed {M} x {N} x {K}", flush=True)
+        want = x.double() @ w.double().T.contiguous() + b.double()
+        for od, tol in ((nb.F32, 2.0 ** -14), (nb.BF16, 2.0 ** -8)):     # summation order; one rounding
+            buf = torch.full((M * N + 256,), 768.0, dtype=torch.float32 if od == nb.F32 else torch.bfloat16, device="cuda")
+            rt.dense(x, w, b, nb.EPI_BIAS, od, out=buf[:M * N].view(M, N))
+            got = buf[:M * N].view(M, N).double()
+            assert ((got - want).abs() / (want.abs() + want.abs().mean())).max().item() <= tol, (rep, od)
+            assert bool((buf[M * N:] == 768.0).all())
