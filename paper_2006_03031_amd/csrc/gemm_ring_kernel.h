@@ -56,8 +56,8 @@ struct RingLink {
 // past N-1 are fetched from the last one, so every load stays in bounds and the pipeline is the interior
 // one; their products land in rows and columns the epilogue does not store (N is a multiple of 8 here, so
 // a 16-byte piece of an output row is stored whole or not at all).
-// STAYS: the output is left in the L2s (output_stays).
-template <int BM, int BN, int WGM, int WGN, int S, bool EDGE, int MODE, bool PF, bool STAYS>
+// STAYS: the output is left in the L2s (output_stays).  ONCE: B is loaded past the caches (one tile row reads it once).
+template <int BM, int BN, int WGM, int WGN, int S, bool EDGE, int MODE, bool PF, bool STAYS, bool ONCE>
 __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, const int n0,
                                               uint4* smem, const RingLink lk = RingLink{}) {
   constexpr bool WIDE = MODE == RING_WIDE;
@@ -136,6 +136,12 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
   const long long b_pass = EDGE ? 0 : (long long)PASS * g.ldb;
   const uint32_t a_dst = __builtin_amdgcn_readfirstlane(lds_addr_of(&As[0][wave * 64]));
   const uint32_t b_dst = __builtin_amdgcn_readfirstlane(lds_addr_of(&Bs[0][wave * 64]));
+  auto load_b = [&](uint32_t voff, const void* base, uint32_t dst) {
+    if (ONCE)
+      dma16_so_once(voff, base, dst);
+    else
+      dma16_so(voff, base, dst);
+  };
   auto dma = [&](int ks, int slot) {
     const int k0 = ks << KSH;
 #pragma unroll
@@ -143,7 +149,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       dma16_so(a_off[i], a_base + k0, a_dst + slot * (BMP * CH * 16) + i * NT * 16);
 #pragma unroll
     for (int i = 0; i < B_LD; ++i)
-      dma16_so(b_off[EDGE ? i : 0], b_base + i * b_pass + k0, b_dst + slot * (BN * CH * 16) + i * NT * 16);
+      load_b(b_off[EDGE ? i : 0], b_base + i * b_pass + k0, b_dst + slot * (BN * CH * 16) + i * NT * 16);
   };
 
   // fragment reads: lane -> row (lane & 15), logical chunk (lane >> 4)
@@ -340,7 +346,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
       if (u < A_LD)
         dma16_so(a_off[u], a_base + k0, a_dst + slot_ * (BMP * CH * 16) + u * NT * 16);
       else
-        dma16_so(b_off[EDGE ? u - A_LD : 0], b_base + (u - A_LD) * b_pass + k0, b_dst + slot_ * (BN * CH * 16) + (u - A_LD) * NT * 16);
+        load_b(b_off[EDGE ? u - A_LD : 0], b_base + (u - A_LD) * b_pass + k0, b_dst + slot_ * (BN * CH * 16) + (u - A_LD) * NT * 16);
     };
     // second halves (CUR == 1) also issue the ring loads of one stage, spread over their weight
     // tiles (ld_k0 < 0 in a two-slot ring: past the end of K, nothing to load)
@@ -538,7 +544,7 @@ __device__ __forceinline__ int gemm_ring_body(const GemmArgs& g, const int m0, c
 // the 8-wave ping-pong, slower at whole rounds, so that shape is not built.
 // BM may be any multiple of 16 * WGM: the 256-wide tile is built at 128..256 rows so that the
 // dispatch function can pick the height at which the run-time M fills whole rounds of the chip.
-template <int BM, int BN, int WGM, int WGN, bool RESIDUE, int S, bool WIDE, bool STAYS>
+template <int BM, int BN, int WGM, int WGN, bool RESIDUE, int S, bool WIDE, bool STAYS, bool ONCE = false>
 __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
     gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m) {
   // WIDE: stages of 64 k (K must be a multiple of 64; the launcher sees to that), S = 2 to 4.
@@ -585,12 +591,12 @@ __global__ void __launch_bounds__(WGM* WGN * 64) __attribute__((amdgpu_waves_per
       }
     }
     if (RESIDUE && (m0 + BM > g.M || n0 + BN > g.N)) {  // same pipeline, clamped loads, masked stores
-      lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, true, kMode, kPF, STAYS>(g, m0, n0, smem, lk);
+      lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, true, kMode, kPF, STAYS, ONCE>(g, m0, n0, smem, lk);
       lk.filled = kPF && lk.next;
       lk.parity ^= 1;
       continue;
     }
-    lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, false, kMode, kPF, STAYS>(g, m0, n0, smem, lk);
+    lk.stores = gemm_ring_body<BM, BN, WGM, WGN, S, false, kMode, kPF, STAYS, ONCE>(g, m0, n0, smem, lk);
     lk.filled = kPF && lk.next;
     lk.parity ^= 1;
   }

@@ -300,6 +300,25 @@ struct Launch {
   double us = 0;
 };
 
+// K slices for 17 to 64 rows of a layer whose weights come from memory, in tiles of 128 columns and all rows, or 0 where the
+// estimates decide.  Each slice of a tile column reads its weights once, past the caches (weights_pass_by), and the chip reads
+// fastest with a workgroup on every compute unit: the most slices that give them one at most, from 160 workgroups on.  Slices of
+// whole 4 KB are left out: then all workgroups read the same few memory channels (8192 x 8192 at 64 rows with K in four 36.8 us,
+// in three 31.1).  Microseconds, several layers in turn, by the estimates / so: 20 and 64 rows of 6144 x 6144 24.9 / 20.4 and 30.7 /
+// 24.5, 7168 x 7168 27.8 / 23.6 and 34.4 / 27.7, 8192 x 8192 29.3 / 28.5 and 43.1 / 31.1; 32 and 64 rows of 5120 x 13824 40.6 /
+// 30.8 and 47.5 / 33.9, 13824 x 5120 36.1 / 31.4 and 46.1 / 36.8, 4096 x 14336 33.4 / 27.3 and 36.9 / 30.8, 8192 x 28672 79.3 / 74.6
+// and 89.5 / 81.3; but 14336 x 4096 (in two, of 4 KB) 29.5 / 31.3 and 38.5 / 34.0.  A layer called over and over, which the
+// memory-side cache keeps: 6144 x 6144 23.0 / 19.3 and 22.5 / 24.3, 4096 x 8192 22.3 / 17.4 and 20.6 / 22.5.
+static int streamed_slices(int variant, int64_t rows, int64_t N, int64_t K) {
+  if (rows <= 16 || rows > 64 || !weights_pass_by(N, K) || K % 64 != 0 || N % 128 != 0) return 0;
+  const int64_t stages = K / 64;
+  for (int sk = 16; sk >= 2; --sk) {
+    if (N / 128 * sk > kCUs || !split_k_ok(variant, 1, N, K, sk) || !wide_stages_ok(K, sk) || ceil_div(stages, sk) % 32 == 0) continue;
+    return N / 128 * sk >= 160 ? sk : 0;
+  }
+  return 0;
+}
+
 // Best single launch for `rows` rows: the least estimated time among weight streaming (up to
 // 64 rows) and every tiled variant and K split that fits the workspace.
 static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int epilogue,
@@ -395,6 +414,14 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
     best = Launch();
     best.variant = NIMBLE_VAR_SKINNY16;
     best.us = skinny_us;
+  }
+  const int tile = rows <= 32 ? NIMBLE_VAR_T32x128 : NIMBLE_VAR_T64x128;
+  const int slices = batch == 1 ? streamed_slices(tile, rows, N, K) : 0;
+  if (slices > 1 && tiled_variant_ok(tile, rows, N, K) && (uint64_t)slices * (uint64_t)rows * (uint64_t)N * 4u <= max_workspace) {
+    best.variant = tile;  // (its estimate stays: what it is compared with was fitted beside it)
+    best.split_k = slices;
+    best.bm = 0;
+    best.halved = false;
   }
   return best;
 }

@@ -32,12 +32,13 @@ bool tile_rows_ok(int variant, int bm, int64_t N, int64_t K);
 // as cache-resident, which is what a layer loop or a token loop sees.
 constexpr double kCachedWeightBytes = 64e6;
 
-// Whether the streaming kernel loads the weights of an [N, K] layer non-temporally: where each call finds them in memory, which
+// Whether the weights of an [N, K] layer that a launch reads once are loaded non-temporally: where each call finds them in memory, which
 // is then read at the rate of a plain read.  Several layers in turn, 512 MB of them, microseconds per layer at 1 / 5 / 16 rows, through the
 // caches / past them: 8192 x 8192 23.7 / 23.6 / 25.9, 21.5 / 21.4 / 24.8 (a plain read of the bytes 21.4), 7168 x 7168 19.5 /
 // 20.2 / 24.7, 17.8 / 18.5 / 22.0, 6144 x 6144 16.7 / 17.0 / 20.7, 15.4 / 15.2 / 19.4.  What the caches could keep is slower: a single layer over
 // and over, 4096 x 4096 4.1 / 4.3 / 5.2, 4.5 / 5.1 / 6.5, 8192 x 8192 (in the memory-side cache then) 21.5 / 21.0 / 21.2,
-// 19.8 / 20.0 / 26.6.  The line is the one above which layers are taken to come from memory everywhere.
+// 19.8 / 20.0 / 26.6.  The line is the one above which layers are taken to come from memory everywhere.  The 32- and
+// 64-row tiles with K cut do so too where one tile row reads all weights once: 8192 x 8192 at 17 / 32 rows 32.0 / 32.7, 28.8 / 30.4.
 inline bool weights_pass_by(int64_t N, int64_t K) { return (double)N * (double)K * 2.0 > kCachedWeightBytes; }
 
 // Whether every one of `slices` K slices gets whole 64-wide stages (the 64-wide ring).  NIMBLE_RING32 (a

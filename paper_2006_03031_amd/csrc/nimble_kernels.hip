@@ -68,6 +68,13 @@ static int launch_ring_copy(const GemmArgs& g, const nimble_plan& p, dim3 grid, 
   };
   using Yes = std::true_type;
   using No = std::false_type;
+  if constexpr (WIDE && S == 3 && WGM == 2 && WGN == 2 && BN == 128) {  // (the tiles of up to 64 rows: K is cut, the sums go to scratch)
+    if (tiles_m == 1 && grid.y > 1 && weights_pass_by(g.N, g.K)) {
+      hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, S, true, false, true>), grid, dim3(WGM * WGN * 64), 0, st, g, tiles_m,
+                         tiles_n, group_m);
+      return check_hip(hipGetLastError(), "ring kernel launch");
+    }
+  }
   if (output_stays(g, grid.y))
     p.residue_copy ? launch(Yes(), Yes()) : launch(No(), Yes());
   else

@@ -28,3 +28,30 @@ def test_weights_loaded_past_the_caches(M, N, K):
             got = buf[:M * N].view(M, N).double()
             assert ((got - want).abs() / (want.abs() + want.abs().mean())).max().item() <= tol, (rep, od)
             assert bool((buf[M * N:] == 768.0).all())
+
+
+# K in three, five, eight and six slices of all rows (32- and 64-row tiles, full and not), the last slice shorter; without scratch the
+# estimates' launch; through the built-in scratch
+@pytest.mark.parametrize("N,K", [(8192, 8192), (6144, 6144), (4096, 14336), (5120, 6912)])
+@pytest.mark.parametrize("M", [17, 32, 33, 64])
+def test_all_rows_in_one_tile_with_k_cut(M, N, K):
+    import paper_2006_03031_amd as nb
+    from paper_2006_03031_amd import runtime as rt
+    nb.load()
+    p = nb.dense_plan(M, N, K, nb.EPI_BIAS)
+    assert p.bm == (32 if M <= 32 else 64) and 160 <= p.grid[0] * p.split_k <= 256 and -(-K // 64 // p.split_k) % 32 != 0
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M * 5 + N)
+    x = torch.empty((M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    b = torch.empty((N,), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    w = torch.empty((N, K), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=gen)
+    want = x.double() @ w.double().T.contiguous() + b.double()
+    print(f"cut {M} x {N} x {K} in {p.split_k}", flush=True)
+    for od, tol in ((nb.F32, 2.0 ** -14), (nb.BF16, 2.0 ** -8)):     # summation order; one rounding
+        outs = [torch.full((M, N), 768.0, dtype=torch.float32 if od == nb.F32 else torch.bfloat16, device="cuda") for _ in range(3)]
+        rt.dense(x, w, b, nb.EPI_BIAS, od, out=outs[0])
+        rt.dense(x, w, b, nb.EPI_BIAS, od, out=outs[1], workspace=torch.empty(16, dtype=torch.uint8, device="cuda"))
+        nb.nimble_dense_noalloc_dyn(x.data_ptr(), w.data_ptr(), b.data_ptr(), outs[2].data_ptr(), M, N, K, nb.EPI_BIAS, od, rt._stream())
+        for out in outs:
+            assert ((out.double() - want).abs() / (want.abs() + want.abs().mean())).max().item() <= tol, od
+        assert torch.equal(outs[0], outs[2])
