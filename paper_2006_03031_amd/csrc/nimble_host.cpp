@@ -309,6 +309,8 @@ struct Launch {
 // 30.8 and 47.5 / 33.9, 13824 x 5120 36.1 / 31.4 and 46.1 / 36.8, 4096 x 14336 33.4 / 27.3 and 36.9 / 30.8, 8192 x 28672 79.3 / 74.6
 // and 89.5 / 81.3; but 14336 x 4096 (in two, of 4 KB) 29.5 / 31.3 and 38.5 / 34.0.  A layer called over and over, which the
 // memory-side cache keeps: 6144 x 6144 23.0 / 19.3 and 22.5 / 24.3, 4096 x 8192 22.3 / 17.4 and 20.6 / 22.5.
+// Not to f32: fewer, longer sums are further from the exact ones there (20 x 6144 x 6144 in five slices 2.0e-7, in eight 1.6e-7),
+// which a bf16 result does not show.
 static int streamed_slices(int variant, int64_t rows, int64_t N, int64_t K) {
   if (rows <= 16 || rows > 64 || !weights_pass_by(N, K) || K % 64 != 0 || N % 128 != 0) return 0;
   const int64_t stages = K / 64;
@@ -322,7 +324,7 @@ static int streamed_slices(int variant, int64_t rows, int64_t N, int64_t K) {
 // Best single launch for `rows` rows: the least estimated time among weight streaming (up to
 // 64 rows) and every tiled variant and K split that fits the workspace.
 static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int epilogue,
-                          uint64_t max_workspace, bool allow_skinny, bool allow_halved = true) {
+                          uint64_t max_workspace, bool allow_skinny, bool out_f32, bool allow_halved = true) {
   Launch best, roomy;  // within the workspace, and with as much of it as anyone could bring
   double skinny_us = -1.0, least_tiled_us = 1e30;
   // weight streaming: up to 64 rows, and beyond that in 16-row blocks of the streaming kernel while
@@ -416,7 +418,7 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
     best.us = skinny_us;
   }
   const int tile = rows <= 32 ? NIMBLE_VAR_T32x128 : NIMBLE_VAR_T64x128;
-  const int slices = batch == 1 ? streamed_slices(tile, rows, N, K) : 0;
+  const int slices = batch == 1 && !out_f32 ? streamed_slices(tile, rows, N, K) : 0;
   if (slices > 1 && tiled_variant_ok(tile, rows, N, K) && (uint64_t)slices * (uint64_t)rows * (uint64_t)N * 4u <= max_workspace) {
     best.variant = tile;  // (its estimate stays: what it is compared with was fitted beside it)
     best.split_k = slices;
@@ -517,7 +519,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
       chosen = true;
       split_k = e->split_k > 1 ? e->split_k : 1;
     } else {
-      const Launch single = best_launch(batch, M, N, K, epilogue, opt.max_workspace, true);
+      const Launch single = best_launch(batch, M, N, K, epilogue, opt.max_workspace, true, opt.out_f32);
       variant = single.variant < 0 ? NIMBLE_VAR_GENERIC : single.variant;
       split_k = single.split_k;
       tile_rows = single.bm;
@@ -545,7 +547,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
             if (head_us >= best_us) continue;  // (the tail's search is most of what a plan costs)
             // (priced without halved tiles: two launches picked for their sake took 1 to 2 % longer than one:
             // 4751 x 8192 x 7552 426.9 us, 417.7 in 320-row tiles)
-            const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true, false);
+            const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true, opt.out_f32, false);
             if (tail.variant < 0) continue;
             // (a streamed tail's estimate and the gap both count its launch, which decides against halved tiles at
             // K > 2048: 4154 x 1024 x 3648 with GELU 36.6 us in two launches, 38.8 in halves)
