@@ -20,12 +20,12 @@
 //       streamed from HBM exactly once straight into MFMA operands, the four waves of a
 //       workgroup split K and reduce through LDS.  LSTM=true gathers the four gate rows of
 //       four hidden units and applies the cell update in the epilogue.
-//   stream_kernel.h      stream_kernel<LSTM,S,NW,XR>: the weight-streaming kernel for up to 16 rows per
+//   stream_kernel.h      stream_kernel<LSTM,S,NW,XR,ONCE>: the weight-streaming kernel for up to 16 rows per
 //       workgroup and K in whole 64-wide stages: operands staged through per-wave LDS rings by
 //       direct global->LDS loads of whole 128-byte lines (what bounds skinny_kernel is cache-line
 //       look-ups, 64 per KiB with its register-layout loads).
 //   attention_kernel.h   attention_kernel<RW,KG,S>: fused softmax(alpha Q.K^T).V for head dimension 64, K and V
-//       streamed through LDS, the keys optionally spread over groups of waves; attention_chain_kernel<KG>: the same
+//       streamed through LDS, the keys optionally spread over groups of waves; attention_chain_kernel<KG,ROWS>: the same
 //       for callers who want the scores and probabilities too.
 //   misc_kernels.h       softmax_rows_kernel (f32 scores -> bf16 probabilities), transpose_kn_kernel.
 //   probe_kernels.h      calibration probes: a register-only MFMA loop and a streaming read.
