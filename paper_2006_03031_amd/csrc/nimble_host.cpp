@@ -300,19 +300,26 @@ struct Launch {
   double us = 0;
 };
 
-// K slices for 17 to 64 rows of a layer whose weights come from memory, in tiles of 128 columns and all rows, or 0 where the
-// estimates decide.  Each slice of a tile column reads its weights once, past the caches (weights_pass_by), and the chip reads
-// fastest with a workgroup on every compute unit: the most slices that give them one at most, from 160 workgroups on.  Slices of
-// whole 4 KB are left out: then all workgroups read the same few memory channels (8192 x 8192 at 64 rows with K in four 36.8 us,
-// in three 31.1).  Microseconds, several layers in turn, by the estimates / so: 20 and 64 rows of 6144 x 6144 24.9 / 20.4 and 30.7 /
-// 24.5, 7168 x 7168 27.8 / 23.6 and 34.4 / 27.7, 8192 x 8192 29.3 / 28.5 and 43.1 / 31.1; 32 and 64 rows of 5120 x 13824 40.6 /
-// 30.8 and 47.5 / 33.9, 13824 x 5120 36.1 / 31.4 and 46.1 / 36.8, 4096 x 14336 33.4 / 27.3 and 36.9 / 30.8, 8192 x 28672 79.3 / 74.6
-// and 89.5 / 81.3; but 14336 x 4096 (in two, of 4 KB) 29.5 / 31.3 and 38.5 / 34.0.  A layer called over and over, which the
-// memory-side cache keeps: 6144 x 6144 23.0 / 19.3 and 22.5 / 24.3, 4096 x 8192 22.3 / 17.4 and 20.6 / 22.5.
+// K slices for 17 to 64 rows of a layer of more than kCachedWeightBytes, in tiles of 128 columns and all rows, or 0 where the
+// estimates decide: the most slices that give each compute unit one workgroup at most, from 160 workgroups on, so that each weight is
+// read once and by all of the chip.  Slices of whole 4 KB are left out: then all workgroups read the same few memory
+// channels (8192 x 8192 at 64 rows with K in four 36.8 us, in three 31.1).  Microseconds, several layers in turn (1 GB of them) / one over
+// and over, by the estimates -> so, both through the caches, at 20, 32 and 64 rows:
+//   4096 x 8192   22.4 / 19.6 -> 19.2 / 17.1   26.2 / 18.0 -> 19.4 / 17.2   23.4 / 19.4 -> 20.7 / 18.9
+//   8192 x 4096   20.0 / 17.2 -> 18.0 / 15.8   20.8 / 18.0 -> 18.5 / 16.1   25.0 / 18.6 -> 19.6 / 17.7
+//   6144 x 6144   23.7 / 19.0 -> 20.8 / 17.5   29.5 / 19.8 -> 21.0 / 17.9   30.5 / 21.4 -> 23.1 / 19.5
+//   7168 x 7168   26.7 / 22.1 -> 24.3 / 20.9   27.3 / 22.8 -> 24.4 / 20.9   34.0 / 24.2 -> 26.4 / 22.7
+//   4096 x 14336  30.6 / 26.1 -> 27.6 / 23.9   31.2 / 26.8 -> 27.6 / 24.1   36.5 / 26.9 -> 28.9 / 26.1
+//   8192 x 8192   31.4 / 26.0 -> 30.5 / 24.3   32.2 / 26.5 -> 30.7 / 24.5   42.9 / 28.7 -> 32.4 / 26.1
+//   5120 x 13824  37.6 / 30.7 -> 31.7 / 26.5   38.6 / 31.1 -> 31.9 / 26.8   46.8 / 33.6 -> 33.5 / 28.8
+//   13824 x 5120  34.5 / 26.4 -> 32.3 / 25.1   35.3 / 27.3 -> 33.0 / 25.6   45.5 / 30.8 -> 36.1 / 27.3
+//   8192 x 28672  86.1 / 85.0 -> 83.6 / 82.6   88.7 / 87.6 -> 85.4 / 84.2   95.2 / 93.4 -> 90.1 / 89.0
+// (14336 x 4096, which would be cut in two of 4 KB, in turn 29.5 -> 31.3 at 20 rows.)  Which of them then load the weights past the caches
+// is weights_pass_by's.
 // Not to f32: fewer, longer sums are further from the exact ones there (20 x 6144 x 6144 in five slices 2.0e-7, in eight 1.6e-7),
 // which a bf16 result does not show.
 static int streamed_slices(int variant, int64_t rows, int64_t N, int64_t K) {
-  if (rows <= 16 || rows > 64 || !weights_pass_by(N, K) || K % 64 != 0 || N % 128 != 0) return 0;
+  if (rows <= 16 || rows > 64 || (double)N * (double)K * 2.0 <= kCachedWeightBytes || K % 64 != 0 || N % 128 != 0) return 0;
   const int64_t stages = K / 64;
   for (int sk = 16; sk >= 2; --sk) {
     if (N / 128 * sk > kCUs || !split_k_ok(variant, 1, N, K, sk) || !wide_stages_ok(K, sk) || ceil_div(stages, sk) % 32 == 0) continue;

@@ -32,14 +32,36 @@ bool tile_rows_ok(int variant, int bm, int64_t N, int64_t K);
 // as cache-resident, which is what a layer loop or a token loop sees.
 constexpr double kCachedWeightBytes = 64e6;
 
-// Whether the weights of an [N, K] layer that a launch reads once are loaded non-temporally: where each call finds them in memory, which
-// is then read at the rate of a plain read.  Several layers in turn, 512 MB of them, microseconds per layer at 1 / 5 / 16 rows, through the
-// caches / past them: 8192 x 8192 23.7 / 23.6 / 25.9, 21.5 / 21.4 / 24.8 (a plain read of the bytes 21.4), 7168 x 7168 19.5 /
-// 20.2 / 24.7, 17.8 / 18.5 / 22.0, 6144 x 6144 16.7 / 17.0 / 20.7, 15.4 / 15.2 / 19.4.  What the caches could keep is slower: a single layer over
-// and over, 4096 x 4096 4.1 / 4.3 / 5.2, 4.5 / 5.1 / 6.5, 8192 x 8192 (in the memory-side cache then) 21.5 / 21.0 / 21.2,
-// 19.8 / 20.0 / 26.6.  The line is the one above which layers are taken to come from memory everywhere.  The 32- and
-// 64-row tiles with K cut do so too where one tile row reads all weights once: 8192 x 8192 at 17 / 32 rows 32.0 / 32.7, 28.8 / 30.4.
-inline bool weights_pass_by(int64_t N, int64_t K) { return (double)N * (double)K * 2.0 > kCachedWeightBytes; }
+// What the memory-side cache holds.
+constexpr double kMemorySideCacheBytes = 256.0 * 1024 * 1024;
+
+// Whether a launch of up to 64 rows that reads the weights of an [N, K] layer once loads them non-temporally.  Where each call finds
+// them in memory that is faster, since memory is then read at the rate of a plain read; but such loads leave nothing in the memory-side
+// cache either, and a layer that this would have held (a wide layer among small ones) is slower with them.  Microseconds
+// per layer, several layers in turn (1 GB of them) / one over and over, through the caches -> past them:
+//   Streaming kernel,   1 row                       8 rows                      16 rows
+//   8192 x 4096         13.3 / 12.2 -> 11.8 / 9.7   13.4 / 11.2 -> 12.0 / 10.5  15.7 / 12.2 -> 14.6 / 13.2
+//   6144 x 6144         16.0 / 12.1 -> 14.6 / 12.7  18.0 / 12.6 -> 16.2 / 14.4  21.0 / 14.4 -> 19.8 / 18.2
+//   7168 x 7168         19.0 / 15.7 -> 17.1 / 15.6  20.3 / 16.1 -> 18.6 / 17.2  25.2 / 17.6 -> 22.5 / 21.2
+//   8192 x 8192         23.9 / 21.1 -> 21.7 / 19.7  24.2 / 20.0 -> 22.1 / 20.3  26.7 / 21.1 -> 25.6 / 24.2
+//   5120 x 13824        30.6 / 24.0 -> 28.2 / 25.9  33.6 / 24.2 -> 31.6 / 29.8  39.3 / 27.4 -> 38.1 / 36.5
+//   32000 x 4096        44.3 / 40.5 -> 39.8 / 37.0  45.7 / 37.5 -> 39.9 / 38.2  56.7 / 41.7 -> 53.0 / 51.1
+//   8192 x 28672        78.5 / 77.5 -> 69.7 / 67.1  79.6 / 78.2 -> 72.2 / 70.1  90.0 / 88.9 -> 84.3 / 82.8
+// Up to 8 rows what is gained in turn is what is lost over and over at most (but for layers that leave the cache to little else), beyond
+// that it is less; what the cache cannot hold gains either way.
+//   32-row tiles with K cut, 20 and 32 rows: 4096 x 8192 19.2 / 17.1 -> 18.9 / 16.8, 19.4 / 17.2 -> 19.7 / 18.2; 8192 x 4096 18.0 / 15.8 -> 15.6 /
+// 14.1, 18.5 / 16.1 -> 15.9 / 14.3; 6144 x 6144 20.8 / 17.5 -> 20.2 / 18.5, 21.0 / 17.9 -> 21.1 / 19.7; 8192 x 8192 30.5 / 24.3 -> 28.1 / 26.8,
+// 30.7 / 24.5 -> 28.6 / 27.4; 5120 x 13824 31.7 / 26.5 -> 29.7 / 28.0, 31.9 / 26.8 -> 30.3 / 29.2; 8192 x 14336 46.0 / 38.1 -> 40.2 / 38.7, 46.4 /
+// 38.3 -> 40.6 / 39.3; with K in two, or more than a workgroup per compute unit, 13824 x 5120 32.3 / 25.1 -> 29.8 / 28.7, 14336 x 4096 28.4 /
+// 22.8 -> 27.1 / 25.6, 32000 x 4096 61.7 / 46.1 -> 58.5 / 59.0.
+//   64-row tiles with K cut, 64 rows: 6144 x 6144 23.1 / 19.5 -> 25.1 / 24.1, 7168 x 7168 26.4 / 22.7 -> 27.6 / 26.7, 8192 x 8192 32.4 /
+// 26.1 -> 30.7 / 30.1, 8192 x 28672 90.1 / 89.0 -> 81.2 / 79.8.
+inline bool weights_pass_by(int64_t rows, int64_t N, int64_t K, int64_t slices) {
+  const double bytes = (double)N * (double)K * 2.0;
+  if (bytes <= kCachedWeightBytes) return false;
+  if (rows <= 8 || bytes > kMemorySideCacheBytes) return true;
+  return rows > 16 && rows <= 32 && slices >= 3 && (N + 127) / 128 * slices <= kComputeUnits;
+}
 
 // Whether every one of `slices` K slices gets whole 64-wide stages (the 64-wide ring).  NIMBLE_RING32 (a
 // measurement knob, read once) turns that ring off.

@@ -69,7 +69,7 @@ static int launch_ring_copy(const GemmArgs& g, const nimble_plan& p, dim3 grid, 
   using Yes = std::true_type;
   using No = std::false_type;
   if constexpr (WIDE && S == 3 && WGM == 2 && WGN == 2 && BN == 128) {  // (the tiles of up to 64 rows: K is cut, the sums go to scratch)
-    if (tiles_m == 1 && grid.y > 1 && weights_pass_by(g.N, g.K)) {
+    if (tiles_m == 1 && grid.y > 1 && weights_pass_by(g.M, g.N, g.K, grid.y)) {
       hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, S, true, false, true>), grid, dim3(WGM * WGN * 64), 0, st, g, tiles_m,
                          tiles_n, group_m);
       return check_hip(hipGetLastError(), "ring kernel launch");
@@ -161,8 +161,8 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
   const int mt = (s.M + 16 * (int)p.grid[1] - 1) / (16 * (int)p.grid[1]);
   if (stream_kernel_ok(LSTM, 16 * mt, s.N, s.K, s.Ix)) {
     // eight waves with three stages each; up to 8 rows the activation tile is 8 rows (measured on a
-    // 134 MB layer from HBM: 23.9 us at one row, 25.0 at four; the 16-row tile 24.7 and 25.6, and 27.9 at
-    // sixteen rows; four waves per workgroup 27.9-30.5 us whatever the ring depth)
+    // 134 MB layer from HBM, through the caches: 23.9 us at one row, 25.0 at four; the 16-row tile 24.7 and 25.6, and 27.9 at
+    // sixteen rows; four waves per workgroup 27.9-30.5 us whatever the ring depth.  Past them, see weights_pass_by, 21.7 at one row)
     // More workgroups than compute units on a cache-resident layer (several 16-row blocks): small
     // workgroups of four waves with two stages each, four to a compute unit, so that one's start-up and
     // reduction overlap the others' streaming (2304 x 768 at 128 rows: 5.2 us against 7.8 with the
@@ -171,7 +171,7 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
                       (double)s.N * (double)s.K * 2.0 <= kCachedWeightBytes;
     if (many)
       hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16>), grid, dim3(256), 0, st, s);
-    else if (!LSTM && weights_pass_by(s.N, s.K) && grid.y == 1) {
+    else if (!LSTM && grid.y == 1 && weights_pass_by(s.M, s.N, s.K, 1)) {
       if (s.M <= 8)
         hipLaunchKernelGGL((stream_kernel<false, 3, 8, 8, true>), grid, dim3(512), 0, st, s);
       else
