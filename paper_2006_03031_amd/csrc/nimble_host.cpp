@@ -424,8 +424,9 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
     best.variant = NIMBLE_VAR_SKINNY16;
     best.us = skinny_us;
   }
+  // (in place of another cut of K only: what ran without scratch still does)
   const int tile = rows <= 32 ? NIMBLE_VAR_T32x128 : NIMBLE_VAR_T64x128;
-  const int slices = batch == 1 && !out_f32 ? streamed_slices(tile, rows, N, K) : 0;
+  const int slices = batch == 1 && best.split_k > 1 && !out_f32 ? streamed_slices(tile, rows, N, K) : 0;
   if (slices > 1 && tiled_variant_ok(tile, rows, N, K) && (uint64_t)slices * (uint64_t)rows * (uint64_t)N * 4u <= max_workspace) {
     best.variant = tile;  // (its estimate stays: what it is compared with was fitted beside it)
     best.split_k = slices;
