@@ -331,7 +331,7 @@ static int streamed_slices(int variant, int64_t rows, int64_t N, int64_t K) {
 // Best single launch for `rows` rows: the least estimated time among weight streaming (up to
 // 64 rows) and every tiled variant and K split that fits the workspace.
 static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int epilogue,
-                          uint64_t max_workspace, bool allow_skinny, bool out_f32, bool allow_halved = true) {
+                          uint64_t max_workspace, bool allow_skinny, bool out_f32, bool allow_streamed, bool allow_halved = true) {
   Launch best, roomy;  // within the workspace, and with as much of it as anyone could bring
   double skinny_us = -1.0, least_tiled_us = 1e30;
   // weight streaming: up to 64 rows, and beyond that in 16-row blocks of the streaming kernel while
@@ -426,9 +426,9 @@ static Launch best_launch(int64_t batch, int64_t rows, int64_t N, int64_t K, int
   }
   // (in place of another cut of K only: what ran without scratch still does)
   const int tile = rows <= 32 ? NIMBLE_VAR_T32x128 : NIMBLE_VAR_T64x128;
-  const int slices = batch == 1 && best.split_k > 1 && !out_f32 ? streamed_slices(tile, rows, N, K) : 0;
+  const int slices = batch == 1 && best.split_k > 1 && allow_streamed && !out_f32 ? streamed_slices(tile, rows, N, K) : 0;
   if (slices > 1 && tiled_variant_ok(tile, rows, N, K) && (uint64_t)slices * (uint64_t)rows * (uint64_t)N * 4u <= max_workspace) {
-    best.variant = tile;  // (its estimate stays: what it is compared with was fitted beside it)
+    best.variant = tile;  // (its estimate stays: nothing is compared with it, 64 rows are never split)
     best.split_k = slices;
     best.bm = 0;
     best.halved = false;
@@ -527,7 +527,9 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
       chosen = true;
       split_k = e->split_k > 1 ? e->split_k : 1;
     } else {
-      const Launch single = best_launch(batch, M, N, K, epilogue, opt.max_workspace, true, opt.out_f32);
+      // (streamed_slices was measured on calls of their own: the rest of a row split, whose weights the first launch has just read, goes
+      // by the estimates with which the split is decided)
+      const Launch single = best_launch(batch, M, N, K, epilogue, opt.max_workspace, true, opt.out_f32, opt.allow_row_split);
       variant = single.variant < 0 ? NIMBLE_VAR_GENERIC : single.variant;
       split_k = single.split_k;
       tile_rows = single.bm;
@@ -555,7 +557,7 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
             if (head_us >= best_us) continue;  // (the tail's search is most of what a plan costs)
             // (priced without halved tiles: two launches picked for their sake took 1 to 2 % longer than one:
             // 4751 x 8192 x 7552 426.9 us, 417.7 in 320-row tiles)
-            const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true, opt.out_f32, false);
+            const Launch tail = best_launch(1, rest, N, K, epilogue, opt.max_workspace, true, opt.out_f32, false, false);
             if (tail.variant < 0) continue;
             // (a streamed tail's estimate and the gap both count its launch, which decides against halved tiles at
             // K > 2048: 4154 x 1024 x 3648 with GELU 36.6 us in two launches, 38.8 in halves)

@@ -218,6 +218,7 @@ struct GemmArgs {
   int out_f32;
   int b_is_kn;
   int batch;
+  int weights_read;  // another launch of the same call has just read b (host only: weights_pass_by is not asked)
 };
 
 // Whether the tiled kernels leave their output in the L2s (plain stores) instead of writing it through them as it is made

@@ -69,7 +69,7 @@ static int launch_ring_copy(const GemmArgs& g, const nimble_plan& p, dim3 grid, 
   using Yes = std::true_type;
   using No = std::false_type;
   if constexpr (WIDE && S == 3 && WGM == 2 && WGN == 2 && BN == 128) {  // (the tiles of up to 64 rows: K is cut, the sums go to scratch)
-    if (tiles_m == 1 && grid.y > 1 && weights_pass_by(g.M, g.N, g.K, grid.y)) {
+    if (tiles_m == 1 && grid.y > 1 && !g.weights_read && weights_pass_by(g.M, g.N, g.K, grid.y)) {
       hipLaunchKernelGGL((gemm_ring_kernel<BM, BN, WGM, WGN, true, S, true, false, true>), grid, dim3(WGM * WGN * 64), 0, st, g, tiles_m,
                          tiles_n, group_m);
       return check_hip(hipGetLastError(), "ring kernel launch");
@@ -155,7 +155,7 @@ static bool stream_kernel_ok(bool lstm, int rows_per_block, int64_t N, int64_t K
 }
 
 template <bool LSTM>
-static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t st) {
+static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t st, bool weights_read = false) {
   dim3 grid(p.grid[0], p.grid[1], 1), block(256);
   // 16-row tiles per workgroup: the rows spread evenly over the plan's row blocks (at most 4 each)
   const int mt = (s.M + 16 * (int)p.grid[1] - 1) / (16 * (int)p.grid[1]);
@@ -171,7 +171,7 @@ static int launch_skinny(const SkinnyArgs& s, const nimble_plan& p, hipStream_t 
                       (double)s.N * (double)s.K * 2.0 <= kCachedWeightBytes;
     if (many)
       hipLaunchKernelGGL((stream_kernel<LSTM, 2, 4, 16>), grid, dim3(256), 0, st, s);
-    else if (!LSTM && grid.y == 1 && weights_pass_by(s.M, s.N, s.K, 1)) {
+    else if (!LSTM && grid.y == 1 && !weights_read && weights_pass_by(s.M, s.N, s.K, 1)) {
       if (s.M <= 8)
         hipLaunchKernelGGL((stream_kernel<false, 3, 8, 8, true>), grid, dim3(512), 0, st, s);
       else
@@ -280,7 +280,7 @@ static int launch_gemm(const GemmArgs& g, const nimble_plan& p, hipStream_t st) 
         return check_hip(hipGetLastError(), "skinny kernel launch");
       }
       return launch_any(g, st);
-    case NIMBLE_VAR_SKINNY16: return launch_skinny<false>(skinny_args(g), p, st);
+    case NIMBLE_VAR_SKINNY16: return launch_skinny<false>(skinny_args(g), p, st, g.weights_read != 0);
     case NIMBLE_VAR_T32x128: return launch_ring<32, 128, 2, 2, 3>(g, p, st);
     case NIMBLE_VAR_T64x128:
       if (lone) return launch_lone<64, 128, 4, 2, 3>(g, p, st);
@@ -543,6 +543,7 @@ int nimble_dense_variant_dyn(const void* x, const void* w, const void* bias, voi
   if (rc != NIMBLE_OK) return rc;
   GemmArgs tail = g;
   tail.M = (int)(M - p.split_rows);
+  tail.weights_read = 1;
   tail.a = (const u16*)x + p.split_rows * K;
   tail.c = g.out_f32 ? (void*)((float*)y + p.split_rows * N) : (void*)((u16*)y + p.split_rows * N);
   return run_dense(tail, rp, workspace, (hipStream_t)stream);

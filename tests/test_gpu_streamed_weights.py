@@ -1,7 +1,7 @@
 """Layers of more than 64 MB of weights against float64: up to 16 rows in the streaming kernel, which loads the weights past the caches
 (up to 8 rows, and of layers beyond 256 MiB) or through them, the 8-row and the 16-row activation tile, a partly filled last block of weight
 rows, the layers just above and just below the line, twice in a row with other weights in the same memory; 17 to 64 rows in one
-row of tiles with K cut, past the caches and through them."""
+row of tiles with K cut, past the caches and through them; and such a layer as the rest of a row split."""
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -63,3 +63,23 @@ def test_all_rows_in_one_tile_with_k_cut(M, N, K, slices, to_f32):
         for out in outs:
             assert ((out.double() - want).abs() / (want.abs() + want.abs().mean())).max().item() <= tol, od
         assert torch.equal(outs[0], outs[2])
+
+
+# 5 rows streamed, 19 and 33 rows with K cut by the estimates, behind a launch of 2048 or 4096 rows
+@pytest.mark.parametrize("M,N,K,rest", [(2053, 4096, 8192, 5), (2067, 4096, 14336, 19), (2081, 4096, 8192, 33), (4111, 8192, 4096, 15)])
+def test_the_rest_of_a_row_split(M, N, K, rest):
+    import paper_2006_03031_amd as nb
+    from paper_2006_03031_amd import runtime as rt
+    nb.load()
+    p = nb.dense_plan(M, N, K)
+    assert M - p.split_rows == rest
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N)
+    x = torch.empty((M, K), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    b = torch.empty((N,), device="cuda").uniform_(-1, 1, generator=gen).to(torch.bfloat16)
+    w = torch.empty((N, K), dtype=torch.bfloat16, device="cuda").normal_(0, 0.02, generator=gen)
+    print(f"split {M} x {N} x {K}, the rest {rest}", flush=True)
+    got = rt.dense(x, w, b)
+    rows = slice(p.split_rows - 64, M)
+    want = x[rows].double() @ w.double().T.contiguous() + b.double()
+    assert ((got[rows].double() - want).abs() / (want.abs() + want.abs().mean())).max().item() <= 2.0 ** -8     # one rounding

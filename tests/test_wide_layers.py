@@ -54,3 +54,10 @@ def test_the_cut(N, K, slices):
 def test_plans_without_scratch_stay_so(M, N, K):
     p = nb.dense_plan(M, N, K)
     assert p.workspace_bytes == 0 and (p.split_k == 1 or p.name == "skinny16"), p
+
+
+# the rest of a row split is planned by the estimates with which the split was decided
+@pytest.mark.parametrize("M,N,K,variant,workspace", [(2081, 4096, 8192, "t32x128", 8 * 33 * 4096 * 4), (2067, 4096, 14336, "t32x128", 16 * 19 * 4096 * 4)])
+def test_the_rest_of_a_row_split(M, N, K, variant, workspace):
+    p = nb.dense_plan(M, N, K)
+    assert p.split_rows == 2048 and nb.variant_name(p.residue_variant) == variant and p.workspace_bytes == workspace
