@@ -12,5 +12,5 @@ from .binding import (  # noqa: F401
     nimble_attention_dyn, nimble_attention_chain_dyn, nimble_lstm_gates_dyn, nimble_lstm_gates_pre_dyn, nimble_softmax_rows_dyn, residue_split, storage_alignment, storage_bytes,
     lstm_seq_shape, lstm_seq_supported, lstm_seq_preferred, lstm_seq_workspace_bytes, nimble_lstm_seq_pre_dyn, nimble_lstm_seq_status,
     lstm_loop_supported, lstm_loop_preferred, lstm_loop_workspace_bytes, nimble_lstm_loop_dyn,
-    variant_name, exported_symbols, nimble_probe_mfma_bf16, nimble_probe_hbm_read,
+    variant_name, exported_symbols, nimble_probe_mfma_bf16, nimble_probe_hbm_read, nimble_probe_lstm_loop,
 )

@@ -125,6 +125,8 @@ def load():
     lib.nimble_lstm_loop_workspace_bytes.restype = ctypes.c_size_t
     lib.nimble_lstm_loop_dyn.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, vp, ctypes.c_size_t,
                                          ctypes.c_uint32, vp]
+    lib.nimble_probe_lstm_loop.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, i64, i64, i64, i64, vp, ctypes.c_size_t,
+                                           ctypes.c_uint32, ctypes.c_uint32, vp]
     lib.nimble_probe_mfma_bf16.argtypes = [vp, vp, i32, i32, ctypes.POINTER(ctypes.c_double), vp]
     lib.nimble_probe_hbm_read.argtypes = [vp, ctypes.c_size_t, vp, vp]
     _lib = lib
@@ -402,3 +404,10 @@ def nimble_probe_mfma_bf16(seed: int, sink: int, waves_per_simd: int, iters: int
 
 def nimble_probe_hbm_read(buf: int, nbytes: int, sink: int, stream: int = 0) -> None:
     _check(load().nimble_probe_hbm_read(buf, nbytes, sink, stream))
+
+
+def nimble_probe_lstm_loop(x: int, pre: int, w: int, bias: int, h0: int, c0: int, h_seq: int, c_out: int, T: int, B: int,
+                           Ix: int, H: int, workspace: int, workspace_bytes: int, max_polls: int, apart: int, stream: int) -> None:
+    """The token loop with workgroups of even (bit 0 of apart) and odd number (bit 1) storing as if their row group did not share an XCD."""
+    _check(load().nimble_probe_lstm_loop(x, pre, w, bias, h0, c0, h_seq, c_out, T, B, Ix, H, workspace, workspace_bytes, max_polls,
+                                         apart, stream))

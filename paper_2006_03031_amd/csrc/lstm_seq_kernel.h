@@ -88,6 +88,7 @@ struct LstmSeqArgs {
   int T, B, Ix, H;
   int ranges;         // of K stages with a sum of their own: 8, or 4 where the per-step launch runs four waves
   uint32_t max_polls;
+  uint32_t apart;     // 0; tests: bit 0 (1) set, workgroups of even (odd) number store as if the row group did not share an XCD
 };
 
 // Clears the control words and the hand-over words, keeps c_0 for the recovery kernel.
@@ -240,7 +241,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       v = __hip_atomic_load(ids, __ATOMIC_RELAXED, SCOPE);
       if (__all(v != 0ull)) break;
     }
-    near = __all(v == here);
+    near = __all(v == here) && (a.apart >> (wg & 1) & 1u) == 0u;
   }
   // word of this lane in a load: R = 8: 32 k, rows by lane & 7, pieces of 4 k by gq and bit 3; R = 4: 64 k
   uint32_t ask;   // (bytes, as is the next)

@@ -778,6 +778,12 @@ int nimble_lstm_seq_pre_dyn(const void* pre, const void* w_h, const void* h0, co
 int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const void* bias, const void* h0,
                          const void* c0, void* h_seq, void* c_out, int64_t T, int64_t B, int64_t Ix, int64_t H,
                          void* workspace, size_t workspace_bytes, uint32_t max_polls, void* stream) {
+  return nimble_probe_lstm_loop(x, pre, w, bias, h0, c0, h_seq, c_out, T, B, Ix, H, workspace, workspace_bytes, max_polls, 0, stream);
+}
+
+int nimble_probe_lstm_loop(const void* x, const void* pre, const void* w, const void* bias, const void* h0,
+                           const void* c0, void* h_seq, void* c_out, int64_t T, int64_t B, int64_t Ix, int64_t H,
+                           void* workspace, size_t workspace_bytes, uint32_t max_polls, uint32_t apart, void* stream) {
   clear_error();
   if (T < 0 || B < 0 || Ix < 0 || H < 0) return fail(NIMBLE_ERR_ARG, "negative extent");
   if (!nimble_lstm_loop_supported(B, Ix, H))
@@ -814,6 +820,7 @@ int nimble_lstm_loop_dyn(const void* x, const void* pre, const void* w, const vo
   if (rc != NIMBLE_OK) return rc;
   a.ranges = step.split_k;
   a.max_polls = max_polls;
+  a.apart = apart;
   rc = launch_lstm_seq(a, (hipStream_t)stream);
   if (rc != NIMBLE_OK) return rc;
   hipLaunchKernelGGL(lstm_seq_recover_kernel, dim3((unsigned)((B + 15) / 16)), dim3(1024), 0, (hipStream_t)stream, a);

@@ -42,8 +42,8 @@ def _steps(rt, x, w, bias, h0, c0):
     return torch.stack(hs), c
 
 
-def _loop(nb, x, w, bias, h0, c0, max_polls=1 << 14):
-    """One call into buffers of NaNs; returns (h_seq, c, gave up)."""
+def _loop(nb, x, w, bias, h0, c0, max_polls=1 << 14, apart=None):
+    """One call into buffers of NaNs; returns (h_seq, c, gave up).  apart: the scope of the stores is set from here."""
     fused = x.dtype is torch.bfloat16
     T, B, H = x.shape[0], h0.shape[0], h0.shape[1]
     Ix = x.shape[2] if fused else 0
@@ -51,10 +51,11 @@ def _loop(nb, x, w, bias, h0, c0, max_polls=1 << 14):
     c = c0.clone()                                        # c_out may be c_0
     ws = torch.full((nb.lstm_loop_workspace_bytes(B, Ix, H),), 255, dtype=torch.uint8, device="cuda")
     st = torch.cuda.current_stream().cuda_stream
-    print(f"loop T={T} B={B} Ix={Ix} H={H} polls={max_polls}", flush=True)
-    nb.nimble_lstm_loop_dyn(x.data_ptr() if fused else 0, 0 if fused else x.data_ptr(), w.data_ptr(), bias.data_ptr(),
-                            h0.data_ptr(), c.data_ptr(), h_seq.data_ptr(), c.data_ptr(), T, B, Ix, H, ws.data_ptr(),
-                            ws.numel(), max_polls, st)
+    print(f"loop T={T} B={B} Ix={Ix} H={H} polls={max_polls} apart={apart}", flush=True)
+    call = nb.nimble_lstm_loop_dyn if apart is None else nb.nimble_probe_lstm_loop
+    call(x.data_ptr() if fused else 0, 0 if fused else x.data_ptr(), w.data_ptr(), bias.data_ptr(),
+         h0.data_ptr(), c.data_ptr(), h_seq.data_ptr(), c.data_ptr(), T, B, Ix, H, ws.data_ptr(),
+         ws.numel(), max_polls, *(() if apart is None else (apart,)), st)
     return h_seq, c, nb.nimble_lstm_seq_status(ws.data_ptr(), st)
 
 
@@ -93,6 +94,29 @@ def test_inputs_that_arrive_three_steps_ahead(rt, nb, T, B, Ix, H):
     want_h, want_c = _steps(rt, *case)
     h, c, gave_up = _loop(nb, *case)
     assert not gave_up and _same(h, want_h) and torch.equal(c, want_c)
+
+
+@pytest.mark.parametrize("B,Ix,H", [(1, 0, 512), (1, 512, 512), (4, 0, 256), (4, 256, 256), (8, 512, 512), (9, 0, 512), (37, 512, 512),
+                                    (33, 0, 512), (3, 64, 64), (41, 192, 320), (3, 128, 640)])
+@pytest.mark.parametrize("apart", [3, 1, 2])
+def test_the_scope_of_the_stores(rt, nb, B, Ix, H, apart):
+    """Up to H = 512 a row group's workgroups share an XCD on an idle GPU and store plainly.  Here all of them, or every other one, store
+    with device scope, as where they do not share one or have not seen that they do; seven steps: either buffer with both
+    phases, the first one over the XCD numbers.  (Above H = 512 they all store so anyway.)"""
+    case = _case(9, 7, B, Ix, H)
+    want_h, want_c = _steps(rt, *case)
+    h, c, gave_up = _loop(nb, *case, apart=apart)
+    assert not gave_up and _same(h, want_h) and torch.equal(c, want_c)
+
+
+@pytest.mark.parametrize("polls", [1, 2, 5])
+@pytest.mark.parametrize("B,Ix", [(1, 0), (4, 512), (37, 512)])
+def test_waits_that_run_out_early(rt, nb, B, Ix, polls):
+    """So few polls that some workgroups miss the XCD numbers and the loop gives up somewhere, if it does: the results are right either way."""
+    case = _case(10, 7, B, Ix, 512)
+    want_h, want_c = _steps(rt, *case)
+    h, c, _ = _loop(nb, *case, max_polls=polls)
+    assert _same(h, want_h) and torch.equal(c, want_c)
 
 
 @pytest.mark.parametrize("T,B,Ix,H", [(4, 37, 512, 512), (3, 4, 0, 512), (3, 11, 0, 576), (3, 3, 64, 64), (2, 64, 0, 512),
