@@ -22,12 +22,13 @@ namespace nimble {
 //   from the L2 at 114 KB per us where each lane's address is a whole 32-bit word, at 35 where it is not, at 54 where every other
 //   row is not.  So such rows are loaded from the element before and moved down on the way to LDS; the word behind a stage's
 //   last chunk is loaded by one lane per row (by all lanes, or all rows, it cost as much as it saved).
-//   What bounds it: a few hundred tiles of some ten stages are the whole launch, so the chain load ->
-//   LDS -> MFMA per stage.  By time stamps, 515 x 1001 x 1003 to f32: first stages 1.7 us, the other three rounds of four 3.6, the
-//   end of the tile 1.7, launch 1.5: 8.7 us; before the words, with a K tail that waited for its loads one by one, and with the first group
-//   alone at the end 10.7.  515 x 1001 x 1008 8.4 -> 7.8, x 64 5.2 -> 4.4, x 2003 16.9 -> 15.3.  Measured earlier, 515 x 1001 x 1003 to f32: 671 us with the scalar kernel
-//   it replaces (one thread per output) -> 13.3 (one group, four register sets) -> 12.1 (two groups) -> 11.5 (four
-//   groups, two register sets each; with four 12.7), the same with K = 1000 9.4; 500 x 500 x 2003 20.6 -> 18.0 -> 16.8;
+//   What bounds it: a few hundred tiles of some ten stages are the whole launch, so that it is the chain load ->
+//   LDS -> MFMA of one tile's stages.  By time stamps, 515 x 1001 x 1003 to f32: first stages 1.7 us, the other three rounds of
+//   four 3.6, the end of the tile 1.7, launch 1.5: 8.7 us; before the words, with a K tail that waited for its loads one by one, and
+//   with the first group alone at the end 10.7.  515 x 1001 x 1008 8.4 -> 7.8, x 64 5.2 -> 4.4, x 2003 16.9 -> 15.3.  Measured
+//   earlier, 515 x 1001 x 1003 to f32: 671 us with the scalar kernel it replaces (one thread per output) -> 13.3 (one
+//   group, four register sets) -> 12.1 (two groups) -> 11.5 (four groups, two register sets each; with four
+//   12.7), the same with K = 1000 9.4; 500 x 500 x 2003 20.6 -> 18.0 -> 16.8;
 //   12 x 333 x 64 x 333 as A.B 88 -> 6.6 us.  128 x 128 tiles were measured too: no faster even at
 //   8000 x 1001 x 1003 (54 us against 51), half the speed on small grids.
 //   THROUGH: f32 outputs are written through the L2s (see any_output_stays).

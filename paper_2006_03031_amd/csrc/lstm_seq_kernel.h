@@ -22,12 +22,12 @@ namespace nimble {
 //   streams never wait for each other's.  (With all groups in one launch, two to an XCD at a time, 64 steps of 128 / 256 rows, H = Ix = 512, took 165 /
 //   302 us instead of 196 / 369; but two such loops could each hold places that the other's next group lacked, and 4 in
 //   70 gave up.  Captured launches per step 338 / 556.)  Per step a
-//   wave multiplies its stages of x_t, loaded a step ahead, or its K range of h_{t-1}, and leaves its partial sums
+//   wave multiplies its stages of x_t, loaded ahead, or its K range of h_{t-1}, and leaves its partial sums
 //   in LDS; after one barrier the first R U lanes, one per (row, unit), add them up and update the cell.  c_t
 //   stays in that lane's register.
-//   Hand-over of h_t: 64-bit words of four neighbouring units of a row, stored into buffer t & 1 of two, in an order in which a wave stores 128 contiguous bytes (8 workgroups' words in one line: 2.4 us
-//   per step) and loads 512 (8 rows of 32 k or 4 rows of 64 k).  |h| <= 1 leaves bit 14 of a bf16, the top bit of
-//   its exponent, zero: in the first value of a word it carries the phase, which changes with every use of a
+//   Hand-over of h_t: 64-bit words of four neighbouring units of a row, stored into buffer t & 1 of two, in an order in
+//   which a wave stores 128 contiguous bytes (8 workgroups' words in one line: 2.4 us per step) and loads
+//   512 (8 rows of 32 k or 4 rows of 64 k).  |h| <= 1 leaves bit 14 of a bf16, the top bit of its exponent, zero: in the first value of a word it carries the phase, which changes with every use of a
 //   buffer, in the second a mark that values of the word are NaN (then written as 0x3fff, which no h is).  A
 //   consumer wave loads the words of its K range, device scope, until all of them are in this step's phase: data
 //   and arrival are one word, no counter, no fence, one store and one load on the critical path (a counter
@@ -43,13 +43,15 @@ namespace nimble {
 //   So each workgroup leaves its XCD's number in the first of its words of buffer 0, which nobody writes before every
 //   workgroup has read them (that takes h_2), without the phase bit; a workgroup that finds all numbers
 //   of its row group equal to its own stores plainly from then on, any other with device scope.  Nobody relies on the
-//   others' choice: all are right, the plain stores are seen by all who can look for them.  128 steps, pre
-//   form of H = 512, 1 / 4 / 16 rows 156 / 150 / 165 -> 122 / 126 / 137 us.
+//   others' choice: all are right, the plain stores are seen by all who can look for them.  128 steps, by kernel
+//   trace, device-scope stores throughout / so: pre form of H = 512, 1, 4 and 16 rows 150 / 131, 151 / 131, 170 / 145 us, of H = 256, 1 row
+//   140 / 123; x form of H = Ix = 512, 4, 37 and 64 rows 175 / 144, 184 / 162, 182 / 159.
 //   x_t comes from memory, and what a compute unit's waves load returns in order, so that polls queue behind x.  The waves
 //   that multiply x load it straight into LDS, three steps ahead and right behind the barrier, when this step's
 //   polls are over and the next ones are some 900 clocks away (loaded into registers behind the products a step
 //   ahead 4 / 37 rows, H = Ix = 512, took 153 / 175 us, into LDS but behind the products 152 / 162, by the polling waves as their words
-//   had arrived 155 / 179; now 139 / 151; before the plain stores 163 / 169).
+//   had arrived 155 / 179, so 139 / 151; before the plain stores 163 / 169).  Those of them that update cells too wait for a step
+//   more than they need, see there.  ORDER 2, whose waves hold units of x beside units of h, loads x into registers a step ahead.
 //   Every wait is bounded: a wave polls at most max_polls times per step, looking at the give-up word with every
 //   eighth; a wave that runs out sets it, and every workgroup leaves at its next check.  So the
 //   grid drains whatever happens (fewer workgroups resident than launched, a stalled neighbour).  Then either
@@ -59,10 +61,10 @@ namespace nimble {
 //   eight or four ranges of K stages, the same two accumulators per range, the same order of adding the ranges' sums,
 //   the same cell function).
 //   What bounds it: a chain of, in clocks by time stamps, products and partial sums to LDS 400, barrier 150, sums 250, cell 600,
-//   and the way through the L2 to the slowest workgroup 700.  Microseconds per step, pre form at
-//   1 / 4 rows: H = 512 0.96 / 0.99, H = 1024 1.41 / 1.56, H = 256 0.95 / - (32-bit words with a step tag each, four lanes
-//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 rows, H = Ix = 512: 1.09 /
-//   1.18 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
+//   and the way through the L2 to the slowest workgroup 700.  Microseconds per step, by kernel trace, pre form at
+//   1 / 4 rows: H = 512 1.02 / 1.02, H = 1024 1.51 / 1.52, H = 256 0.96 / - (32-bit words with a step tag each, four lanes
+//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 / 64 rows, H = Ix = 512: 1.13 / 1.26 /
+//   1.24 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
 //   per cell, 32-byte stores 2.31; one lane per cell, 128-byte stores 1.95; a row group's workgroups on one XCD
 //   and a late first poll 1.56; operands polled straight into their registers, no address arithmetic in the loop 1.37.
 //   Tried and not kept: system scope, exchanges instead of stores, raised priority for the cells (no change); a
@@ -256,7 +258,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
     from = (uint32_t)(of_x ? orow * Ix + k_begin + gq * 8 : orow * H + h_begin + gq * 8) * 2u;
   }
 
-  // operands of this wave's units for the step to come: x_t, loaded a step ahead, or h_{t-1}
+  // operands of this wave's units for the step to come: x_t (from its ring; MIX: loaded a step ahead) or h_{t-1}
   uint4 f[NU];
 #pragma unroll
   for (int j = 0; j < NU; ++j) f[j] = make_uint4(0, 0, 0, 0);  // (units that this wave does not have: zeros)
@@ -307,8 +309,9 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   }
   for (int t = 1;; ++t) {
     if (XR && of_x) {
-      // this step's loads were issued three steps ago: behind them are those of two more steps and, from the cells' waves,
-      // at least a store per step
+      // this step's loads were issued three steps ago: behind them are those of two more steps and, from the cells' waves, two
+      // stores per step (each such wave has a lane in row 0 that stores).  Half of these are counted: with a load per step
+      // those waves wait for the next step's load too, i.e. run two steps ahead.
       if (cells)
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * XLOADS + 3) : "memory");
       else

@@ -228,9 +228,9 @@ static int64_t skinny_row_blocks(int64_t rows, int64_t N, int64_t K, bool stream
 
 // The weight-streaming kernels, launch latency included.
 // Streaming kernel (blocks of 16 rows): whichever is longer of the weight stream and the waves'
-// walk over their K stages, round of workgroups after round.  Measured: a 134 MB layer from HBM
-// 24.0 us at 1..8 rows and 27.9 at 16; cache-resident layers 2.5-2.8 us at K = 768..1024, 3.3-4.1 at
-// K = 3072..4096 (0.14-0.20 us per stage of a wave's eight-way share of K); 17..64 rows on the 8 MB
+// walk over their K stages, round of workgroups after round.  Measured: a 134 MB layer from HBM, through the caches,
+// 24.0 us at 1..8 rows and 27.9 at 16 (past them 22 up to 8 rows, where nothing else is compared);
+// cache-resident layers 2.5-2.8 us at K = 768..1024, 3.3-4.1 at K = 3072..4096 (0.14-0.20 us per stage of a wave's eight-way share of K); 17..64 rows on the 8 MB
 // layers 3.6-4.9 us; 128 rows on 768 -> 768, 3072 -> 768 and 4096 -> 1024: 3.3, 5.7 and 6.7 us, where the
 // best tile with K cut takes 6.9, 10.5 and 11.3; 256 rows on 768 -> 2304: 7.8 us (the 64-row tile 7.1).
 // Register-layout kernel (any K): the activations are re-read once per 16 weight rows, which shows
@@ -819,7 +819,7 @@ int nimble_lstm_seq_supported(int64_t B, int64_t H) {
 }
 
 // A fixed rule, kept as callers know it: drawn when the loop took 2.4 microseconds per step at H = 512 with 4 rows and 2.7 / 4.0
-// at H = 1024 with 1 / 4, against 2.65-2.95 for a captured graph of per-step launches.  It takes 1.2 and 1.4 / 1.6 now.
+// at H = 1024 with 1 / 4, against 2.65-2.95 for a captured graph of per-step launches.  It takes 1.0 and 1.5 / 1.5 now.
 int nimble_lstm_seq_preferred(int64_t B, int64_t H) {
   return nimble_lstm_seq_supported(B, H) && (H <= 512 || B == 1);
 }

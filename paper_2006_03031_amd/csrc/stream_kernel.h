@@ -44,12 +44,12 @@ __device__ __forceinline__ void wait_vmcnt_of(int n) {  // n is a constant after
   }
 }
 
-// Measured on a 134 MB layer (8192 x 8192) streamed from HBM, microseconds at 1 / 16 rows (skinny_kernel:
+// Measured on a 134 MB layer (8192 x 8192) streamed from HBM through the caches, microseconds at 1 / 16 rows (skinny_kernel:
 // 31.8 / 38.1): NW = 4 with S = 2, 3, 4, 6, 8: 31.8, 30.0, 27.9, 30.7, 31.1 / 34.3, 30.8, 30.5, 32.7, 33.3;
 // NW = 8 with S = 2, 3, 4: 24.7, 24.5, 24.4 / 27.6, 28.0, 27.9; NW = 8, XR = 8, S = 3: 23.9 (four rows:
 // 25.0).  Two groups of 16 weight rows per workgroup sharing one activation tile (half the activation
 // traffic, but one workgroup per compute unit): 25.9-27.4 / 27.5-28.8, not kept.
-// ONCE: the weights are loaded non-temporally, past the caches (weights_pass_by).
+// ONCE: the weights are loaded non-temporally, past the caches (weights_pass_by): 1 / 8 rows 23.9 / 24.2 -> 21.7 / 22.1.
 template <bool LSTM, int S, int NW = 8, int XR = 16, bool ONCE = false>
 __global__ void __launch_bounds__(NW * 64) stream_kernel(SkinnyArgs s) {
   static_assert(XR == 8 || XR == 16, "the activation tile is one or two loads of 8 rows");
