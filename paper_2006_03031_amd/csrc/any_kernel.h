@@ -21,7 +21,9 @@ namespace nimble {
 //   ODD: K is odd, every other row of either operand starts at an odd element.  16 waves of one compute unit load rows of 128 bytes
 //   from the L2 at 114 KB per us where each lane's address is a whole 32-bit word, at 35 where it is not, at 54 where every other
 //   row is not.  So such rows are loaded from the element before and moved down on the way to LDS; the word behind a stage's
-//   last chunk is loaded by one lane per row (by all lanes, or all rows, it cost as much as it saved).
+//   last chunk is loaded by one lane per row (by all lanes, or all rows, it cost as much as it saved).  With four groups
+//   only: in one group these words take the kernel from four workgroups per compute unit to three, 836 tiles (4819 x 665 x 641) 20.6 ->
+//   23.6 us, 912 (1002 x 3587 x 453) 18.6 -> 20.6, without them 20.4 and 17.7; below 768 tiles they would gain 1 %.
 //   What bounds it: a few hundred tiles of some ten stages are the whole launch, so that it is the chain load ->
 //   LDS -> MFMA of one tile's stages.  By time stamps, 515 x 1001 x 1003 to f32: first stages 1.7 us, the other three rounds of
 //   four 3.6, the end of the tile 1.7, launch 1.5: 8.7 us; before the words, with a K tail that waited for its loads one by one, and
@@ -86,7 +88,7 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
   // ODD: some rows start at an odd element.  These are loaded from the element before, where a whole 32-bit word starts (a
   // 16-byte load whose address is not one takes three times as long), and moved down on their way to LDS, for which a
   // stage's last chunk needs the word behind it: shifts of this thread's rows, 0 or 16 bits.
-  static_assert(!KN || !ODD, "rows of a [K, N] operand are loaded as they are");
+  static_assert(!ODD || (!KN && KG > 1), "rows of a [K, N] operand, and those of one group, are loaded as they are");
   uint32_t sh_a[A_CH], sh_b[B_CH];
 #pragma unroll
   for (int i = 0; i < A_CH; ++i) sh_a[i] = ODD ? ((uint32_t)(uintptr_t)a_src[i] & 2u) * 8u : 0u;
@@ -125,23 +127,29 @@ __global__ void __launch_bounds__(256 * KG) any_kernel(GemmArgs g, int tiles_m, 
       for (int i = 0; i < B_CH; ++i) rb[SET][i] = chunk_kn(i, k0);
     }
   };
-  // A or K-contiguous B chunks of stage s as they go to LDS
-  auto settle = [&](const uint4& v, uint32_t next, uint32_t sh, int s) {
-    const int k0 = (s * KG + grp) << 6;
-    if (k0 + 64 > K) {
-      const int left = K - (k0 + ld_c * 8);
-      return keep_first8(v, left < 0 ? 0 : left > 8 ? 8 : left);
-    }
-    return ODD ? shift8(v, next, sh, ld_c == 7) : v;
-  };
+  // Chunks of stage s as they go to LDS.  (The tail is told apart once for all of them: chunk by chunk every one waited for its own load
+  // behind a branch, 2 % of launches of more tiles than compute units.)
   auto store = [&](auto set_tag, int buf, int s) {
     constexpr int SET = decltype(set_tag)::value;
+    const int k0 = (s * KG + grp) << 6, left = K - (k0 + ld_c * 8), n = left < 0 ? 0 : left > 8 ? 8 : left;
+    auto rows = [&](auto tail) {
+      auto settle = [&](const uint4& v, uint32_t next, uint32_t sh) {
+        if constexpr (decltype(tail)::value) return keep_first8(v, n);
+        return ODD ? shift8(v, next, sh, ld_c == 7) : v;
+      };
 #pragma unroll
-    for (int i = 0; i < A_CH; ++i) smem[buf][phys(ld_row + 32 * i, ld_c)] = settle(ra[SET][i], na[SET][i], sh_a[i], s);
+      for (int i = 0; i < A_CH; ++i) smem[buf][phys(ld_row + 32 * i, ld_c)] = settle(ra[SET][i], na[SET][i], sh_a[i]);
+      if (!KN) {
 #pragma unroll
-    for (int i = 0; i < B_CH; ++i)
-      smem[buf][BM * 8 + (KN ? phys_kn(tid / NC + i * (256 / NC), tid % NC) : phys(ld_row + 32 * i, ld_c))] =
-          KN ? rb[SET][i] : settle(rb[SET][i], nb[SET][i], sh_b[i], s);
+        for (int i = 0; i < B_CH; ++i) smem[buf][BM * 8 + phys(ld_row + 32 * i, ld_c)] = settle(rb[SET][i], nb[SET][i], sh_b[i]);
+      }
+    };
+    if (k0 + 64 > K) rows(std::true_type());
+    else rows(std::false_type());
+    if (KN) {
+#pragma unroll
+      for (int i = 0; i < B_CH; ++i) smem[buf][BM * 8 + phys_kn(tid / NC + i * (256 / NC), tid % NC)] = rb[SET][i];
+    }
   };
 
   const int r = lane & 15, gq = lane >> 4;

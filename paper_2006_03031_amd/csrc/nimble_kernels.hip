@@ -234,8 +234,8 @@ static int launch_any(const GemmArgs& g, hipStream_t st) {
         constexpr bool KN = decltype(kn)::value, THROUGH = decltype(through)::value, ODD = decltype(odd)::value;
         if (four)  // (one round of workgroups)
           hipLaunchKernelGGL((any_kernel<KN, 2, 4, true, ODD>), grid, dim3(1024), 0, st, part, pm, pn);
-        else
-          hipLaunchKernelGGL((any_kernel<KN, 4, 1, THROUGH, ODD>), grid, dim3(256), 0, st, part, pm, pn);
+        else  // (never ODD, see there)
+          hipLaunchKernelGGL((any_kernel<KN, 4, 1, THROUGH, false>), grid, dim3(256), 0, st, part, pm, pn);
       };
       auto pick = [&](auto kn, auto odd) {
         if (any_output_stays((int64_t)pm * pn * g.batch, g.K, g.out_f32 != 0)) launch(kn, std::false_type(), odd);

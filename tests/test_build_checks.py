@@ -74,9 +74,22 @@ def test_checker_counts_spills_only_at_the_deepest_loop_level_that_holds_stateme
     assert spills == [("_Z4testv", ".LBB0_2", 1)]
 
 
+@pytest.fixture(scope="module")
+def asm():
+    return build.device_assembly()
+
+
+# Launches of any_kernel in one group of waves are of many rounds of workgroups: four to a compute unit (128 registers per lane).
+# With three, 800 to 1000 tiles of odd K took 5 to 20 % longer.
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
-def test_generated_kernels_keep_clear_of_statement_mfma_results_and_do_not_spill_in_main_loops():
-    asm = build.device_assembly()
+def test_one_group_of_waves_leaves_room_for_four_workgroups(asm):
+    import re
+    found = re.findall(r"; -- Begin function (_ZN6nimble10any_kernelILb0ELi4ELi1E\w+).*?; Occupancy: (\d+)", asm, re.S)
+    assert len(found) >= 2 and all(int(waves) >= 4 for _, waves in found), found
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+def test_generated_kernels_keep_clear_of_statement_mfma_results_and_do_not_spill_in_main_loops(asm):
     assert asm.count("v_mfma_f32_16x16x32_bf16") > 1000  # the ring kernels are in there
     hazards, spills = build.asm_mfma_findings(asm)
     assert hazards == [], hazards[:5]
