@@ -582,13 +582,15 @@ int plan_dense(int64_t batch, int64_t M, int64_t N, int64_t K, int epilogue, int
     // Any shape and alignment.  A grid of at most two workgroups per compute unit, or a single block of
     // rows, streams both operands in 16 x 16 blocks whose waves share K; everything else runs in 64 x 64
     // tiles (any_kernel).  With K odd the blocks' loads of rows that start at odd elements take three times as long, and from some
-    // length on the second workgroup of a compute unit is not worth it.  Microseconds, blocks / tiles: K = 1003 on N = 1001,
-    // 64 rows (252 blocks) 6.3 / 8.3, 80 10.0 / 8.3, 128 10.2 / 8.4; K = 1002, 64 rows 3.7 / 7.3, 128 (504) 4.5 / 7.4; K =
-    // 257 on N = 1001, 64 rows 4.0 / 5.5, 80 5.5 / 5.3; 333 columns, K = 1399, 192 rows (252) 8.4 / 9.8, 256 14.6 / 9.8; 517
-    // columns, K = 131, 192 rows (396) 3.5 / 4.9; 250 columns, K = 777, 256 rows (256) 5.5 / 7.4, 320 8.5 / 7.4.
+    // length on the second workgroup of a compute unit is not worth it: on 120 shapes of 257 to 512 blocks tiles took, over blocks, 1.22
+    // at K = 257 ... 320, 1.11 to 384, 1.05 to 512, 1.11 to 570, 0.92 from 571 to 704, 0.85 to 896, 0.75 to 1150.  Microseconds, blocks /
+    // tiles: 52 x 1397 x 261 3.9 / 5.1, 28 x 2593 x 335 4.5 / 5.4, 226 x 413 x 499 5.7 / 6.5, 50 x 1079 x 523 5.1 / 6.4, 760 x 112 x 583
+    // 6.4 / 6.2, 82 x 1265 x 635 7.1 / 6.5, 114 x 1024 x 979 10.0 / 8.0, 80 and 128 x 1001 x 1003 10.0 / 8.3 and 10.2 / 8.4, 154 x 487 x
+    // 1121 11.5 / 8.5.  One block per compute unit: 64 x 1001 x 1003 (252) 6.3 / 8.3, 192 x 333 x 1399 8.4 / 9.8; K even: 64 and 128 x 1001 x
+    // 1002 3.7 / 7.3 and 4.5 / 7.4.
     const int64_t cols16 = ceil_div(N, 16), rows16 = ceil_div(M, 16);
     const bool rows = opt.generic_rows && batch == 1 && K > 0 && rows16 <= 65535 &&
-                      (rows16 <= 1 || cols16 * rows16 <= (K % 2 != 0 && K > 256 ? 1 : 2) * kCUs);
+                      (rows16 <= 1 || cols16 * rows16 <= (K % 2 != 0 && K > 576 ? 1 : 2) * kCUs);
     p->variant = variant;
     fill_any(p, batch, M, N, K, !opt.generic_rows);
     if (rows) {

@@ -58,8 +58,8 @@ def test_dense_of_any_shape(nb, M, N, K):
 
 
 # K odd (every other row starts at an odd element) and even at the edges of chunks, of stages and of rounds of four stages; one
-# group of waves (more than 256 tiles, or one stage) and four; the last element of the last row is the end of the buffer
-@pytest.mark.parametrize("K", [5, 7, 8, 9, 57, 63, 64, 65, 66, 71, 72, 73, 127, 129, 191, 193, 255, 256, 257, 263, 321])
+# group of waves (more than 256 tiles, or one stage) and four, and the 16 x 16 blocks that small grids run in up to K = 576; the last element of the last row is the end of the buffer
+@pytest.mark.parametrize("K", [5, 7, 8, 9, 57, 63, 64, 65, 66, 71, 72, 73, 127, 129, 191, 193, 255, 256, 257, 263, 321, 577, 639, 641, 769])
 @pytest.mark.parametrize("M,N", [(80, 1001), (129, 1001), (63, 2003), (1100, 1031)])
 def test_rows_that_start_at_odd_elements(nb, M, N, K):
     from paper_2006_03031_amd import runtime as rt
