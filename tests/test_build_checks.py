@@ -88,6 +88,16 @@ def test_one_group_of_waves_leaves_room_for_four_workgroups(asm):
     assert len(found) >= 2 and all(int(waves) >= 4 for _, waves in found), found
 
 
+# ... and their bias is there before the products end (loaded behind them it took 0.5 to 1 us of launches of 6 to 8)
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+def test_one_group_of_waves_loads_nothing_behind_its_products(asm):
+    import re
+    found = re.findall(r"; -- Begin function _ZN6nimble10any_kernelILb0ELi4ELi1E\w+(.*?)s_endpgm", asm, re.S)
+    assert len(found) >= 2
+    for body in found:
+        assert "global_load_ushort" in body and "global_load" not in body[body.rindex("v_mfma"):]
+
+
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 def test_generated_kernels_keep_clear_of_statement_mfma_results_and_do_not_spill_in_main_loops(asm):
     assert asm.count("v_mfma_f32_16x16x32_bf16") > 1000  # the ring kernels are in there
