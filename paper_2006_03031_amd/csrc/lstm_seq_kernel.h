@@ -144,7 +144,10 @@ __device__ __forceinline__ uint32_t lstm_seq_nans(uint32_t v) {
 // waves, each with the first halves of its stages in one chain and the second halves in the other; here waves 2 w and
 // 2 w + 1 have one of these chains each, which gives the same sums without a wave doing more.  ORDER 2: as 1 where a
 // range holds stages of x and of h (in place of 1 it takes 128 steps of 37 rows, H = Ix = 512, from 188 us to 204).
-template <bool PRE, int PW, int G, int R, int ORDER>
+// ONE: a row group's workgroups go to one XCD, else to two (above H = 512).  Only there do the words meet in an L2, and only there is x
+// loaded into LDS: with the words on their way for longer, x in registers a step ahead costs nothing, and the ring's waits and reads 3 to 4 %
+// (128 steps of 5 rows, Ix = 128, H = 640, 200 us, with the ring 208; 4 rows, 256, 768, 194 and 202).
+template <bool PRE, int PW, int G, int R, int ORDER, bool ONE>
 __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int group0, int row_groups, int rs_few, int xcd0) {
   static_assert(R == 4 || R == 8, "a load brings 8 rows of 32 k or 4 rows of 64");
   static_assert(ORDER == 0 || R == 8, "up to 4 rows the per-step launch runs eight waves");
@@ -158,8 +161,8 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   constexpr int CELLS = R * U;  // one lane each, in the first waves
   // partial sums [buffer][wave][cell]: the four gates of a cell are one 16-byte word
   __shared__ f32x4 red[2][8][CELLS];
-  // operands of the waves that multiply x: three steps' [chunk of 8 k][row] (MIX keeps them in registers)
-  constexpr bool XR = !PRE && !MIX;
+  // operands of the waves that multiply x: three steps' [chunk of 8 k][row] (MIX and two XCDs: in registers)
+  constexpr bool XR = !PRE && !MIX && ONE;
   constexpr int XLOADS = NU * 4 * R > 64 ? NU * 4 * R / 64 : 1;  // of 64 chunks, per step
   __shared__ uint4 x_ring[XR ? 7 : 1][3][XR ? XLOADS * 64 : 1];
   __shared__ int s_abort[2];  // by step parity: a wave already polling for step t+1 never writes the word step t reads
@@ -167,7 +170,8 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   // Workgroups go to the 8 XCDs in turn: a row group's workgroups are those of one XCD (of two, above 32 of them), so that
   // the hand-over words meet in that XCD's L2.  (Where they go elsewhere the loop is slower and as right.)
   const int H = a.H, Ix = PRE ? 0 : a.Ix, B = a.B, T = a.T;
-  const int n_wg = H / U, span = n_wg > 32 ? 2 : 1, per_xcd = n_wg / span;
+  constexpr int span = ONE ? 1 : 2;
+  const int n_wg = H / U, per_xcd = n_wg / span;
   const int xcd = ((int)blockIdx.x + xcd0) & 7, nth = (int)blockIdx.x >> 3;
   const int group = group0 + nth / per_xcd * (8 / span) + xcd / span;
   if (group >= row_groups) return;
@@ -177,7 +181,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   const int plane = rs * (H >> 2);
   unsigned long long* exch = a.exch + (long long)row0 * (H >> 1);  // (groups but the last are R rows of rs = R)
   const unsigned long long here = xcc_id() + 1;  // (1 ... 8: neither phase nor mark)
-  if (span == 1 && threadIdx.x == 0) __hip_atomic_store(exch + wg * G * rs, here, __ATOMIC_RELAXED, SCOPE);
+  if (ONE && threadIdx.x == 0) __hip_atomic_store(exch + wg * G * rs, here, __ATOMIC_RELAXED, SCOPE);
   const int rows = B - row0 < R ? B - row0 : R;  // of this group
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -235,7 +239,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   __syncthreads();
   // whether the row group's workgroups share an XCD, that is an L2
   bool near = false;
-  if (span == 1) {
+  if (ONE) {
     const unsigned long long* ids = exch + (lane < n_wg ? lane : 0) * G * rs;
     const uint32_t most = a.max_polls < 256u ? a.max_polls : 256u;
     unsigned long long v = 0;
@@ -340,7 +344,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
       for (int g = 0; g < 2; ++g)
         if (r < R) red[t & 1][wave][((g0 + g) * R + r) * 4 + gq] = ORDER == 0 ? acc[g][0] + acc[g][1] : acc[g][0];  // rows past the group's are never used
     }
-    if (MIX && of_x && t < T) load_rows(a.x + (long long)t * B * Ix);
+    if (!XR && of_x && t < T) load_rows(a.x + (long long)t * B * Ix);
     if (PRE && owner && t < T) {
       const float* src = a.pre + (long long)t * B * 4 * H;
 #pragma unroll

@@ -361,11 +361,16 @@ static void launch_lstm_seq_as(const LstmSeqArgs& a, int rs, int xcd0, hipStream
   // (four ranges: whole ranges of 2 per_wave stages, see nimble_lstm_loop_supported)
   const bool mixed = a.ranges == 4 && a.Ix / 64 % (2 * per_wave) != 0;
   const int order = a.ranges != 4 ? 0 : mixed ? 2 : 1;
-  auto launch = [&](auto pre, auto pw, auto ord) {
+  auto launch_as = [&](auto pre, auto pw, auto ord, auto one) {
     constexpr int ORDER = R == 8 ? decltype(ord)::value : 0;
     for (int group0 = 0; group0 < row_groups; group0 += per_launch)
-      hipLaunchKernelGGL((lstm_seq_kernel<decltype(pre)::value, decltype(pw)::value, 4, R, ORDER>), grid, block, 0, st, a,
-                         group0, row_groups, rs, xcd0);
+      hipLaunchKernelGGL((lstm_seq_kernel<decltype(pre)::value, decltype(pw)::value, 4, R, ORDER, decltype(one)::value>), grid, block, 0,
+                         st, a, group0, row_groups, rs, xcd0);
+  };
+  auto launch = [&](auto pre, auto pw, auto ord) {
+    if constexpr (decltype(pw)::value == 1) launch_as(pre, pw, ord, std::true_type());  // (H <= 512)
+    else if (span == 1) launch_as(pre, pw, ord, std::true_type());
+    else launch_as(pre, pw, ord, std::false_type());
   };
   auto pick = [&](auto pw) {
     if (a.pre && order == 0) launch(std::true_type(), pw, Int<0>());

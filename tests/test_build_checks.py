@@ -98,6 +98,14 @@ def test_one_group_of_waves_loads_nothing_behind_its_products(asm):
         assert "global_load_ushort" in body and "global_load" not in body[body.rindex("v_mfma"):]
 
 
+# The token loop over two XCDs (its last template argument) keeps x in registers: with the ring in LDS 128 steps took 3 to 4 % longer.
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
+def test_the_token_loop_over_two_xcds_has_no_ring_of_inputs(asm):
+    import re
+    found = re.findall(r"; -- Begin function _ZN6nimble15lstm_seq_kernelILb0E\w*Lb0EEEv.*?; LDSByteSize: (\d+)", asm, re.S)
+    assert len(found) >= 2 and all(int(size) < 40000 for size in found), found
+
+
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 def test_generated_kernels_keep_clear_of_statement_mfma_results_and_do_not_spill_in_main_loops(asm):
     assert asm.count("v_mfma_f32_16x16x32_bf16") > 1000  # the ring kernels are in there

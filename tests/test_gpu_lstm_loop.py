@@ -85,10 +85,10 @@ def test_the_loop_equals_the_steps_one_by_one(rt, nb, T, B, Ix, H):
 
 @pytest.mark.parametrize("T", [1, 2, 3, 4, 5, 8])
 @pytest.mark.parametrize("B,Ix,H", [(1, 512, 512), (4, 256, 256), (7, 256, 256), (9, 768, 256), (33, 512, 512), (41, 256, 256),
-                                    (3, 896, 128), (8, 448, 64), (12, 64, 448)])
+                                    (3, 896, 128), (8, 448, 64), (12, 64, 448), (3, 128, 640), (7, 256, 768), (37, 640, 384)])
 def test_inputs_that_arrive_three_steps_ahead(rt, nb, T, B, Ix, H):
     """Fewer steps than the inputs' ring holds, as many, and more; one to seven of the eight waves multiply x, one or two stages
-    each, rows that are not the group's."""
+    each, rows that are not the group's.  Over two XCDs, and beside units of h, x is a step ahead in registers."""
     assert nb.lstm_loop_supported(B, Ix, H)
     case = _case(6, T, B, Ix, H)
     want_h, want_c = _steps(rt, *case)
