@@ -237,18 +237,6 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
 
   if (tid < 2) s_abort[tid] = 0;
   __syncthreads();
-  // whether the row group's workgroups share an XCD, that is an L2
-  bool near = false;
-  if (ONE) {
-    const unsigned long long* ids = exch + (lane < n_wg ? lane : 0) * G * rs;
-    const uint32_t most = a.max_polls < 256u ? a.max_polls : 256u;
-    unsigned long long v = 0;
-    for (uint32_t polls = 0; polls < most; ++polls) {
-      v = __hip_atomic_load(ids, __ATOMIC_RELAXED, SCOPE);
-      if (__all(v != 0ull)) break;
-    }
-    near = __all(v == here) && (a.apart >> (wg & 1) & 1u) == 0u;
-  }
   // word of this lane in a load: R = 8: 32 k, rows by lane & 7, pieces of 4 k by gq and bit 3; R = 4: 64 k
   uint32_t ask;   // (bytes, as is the next)
   uint32_t from;  // this lane's operand row in x_t or h_0 (lanes past the group's rows: columns never used)
@@ -288,7 +276,6 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
     load_x(1);
     load_x(2);
     load_x(3);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   }
   if (MIX) {
     const int orow = row0 + (r < rows ? r : rows - 1);
@@ -311,6 +298,19 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
     for (int q = 0; q < 4; ++q)
       pr[q] = PRE ? *at(a.pre + q * H, pre_at) : bf2f(a.bias[q * H + wg * U + cg * 4 + uu]);
   }
+  // whether the row group's workgroups share an XCD, that is an L2 (behind the first loads, which take as long)
+  bool near = false;
+  if (ONE) {
+    const unsigned long long* ids = exch + (lane < n_wg ? lane : 0) * G * rs;
+    const uint32_t most = a.max_polls < 256u ? a.max_polls : 256u;
+    unsigned long long v = 0;
+    for (uint32_t polls = 0; polls < most; ++polls) {
+      v = __hip_atomic_load(ids, __ATOMIC_RELAXED, SCOPE);
+      if (__all(v != 0ull)) break;
+    }
+    near = __all(v == here) && (a.apart >> (wg & 1) & 1u) == 0u;
+  }
+  if (XR && of_x) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   for (int t = 1;; ++t) {
     if (XR && of_x) {
       // this step's loads were issued three steps ago: behind them are those of two more steps and, from the cells' waves, two
