@@ -44,14 +44,15 @@ namespace nimble {
 //   workgroup has read them (that takes h_2), without the phase bit; a workgroup that finds all numbers
 //   of its row group equal to its own stores plainly from then on, any other with device scope.  Nobody relies on the
 //   others' choice: all are right, the plain stores are seen by all who can look for them.  128 steps, by kernel
-//   trace, device-scope stores throughout / so: pre form of H = 512, 1, 4 and 16 rows 150 / 131, 151 / 131, 170 / 145 us, of H = 256, 1 row
-//   140 / 123; x form of H = Ix = 512, 4, 37 and 64 rows 175 / 144, 184 / 162, 182 / 159.
+//   trace, device-scope stores throughout / so: pre form of H = 512, 1, 4 and 16 rows 154 / 130, 154 / 133, 175 / 145 us, of H = 256, 1 row
+//   137 / 122; x form of H = Ix = 512, 4, 37 and 64 rows 171 / 144, 182 / 159, 180 / 155.
 //   x_t comes from memory, and what a compute unit's waves load returns in order, so that polls queue behind x.  The waves
 //   that multiply x load it straight into LDS, three steps ahead and right behind the barrier, when this step's
 //   polls are over and the next ones are some 900 clocks away (loaded into registers behind the products a step
 //   ahead 4 / 37 rows, H = Ix = 512, took 153 / 175 us, into LDS but behind the products 152 / 162, by the polling waves as their words
 //   had arrived 155 / 179, so 139 / 151; before the plain stores 163 / 169).  Those of them that update cells too wait for a step
-//   more than they need, see there.  ORDER 2, whose waves hold units of x beside units of h, loads x into registers a step ahead.
+//   more than they need, see there.  Over two XCDs, and in ORDER 2, whose waves hold units of x beside units of h, x is loaded into registers
+//   a step ahead.
 //   Every wait is bounded: a wave polls at most max_polls times per step, looking at the give-up word with every
 //   eighth; a wave that runs out sets it, and every workgroup leaves at its next check.  So the
 //   grid drains whatever happens (fewer workgroups resident than launched, a stalled neighbour).  Then either
@@ -62,9 +63,9 @@ namespace nimble {
 //   the same cell function).
 //   What bounds it: a chain of, in clocks by time stamps, products and partial sums to LDS 400, barrier 150, sums 250, cell 600,
 //   and the way through the L2 to the slowest workgroup 700.  Microseconds per step, by kernel trace, pre form at
-//   1 / 4 rows: H = 512 1.02 / 1.02, H = 1024 1.51 / 1.52, H = 256 0.96 / - (32-bit words with a step tag each, four lanes
-//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 / 64 rows, H = Ix = 512: 1.13 / 1.26 /
-//   1.24 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
+//   1 / 4 rows: H = 512 1.02 / 1.04, H = 1024 1.50 / 1.52, H = 256 0.96 / - (32-bit words with a step tag each, four lanes
+//   per cell, workgroups over all XCDs: 1.60 / 1.64, 1.76 / 1.96); x form at 4 / 37 / 64 rows, H = Ix = 512: 1.12 / 1.24 /
+//   1.21 (a captured graph of per-step launches: 2.9 / 3.65 / 3.7).  On the way there, 37 rows, x form: four lanes
 //   per cell, 32-byte stores 2.31; one lane per cell, 128-byte stores 1.95; a row group's workgroups on one XCD
 //   and a late first poll 1.56; operands polled straight into their registers, no address arithmetic in the loop 1.37.
 //   Tried and not kept: system scope, exchanges instead of stores, raised priority for the cells (no change); a
@@ -152,6 +153,9 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   static_assert(R == 4 || R == 8, "a load brings 8 rows of 32 k or 4 rows of 64");
   static_assert(ORDER == 0 || R == 8, "up to 4 rows the per-step launch runs eight waves");
   constexpr bool MIX = ORDER == 2;
+  // Waves that hold two stages of x and of h wait for x from memory in front of their polls, whatever the stores' scope: 128 steps of 37
+  // rows, Ix = 640, H = 384, 194 us, with plain stores 200.  (With one stage per wave 97 rows, 192, 320 347 and 285.)
+  constexpr bool NEAR = ONE && !(MIX && PW == 2);
   constexpr int NU = 2 * PW;               // units of 32 k per wave
   constexpr int STEP = ORDER == 0 ? 32 : 64;  // k from one of them to the next
   const int rs = R == 8 ? 8 : rs_few;
@@ -181,7 +185,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   const int plane = rs * (H >> 2);
   unsigned long long* exch = a.exch + (long long)row0 * (H >> 1);  // (groups but the last are R rows of rs = R)
   const unsigned long long here = xcc_id() + 1;  // (1 ... 8: neither phase nor mark)
-  if (ONE && threadIdx.x == 0) __hip_atomic_store(exch + wg * G * rs, here, __ATOMIC_RELAXED, SCOPE);
+  if (NEAR && threadIdx.x == 0) __hip_atomic_store(exch + wg * G * rs, here, __ATOMIC_RELAXED, SCOPE);
   const int rows = B - row0 < R ? B - row0 : R;  // of this group
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -300,7 +304,7 @@ __global__ void __launch_bounds__(512, 4) lstm_seq_kernel(LstmSeqArgs a, int gro
   }
   // whether the row group's workgroups share an XCD, that is an L2 (behind the first loads, which take as long)
   bool near = false;
-  if (ONE) {
+  if (NEAR) {
     const unsigned long long* ids = exch + (lane < n_wg ? lane : 0) * G * rs;
     const uint32_t most = a.max_polls < 256u ? a.max_polls : 256u;
     unsigned long long v = 0;
